@@ -268,9 +268,7 @@ int octopus_attn_decode_static(const octopus_codebooks_t *cb,
  *   signs2, qjl as for octopus_encode_qjl (read only here).
  *   v_dtype     BF16 only (EUNSUPPORTED otherwise).
  * Query rows sharing a KV head (n_q * n_q_heads / n_kv_heads) are served in
- * groups of 8, 4 or 2 rows (the most whose lookup table fits on-chip memory
- * for this head dimension and bit width: 4 at d = 128, b = 3; 2 at d = 256,
- * b = 3); each group reads the head's keys once.  Workspace: octopus_attn_decode_workspace(...) of the
+ * groups of at most 8; each group reads the head's keys once.  Workspace: octopus_attn_decode_workspace(...) of the
  * same shapes.  Other arguments and errors as octopus_attn_decode; EINVAL if
  * signs2 or qjl is NULL. */
 int octopus_attn_decode_qjl(const octopus_codebooks_t *cb,

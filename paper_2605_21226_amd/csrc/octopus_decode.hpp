@@ -742,16 +742,37 @@ struct DecodeSmemMfma {
     uint16_t pbuf[kDecodeWaves][16][prob_row<KPL>()];
 };
 
-// Optional 1-bit QJL residual (Sec. 3.6).  The correction of a key, sum_j sigma_j q2_j per query row, is
-// looked up a byte of sign bits at a time: entry [position][byte value][row] holds the signed sum of the 8
-// q2 coordinates of that byte.  The table is rebuilt per work item (it depends on the queries).
-template <class P, int RG>
-constexpr int qjl_table_floats() { return (P::D / 8) * 256 * RG; }
-template <class P, int RG>
-constexpr bool qjl_fits() {
-    return sizeof(DecodeSmemMfma<P, decode_keys_per_lane<P::D>()>) + qjl_table_floats<P, RG>() * 4 +
-               sizeof(QueryOperands<P, RG>) + 64 <= 160 * 1024;
-}
+// Optional 1-bit QJL residual (Sec. 3.6).  The correction of a key is a product with signs, sum_j sigma_j q2_j per
+// query row: 16 keys x 16 operand rows x 32 coordinates at a time on v_mfma_f32_16x16x32_bf16, the signs as bf16 +-1
+// (exact) and each q2 as the sum of three bf16 numbers (24 bits: exact as well, up to numbers far below the row's size).
+//   * B: lane (n, g) = (l % 16, l / 16) holds the sign words of group g of key n of each block of 16 keys, loaded in that
+//     form from the side-car.  Bits i and i + 16 of a word become one register of two bf16 numbers with a shift and an
+//     and-or (their sign bits under a constant 1.0).
+//   * A: operand rows as in LDS below: with up to four query rows the three parts are rows r, 4 + r and 8 + r of one
+//     operand, with eight the leading parts and first remainders are rows r and 8 + r of one operand and the second
+//     remainders rows r of another one that adds to the same accumulators.
+//   * the parts of a key's sum sit in lane groups of the accumulators of its block; three to five exchanges of lane rows
+//     per register add them up and leave every lane with the sums of its own key.
+// This took the place of a table of signed sums per byte of signs (d / 8 x 256 x rows floats), which cost d / 8 random
+// 16-byte LDS reads and their additions per key, limited the row group to what fitted LDS (4 at d = 128, 2 at d = 256: more
+// rows read the keys again) and was rebuilt for every work item: 0.243 -> 0.233 ms for 16 x 32768 tokens x 8 KV heads at
+// d = 128, b = 3 with four query heads per KV head, where the kernel is now bound by memory as without the residual.
+template <int D, int RG>
+struct QjlOperands {
+    static constexpr int WORDS = D / 32;                        // sign words per key
+    static constexpr int WPL = WORDS < 4 ? 1 : WORDS / 4;       // sign words per lane and key
+    static constexpr int STEPS = D / 32;                        // k-steps of 32 coordinates
+    static constexpr int SETS = RG <= 4 ? 1 : 2;                // A operands per k-step
+    uint4 a[SETS][STEPS][4][16];                                // [set][k-step][lane group][operand row]
+    // word i of a lane's (at d = 64 two lane groups share a word)
+    static __device__ __forceinline__ int word(int g, int i) { return WORDS < 4 ? g >> 1 : g * WPL + i; }
+    // coordinate of element j of lane group g in k-step s
+    static __device__ __forceinline__ int coordinate(int g, int s, int j) {
+        const int pair = (j >> 1) + 16 * (j & 1);
+        if constexpr (D == 64) return 32 * (g >> 1) + 8 * (g & 1) + 4 * s + pair;
+        else return 32 * (g * WPL + s / 4) + 4 * (s % 4) + pair;
+    }
+};
 
 // SCORES: also store the scaled scores (a second instantiation, so that the usual one carries none of
 // the addressing state of that store through its loop).
@@ -785,7 +806,8 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
     // static, so that table addresses are compile-time constants that fold into the LDS instructions
     constexpr bool MX = mx_scores<P>();    // scores on the matrix cores (every plan up to 3 bits per coordinate)
     __shared__ DecodeSmemMfma<P, KPL> sm;
-    __shared__ __attribute__((aligned(16))) float qtab[QJL ? qjl_table_floats<P, RG>() : 4];
+    using QO = QjlOperands<D, RG>;
+    __shared__ __attribute__((aligned(16))) uint4 qjl_store[QJL ? sizeof(QO) / 16 : 1];
     __shared__ __attribute__((aligned(16))) uint4 qop_store[MX ? P::NTRI * QueryOperands<P, RG>::ROWS : 1];
     const QueryOperands<P, RG> &qop = *reinterpret_cast<const QueryOperands<P, RG> *>(&qop_store[0]);
 
@@ -889,53 +911,82 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
     };
     int64_t slot_cur[KPL];   // PAGED: pool positions of the step being worked on
     int page_nxt[KPL];       // PAGED: page ids of the wave's next step
-    // QJL side-car of a step: per key d / 32 words of sign bits (bit set: negative) and the fp16 residual
-    // norm; tile layout [word][key] then [key].
+    // QJL side-car of a tile, layout [word][key] uint32 (bit set: negative), then [key] fp16 residual norms.  Lane (n, g)
+    // holds the words of group g of keys 16 b + n, b = 0 .. 3, and the norm of its own key.
     const char *j_region = reinterpret_cast<const char *>(qjl);
-    auto load_sidecar = [&](int step, uint32_t (&sc)[KPL][QW + 1]) {
+    auto load_signs = [&](const char *src, uint32_t (&sc)[4 * QO::WPL + 1]) {
 #pragma unroll
-        for (int k = 0; k < KPL; ++k) {
-            const char *src = j_region + static_cast<int64_t>(min(step * KPL + k, ww.n_tiles - 1)) * TQ;
+        for (int i = 0; i < QO::WPL; ++i)
 #pragma unroll
-            for (int wq = 0; wq < QW; ++wq)
-                sc[k][wq] = *reinterpret_cast<const uint32_t *>(src + wq * (kWave * 4) + lane * 4);
-            sc[k][QW] = *reinterpret_cast<const uint16_t *>(src + QW * (kWave * 4) + lane * 2);
-        }
+            for (int b = 0; b < 4; ++b)
+                sc[4 * i + b] = *reinterpret_cast<const uint32_t *>(src + QO::word(g4, i) * (kWave * 4) + (16 * b + n16) * 4);
+        sc[4 * QO::WPL] = *reinterpret_cast<const uint16_t *>(src + QW * (kWave * 4) + lane * 2);
+    };
+    auto load_sidecar = [&](int step, uint32_t (&sc)[KPL][4 * QO::WPL + 1]) {
+#pragma unroll
+        for (int k = 0; k < KPL; ++k)
+            load_signs(j_region + static_cast<int64_t>(min(step * KPL + k, ww.n_tiles - 1)) * TQ, sc[k]);
     };
     // PAGED: the side-car is a pool of [page][KV head] tiles like the keys'; slot = page * n_kv_heads + KV head
-    auto load_sidecar_at = [&](const int64_t (&slot)[KPL], uint32_t (&sc)[KPL][QW + 1]) {
+    auto load_sidecar_at = [&](const int64_t (&slot)[KPL], uint32_t (&sc)[KPL][4 * QO::WPL + 1]) {
 #pragma unroll
-        for (int k = 0; k < KPL; ++k) {
-            const char *src = j_region + slot[k] * TQ;
-#pragma unroll
-            for (int wq = 0; wq < QW; ++wq)
-                sc[k][wq] = *reinterpret_cast<const uint32_t *>(src + wq * (kWave * 4) + lane * 4);
-            sc[k][QW] = *reinterpret_cast<const uint16_t *>(src + QW * (kWave * 4) + lane * 2);
-        }
+        for (int k = 0; k < KPL; ++k) load_signs(j_region + slot[k] * TQ, sc[k]);
     };
-    // Sum over the d / 8 sign bytes of a key of the table rows they select: q2 . sigma per query row.
-    auto qjl_dot = [&](const uint32_t (&sc)[QW + 1], float (&corr)[RG]) {
+    // q2 . sigma per query row of this lane's key
+    auto qjl_dot = [&](const uint32_t (&sc)[4 * QO::WPL + 1], float (&corr)[RG]) __attribute__((always_inline)) {
+        const uint4 *a_lane = &qjl_store[g4 * 16 + n16];
+        f32x4_t cacc[4];
 #pragma unroll
-        for (int r = 0; r < RG; ++r) corr[r] = 0.0f;
+        for (int b = 0; b < 4; ++b) cacc[b] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        uint32_t wrd[4 * QO::WPL];
 #pragma unroll
-        for (int wq = 0; wq < QW; ++wq)
+        for (int e = 0; e < 4 * QO::WPL; ++e) wrd[e] = D == 64 ? sc[e] << (8 - 8 * (g4 & 1)) : sc[e];
+        // the A operands one k-step ahead; the barriers keep the compiler from expanding all signs first (spills)
+        union AOp { uint4 u; bf16x8_t b; };
+        AOp qa[2][QO::SETS];
+#pragma unroll
+        for (int t = 0; t < QO::SETS; ++t) qa[0][t].u = a_lane[t * QO::STEPS * 64];
+#pragma unroll
+        for (int st = 0; st < QO::STEPS; ++st) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < QO::SETS; ++t)
+                if (st + 1 < QO::STEPS) qa[(st + 1) & 1][t].u = a_lane[(t * QO::STEPS + st + 1) * 64];
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
-                const uint32_t byte = (sc[wq] >> (8 * b)) & 0xffu;
-                const float *row = &qtab[((4 * wq + b) * 256 + byte) * RG];
-                if constexpr (RG == 1) {
-                    corr[0] += row[0];
-                } else if constexpr (RG == 2) {
-                    const float2 t = *reinterpret_cast<const float2 *>(row);
-                    corr[0] += t.x; corr[1] += t.y;
-                } else {
+                union { uint32_t u[4]; bf16x8_t b; } sg;
 #pragma unroll
-                    for (int h = 0; h < RG / 4; ++h) {
-                        const float4 t = *reinterpret_cast<const float4 *>(row + 4 * h);
-                        corr[4 * h] += t.x; corr[4 * h + 1] += t.y; corr[4 * h + 2] += t.z; corr[4 * h + 3] += t.w;
-                    }
+                for (int jj = 0; jj < 4; ++jj) {
+                    const int sh = D == 64 ? 7 - 4 * st - jj : 15 - 4 * (st % 4) - jj;
+                    const uint32_t moved = wrd[D == 64 ? b : 4 * (st / 4) + b] << sh;
+                    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(sg.u[jj]) : "v"(moved), "s"(0x80008000u), "v"(0x3f803f80u));
                 }
+#pragma unroll
+                for (int t = 0; t < QO::SETS; ++t)
+                    cacc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[st & 1][t].b, sg.b, cacc[b], 0, 0, 0);
             }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float x0 = cacc[0][i], x1 = cacc[1][i], x2 = cacc[2][i], x3 = cacc[3][i];
+            if constexpr (RG <= 4) {
+                // lane groups of a block: [leading, first remainder, second remainder, 0]
+                swap16(x0, x1);            // x0: leading parts of blocks 0, 1, then second remainders; x1: first remainders
+                swap16(x2, x3);
+                float a = x0 + x1, b = x2 + x3;
+                swap32(a, b);              // a: (leading + first) of blocks 0 .. 3, b: second remainders of blocks 0 .. 3
+                if (i < RG) corr[i < RG ? i : 0] = a + b;
+            } else {
+                // lane groups of a block: [rows 0-3, rows 4-7, first remainders of rows 0-3, of rows 4-7]
+                swap32(x0, x2);            // x0: rows of blocks 0 and 2, x2: their remainders
+                swap32(x1, x3);
+                float a = x0 + x2, b = x1 + x3;
+                swap16(a, b);              // a: rows 0-3 of blocks 0 .. 3, b: rows 4-7
+                corr[i] = a;
+                corr[RG > 4 ? 4 + i : 0] = b;
+            }
+        }
     };
     float m_run[RG], l_lane[RG];
     f32x4_t acc[CPL];
@@ -1023,7 +1074,7 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
     // swapping roles, so that no register copies (and no full memory wait in front of them) carry the
     // prefetched records over.
     auto process_step = [&](int step, const uint32_t (&w)[KPL][P::NWORDS], uint32_t (&w_next)[KPL][P::NWORDS],
-                            const uint32_t (&sc)[KPL][QW + 1], uint32_t (&sc_next)[KPL][QW + 1])
+                            const uint32_t (&sc)[KPL][4 * QO::WPL + 1], uint32_t (&sc_next)[KPL][4 * QO::WPL + 1])
                             __attribute__((always_inline)) {
         const int t0 = step * (KPL * kWave);
         const int n_valid = min(KPL * kWave, ww.len - t0);
@@ -1097,7 +1148,7 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
                 // Sec. 3.6: q . k = gamma (q_rot . u^ + gamma_r q2 . sigma), the estimator's constant is in q2
                 float corr[RG];
                 qjl_dot(sc[k], corr);
-                const float gamma_r = __half2float(__ushort_as_half(static_cast<unsigned short>(sc[k][QW])));
+                const float gamma_r = __half2float(__ushort_as_half(static_cast<unsigned short>(sc[k][4 * QO::WPL])));
 #pragma unroll
                 for (int r = 0; r < RG; ++r) s[k][r] = fmaf(gamma_r, corr[r], s[k][r]);
             }
@@ -1153,27 +1204,32 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
         }
     };
     uint32_t w_a[KPL][P::NWORDS], w_b[KPL][P::NWORDS];
-    uint32_t sc_a[KPL][QW + 1], sc_b[KPL][QW + 1];
+    uint32_t sc_a[KPL][4 * QO::WPL + 1], sc_b[KPL][4 * QO::WPL + 1];
     int it, taken = 0;
     while (next_item(plan, &item_slot, tid, &taken, &it)) {
         item_work(shp, plan, seq_lens, it, wave, KPL, &ww);
         qg = q_rot + ww.group_id * (P::QS * RG);
         if constexpr (QJL) {
-            // Every wavefront is past the previous item here (next_item's barriers, or this is the
-            // workgroup's only item).  Thread `tid` is the byte value: entry [pos][tid][r] is the sum of
-            // the 8 coordinates of q2 at position pos, each negated where tid has its bit set.
+            // A operands of the correction.  Every wavefront is past the previous item here (next_item's barriers, or
+            // this is the workgroup's only item).
             const float *q2g = q2 + ww.group_id * (RG * D);
-            for (int pos = 0; pos < D / 8; ++pos)
+            constexpr int ENTRIES = QO::SETS * QO::STEPS * 64;
+            for (int e = tid; e < ENTRIES; e += kDecodeWaves * kWave) {
+                const int m = e % 16, g = (e / 16) % 4, st = (e / 64) % QO::STEPS, set = e / (64 * QO::STEPS);
+                // query row and part (0 leading, 1 and 2 the remainders) of operand row m
+                const int r = RG <= 4 ? m % 4 : m % 8, part = RG <= 4 ? m / 4 : (set == 0 ? m / 8 : (m < 8 ? 2 : 3));
+                uint32_t h[8];
 #pragma unroll
-                for (int r = 0; r < RG; ++r) {
-                    float t = 0.0f;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const float x = q2g[r * D + 8 * pos + e];
-                        t += ((tid >> e) & 1) ? -x : x;
+                for (int j = 0; j < 8; ++j) {
+                    float x = (r < RG && part < 3) ? q2g[r * D + QO::coordinate(g, st, j)] : 0.0f;
+                    h[j] = bf16_rne(x);
+                    for (int t = 0; t < part; ++t) {
+                        x -= __uint_as_float(h[j] << 16);
+                        h[j] = bf16_rne(x);
                     }
-                    qtab[(pos * 256 + tid) * RG + r] = t;
                 }
+                qjl_store[e] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+            }
             __syncthreads();
             j_region = reinterpret_cast<const char *>(qjl) + (PAGED ? 0 : ww.pair * (shp.t_capacity / kWave) * TQ);
         }
@@ -1605,16 +1661,12 @@ int launch_decode_paged_qjl_rg(const octopus_codebooks_t &cb, const DecodeShape 
                                const void *k_pool, const void *qjl_pool, const float *q2, const void *v_pool,
                                const PageTable &pt, const int32_t *seq_lens, float *part_ml, float *part_acc,
                                int32_t *plan, hipStream_t stream) {
-    if constexpr (qjl_fits<P, RG>()) {
-        const DeviceBooks books = device_books(cb);
-        hipLaunchKernelGGL((decode_kernel_mfma<P, RG, true, true, true>), dim3(kDecodeWorkgroups),
-                           dim3(kDecodeWaves * kWave), 0, stream, books, s, q_rot, static_cast<const uint4 *>(k_pool),
-                           static_cast<const uint32_t *>(v_pool), seq_lens, part_ml, part_acc, nullptr, plan,
-                           static_cast<const unsigned char *>(qjl_pool), q2, pt.table, pt.stride, pt.n_pages);
-        return static_cast<int>(hipGetLastError());
-    } else {
-        return static_cast<int>(hipErrorInvalidValue);
-    }
+    const DeviceBooks books = device_books(cb);
+    hipLaunchKernelGGL((decode_kernel_mfma<P, RG, true, true, true>), dim3(kDecodeWorkgroups),
+                       dim3(kDecodeWaves * kWave), 0, stream, books, s, q_rot, static_cast<const uint4 *>(k_pool),
+                       static_cast<const uint32_t *>(v_pool), seq_lens, part_ml, part_acc, nullptr, plan,
+                       static_cast<const unsigned char *>(qjl_pool), q2, pt.table, pt.stride, pt.n_pages);
+    return static_cast<int>(hipGetLastError());
 }
 
 template <class P>
@@ -1708,22 +1760,17 @@ int launch_decode_vq_plan(const octopus_codebooks_t &cb, const DecodeShape &s, c
     }
 }
 
-// Largest row group whose sign-byte table fits LDS beside the codebook tables (8 at d = 64, 4 at
-// d = 128, 2 at d = 256).
+// bf16 values with the QJL residual.
 template <class P, int RG>
 int launch_decode_qjl_rg(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *cache,
                          const void *qjl, const float *q2, const void *v, const int32_t *seq_lens, float *part_ml,
                          float *part_acc, float *scores_out, int32_t *plan, hipStream_t stream) {
-    if constexpr (qjl_fits<P, RG>()) {
-        const DeviceBooks books = device_books(cb);
-        hipLaunchKernelGGL((decode_kernel_mfma<P, RG, true, true>), dim3(kDecodeWorkgroups),
-                           dim3(kDecodeWaves * kWave), 0, stream, books, s, q_rot, static_cast<const uint4 *>(cache),
-                           static_cast<const uint32_t *>(v), seq_lens, part_ml, part_acc, scores_out, plan,
-                           static_cast<const unsigned char *>(qjl), q2, nullptr, 0, 0);
-        return static_cast<int>(hipGetLastError());
-    } else {
-        return static_cast<int>(hipErrorInvalidValue);
-    }
+    const DeviceBooks books = device_books(cb);
+    hipLaunchKernelGGL((decode_kernel_mfma<P, RG, true, true>), dim3(kDecodeWorkgroups),
+                       dim3(kDecodeWaves * kWave), 0, stream, books, s, q_rot, static_cast<const uint4 *>(cache),
+                       static_cast<const uint32_t *>(v), seq_lens, part_ml, part_acc, scores_out, plan,
+                       static_cast<const unsigned char *>(qjl), q2, nullptr, 0, 0);
+    return static_cast<int>(hipGetLastError());
 }
 
 template <class P>

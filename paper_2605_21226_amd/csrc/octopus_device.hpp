@@ -157,6 +157,19 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
+// Rows of 16 lanes exchanged between two registers: swap16 trades the odd rows of a for the even rows of b
+// (rows 1 and 3 of a, rows 0 and 2 of b), swap32 the upper two rows of a for the lower two of b.
+__device__ __forceinline__ void swap16(float &a, float &b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap32(float &a, float &b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+
 }  // namespace octopus
 
 #endif

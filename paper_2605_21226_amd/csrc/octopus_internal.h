@@ -81,8 +81,7 @@ int launch_decode(const octopus_codebooks_t &cb, const DecodeShape &s, const flo
 int launch_decode_qjl(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *cache,
                       const void *qjl, const float *q2, const void *v, const int32_t *seq_lens, float *part_ml,
                       float *part_acc, float *scores_out, int32_t *work_plan, void *stream);
-// Query rows one workgroup of the QJL decode kernel serves: the largest of 8, 4, 2, 1 whose sign-byte table
-// fits LDS beside the plan's decode tables; 0 if the plan is not built.
+// Query rows one workgroup of the QJL decode kernel serves at most (8); 0 if the plan is not built.
 int qjl_rows_cap(const octopus_plan_t &plan);
 // win_ml / win_acc: the partial of a native-precision window per output row, or NULL
 int launch_merge(const octopus_plan_t &plan, const DecodeShape &s, const float *part_ml, const float *part_acc,
