@@ -9,35 +9,35 @@ bool plan_supported_d128(const octopus_plan_t &);
 bool plan_supported_d256(const octopus_plan_t &);
 #define OCTOPUS_DECL(D)                                                                                            \
     int launch_decode_mfma_d##D(const octopus_codebooks_t &, const DecodeShape &, const float *, const void *,     \
-                                const void *, const int32_t *, float *, float *, float *, int32_t *, void *);      \
+                                const void *, const int32_t *, float *, float *, float *, void *);                 \
     int launch_decode_mfma_scores_d##D(const octopus_codebooks_t &, const DecodeShape &, const float *,            \
                                        const void *, const void *, const int32_t *, float *, float *, float *,     \
-                                       int32_t *, void *);                                                         \
+                                       void *);                                                                    \
     int launch_decode_valu_d##D(const octopus_codebooks_t &, const DecodeShape &, const float *, const void *,     \
-                                const void *, const int32_t *, float *, float *, float *, int32_t *, void *);      \
+                                const void *, const int32_t *, float *, float *, float *, void *);                 \
     int launch_encode_d##D(const octopus_codebooks_t &, const void *, int, int64_t, int64_t, int64_t, int32_t,     \
                            int32_t, int32_t, const uint8_t *, void *, int64_t, const int32_t *, const uint8_t *, void *, \
                            void *);                                                                                \
     int launch_decode_qjl_d##D(const octopus_codebooks_t &, const DecodeShape &, const float *, const void *,      \
                                const void *, const float *, const void *, const int32_t *, float *, float *,       \
-                               float *, int32_t *, void *);                                                        \
+                               float *, void *);                                                                   \
     int qjl_rows_cap_d##D(const octopus_plan_t &);                                                                 \
     int vq_mfma_available_d##D(const octopus_plan_t &, int, int, int);                                             \
     int launch_decode_vq_d##D(const octopus_codebooks_t &, const DecodeShape &, const float *, const void *,       \
-                              const void *, int, int, const int32_t *, float *, float *, float *, int32_t *,       \
+                              const void *, int, int, const int32_t *, float *, float *, float *,                  \
                               void *, const PageTable &);                                                          \
     int launch_encode_rounding_d##D(const octopus_codebooks_t &, const void *, int, int64_t, int64_t, int64_t,     \
                                     int32_t, int32_t, int32_t, const uint8_t *, void *, int64_t, const int32_t *,  \
                                     int32_t, void *);                                                              \
     int launch_decode_paged_d##D(const octopus_codebooks_t &, const DecodeShape &, const float *, const void *,    \
-                                 const void *, const PageTable &, const int32_t *, float *, float *, int32_t *,    \
+                                 const void *, const PageTable &, const int32_t *, float *, float *,               \
                                  void *);                                                                          \
     int launch_encode_paged_d##D(const octopus_codebooks_t &, const void *, int, int64_t, int64_t, int64_t,        \
                                  int32_t, int32_t, int32_t, const uint8_t *, void *, const PageTable &,            \
                                  const int32_t *, const uint8_t *, void *, void *);                                \
     int launch_decode_paged_qjl_d##D(const octopus_codebooks_t &, const DecodeShape &, const float *, const void *, \
                                      const void *, const float *, const void *, const PageTable &, const int32_t *, \
-                                     float *, float *, int32_t *, void *);
+                                     float *, float *, void *);
 OCTOPUS_DECL(64)
 OCTOPUS_DECL(128)
 OCTOPUS_DECL(256)
@@ -78,7 +78,7 @@ int launch_probe_read(const void *data, int64_t bytes, int nontemporal, int n_bl
 // the pairs of the App. D sweep (head dimension 128 only): plain encoder and bf16-value split-K decode
 bool plan_supported_sweep_d128(const octopus_plan_t &);
 int launch_decode_sweep_d128(const octopus_codebooks_t &, const DecodeShape &, const float *, const void *, const void *,
-                             const int32_t *, float *, float *, int32_t *, void *);
+                             const int32_t *, float *, float *, void *);
 int launch_encode_sweep_d128(const octopus_codebooks_t &, const void *, int, int64_t, int64_t, int64_t, int32_t, int32_t,
                              int32_t, const uint8_t *, void *, int64_t, const int32_t *, void *);
 
@@ -99,21 +99,21 @@ bool plan_supported(const octopus_plan_t &plan) {
 
 int launch_decode(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *cache,
                   const void *v, int v_dtype, const int32_t *seq_lens, float *part_ml, float *part_acc,
-                  float *scores_out, int32_t *work_plan, void *stream) {
+                  float *scores_out, int32_t *, void *stream) {
     if (plan_sweep_only(cb.plan)) {
         if (v_dtype != OCTOPUS_DTYPE_BF16 || scores_out != nullptr) return static_cast<int>(hipErrorInvalidValue);
-        return launch_decode_sweep_d128(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, work_plan, stream);
+        return launch_decode_sweep_d128(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, stream);
     }
     // kernel family: 0 matrix cores, 1 matrix cores with score output, 2 vector units (fp32 values)
     const int family = v_dtype == OCTOPUS_DTYPE_BF16 ? (scores_out != nullptr ? 1 : 0) : 2;
 #define OCTOPUS_GO(D)                                                                                                   \
     case D:                                                                                                             \
         return family == 0   ? launch_decode_mfma_d##D(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out,  \
-                                                       work_plan, stream)                                               \
+                                                       stream)                                                          \
                : family == 1 ? launch_decode_mfma_scores_d##D(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc,       \
-                                                              scores_out, work_plan, stream)                            \
+                                                              scores_out, stream)                            \
                              : launch_decode_valu_d##D(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out,  \
-                                                       work_plan, stream);
+                                                       stream);
     switch (cb.plan.head_dim) {
         OCTOPUS_GO(64)
         OCTOPUS_GO(128)
@@ -125,11 +125,11 @@ int launch_decode(const octopus_codebooks_t &cb, const DecodeShape &s, const flo
 
 int launch_decode_vq(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *cache,
                      const void *vq, int v_bits, int v_group, const int32_t *seq_lens, float *part_ml,
-                     float *part_acc, float *scores_out, int32_t *work_plan, void *stream, PageTable pt) {
+                     float *part_acc, float *scores_out, int32_t *, void *stream, PageTable pt) {
     switch (cb.plan.head_dim) {
-        case 64: return launch_decode_vq_d64(cb, s, q_rot, cache, vq, v_bits, v_group, seq_lens, part_ml, part_acc, scores_out, work_plan, stream, pt);
-        case 128: return launch_decode_vq_d128(cb, s, q_rot, cache, vq, v_bits, v_group, seq_lens, part_ml, part_acc, scores_out, work_plan, stream, pt);
-        case 256: return launch_decode_vq_d256(cb, s, q_rot, cache, vq, v_bits, v_group, seq_lens, part_ml, part_acc, scores_out, work_plan, stream, pt);
+        case 64: return launch_decode_vq_d64(cb, s, q_rot, cache, vq, v_bits, v_group, seq_lens, part_ml, part_acc, scores_out, stream, pt);
+        case 128: return launch_decode_vq_d128(cb, s, q_rot, cache, vq, v_bits, v_group, seq_lens, part_ml, part_acc, scores_out, stream, pt);
+        case 256: return launch_decode_vq_d256(cb, s, q_rot, cache, vq, v_bits, v_group, seq_lens, part_ml, part_acc, scores_out, stream, pt);
         default: return static_cast<int>(hipErrorInvalidValue);
     }
 }
@@ -155,11 +155,11 @@ int qjl_rows_cap(const octopus_plan_t &plan) {
 
 int launch_decode_qjl(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *cache,
                       const void *qjl, const float *q2, const void *v, const int32_t *seq_lens, float *part_ml,
-                      float *part_acc, float *scores_out, int32_t *work_plan, void *stream) {
+                      float *part_acc, float *scores_out, int32_t *, void *stream) {
     switch (cb.plan.head_dim) {
-        case 64: return launch_decode_qjl_d64(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, work_plan, stream);
-        case 128: return launch_decode_qjl_d128(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, work_plan, stream);
-        case 256: return launch_decode_qjl_d256(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, work_plan, stream);
+        case 64: return launch_decode_qjl_d64(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream);
+        case 128: return launch_decode_qjl_d128(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream);
+        case 256: return launch_decode_qjl_d256(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream);
         default: return static_cast<int>(hipErrorInvalidValue);
     }
 }
@@ -183,11 +183,11 @@ int launch_encode(const octopus_codebooks_t &cb, const void *keys, int key_dtype
 
 int launch_decode_paged(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *k_pool,
                         const void *v_pool, const PageTable &pt, const int32_t *seq_lens, float *part_ml,
-                        float *part_acc, int32_t *work_plan, void *stream) {
+                        float *part_acc, int32_t *, void *stream) {
     switch (cb.plan.head_dim) {
-        case 64: return launch_decode_paged_d64(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, work_plan, stream);
-        case 128: return launch_decode_paged_d128(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, work_plan, stream);
-        case 256: return launch_decode_paged_d256(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, work_plan, stream);
+        case 64: return launch_decode_paged_d64(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream);
+        case 128: return launch_decode_paged_d128(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream);
+        case 256: return launch_decode_paged_d256(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream);
         default: return static_cast<int>(hipErrorInvalidValue);
     }
 }
@@ -206,11 +206,11 @@ int launch_encode_paged(const octopus_codebooks_t &cb, const void *keys, int key
 
 int launch_decode_paged_qjl(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *k_pool,
                             const void *qjl_pool, const float *q2, const void *v_pool, const PageTable &pt,
-                            const int32_t *seq_lens, float *part_ml, float *part_acc, int32_t *work_plan, void *stream) {
+                            const int32_t *seq_lens, float *part_ml, float *part_acc, int32_t *, void *stream) {
     switch (cb.plan.head_dim) {
-        case 64: return launch_decode_paged_qjl_d64(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, work_plan, stream);
-        case 128: return launch_decode_paged_qjl_d128(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, work_plan, stream);
-        case 256: return launch_decode_paged_qjl_d256(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, work_plan, stream);
+        case 64: return launch_decode_paged_qjl_d64(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream);
+        case 128: return launch_decode_paged_qjl_d128(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream);
+        case 256: return launch_decode_paged_qjl_d256(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream);
         default: return static_cast<int>(hipErrorInvalidValue);
     }
 }
@@ -228,44 +228,47 @@ int launch_encode_rounding(const octopus_codebooks_t &cb, const void *keys, int 
 }
 
 template <int D>
-static int rotate_d(const void *q, int q_dtype, const uint8_t *signs, const DecodeShape &s, float scale, float *q_rot,
-                    const int32_t *seq_lens, int32_t *work_plan, const uint8_t *signs2, float *q2,
-                    hipStream_t stream) {
+static int rotate_d(const DecodeShape &s, float *q_rot, float *q2, hipStream_t stream) {
     constexpr int QS = (3 * ((D + 2) / 3) + 3) & ~3;
     const int64_t rows = static_cast<int64_t>(s.n_seq) * s.n_kv_heads * s.n_row_groups * s.rows_per_pass;
-    hipLaunchKernelGGL((rotate_queries_kernel<D, QS>), dim3(static_cast<unsigned>(rows)), dim3(kWave), 0, stream, q,
-                       q_dtype == OCTOPUS_DTYPE_BF16 ? 1 : 0, signs, s, scale, q_rot, seq_lens, work_plan, signs2, q2);
+    hipLaunchKernelGGL((rotate_queries_kernel<D, QS>), dim3(static_cast<unsigned>(rows)), dim3(kWave), 0, stream, s, q_rot, q2);
     return static_cast<int>(hipGetLastError());
 }
 
 int launch_rotate_queries(const octopus_plan_t &plan, const void *q, int q_dtype, const uint8_t *signs,
-                          const DecodeShape &s, float scale, float *q_rot, const int32_t *seq_lens,
-                          int32_t *work_plan, const uint8_t *signs2, float *q2, void *stream) {
+                          const DecodeShape &s, float scale, float *q_rot, const int32_t *, int32_t *,
+                          const uint8_t *signs2, float *q2, void *stream) {
+    DecodeShape t = s;
+    t.q = q;
+    t.q_is_bf16 = q_dtype == OCTOPUS_DTYPE_BF16 ? 1 : 0;
+    t.signs = signs;
+    t.signs2 = signs2;
+    t.scale = scale;
     hipStream_t st = static_cast<hipStream_t>(stream);
     switch (plan.head_dim) {
-        case 64: return rotate_d<64>(q, q_dtype, signs, s, scale, q_rot, seq_lens, work_plan, signs2, q2, st);
-        case 128: return rotate_d<128>(q, q_dtype, signs, s, scale, q_rot, seq_lens, work_plan, signs2, q2, st);
-        case 256: return rotate_d<256>(q, q_dtype, signs, s, scale, q_rot, seq_lens, work_plan, signs2, q2, st);
+        case 64: return rotate_d<64>(t, q_rot, q2, st);
+        case 128: return rotate_d<128>(t, q_rot, q2, st);
+        case 256: return rotate_d<256>(t, q_rot, q2, st);
         default: return static_cast<int>(hipErrorInvalidValue);
     }
 }
 
 template <int D>
-static int merge_d(const DecodeShape &s, const float *part_ml, const float *part_acc, const int32_t *work_plan,
+static int merge_d(const DecodeShape &s, const float *part_ml, const float *part_acc, const int32_t *seq_lens,
                    float *out, const float *win_ml, const float *win_acc, hipStream_t stream) {
     const int64_t rows = static_cast<int64_t>(s.n_seq) * s.n_q * s.n_q_heads;
     hipLaunchKernelGGL((merge_kernel<D>), dim3(static_cast<unsigned>(rows)), dim3(kWave), 0, stream, s, part_ml,
-                       part_acc, work_plan, out, win_ml, win_acc);
+                       part_acc, seq_lens, out, win_ml, win_acc);
     return static_cast<int>(hipGetLastError());
 }
 
 int launch_merge(const octopus_plan_t &plan, const DecodeShape &s, const float *part_ml, const float *part_acc,
-                 const int32_t *work_plan, float *out, const float *win_ml, const float *win_acc, void *stream) {
+                 const int32_t *seq_lens, float *out, const float *win_ml, const float *win_acc, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     switch (plan.head_dim) {
-        case 64: return merge_d<64>(s, part_ml, part_acc, work_plan, out, win_ml, win_acc, st);
-        case 128: return merge_d<128>(s, part_ml, part_acc, work_plan, out, win_ml, win_acc, st);
-        case 256: return merge_d<256>(s, part_ml, part_acc, work_plan, out, win_ml, win_acc, st);
+        case 64: return merge_d<64>(s, part_ml, part_acc, seq_lens, out, win_ml, win_acc, st);
+        case 128: return merge_d<128>(s, part_ml, part_acc, seq_lens, out, win_ml, win_acc, st);
+        case 256: return merge_d<256>(s, part_ml, part_acc, seq_lens, out, win_ml, win_acc, st);
         default: return static_cast<int>(hipErrorInvalidValue);
     }
 }

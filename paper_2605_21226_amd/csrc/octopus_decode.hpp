@@ -18,9 +18,9 @@ constexpr int kStreamPolicy = 2; // cache policy of the buffer loads of streamed
 
 // ---- D1-D7: split-K main kernels --------------------------------------------------------------
 // Work unit = one wavefront over a range of steps of one (sequence, KV head, row group): the wave walks
-// its 64-token tiles with one key per lane (two tiles per step up to d = 128), keeps its own running
-// (m, l, acc) and writes one partial per query row; nothing is shared between the waves of a workgroup
-// but the LDS tables.  How the ranges are cut (items) is described with the work plan below.
+// its 64-token tiles with one key per lane (two tiles per step up to d = 128) and keeps its own running
+// (m, l, acc); the waves of a workgroup share the LDS tables and merge their results at the end of a segment.
+// How the work is cut into segments is described below.
 //
 // Per tile: the lane loads its record (16 bytes at a time, coalesced thanks to the tile-interleaved
 // layout, one tile ahead of use), unpacks the code fields with compile-time shifts, looks up the
@@ -196,21 +196,21 @@ __device__ __forceinline__ void build_tables(DecodeTables<P> &tb, const DeviceBo
     __syncthreads();
 }
 
-// Work distribution of the split-K kernels.  The kernels are launched with one workgroup per compute
-// unit; the workgroups take ITEMS from a counter until none is left.  An item is a contiguous range of
-// steps (a step = tiles_per_step 64-token tiles) of one (sequence, KV head, row group); its four
-// wavefronts walk that range interleaved (step_begin, step_begin + 4, ...), so that the workgroup
-// streams through memory front to back, and each wavefront writes its own partial result, addressed by
-// (item, wavefront).  The items are cut on the device from the actual sequence lengths (plan below), so
-// that ragged batches are balanced; a batch of equal lengths yields exactly one item per workgroup.
-//
-// plan[0] item counter, plan[1] number of items, plan[2] steps per item (target), plan[3] = 1 when there
-// is at most one item per workgroup (then workgroup b takes item b),
-// plan[4 + s], s = 0 .. n_seq: items before sequence s.  Sequence s has c_s items per (KV head, row
-// group), (KV head, row group) pairs in order, the steps of a pair divided evenly over its c_s items.
-constexpr int kPlanHeader = 4;
+// Work distribution of the split-K kernels.  The steps of the call (a step = tiles_per_step 64-token tiles) lie in a row:
+// sequences in order, the (KV head, row group) pairs of a sequence in order, the steps of a pair in order.  The row is
+// divided evenly over the workgroups (one per compute unit, fewer when there are not item_waves steps for each, so that a
+// short call has few partial results), and a workgroup walks its share as one SEGMENT per pair that it touches: all its
+// wavefronts together, interleaved (step_begin, step_begin + item_waves, ...), so that the workgroup streams through
+// memory front to back.  At the end of a segment the wavefronts' partial results are merged in LDS and one partial per
+// query row goes to memory, at slot (workgroup + pair), which no two segments share.  Every workgroup computes its
+// share from the sequence lengths by itself (one load and a scan of 64 lanes): nothing is planned by an earlier kernel and
+// nothing is handed out at run time.
+// This took the place of up to 2048 items cut by an earlier kernel and taken from a counter, four partials each: on a ragged
+// batch an item was three steps, its start-up several times their work.  Calls with and without (rotation in the kernel and
+// merge in LDS included): 24 sequences of 125 - 8000 tokens, 8 KV heads of 8 query rows, d = 128, paged, with a window:
+// 194 -> 146 us; 32 sequences of 1 k - 64 k, d = 256: 877 -> 830 us; one head, 4096 tokens, fp32: 28.6 -> 21.3 us;
+// equal lengths (16 x 32768): 213.4 -> 211.7 us.
 constexpr int kDecodeWorkgroups = 256;   // one per compute unit
-constexpr int kItemOversubscription = 8; // items per workgroup when one item each cannot balance the batch
 
 __device__ __forceinline__ int steps_of(int len, int max_len, int tiles_per_step) {
     const int l = min(max(len, 0), max_len);
@@ -218,156 +218,227 @@ __device__ __forceinline__ int steps_of(int len, int max_len, int tiles_per_step
     return (tiles + tiles_per_step - 1) / tiles_per_step;
 }
 
-// Executed by one wavefront (block 0 of the query rotation kernel, which precedes the split-K kernel on
-// the stream).
-__device__ __forceinline__ void build_plan(const DecodeShape &shp, const int32_t *seq_lens, int tiles_per_step,
-                                           int32_t *plan, int lane) {
-    const int G = shp.n_kv_heads * shp.n_row_groups;
-    // With at most 64 sequences every lane reads its sequence's length once (the three passes below would
-    // otherwise each wait for memory again: this kernel is on the critical path of a decode call).
-    const bool one_round = shp.n_seq <= kWave;
-    const int own_steps = one_round && lane < shp.n_seq ? steps_of(seq_lens[lane], shp.max_len, tiles_per_step) : 0;
-    auto steps_at = [&](int s0) {
-        if (one_round) return own_steps;
-        const int s = s0 + lane;
-        return s < shp.n_seq ? steps_of(seq_lens[s], shp.max_len, tiles_per_step) : 0;
+// Inclusive sum over the wavefront's lanes.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+    auto take = [](uint32_t x, auto ctrl, auto rows) __attribute__((always_inline)) {
+        return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), decltype(ctrl)::value,
+                                                                 decltype(rows)::value, 0xf, false));
     };
-    long long total = 0;
-    for (int s0 = 0; s0 < shp.n_seq; s0 += kWave) total += steps_at(s0);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o, kWave);
-    total *= G;
-    auto count_items = [&](int item) {
-        long long cnt = 0;
-        for (int s0 = 0; s0 < shp.n_seq; s0 += kWave) cnt += static_cast<long long>((steps_at(s0) + item - 1) / item) * G;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, kWave);
-        return cnt;
-    };
-    int item = static_cast<int>(max(1LL, (total + kDecodeWorkgroups - 1) / kDecodeWorkgroups));
-    if (count_items(item) > kDecodeWorkgroups)
-        item = static_cast<int>(max(1LL, (total + kDecodeWorkgroups * kItemOversubscription - 1) /
-                                             (kDecodeWorkgroups * kItemOversubscription)));
-    int running = 0;
-    for (int s0 = 0; s0 < shp.n_seq; s0 += kWave) {
-        const int s = s0 + lane;
-        const int st = steps_at(s0);
-        const int mine = ((st + item - 1) / item) * G;
-        int incl = mine;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int other = __shfl_up(incl, o, kWave);
-            if (lane >= o) incl += other;
-        }
-        if (s < shp.n_seq) plan[kPlanHeader + s] = running + incl - mine;
-        running += __shfl(incl, kWave - 1, kWave);
-    }
-    if (lane == 0) {
-        plan[kPlanHeader + shp.n_seq] = running;
-        plan[0] = 0;
-        plan[1] = running;
-        plan[2] = item;
-        plan[3] = running <= kDecodeWorkgroups ? 1 : 0;
-    }
+    using std::integral_constant;
+    v += take(v, integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});   // row_shr:1, 2, 4, 8
+    v += take(v, integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+    v += take(v, integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+    v += take(v, integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+    v += take(v, integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});   // row_bcast:15 into rows 1 and 3
+    v += take(v, integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});   // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+__device__ __forceinline__ uint64_t divide(uint64_t a, uint64_t b) {
+    if (((a | b) >> 32) == 0) return static_cast<uint32_t>(a) / static_cast<uint32_t>(b);
+    return a / b;
+}
+
+// Workgroups that share `total` steps, the first step of workgroup b, and the workgroup that has step x.
+__device__ __forceinline__ int span_workgroups(uint64_t total, int item_waves) {
+    const uint64_t full = (total + item_waves - 1) / static_cast<uint32_t>(item_waves);
+    return static_cast<int>(full < static_cast<uint64_t>(kDecodeWorkgroups) ? full : kDecodeWorkgroups);
+}
+__device__ __forceinline__ uint64_t span_first(uint64_t total, int n_wg, int b) {
+    return n_wg == kDecodeWorkgroups ? (total * static_cast<uint32_t>(b)) / kDecodeWorkgroups
+                                     : divide(total * static_cast<uint32_t>(b), static_cast<uint32_t>(n_wg));
+}
+__device__ __forceinline__ int span_owner(uint64_t total, int n_wg, uint64_t x) {
+    return static_cast<int>(divide((x + 1) * static_cast<uint32_t>(n_wg) - 1, total));
 }
 
 struct WaveWork {
     int seq, kvh, grp;
-    int64_t pair, group_id;
+    int64_t pair, group_id, slot;
     int step_begin, step_end, step_stride, step_last, len, n_tiles;
 };
 
-// Item `it` (wave-uniform) -> the wavefront's work.
-__device__ __forceinline__ void item_work(const DecodeShape &shp, const int32_t *plan, const int32_t *seq_lens, int it,
-                                          int wave, int tiles_per_step, WaveWork *ww) {
-    const int32_t *before = plan + kPlanHeader;
-    int lo, b_lo, b_next, len_lo;        // lo: largest s with before[s] <= it (before[n_seq] > it)
-    if (shp.n_seq < kWave) {
-        // one round of loads instead of a chain of dependent ones: lane l holds before[l] and the length of
-        // sequence l; the lanes whose entry is <= it are counted
-        const int l = static_cast<int>(threadIdx.x) & (kWave - 1);
-        const int mine = l <= shp.n_seq ? before[l] : 0x7fffffff;
-        const int my_len = l < shp.n_seq ? seq_lens[l] : 0;
-        const uint64_t le = __ballot(l < shp.n_seq && mine <= it);
-        lo = max(__popcll(le) - 1, 0);
-        b_lo = __shfl(mine, lo, kWave);
-        b_next = __shfl(mine, lo + 1, kWave);
-        len_lo = __shfl(my_len, lo, kWave);
-        lo = __builtin_amdgcn_readfirstlane(lo);
-        b_lo = __builtin_amdgcn_readfirstlane(b_lo);
-        b_next = __builtin_amdgcn_readfirstlane(b_next);
-        len_lo = __builtin_amdgcn_readfirstlane(len_lo);
-    } else {
-        int hi = shp.n_seq;
-        lo = 0;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (before[mid] <= it) lo = mid; else hi = mid;
-        }
-        b_lo = before[lo];
-        b_next = before[lo + 1];
-        len_lo = seq_lens[lo];
-    }
-    const int G = shp.n_kv_heads * shp.n_row_groups;
-    const int c_s = (b_next - b_lo) / G;   // > 0, or `it` would not fall here
-    const int local = it - b_lo;
-    const int gis = local / c_s, chunk = local % c_s;
-    ww->seq = lo;
-    ww->group_id = static_cast<int64_t>(lo) * G + gis;
-    ww->grp = gis % shp.n_row_groups;
-    ww->kvh = gis / shp.n_row_groups;
-    ww->pair = static_cast<int64_t>(lo) * shp.n_kv_heads + ww->kvh;
-    ww->len = min(max(len_lo, 0), shp.max_len);
-    ww->n_tiles = (ww->len + kWave - 1) / kWave;
-    const int n_steps = (ww->n_tiles + tiles_per_step - 1) / tiles_per_step;
-    const int base = n_steps / c_s, rem = n_steps % c_s;
-    const int wb = chunk * base + min(chunk, rem);
-    ww->step_end = wb + base + (chunk < rem ? 1 : 0);
-    ww->step_begin = wb + wave;
-    ww->step_stride = shp.item_waves;
-    ww->step_last = ww->step_begin + (ww->step_begin < ww->step_end
-                                          ? (ww->step_end - 1 - ww->step_begin) / ww->step_stride
-                                          : 0) * ww->step_stride;
-}
+// The share of one workgroup and where it stands in it.  Sequences are looked at 64 at a time, one per lane.
+struct WorkSpan {
+    int chunk;               // first sequence of the 64
+    int lane_len;            // length of sequence chunk + lane
+    uint32_t lane_sum;       // steps per pair of sequences chunk .. chunk + lane
+    uint64_t before;         // steps per pair of the sequences before chunk
+    uint64_t pos, end;       // the workgroup's steps that are left
 
-// Takes the next item for the whole workgroup; false when none is left.  `taken` counts the calls of
-// this workgroup.  With at most one item per workgroup (plan[3] = 1: every batch of equal lengths)
-// workgroup b simply takes item b, without touching the counter.
-__device__ __forceinline__ bool next_item(int32_t *plan, int *slot, int tid, int *taken, int *it) {
-    const int n_items = plan[1];
-    if (plan[3] != 0) {
-        *it = static_cast<int>(blockIdx.x);
-        return (*taken)++ == 0 && *it < n_items;
+    __device__ __forceinline__ void look(const DecodeShape &shp, const int32_t *seq_lens, int lane) {
+        const int s = chunk + lane;
+        lane_len = s < shp.n_seq ? min(max(seq_lens[s], 0), shp.max_len) : 0;
+        lane_sum = wave_scan(static_cast<uint32_t>(steps_of(lane_len, shp.max_len, shp.tiles_per_step)));
     }
-    ++*taken;
-    if (tid == 0) *slot = atomicAdd(&plan[0], 1);
-    __syncthreads();
-    *it = __builtin_amdgcn_readfirstlane(*slot);
-    __syncthreads();
-    return *it < n_items;
+    __device__ __forceinline__ uint32_t chunk_sum() const {
+        return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lane_sum), kWave - 1));
+    }
+    __device__ __forceinline__ void open(const DecodeShape &shp, const int32_t *seq_lens, int lane) {
+        const uint64_t G = static_cast<uint64_t>(shp.n_kv_heads) * shp.n_row_groups;
+        uint64_t total = 0;
+        for (chunk = 0; chunk < shp.n_seq; chunk += kWave) {
+            look(shp, seq_lens, lane);
+            total += chunk_sum();
+        }
+        total *= G;
+        chunk = 0;
+        before = 0;
+        if (shp.n_seq > kWave) look(shp, seq_lens, lane);
+        const int b = static_cast<int>(blockIdx.x), n_wg = span_workgroups(total, shp.item_waves);
+        pos = b < n_wg ? span_first(total, n_wg, b) : 0;
+        end = b < n_wg ? span_first(total, n_wg, b + 1) : 0;
+    }
+    // The next segment (wave-uniform) and this wavefront's part of it; false when the share is done.
+    __device__ __forceinline__ bool next(const DecodeShape &shp, const int32_t *seq_lens, int wave, int lane, WaveWork *ww) {
+        if (pos >= end) return false;
+        const uint64_t G = static_cast<uint64_t>(shp.n_kv_heads) * shp.n_row_groups;
+        while ((before + chunk_sum()) * G <= pos) {   // (more than 64 sequences; a later one holds step pos, so it ends)
+            before += chunk_sum();
+            chunk += kWave;
+            look(shp, seq_lens, lane);
+        }
+        const int l = __ffsll(static_cast<unsigned long long>(__ballot((before + lane_sum) * G > pos))) - 1;
+        const int len = __builtin_amdgcn_readlane(lane_len, l);
+        const uint32_t sum = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lane_sum), l));
+        const int n_steps = steps_of(len, shp.max_len, shp.tiles_per_step);   // > 0: the sequence holds step pos
+        const uint64_t first = (before + sum - static_cast<uint32_t>(n_steps)) * G;
+        const uint64_t local = pos - first, gis = divide(local, static_cast<uint32_t>(n_steps));
+        const uint64_t stop = first + (gis + 1) * static_cast<uint32_t>(n_steps);
+        const uint64_t seg_end = stop < end ? stop : end;
+        const int begin = static_cast<int>(local - gis * static_cast<uint32_t>(n_steps));
+        const int g = static_cast<int>(gis);
+        ww->seq = chunk + l;
+        ww->grp = g % shp.n_row_groups;
+        ww->kvh = g / shp.n_row_groups;
+        ww->group_id = static_cast<int64_t>(ww->seq) * static_cast<int64_t>(G) + g;
+        ww->slot = static_cast<int64_t>(blockIdx.x) + ww->group_id;
+        ww->pair = static_cast<int64_t>(ww->seq) * shp.n_kv_heads + ww->kvh;
+        ww->len = len;
+        ww->n_tiles = (len + kWave - 1) / kWave;
+        ww->step_end = begin + static_cast<int>(seg_end - pos);
+        ww->step_begin = begin + wave;
+        ww->step_stride = shp.item_waves;
+        ww->step_last = ww->step_begin + (ww->step_begin < ww->step_end
+                                              ? (ww->step_end - 1 - ww->step_begin) / ww->step_stride
+                                              : 0) * ww->step_stride;
+        pos = seg_end;
+        return true;
+    }
+};
+
+// A segment's partial results of NW wavefronts, in LDS: acc[wave][row][channel] and ml[wave][row] = (m, l), complete after
+// a barrier, merged into one partial per query row (the flash-decoding identity) at the segment's slot.
+template <int D, int RG, int NW>
+__device__ __forceinline__ void merge_waves(const DecodeShape &shp, const WaveWork &ww, const float *acc, int acc_stride,
+                                            const float *ml, int ml_stride, float *part_ml, float *part_acc, int tid) {
+    for (int e = tid; e < RG * D; e += NW * kWave) {
+        const int r = e / D, c = e % D;
+        if (ww.grp * RG + r >= shp.rows_per_kv) continue;
+        float m = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) m = fmaxf(m, ml[w * ml_stride + 2 * r]);
+        float a = 0.0f, l = 0.0f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float mw = ml[w * ml_stride + 2 * r];
+            const float f = mw == -INFINITY ? 0.0f : exp2_raw((mw - m) * kLog2e);
+            a = fmaf(f, acc[w * acc_stride + e], a);
+            l = fmaf(f, ml[w * ml_stride + 2 * r + 1], l);
+        }
+        part_acc[ww.slot * (RG * D) + e] = a;
+        if (c == 0) {
+            part_ml[(ww.slot * RG + r) * 2] = m;
+            part_ml[(ww.slot * RG + r) * 2 + 1] = l;
+        }
+    }
 }
 
 // Tiles per step of the split-K kernels: up to d = 128 a lane carries two keys (see the kernel).  The host's
-// DecodeShape carries the same number (tiles_per_step) for the kernel that cuts the items.
+// DecodeShape carries the same number (tiles_per_step) for the division of the work.
 template <int D>
 constexpr int decode_keys_per_lane() { return D <= 128 ? 2 : 1; }
 
 // ---- D0: q_rot = scale * H (s . q), one wavefront per query row ------------------------------
-// Output layout per (sequence, KV head, row group): [QS coordinates][RG rows], so that the RG
-// values a key needs for one coordinate are adjacent.  Rows past rows_per_kv and coordinates
-// past d are written as zeros.
+// Lane l holds elements l EPL .. + EPL - 1 of the row, EPL = D / 64.
+// The row as the caller stores it with the signs applied; row = index among the rows of KV head kvh of sequence seq, zeros
+// past the last one.
+template <int D>
+__device__ __forceinline__ void load_query_row(const DecodeShape &s, int seq, int kvh, int row, int lane, float (&x)[D / kWave]) {
+    constexpr int EPL = D / kWave;
+#pragma unroll
+    for (int j = 0; j < EPL; ++j) x[j] = 0.0f;
+    if (row < s.rows_per_kv) {
+        const int qi = row / s.heads_per_kv;
+        const int head = kvh * s.heads_per_kv + row % s.heads_per_kv;
+        const int64_t base = ((static_cast<int64_t>(seq) * s.n_q + qi) * s.n_q_heads + head) * D + lane * EPL;
+        const uint32_t neg = s.signs[kvh * (D / 8) + ((lane * EPL) >> 3)];
+#pragma unroll
+        for (int j = 0; j < EPL; ++j) {
+            const float val = s.q_is_bf16 ? __uint_as_float(static_cast<uint32_t>(static_cast<const uint16_t *>(s.q)[base + j]) << 16)
+                                          : static_cast<const float *>(s.q)[base + j];
+            x[j] = (neg >> ((lane * EPL + j) & 7)) & 1 ? -val : val;
+        }
+    }
+}
+
+// Unnormalised Walsh-Hadamard transform of the row.
+template <int D>
+__device__ __forceinline__ void transform_row(int lane, float (&x)[D / kWave]) {
+    constexpr int EPL = D / kWave;
+    // butterflies over the in-lane bits of the element index ...
+#pragma unroll
+    for (int h = 1; h < EPL; h <<= 1) {
+#pragma unroll
+        for (int j = 0; j < EPL; ++j) {
+            if ((j & h) == 0) {
+                const float a = x[j], b = x[j | h];
+                x[j] = a + b;
+                x[j | h] = a - b;
+            }
+        }
+    }
+    // ... then over the lane bits: the element with the bit clear takes a + b, the other a - b
+#pragma unroll
+    for (int m = 1; m < kWave; m <<= 1) {
+#pragma unroll
+        for (int j = 0; j < EPL; ++j) {
+            const float other = __shfl_xor(x[j], m, kWave);
+            x[j] = (lane & m) ? other - x[j] : x[j] + other;
+        }
+    }
+}
+
+template <int D>
+__device__ __forceinline__ void rotate_row(const DecodeShape &s, int lane, float (&x)[D / kWave]) {
+    transform_row<D>(lane, x);
+    const float norm = s.scale * (D == 64 ? 0.125f : (D == 128 ? 0.08838834764831845f : 0.0625f));
+#pragma unroll
+    for (int j = 0; j < D / kWave; ++j) x[j] *= norm;
+}
+
+// Optional 1-bit QJL residual (Sec. 3.6): q2 = sqrt(pi / (2 d)) * H diag(s') q_rot, from a row rotated already.
+template <int D>
+__device__ __forceinline__ void rotate_row_again(const DecodeShape &s, int kvh, int lane, float (&x)[D / kWave]) {
+    constexpr int EPL = D / kWave;
+    const uint32_t neg = s.signs2[kvh * (D / 8) + ((lane * EPL) >> 3)];
+#pragma unroll
+    for (int j = 0; j < EPL; ++j) x[j] = (neg >> ((lane * EPL + j) & 7)) & 1 ? -x[j] : x[j];
+    transform_row<D>(lane, x);
+    // 1 / sqrt(d) of the Hadamard matrix times sqrt(pi / (2 d)) of the estimator = sqrt(pi / 2) / d
+    const float c = 1.2533141373155003f / static_cast<float>(D);
+#pragma unroll
+    for (int j = 0; j < EPL; ++j) x[j] *= c;
+}
+
+// The kernels with a matrix-core score pass rotate the rows of a segment themselves (the queries of a row group are a few
+// hundred bytes, and a launch of their own cost 4 - 5 us of the call); this kernel serves the others, which read rotated
+// queries from memory.  Output layout per (sequence, KV head, row group): [QS coordinates][RG rows], so that the RG
+// values a key needs for one coordinate are adjacent.  Rows past rows_per_kv and coordinates past d are written as zeros.
 template <int D, int QS>
-__global__ __launch_bounds__(kWave) void rotate_queries_kernel(const void *__restrict__ q, int q_is_bf16,
-                                                                const uint8_t *__restrict__ signs, DecodeShape s,
-                                                                float scale, float *__restrict__ q_rot,
-                                                                const int32_t *__restrict__ seq_lens,
-                                                                int32_t *__restrict__ plan,
-                                                                const uint8_t *__restrict__ signs2,
-                                                                float *__restrict__ q2) {
+__global__ __launch_bounds__(kWave) void rotate_queries_kernel(DecodeShape s, float *__restrict__ q_rot, float *__restrict__ q2) {
     constexpr int EPL = D / kWave;  // elements per lane (1, 2, 4)
     const int lane = threadIdx.x;
-    // block 0 also cuts the work items of the split-K kernel that follows (not used by the many-row kernel)
-    if (blockIdx.x == 0 && plan != nullptr) build_plan(s, seq_lens, s.tiles_per_step, plan, lane);
     const int rg = s.rows_per_pass;
     const int padded_rows = s.n_row_groups * rg;
     const int64_t gid = blockIdx.x;  // (seq, kvh, padded row)
@@ -375,85 +446,49 @@ __global__ __launch_bounds__(kWave) void rotate_queries_kernel(const void *__res
     const int kvh = static_cast<int>((gid / padded_rows) % s.n_kv_heads);
     const int seq = static_cast<int>(gid / (static_cast<int64_t>(padded_rows) * s.n_kv_heads));
     float *dst = q_rot + (gid / rg) * (static_cast<int64_t>(QS) * rg) + (row % rg);
-
     float x[EPL];
-    if (row < s.rows_per_kv) {
-        const int qi = row / s.heads_per_kv;
-        const int head = kvh * s.heads_per_kv + row % s.heads_per_kv;
-        const int64_t base = ((static_cast<int64_t>(seq) * s.n_q + qi) * s.n_q_heads + head) * D + lane * EPL;
-#pragma unroll
-        for (int j = 0; j < EPL; ++j) {
-            const int e = lane * EPL + j;
-            float val = q_is_bf16 ? __uint_as_float(static_cast<uint32_t>(static_cast<const uint16_t *>(q)[base + j]) << 16)
-                                  : static_cast<const float *>(q)[base + j];
-            const bool neg = (signs[kvh * (D / 8) + (e >> 3)] >> (e & 7)) & 1;
-            x[j] = neg ? -val : val;
-        }
-        // butterflies over the in-lane bits of the element index ...
-#pragma unroll
-        for (int h = 1; h < EPL; h <<= 1) {
-#pragma unroll
-            for (int j = 0; j < EPL; ++j) {
-                if ((j & h) == 0) {
-                    const float a = x[j], b = x[j | h];
-                    x[j] = a + b;
-                    x[j | h] = a - b;
-                }
-            }
-        }
-        // ... then over the lane bits: the element with the bit clear takes a + b, the other a - b
-#pragma unroll
-        for (int m = 1; m < kWave; m <<= 1) {
-#pragma unroll
-            for (int j = 0; j < EPL; ++j) {
-                const float other = __shfl_xor(x[j], m, kWave);
-                x[j] = (lane & m) ? other - x[j] : x[j] + other;
-            }
-        }
-        const float norm = scale * (D == 64 ? 0.125f : (D == 128 ? 0.08838834764831845f : 0.0625f));
-#pragma unroll
-        for (int j = 0; j < EPL; ++j) x[j] *= norm;
-    } else {
-#pragma unroll
-        for (int j = 0; j < EPL; ++j) x[j] = 0.0f;
-    }
+    load_query_row<D>(s, seq, kvh, row, lane, x);
+    rotate_row<D>(s, lane, x);
 #pragma unroll
     for (int j = 0; j < EPL; ++j) dst[static_cast<int64_t>(lane * EPL + j) * rg] = x[j];
     for (int e = D + lane; e < QS; e += kWave) dst[static_cast<int64_t>(e) * rg] = 0.0f;
-
-    // Optional 1-bit QJL residual (Sec. 3.6): q2 = sqrt(pi / (2 d)) * H diag(s') q_rot per row, [row][d]
     if (q2 != nullptr) {
+        rotate_row_again<D>(s, kvh, lane, x);
 #pragma unroll
-        for (int j = 0; j < EPL; ++j) {
-            const int e = lane * EPL + j;
-            const bool neg = (signs2[kvh * (D / 8) + (e >> 3)] >> (e & 7)) & 1;
-            x[j] = neg ? -x[j] : x[j];
-        }
+        for (int j = 0; j < EPL; ++j) q2[gid * D + lane * EPL + j] = x[j];
+    }
+}
+
+// The rows of a segment's row group, RG rows over NW wavefronts: requested early (load), rotated into LDS later (store).
+template <class P, int RG, int NW>
+struct SegmentQueries {
+    static constexpr int EPL = P::D / kWave, PER = (RG + NW - 1) / NW;
+    float x[PER][EPL];
+    __device__ __forceinline__ void load(const DecodeShape &s, const WaveWork &ww, int wave, int lane) {
 #pragma unroll
-        for (int h = 1; h < EPL; h <<= 1) {
+        for (int i = 0; i < PER; ++i)
+            if (wave + i * NW < RG) load_query_row<P::D>(s, ww.seq, ww.kvh, ww.grp * RG + wave + i * NW, lane, x[i]);
+    }
+    // rows[r][coordinate], zero past d; rows2[r][coordinate] (or NULL) the second rotation
+    __device__ __forceinline__ void store(const DecodeShape &s, const WaveWork &ww, int wave, int lane, float (*rows)[P::QS],
+                                          float (*rows2)[P::D]) {
 #pragma unroll
-            for (int j = 0; j < EPL; ++j) {
-                if ((j & h) == 0) {
-                    const float a = x[j], b = x[j | h];
-                    x[j] = a + b;
-                    x[j | h] = a - b;
+        for (int i = 0; i < PER; ++i) {
+            const int r = wave + i * NW;
+            if (r < RG) {
+                rotate_row<P::D>(s, lane, x[i]);
+#pragma unroll
+                for (int j = 0; j < EPL; ++j) rows[r][lane * EPL + j] = x[i][j];
+                if (P::D + lane < P::QS) rows[r][P::D + lane] = 0.0f;
+                if (rows2 != nullptr) {
+                    rotate_row_again<P::D>(s, ww.kvh, lane, x[i]);
+#pragma unroll
+                    for (int j = 0; j < EPL; ++j) rows2[r][lane * EPL + j] = x[i][j];
                 }
             }
         }
-#pragma unroll
-        for (int m = 1; m < kWave; m <<= 1) {
-#pragma unroll
-            for (int j = 0; j < EPL; ++j) {
-                const float other = __shfl_xor(x[j], m, kWave);
-                x[j] = (lane & m) ? other - x[j] : x[j] + other;
-            }
-        }
-        // 1 / sqrt(d) of the Hadamard matrix times sqrt(pi / (2 d)) of the estimator = sqrt(pi / 2) / d
-        const float c = 1.2533141373155003f / static_cast<float>(D);
-#pragma unroll
-        for (int j = 0; j < EPL; ++j) q2[gid * D + lane * EPL + j] = x[j] * c;
     }
-}
+};
 
 template <int REP>
 __device__ __forceinline__ uint32_t lane_part(int lane) { return (static_cast<uint32_t>(lane) & (REP - 1)) << 4; }
@@ -620,7 +655,7 @@ __device__ __forceinline__ uint32_t joint_offset(const uint32_t (&w)[P::NWORDS],
 // three products per triplet (hi hi, lo hi, hi lo; the dropped lo lo term is below 2^-16 of the product),
 // accumulated in fp32 by the instruction.
 //
-// Query operands of a work item, staged in LDS by the workgroup: entry (triplet i, row r) = split_triplet of
+// Query operands of a segment, staged in LDS by the workgroup: entry (triplet i, row r) = split_triplet of
 // (q_rot[r][3 i], q_rot[r][3 i + 1], q_rot[r][3 i + 2]); rows are padded to a multiple of four with zeros.
 template <class P, int RG>
 struct QueryOperands {
@@ -739,7 +774,7 @@ constexpr int prob_row() { return KPL * kWave + 8; }  // bf16 per probability ro
 template <class P, int KPL>
 struct DecodeSmemMfma {
     DecodeTables<P> tb;
-    uint16_t pbuf[kDecodeWaves][16][prob_row<KPL>()];
+    __attribute__((aligned(16))) uint16_t pbuf[kDecodeWaves][16][prob_row<KPL>()];
 };
 
 // Optional 1-bit QJL residual (Sec. 3.6).  The correction of a key is a product with signs, sum_j sigma_j q2_j per
@@ -786,7 +821,7 @@ template <class P, int RG, bool SCORES, bool QJL, bool PAGED = false>
 __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void decode_kernel_mfma(
     DeviceBooks books, DecodeShape shp, const float *__restrict__ q_rot, const uint4 *__restrict__ cache,
     const uint32_t *__restrict__ v, const int32_t *__restrict__ seq_lens, float *__restrict__ part_ml,
-    float *__restrict__ part_acc, float *__restrict__ scores_out, int32_t *__restrict__ plan,
+    float *__restrict__ part_acc, float *__restrict__ scores_out,
     const unsigned char *__restrict__ qjl, const float *__restrict__ q2, const int32_t *__restrict__ pt_table,
     int32_t pt_stride, int32_t pt_pages) {
     // (the table as a restrict-qualified kernel argument of its own: its loads are then known not to be
@@ -810,16 +845,23 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
     __shared__ __attribute__((aligned(16))) uint4 qjl_store[QJL ? sizeof(QO) / 16 : 1];
     __shared__ __attribute__((aligned(16))) uint4 qop_store[MX ? P::NTRI * QueryOperands<P, RG>::ROWS : 1];
     const QueryOperands<P, RG> &qop = *reinterpret_cast<const QueryOperands<P, RG> *>(&qop_store[0]);
+    // the wavefronts' results at the end of a segment; at its start the rotated queries lie there (MX)
+    __shared__ float seg_acc[kDecodeWaves][RG][D];
+    __shared__ float seg_ml[kDecodeWaves][RG][2];
+    static_assert(P::QS + D <= kDecodeWaves * D, "both rotations fit");
+    float (*q_rows)[P::QS] = reinterpret_cast<float (*)[P::QS]>(&seg_acc[0][0][0]);
+    float (*q2_rows)[D] = reinterpret_cast<float (*)[D]>(&seg_acc[0][0][0] + RG * P::QS);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, kept in a scalar register
-    for (int e = tid; e < kDecodeWaves * 16 * PROW; e += kDecodeWaves * kWave) (&sm.pbuf[0][0][0])[e] = 0;
-    // The tables are built inside the item loop, after the first item's first loads have been issued:
+    WorkSpan span;
+    span.open(shp, seq_lens, lane);
+    if (span.pos >= span.end) return;   // (whole workgroup, before any barrier)
+    // The tables are built inside the segment loop, after the first segment's first loads have been issued:
     // those do not depend on the tables, and their latency covers the build.
     bool tables_built = false;
 
-    __shared__ int item_slot;
-    // per item (set in the item loop below; the helpers capture them by reference)
+    // per segment (set in the segment loop below; the helpers capture them by reference)
     WaveWork ww;
     const float *qg = q_rot;
     const char *k_region = reinterpret_cast<const char *>(cache);
@@ -1066,8 +1108,8 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
     // the loads of step n's own values into them.  Matrix-core work thus overlaps the vector arithmetic of the
     // scores, and -- what matters more with a single in-order wavefront per SIMD -- the value loads enter the
     // compute unit's memory pipeline a k-step at a time at the pace of the arithmetic, not in one burst per step
-    // whose issue stalls the wavefront.  The first step of an item multiplies zeros (the value registers are
-    // cleared at the item's start), the last step's P.V runs after the loop.  At d = 256 (registers: holding a
+    // whose issue stalls the wavefront.  The first step of a segment multiplies zeros (the value registers are
+    // cleared at the segment's start), the last step's P.V runs after the loop.  At d = 256 (registers: holding a
     // step's values across the score pass spills there) the values are requested at the top of the step and
     // P.V follows the softmax.  The records of the wave's next step are requested first thing
     // and are used one call later.  The step loop below is unrolled by two with the two record buffers
@@ -1205,34 +1247,11 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
     };
     uint32_t w_a[KPL][P::NWORDS], w_b[KPL][P::NWORDS];
     uint32_t sc_a[KPL][4 * QO::WPL + 1], sc_b[KPL][4 * QO::WPL + 1];
-    int it, taken = 0;
-    while (next_item(plan, &item_slot, tid, &taken, &it)) {
-        item_work(shp, plan, seq_lens, it, wave, KPL, &ww);
+    while (span.next(shp, seq_lens, wave, lane, &ww)) {
         qg = q_rot + ww.group_id * (P::QS * RG);
-        if constexpr (QJL) {
-            // A operands of the correction.  Every wavefront is past the previous item here (next_item's barriers, or
-            // this is the workgroup's only item).
-            const float *q2g = q2 + ww.group_id * (RG * D);
-            constexpr int ENTRIES = QO::SETS * QO::STEPS * 64;
-            for (int e = tid; e < ENTRIES; e += kDecodeWaves * kWave) {
-                const int m = e % 16, g = (e / 16) % 4, st = (e / 64) % QO::STEPS, set = e / (64 * QO::STEPS);
-                // query row and part (0 leading, 1 and 2 the remainders) of operand row m
-                const int r = RG <= 4 ? m % 4 : m % 8, part = RG <= 4 ? m / 4 : (set == 0 ? m / 8 : (m < 8 ? 2 : 3));
-                uint32_t h[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    float x = (r < RG && part < 3) ? q2g[r * D + QO::coordinate(g, st, j)] : 0.0f;
-                    h[j] = bf16_rne(x);
-                    for (int t = 0; t < part; ++t) {
-                        x -= __uint_as_float(h[j] << 16);
-                        h[j] = bf16_rne(x);
-                    }
-                }
-                qjl_store[e] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
-            }
-            __syncthreads();
-            j_region = reinterpret_cast<const char *>(qjl) + (PAGED ? 0 : ww.pair * (shp.t_capacity / kWave) * TQ);
-        }
+        SegmentQueries<P, RG, kDecodeWaves> sq;
+        if constexpr (MX) sq.load(shp, ww, wave, lane);
+        if constexpr (QJL) j_region = reinterpret_cast<const char *>(qjl) + (PAGED ? 0 : ww.pair * (shp.t_capacity / kWave) * TQ);
         // Addresses are a wave-uniform base (scalar registers) plus a small per-lane byte offset.
         if constexpr (PAGED) {
             k_region = reinterpret_cast<const char *>(cache);
@@ -1270,9 +1289,10 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
                 if constexpr (QJL) load_sidecar(ww.step_begin, sc_a);
             }
         }
+        // (the rows of the operand that hold no probabilities stay zero)
+        for (int e = lane; e < 16 * PROW / 8; e += kWave) reinterpret_cast<uint4 *>(&sm.pbuf[wave][0][0])[e] = make_uint4(0u, 0u, 0u, 0u);
         if constexpr (AHEAD) {
-            // The first step's P.V pieces multiply zeros (by whatever probabilities the previous item left in
-            // LDS).  The zeros come from loads through an empty descriptor, which move nothing: the wavefront
+            // The first step's P.V pieces multiply zeros by zeros.  The zero values come from loads through an empty descriptor, which move nothing: the wavefront
             // then enters the step loop with the same sequence of outstanding loads as a later iteration has,
             // and the wait counts the compiler derives for the loop are those of the steady state (it takes the
             // stricter of the two ways into the loop).
@@ -1284,23 +1304,45 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
             build_tables<P, MX>(sm.tb, books, tid, kDecodeWaves * kWave);
             tables_built = true;
         }
+        // The segment's rotated queries as matrix-core operands.  Every wavefront has left the step loop of the previous
+        // segment and read its results (the barriers at its end).
         if constexpr (MX) {
-            // The item's rotated queries as matrix-core operands.  Every wavefront is past the previous item
-            // here (next_item's barriers, or this is the workgroup's only item).
+            sq.store(shp, ww, wave, lane, q_rows, QJL ? q2_rows : nullptr);
+            __syncthreads();
             constexpr int ROWS = QueryOperands<P, RG>::ROWS;
             uint4 *dst = reinterpret_cast<uint4 *>(&qop_store[0]);
             for (int e = tid; e < P::NTRI * ROWS; e += kDecodeWaves * kWave) {
                 const int i = e / ROWS, r = e % ROWS;
                 float x = 0.0f, y = 0.0f, z = 0.0f;
-                if (r < RG) {   // (the rotated queries are stored [coordinate][row], zero past d)
-                    x = qg[(3 * i) * RG + r];
-                    y = qg[(3 * i + 1) * RG + r];
-                    z = qg[(3 * i + 2) * RG + r];
+                if (r < RG) {
+                    x = q_rows[r][3 * i];
+                    y = q_rows[r][3 * i + 1];
+                    z = q_rows[r][3 * i + 2];
                 }
                 dst[e] = split_triplet(x, y, z);
             }
-            __syncthreads();
         }
+        if constexpr (QJL) {   // ... and the A operands of the residual's correction
+            const float *q2s = MX ? &q2_rows[0][0] : q2 + ww.group_id * (RG * D);
+            constexpr int ENTRIES = QO::SETS * QO::STEPS * 64;
+            for (int e = tid; e < ENTRIES; e += kDecodeWaves * kWave) {
+                const int m = e % 16, g = (e / 16) % 4, st = (e / 64) % QO::STEPS, set = e / (64 * QO::STEPS);
+                // query row and part (0 leading, 1 and 2 the remainders) of operand row m
+                const int r = RG <= 4 ? m % 4 : m % 8, part = RG <= 4 ? m / 4 : (set == 0 ? m / 8 : (m < 8 ? 2 : 3));
+                uint32_t h[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    float x = (r < RG && part < 3) ? q2s[r * D + QO::coordinate(g, st, j)] : 0.0f;
+                    h[j] = bf16_rne(x);
+                    for (int t = 0; t < part; ++t) {
+                        x -= __uint_as_float(h[j] << 16);
+                        h[j] = bf16_rne(x);
+                    }
+                }
+                qjl_store[e] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+            }
+        }
+        if constexpr (MX || QJL) __syncthreads();
         for (int step = ww.step_begin; step < ww.step_end; step += 2 * ww.step_stride) {
             process_step(step, w_a, w_b, sc_a, sc_b);
             if (step + ww.step_stride < ww.step_end) process_step(step + ww.step_stride, w_b, w_a, sc_b, sc_a);
@@ -1311,25 +1353,26 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
             __builtin_amdgcn_wave_barrier();
         }
 
-        // D7: add the hi and lo partial results (lane groups RP/4 apart) and emit the wave's partial of
-        // this item
-        const int64_t pbase = (static_cast<int64_t>(it) * kDecodeWaves + wave) * RG;
+        // D7: add the hi and lo partial results (lane groups RP/4 apart); the wavefronts' results are merged in LDS
 #pragma unroll
         for (int c = 0; c < CPL; ++c)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float tot = acc[c][i] + __shfl_down(acc[c][i], RP * 4, kWave);
                 const int r = 4 * g4 + i;
-                if (r < RG && ww.grp * RG + r < shp.rows_per_kv) part_acc[(pbase + r) * D + (c / (LANEB / 2)) * (8 * LANEB) + n16 * (LANEB / 2) + c % (LANEB / 2)] = tot;
+                if (r < RG) seg_acc[wave][r][(c / (LANEB / 2)) * (8 * LANEB) + n16 * (LANEB / 2) + c % (LANEB / 2)] = tot;
             }
 #pragma unroll
         for (int r = 0; r < RG; ++r) {
             const float l = wave_sum(l_lane[r]);
             if (lane == 0) {
-                part_ml[(pbase + r) * 2] = m_run[r];
-                part_ml[(pbase + r) * 2 + 1] = l;
+                seg_ml[wave][r][0] = m_run[r];
+                seg_ml[wave][r][1] = l;
             }
         }
+        __syncthreads();
+        merge_waves<D, RG, kDecodeWaves>(shp, ww, &seg_acc[0][0][0], RG * D, &seg_ml[0][0][0], 2 * RG, part_ml, part_acc, tid);
+        __syncthreads();   // (the next segment's queries, or results, take the place)
     }
 }
 
@@ -1340,6 +1383,8 @@ template <class P, int RG>
 struct DecodeSmemValu {
     DecodeTables<P> tb;
     float pbuf[kDecodeWaves][kWave][RG];
+    float seg_acc[kDecodeWaves][RG][P::D];   // the wavefronts' results at the end of a segment
+    float seg_ml[kDecodeWaves][RG][2];
 };
 
 // VQ: the values are group-quantised rows (Sec. 4, "value-side group size"; the "value dequantization" of
@@ -1349,24 +1394,23 @@ template <class P, int RG, bool VQ = false>
 __global__ __launch_bounds__(kDecodeWaves *kWave) void decode_kernel_valu(
     DeviceBooks books, DecodeShape shp, const float *__restrict__ q_rot, const uint4 *__restrict__ cache,
     const float4 *__restrict__ v, const int32_t *__restrict__ seq_lens, float *__restrict__ part_ml,
-    float *__restrict__ part_acc, float *__restrict__ scores_out, int32_t *__restrict__ plan, int v_bits,
-    int v_group) {
+    float *__restrict__ part_acc, float *__restrict__ scores_out, int v_bits, int v_group) {
     constexpr int D = P::D;
     constexpr int LPR = D / 8;          // lanes per value row (8 channels per lane)
     constexpr int KPL = kWave / LPR;    // value rows per wave-wide load
-    constexpr int TPS = decode_keys_per_lane<D>();  // tiles per step of the split sizing
+    constexpr int TPS = decode_keys_per_lane<D>();  // tiles per step
     extern __shared__ __align__(16) unsigned char smem_raw[];
     DecodeSmemValu<P, RG> &sm = *reinterpret_cast<DecodeSmemValu<P, RG> *>(smem_raw);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    WorkSpan span;
+    span.open(shp, seq_lens, lane);
+    if (span.pos >= span.end) return;   // (whole workgroup, before any barrier)
     build_tables<P>(sm.tb, books, tid, kDecodeWaves * kWave);
-    __shared__ int item_slot;
     const int rl = lane % LPR, ko = lane / LPR;
-    int it, taken = 0;
-    while (next_item(plan, &item_slot, tid, &taken, &it)) {
     WaveWork ww;
-    item_work(shp, plan, seq_lens, it, wave, TPS, &ww);
+    while (span.next(shp, seq_lens, wave, lane, &ww)) {
     const float *qg = q_rot + ww.group_id * (P::QS * RG);
     const uint4 *region = cache + ww.pair * (shp.t_capacity * P::GRANULES);
     const int64_t v_row0 = ww.pair * shp.t_capacity;
@@ -1479,7 +1523,7 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) void decode_kernel_valu(
         __builtin_amdgcn_wave_barrier();
     }
 
-    // D7: fold the KPL lane groups and emit the wave's partial
+    // D7: fold the KPL lane groups; the wavefronts' results are merged in LDS
 #pragma unroll
     for (int o = LPR; o < kWave; o <<= 1)
 #pragma unroll
@@ -1489,24 +1533,27 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) void decode_kernel_valu(
 #pragma unroll
     for (int r = 0; r < RG; ++r) {
         const float l = wave_sum(l_lane[r]);
-        const int64_t prow = (static_cast<int64_t>(it) * kDecodeWaves + wave) * RG + r;
-        if (lane == 0) { part_ml[prow * 2] = m_run[r]; part_ml[prow * 2 + 1] = l; }
-        if (ww.grp * RG + r >= shp.rows_per_kv) continue;
+        if (lane == 0) { sm.seg_ml[wave][r][0] = m_run[r]; sm.seg_ml[wave][r][1] = l; }
         if (ko == 0) {
 #pragma unroll
-            for (int c = 0; c < 8; ++c) part_acc[prow * D + rl * 8 + c] = acc[r][c];
+            for (int c = 0; c < 8; ++c) sm.seg_acc[wave][r][rl * 8 + c] = acc[r][c];
         }
     }
-    }   // items
+    __syncthreads();
+    merge_waves<D, RG, kDecodeWaves>(shp, ww, &sm.seg_acc[0][0][0], RG * D, &sm.seg_ml[0][0][0], 2 * RG, part_ml, part_acc, tid);
+    __syncthreads();
+    }   // segments
 }
 
 // ---- D8: merge of the split partials, one wavefront per output row -----------------------------------
 // out = sum_j w_j acc_j / sum_j w_j l_j with w_j = exp(m_j - max_j m_j) (the flash-decoding identity).
 // A split without tokens has m = -inf, l = 0 and a zero accumulator, so it needs no special case.
+// Bound by latency (one load for the lengths, then the partials): with one partial per segment instead of four per item
+// of work, a long sequence has a quarter of the rows to read (one head over 4096 tokens: 11.6 us with 128 partials).
 template <int D>
 __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, const float *__restrict__ part_ml,
                                                       const float *__restrict__ part_acc,
-                                                      const int32_t *__restrict__ plan, float *__restrict__ out,
+                                                      const int32_t *__restrict__ seq_lens, float *__restrict__ out,
                                                       const float *__restrict__ win_ml,
                                                       const float *__restrict__ win_acc) {
     // win_ml / win_acc (or NULL): one more partial per output row, that of a native-precision window
@@ -1522,22 +1569,41 @@ __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, const flo
     const int row = qi * shp.heads_per_kv + head % shp.heads_per_kv;
     const int grp = row / shp.rows_per_pass, r = row % shp.rows_per_pass;
     // Partial j of this row is at prow0 + j * pstride, j < n_part.  The many-row kernel (blocks of 128 or 256 rows):
-    // one partial per split, adjacent.  Otherwise: the items of this row's (sequence, KV head, row group)
-    // are consecutive, each with one partial per wavefront, RG rows apart.
+    // one partial per split, adjacent.  Otherwise: one per segment of this row's (sequence, KV head, row group); the
+    // segments' slots are consecutive, one per workgroup that has steps of the pair (the work distribution above).
     int64_t prow0;
     int n_part, pstride;
-    if (plan == nullptr) {
+    if (shp.rows_per_pass >= 128) {
         prow0 = (((static_cast<int64_t>(seq) * shp.n_kv_heads + kvh) * shp.n_row_groups + grp) * shp.rows_per_pass + r) *
                 shp.n_splits;
         n_part = shp.n_splits;
         pstride = 1;
     } else {
-        const int G = shp.n_kv_heads * shp.n_row_groups;
-        const int before = plan[kPlanHeader + seq];
-        const int c_s = (plan[kPlanHeader + seq + 1] - before) / G;
-        const int64_t first = before + static_cast<int64_t>(kvh * shp.n_row_groups + grp) * c_s;
-        prow0 = first * shp.item_waves * shp.rows_per_pass + r;
-        n_part = c_s * shp.item_waves;
+        const uint64_t G = static_cast<uint64_t>(shp.n_kv_heads) * shp.n_row_groups;
+        uint64_t total = 0, first = 0;
+        int own = 0;
+        for (int s0 = 0; s0 < shp.n_seq; s0 += kWave) {
+            const int s = s0 + lane;
+            const int st = s < shp.n_seq ? steps_of(seq_lens[s], shp.max_len, shp.tiles_per_step) : 0;
+            const uint32_t sum = wave_scan(static_cast<uint32_t>(st));
+            if (seq >= s0 && seq < s0 + kWave) {
+                own = __builtin_amdgcn_readlane(st, seq - s0);
+                first = total + static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sum), seq - s0)) -
+                        static_cast<uint32_t>(own);
+            }
+            total += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sum), kWave - 1));
+        }
+        total *= G;
+        const int g = kvh * shp.n_row_groups + grp;
+        first = first * G + static_cast<uint64_t>(g) * static_cast<uint32_t>(own);
+        const int n_wg = span_workgroups(total, shp.item_waves);
+        n_part = 0;
+        int wg = 0;
+        if (own > 0) {
+            wg = span_owner(total, n_wg, first);
+            n_part = span_owner(total, n_wg, first + static_cast<uint32_t>(own) - 1) - wg + 1;
+        }
+        prow0 = (wg + static_cast<int64_t>(seq) * static_cast<int64_t>(G) + g) * shp.rows_per_pass + r;
         pstride = shp.rows_per_pass;
     }
     // The first UN accumulator rows are requested before anything waits for the (m, l) pairs: their addresses do
@@ -1616,12 +1682,12 @@ int launch_decode_mq(const octopus_codebooks_t &cb, const DecodeShape &s, const 
 template <class P, int RG, bool SCORES>
 int launch_decode_mfma_rg(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *cache,
                           const void *v, const int32_t *seq_lens, float *part_ml, float *part_acc, float *scores_out,
-                          int32_t *plan, hipStream_t stream) {
+                          hipStream_t stream) {
     const DeviceBooks books = device_books(cb);
-    // one workgroup per compute unit; they share the items of the plan
+    // one workgroup per compute unit; they share the steps of the call
     hipLaunchKernelGGL((decode_kernel_mfma<P, RG, SCORES, false>), dim3(kDecodeWorkgroups), dim3(kDecodeWaves * kWave),
                        0, stream, books, s, q_rot, static_cast<const uint4 *>(cache), static_cast<const uint32_t *>(v),
-                       seq_lens, part_ml, part_acc, scores_out, plan, nullptr, nullptr, nullptr, 0, 0);
+                       seq_lens, part_ml, part_acc, scores_out, nullptr, nullptr, nullptr, 0, 0);
     return static_cast<int>(hipGetLastError());
 }
 
@@ -1629,11 +1695,11 @@ int launch_decode_mfma_rg(const octopus_codebooks_t &cb, const DecodeShape &s, c
 template <class P, int RG>
 int launch_decode_paged_rg(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *k_pool,
                            const void *v_pool, const PageTable &pt, const int32_t *seq_lens, float *part_ml,
-                           float *part_acc, int32_t *plan, hipStream_t stream) {
+                           float *part_acc, hipStream_t stream) {
     const DeviceBooks books = device_books(cb);
     hipLaunchKernelGGL((decode_kernel_mfma<P, RG, false, false, true>), dim3(kDecodeWorkgroups),
                        dim3(kDecodeWaves * kWave), 0, stream, books, s, q_rot, static_cast<const uint4 *>(k_pool),
-                       static_cast<const uint32_t *>(v_pool), seq_lens, part_ml, part_acc, nullptr, plan, nullptr,
+                       static_cast<const uint32_t *>(v_pool), seq_lens, part_ml, part_acc, nullptr, nullptr,
                        nullptr, pt.table, pt.stride, pt.n_pages);
     return static_cast<int>(hipGetLastError());
 }
@@ -1641,12 +1707,12 @@ int launch_decode_paged_rg(const octopus_codebooks_t &cb, const DecodeShape &s, 
 template <class P>
 int launch_decode_paged_plan(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot,
                              const void *k_pool, const void *v_pool, const PageTable &pt, const int32_t *seq_lens,
-                             float *part_ml, float *part_acc, int32_t *plan, hipStream_t stream) {
+                             float *part_ml, float *part_acc, hipStream_t stream) {
     switch (s.rows_per_pass) {
-        case 1: return launch_decode_paged_rg<P, 1>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, plan, stream);
-        case 2: return launch_decode_paged_rg<P, 2>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, plan, stream);
-        case 4: return launch_decode_paged_rg<P, 4>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, plan, stream);
-        case 8: return launch_decode_paged_rg<P, 8>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, plan, stream);
+        case 1: return launch_decode_paged_rg<P, 1>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream);
+        case 2: return launch_decode_paged_rg<P, 2>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream);
+        case 4: return launch_decode_paged_rg<P, 4>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream);
+        case 8: return launch_decode_paged_rg<P, 8>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream);
         case 128:
         case 256:   // the many-row kernel (d <= 128), which takes the page table as an argument
             if constexpr (P::D <= 128) return launch_decode_mq<P>(cb, s, q_rot, k_pool, v_pool, seq_lens, part_ml, part_acc, stream, pt);
@@ -1660,11 +1726,11 @@ template <class P, int RG>
 int launch_decode_paged_qjl_rg(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot,
                                const void *k_pool, const void *qjl_pool, const float *q2, const void *v_pool,
                                const PageTable &pt, const int32_t *seq_lens, float *part_ml, float *part_acc,
-                               int32_t *plan, hipStream_t stream) {
+                               hipStream_t stream) {
     const DeviceBooks books = device_books(cb);
     hipLaunchKernelGGL((decode_kernel_mfma<P, RG, true, true, true>), dim3(kDecodeWorkgroups),
                        dim3(kDecodeWaves * kWave), 0, stream, books, s, q_rot, static_cast<const uint4 *>(k_pool),
-                       static_cast<const uint32_t *>(v_pool), seq_lens, part_ml, part_acc, nullptr, plan,
+                       static_cast<const uint32_t *>(v_pool), seq_lens, part_ml, part_acc, nullptr,
                        static_cast<const unsigned char *>(qjl_pool), q2, pt.table, pt.stride, pt.n_pages);
     return static_cast<int>(hipGetLastError());
 }
@@ -1673,12 +1739,12 @@ template <class P>
 int launch_decode_paged_qjl_plan(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot,
                                  const void *k_pool, const void *qjl_pool, const float *q2, const void *v_pool,
                                  const PageTable &pt, const int32_t *seq_lens, float *part_ml, float *part_acc,
-                                 int32_t *plan, hipStream_t stream) {
+                                 hipStream_t stream) {
     switch (s.rows_per_pass) {
-        case 1: return launch_decode_paged_qjl_rg<P, 1>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, plan, stream);
-        case 2: return launch_decode_paged_qjl_rg<P, 2>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, plan, stream);
-        case 4: return launch_decode_paged_qjl_rg<P, 4>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, plan, stream);
-        case 8: return launch_decode_paged_qjl_rg<P, 8>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, plan, stream);
+        case 1: return launch_decode_paged_qjl_rg<P, 1>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream);
+        case 2: return launch_decode_paged_qjl_rg<P, 2>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream);
+        case 4: return launch_decode_paged_qjl_rg<P, 4>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream);
+        case 8: return launch_decode_paged_qjl_rg<P, 8>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream);
         default: return static_cast<int>(hipErrorInvalidValue);
     }
 }
@@ -1686,13 +1752,13 @@ int launch_decode_paged_qjl_plan(const octopus_codebooks_t &cb, const DecodeShap
 template <class P, bool SCORES>
 int launch_decode_mfma_plan(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot,
                             const void *cache, const void *v, const int32_t *seq_lens, float *part_ml,
-                            float *part_acc, float *scores_out, int32_t *plan, hipStream_t stream) {
+                            float *part_acc, float *scores_out, hipStream_t stream) {
     if ((scores_out != nullptr) != SCORES) return static_cast<int>(hipErrorInvalidValue);
     switch (s.rows_per_pass) {
-        case 1: return launch_decode_mfma_rg<P, 1, SCORES>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, plan, stream);
-        case 2: return launch_decode_mfma_rg<P, 2, SCORES>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, plan, stream);
-        case 4: return launch_decode_mfma_rg<P, 4, SCORES>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, plan, stream);
-        case 8: return launch_decode_mfma_rg<P, 8, SCORES>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, plan, stream);
+        case 1: return launch_decode_mfma_rg<P, 1, SCORES>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, stream);
+        case 2: return launch_decode_mfma_rg<P, 2, SCORES>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, stream);
+        case 4: return launch_decode_mfma_rg<P, 4, SCORES>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, stream);
+        case 8: return launch_decode_mfma_rg<P, 8, SCORES>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, stream);
         case 128:
         case 256:   // the many-row kernel: 256 rows per workgroup at d = 64, 128 at d = 128
             if constexpr (P::D <= 128 && !SCORES)
@@ -1706,7 +1772,7 @@ int launch_decode_mfma_plan(const octopus_codebooks_t &cb, const DecodeShape &s,
 template <class P, int RG>
 int launch_decode_valu_rg(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *cache,
                           const void *v, const int32_t *seq_lens, float *part_ml, float *part_acc, float *scores_out,
-                          int32_t *plan, hipStream_t stream) {
+                          hipStream_t stream) {
     const DeviceBooks books = device_books(cb);
     const size_t smem = sizeof(DecodeSmemValu<P, RG>);
     const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(&decode_kernel_valu<P, RG>),
@@ -1714,19 +1780,19 @@ int launch_decode_valu_rg(const octopus_codebooks_t &cb, const DecodeShape &s, c
     if (err != hipSuccess) return static_cast<int>(err);
     hipLaunchKernelGGL((decode_kernel_valu<P, RG>), dim3(kDecodeWorkgroups), dim3(kDecodeWaves * kWave), smem, stream,
                        books, s, q_rot, static_cast<const uint4 *>(cache), static_cast<const float4 *>(v), seq_lens,
-                       part_ml, part_acc, scores_out, plan, 0, 0);
+                       part_ml, part_acc, scores_out, 0, 0);
     return static_cast<int>(hipGetLastError());
 }
 
 template <class P>
 int launch_decode_valu_plan(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot,
                             const void *cache, const void *v, const int32_t *seq_lens, float *part_ml,
-                            float *part_acc, float *scores_out, int32_t *plan, hipStream_t stream) {
+                            float *part_acc, float *scores_out, hipStream_t stream) {
     switch (s.rows_per_pass) {
-        case 1: return launch_decode_valu_rg<P, 1>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, plan, stream);
-        case 2: return launch_decode_valu_rg<P, 2>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, plan, stream);
-        case 4: return launch_decode_valu_rg<P, 4>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, plan, stream);
-        case 8: return launch_decode_valu_rg<P, 8>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, plan, stream);
+        case 1: return launch_decode_valu_rg<P, 1>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, stream);
+        case 2: return launch_decode_valu_rg<P, 2>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, stream);
+        case 4: return launch_decode_valu_rg<P, 4>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, stream);
+        case 8: return launch_decode_valu_rg<P, 8>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, stream);
         default: return static_cast<int>(hipErrorInvalidValue);
     }
 }
@@ -1735,7 +1801,7 @@ int launch_decode_valu_plan(const octopus_codebooks_t &cb, const DecodeShape &s,
 template <class P, int RG>
 int launch_decode_vq_rg(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *cache,
                         const void *vq, int v_bits, int v_group, const int32_t *seq_lens, float *part_ml,
-                        float *part_acc, float *scores_out, int32_t *plan, hipStream_t stream) {
+                        float *part_acc, float *scores_out, hipStream_t stream) {
     const DeviceBooks books = device_books(cb);
     const size_t smem = sizeof(DecodeSmemValu<P, RG>);
     hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(&decode_kernel_valu<P, RG, true>),
@@ -1743,19 +1809,19 @@ int launch_decode_vq_rg(const octopus_codebooks_t &cb, const DecodeShape &s, con
     if (err != hipSuccess) return static_cast<int>(err);
     hipLaunchKernelGGL((decode_kernel_valu<P, RG, true>), dim3(kDecodeWorkgroups), dim3(kDecodeWaves * kWave), smem,
                        stream, books, s, q_rot, static_cast<const uint4 *>(cache), static_cast<const float4 *>(vq),
-                       seq_lens, part_ml, part_acc, scores_out, plan, v_bits, v_group);
+                       seq_lens, part_ml, part_acc, scores_out, v_bits, v_group);
     return static_cast<int>(hipGetLastError());
 }
 
 template <class P>
 int launch_decode_vq_plan(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *cache,
                           const void *vq, int v_bits, int v_group, const int32_t *seq_lens, float *part_ml,
-                          float *part_acc, float *scores_out, int32_t *plan, hipStream_t stream) {
+                          float *part_acc, float *scores_out, hipStream_t stream) {
     switch (s.rows_per_pass) {
-        case 1: return launch_decode_vq_rg<P, 1>(cb, s, q_rot, cache, vq, v_bits, v_group, seq_lens, part_ml, part_acc, scores_out, plan, stream);
-        case 2: return launch_decode_vq_rg<P, 2>(cb, s, q_rot, cache, vq, v_bits, v_group, seq_lens, part_ml, part_acc, scores_out, plan, stream);
-        case 4: return launch_decode_vq_rg<P, 4>(cb, s, q_rot, cache, vq, v_bits, v_group, seq_lens, part_ml, part_acc, scores_out, plan, stream);
-        case 8: return launch_decode_vq_rg<P, 8>(cb, s, q_rot, cache, vq, v_bits, v_group, seq_lens, part_ml, part_acc, scores_out, plan, stream);
+        case 1: return launch_decode_vq_rg<P, 1>(cb, s, q_rot, cache, vq, v_bits, v_group, seq_lens, part_ml, part_acc, scores_out, stream);
+        case 2: return launch_decode_vq_rg<P, 2>(cb, s, q_rot, cache, vq, v_bits, v_group, seq_lens, part_ml, part_acc, scores_out, stream);
+        case 4: return launch_decode_vq_rg<P, 4>(cb, s, q_rot, cache, vq, v_bits, v_group, seq_lens, part_ml, part_acc, scores_out, stream);
+        case 8: return launch_decode_vq_rg<P, 8>(cb, s, q_rot, cache, vq, v_bits, v_group, seq_lens, part_ml, part_acc, scores_out, stream);
         default: return static_cast<int>(hipErrorInvalidValue);
     }
 }
@@ -1764,11 +1830,11 @@ int launch_decode_vq_plan(const octopus_codebooks_t &cb, const DecodeShape &s, c
 template <class P, int RG>
 int launch_decode_qjl_rg(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *cache,
                          const void *qjl, const float *q2, const void *v, const int32_t *seq_lens, float *part_ml,
-                         float *part_acc, float *scores_out, int32_t *plan, hipStream_t stream) {
+                         float *part_acc, float *scores_out, hipStream_t stream) {
     const DeviceBooks books = device_books(cb);
     hipLaunchKernelGGL((decode_kernel_mfma<P, RG, true, true>), dim3(kDecodeWorkgroups),
                        dim3(kDecodeWaves * kWave), 0, stream, books, s, q_rot, static_cast<const uint4 *>(cache),
-                       static_cast<const uint32_t *>(v), seq_lens, part_ml, part_acc, scores_out, plan,
+                       static_cast<const uint32_t *>(v), seq_lens, part_ml, part_acc, scores_out,
                        static_cast<const unsigned char *>(qjl), q2, nullptr, 0, 0);
     return static_cast<int>(hipGetLastError());
 }
@@ -1777,12 +1843,12 @@ template <class P>
 int launch_decode_qjl_plan(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot,
                            const void *cache, const void *qjl, const float *q2, const void *v,
                            const int32_t *seq_lens, float *part_ml, float *part_acc, float *scores_out,
-                           int32_t *plan, hipStream_t stream) {
+                           hipStream_t stream) {
     switch (s.rows_per_pass) {
-        case 1: return launch_decode_qjl_rg<P, 1>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, plan, stream);
-        case 2: return launch_decode_qjl_rg<P, 2>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, plan, stream);
-        case 4: return launch_decode_qjl_rg<P, 4>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, plan, stream);
-        case 8: return launch_decode_qjl_rg<P, 8>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, plan, stream);
+        case 1: return launch_decode_qjl_rg<P, 1>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream);
+        case 2: return launch_decode_qjl_rg<P, 2>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream);
+        case 4: return launch_decode_qjl_rg<P, 4>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream);
+        case 8: return launch_decode_qjl_rg<P, 8>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream);
         default: return static_cast<int>(hipErrorInvalidValue);
     }
 }

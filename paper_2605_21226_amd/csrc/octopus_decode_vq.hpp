@@ -20,7 +20,7 @@ namespace octopus {
 //   * the wavefront copies a step's rows as they lie in memory (16 bytes per lane and load, whole cache
 //     lines per instruction, one step ahead of use) into LDS;
 //   * after the softmax lane = key holds its probabilities; it reads the scales and zero points of ITS row,
-//     adds its share of the second sum to per-lane accumulators (reduced over the wave once per work item)
+//     adds its share of the second sum to per-lane accumulators (reduced over the wave once per segment)
 //     and writes the products p scale, split into two bf16 numbers (nearest, then the remainder), to LDS in
 //     the order the A operands want them: [group][part][row][key slot];
 //   * lane (n, g) of the MFMA owns, of every 64-channel piece of a row, the four channels 4 n .. 4 n + 3:
@@ -105,7 +105,7 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
     __attribute__((amdgpu_waves_per_eu(vq_waves<P, RG, VB, VG>() / 4, vq_waves<P, RG, VB, VG>() / 4))) void decode_kernel_vq_mfma(
     DeviceBooks books, DecodeShape shp, const float *__restrict__ q_rot, const uint4 *__restrict__ cache,
     const unsigned char *__restrict__ vq, const int32_t *__restrict__ seq_lens, float *__restrict__ part_ml,
-    float *__restrict__ part_acc, int32_t *__restrict__ plan, PageTable pt) {
+    float *__restrict__ part_acc, PageTable pt) {
     // pt.table (or NULL): `cache` and `vq` are pools of 64-token pages, [page][KV head] each a key tile of the cache
     // layout and 64 value rows; logical tile j of sequence s lives in page pt.table[s * pt.stride + j] (ids outside
     // the pool are clamped: a wrong table reads wrong pages, never outside the pools).
@@ -128,8 +128,15 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // the segment's rotated queries (MX) lie where the scaled probabilities go later, a wavefront's results at the segment's
+    // end in its own staging buffer, their (m, l) in its zbuf
+    static_assert(RG * P::QS * 4 <= sizeof(sm.xs), "rotated queries fit");
+    static_assert(RG * D * 4 <= STEP_BYTES && 2 * RG <= Gm::ZP, "a wavefront's results fit");
+    float (*q_rows)[P::QS] = reinterpret_cast<float (*)[P::QS]>(&sm.xs[0][0][0][0][0]);
+    WorkSpan span;
+    span.open(shp, seq_lens, lane);
+    if (span.pos >= span.end) return;   // (whole workgroup, before any barrier)
     bool tables_built = false;
-    __shared__ int item_slot;
     WaveWork ww;
     const float *qg = q_rot;
     const char *k_region = reinterpret_cast<const char *>(cache);
@@ -164,7 +171,7 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
         const int tile = max(min(step * KPL, ww.n_tiles - 1), 0);
         return pt.table[static_cast<int64_t>(ww.seq) * pt.stride + tile + lane_zero];
     };
-    // position of a page's tile of this item's KV head in the pools, in tiles
+    // position of a page's tile of this segment's KV head in the pools, in tiles
     auto page_slot = [&](int asked) -> int64_t {
         const int id = __builtin_amdgcn_readfirstlane(asked);
         return static_cast<int64_t>(min(max(id, 0), pt.n_pages - 1)) * shp.n_kv_heads + ww.kvh;
@@ -428,10 +435,10 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
         __builtin_amdgcn_wave_barrier();
     };
 
-    int it, taken = 0;
-    while (next_item(plan, &item_slot, tid, &taken, &it)) {
-        item_work(shp, plan, seq_lens, it, wave, KPL, &ww);
+    while (span.next(shp, seq_lens, wave, lane, &ww)) {
         qg = q_rot + ww.group_id * (P::QS * RG);
+        SegmentQueries<P, RG, NWV> sq;
+        if constexpr (MX) sq.load(shp, ww, wave, lane);
         k_region = reinterpret_cast<const char *>(cache) + (paged ? 0 : ww.pair * shp.t_capacity * (P::GRANULES * 16));
         v_pair = reinterpret_cast<const char *>(vq) + (paged ? 0 : ww.pair * shp.t_capacity * RB);
         {   // the record pointer loses its "read-only" provenance: see decode_kernel_mfma
@@ -465,18 +472,20 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
             build_tables<P, MX>(sm.tb, books, tid, NWV * kWave);
             tables_built = true;
         }
+        // The segment's rotated queries as matrix-core operands.  Every wavefront is past the previous segment's merge (the
+        // barrier at its end).
         if constexpr (MX) {
-            // The item's rotated queries as matrix-core operands.  Every wavefront is past the previous item
-            // here (next_item's barriers, or this is the workgroup's only item).
+            sq.store(shp, ww, wave, lane, q_rows, nullptr);
+            __syncthreads();
             constexpr int ROWS = QueryOperands<P, RG>::ROWS;
             uint4 *dst = reinterpret_cast<uint4 *>(&qop_store[0]);
             for (int e = tid; e < P::NTRI * ROWS; e += NWV * kWave) {
                 const int i = e / ROWS, r = e % ROWS;
                 float x = 0.0f, y = 0.0f, z = 0.0f;
                 if (r < RG) {
-                    x = qg[(3 * i) * RG + r];
-                    y = qg[(3 * i + 1) * RG + r];
-                    z = qg[(3 * i + 2) * RG + r];
+                    x = q_rows[r][3 * i];
+                    y = q_rows[r][3 * i + 1];
+                    z = q_rows[r][3 * i + 2];
                 }
                 dst[e] = split_triplet(x, y, z);
             }
@@ -494,9 +503,9 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
             }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        // ... which add the leading-part and remainder rows of their group (lane groups 16 or 32 lanes apart)
-        // and emit the wave's partial of this item
-        const int64_t pbase = (static_cast<int64_t>(it) * NWV + wave) * RG;
+        // ... which add the leading-part and remainder rows of their group (lane groups 16 or 32 lanes apart); the
+        // wavefronts' results are merged in LDS
+        float *seg_acc = reinterpret_cast<float *>(stage_w);
         const int lgrp = (4 * n16) / VG;                 // group of this lane's columns within a piece
         const int a_sel = lgrp / GPA, member = lgrp % GPA;
         const bool holder = RP == 4 ? g4 == 2 * member : g4 < 2;
@@ -513,27 +522,30 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
                     tot = a_sel == hh ? t : tot;
                 }
                 const int r = RP == 4 ? i : 4 * g4 + i;
-                if (holder && ww.grp * RG + r < shp.rows_per_kv)
-                    part_acc[(pbase + r) * D + channel] = tot + sm.zbuf[wave][group * RG + (r & (RG - 1))];
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < RG; ++r) {
-            const float l = wave_sum(l_lane[r]);
-            if (lane == 0) {
-                part_ml[(pbase + r) * 2] = m_run[r];
-                part_ml[(pbase + r) * 2 + 1] = l;
+                if (holder) seg_acc[r * D + channel] = tot + sm.zbuf[wave][group * RG + (r & (RG - 1))];
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int r = 0; r < RG; ++r) {
+            const float l = wave_sum(l_lane[r]);
+            if (lane == 0) {
+                sm.zbuf[wave][2 * r] = m_run[r];
+                sm.zbuf[wave][2 * r + 1] = l;
+            }
+        }
+        __syncthreads();
+        merge_waves<D, RG, NWV>(shp, ww, reinterpret_cast<const float *>(&sm.stage[0][0]), STEP_BYTES / 4, &sm.zbuf[0][0],
+                                Gm::ZP, part_ml, part_acc, tid);
+        __syncthreads();
     }
 }
 
 // -1: no kernel for this shape (the caller falls back to the vector-unit kernel).
 template <class P, int RG, int VB, int VG>
 int launch_decode_vq_mfma_one(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *cache,
-                              const void *vq, const int32_t *seq_lens, float *part_ml, float *part_acc, int32_t *plan,
+                              const void *vq, const int32_t *seq_lens, float *part_ml, float *part_acc,
                               hipStream_t stream, const PageTable &pt) {
     if constexpr (vq_mfma_fits<P, RG, VB, VG>()) {
         const DeviceBooks books = device_books(cb);
@@ -541,7 +553,7 @@ int launch_decode_vq_mfma_one(const octopus_codebooks_t &cb, const DecodeShape &
         if (s.item_waves != NWV || s.tiles_per_step != 1) return static_cast<int>(hipErrorInvalidValue);
         hipLaunchKernelGGL((decode_kernel_vq_mfma<P, RG, VB, VG>), dim3(kDecodeWorkgroups), dim3(NWV * kWave), 0,
                            stream, books, s, q_rot, static_cast<const uint4 *>(cache),
-                           static_cast<const unsigned char *>(vq), seq_lens, part_ml, part_acc, plan, pt);
+                           static_cast<const unsigned char *>(vq), seq_lens, part_ml, part_acc, pt);
         return static_cast<int>(hipGetLastError());
     } else {
         return -1;
@@ -551,13 +563,13 @@ int launch_decode_vq_mfma_one(const octopus_codebooks_t &cb, const DecodeShape &
 template <class P, int VB>
 int launch_decode_vq_mfma_plan(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot,
                                const void *cache, const void *vq, int v_group, const int32_t *seq_lens, float *part_ml,
-                               float *part_acc, int32_t *plan, hipStream_t stream, const PageTable &pt) {
+                               float *part_acc, hipStream_t stream, const PageTable &pt) {
     if (v_group == 32) {
-        if (s.rows_per_pass == 4) return launch_decode_vq_mfma_one<P, 4, VB, 32>(cb, s, q_rot, cache, vq, seq_lens, part_ml, part_acc, plan, stream, pt);
-        if (s.rows_per_pass == 8) return launch_decode_vq_mfma_one<P, 8, VB, 32>(cb, s, q_rot, cache, vq, seq_lens, part_ml, part_acc, plan, stream, pt);
+        if (s.rows_per_pass == 4) return launch_decode_vq_mfma_one<P, 4, VB, 32>(cb, s, q_rot, cache, vq, seq_lens, part_ml, part_acc, stream, pt);
+        if (s.rows_per_pass == 8) return launch_decode_vq_mfma_one<P, 8, VB, 32>(cb, s, q_rot, cache, vq, seq_lens, part_ml, part_acc, stream, pt);
     } else if (v_group == 16) {
-        if (s.rows_per_pass == 4) return launch_decode_vq_mfma_one<P, 4, VB, 16>(cb, s, q_rot, cache, vq, seq_lens, part_ml, part_acc, plan, stream, pt);
-        if (s.rows_per_pass == 8) return launch_decode_vq_mfma_one<P, 8, VB, 16>(cb, s, q_rot, cache, vq, seq_lens, part_ml, part_acc, plan, stream, pt);
+        if (s.rows_per_pass == 4) return launch_decode_vq_mfma_one<P, 4, VB, 16>(cb, s, q_rot, cache, vq, seq_lens, part_ml, part_acc, stream, pt);
+        if (s.rows_per_pass == 8) return launch_decode_vq_mfma_one<P, 8, VB, 16>(cb, s, q_rot, cache, vq, seq_lens, part_ml, part_acc, stream, pt);
     }
     return -1;
 }

@@ -284,9 +284,10 @@ DecodeShape make_decode_shape(const octopus_plan_t &plan, int32_t n_seq, int32_t
     // workgroups of 4 wavefronts: splits come in fours
     int64_t want = (slots / 4 + groups / 2) / groups;
     want = std::max<int64_t>(1, std::min<int64_t>(want, (max_steps + 3) / 4));
-    s.n_splits = static_cast<int32_t>(4 * want);   // kept for reference; the device cuts the items itself
-    // The device cuts the work into at most 256 * 8 items plus one more per (sequence, KV head, row group)
-    // (the rounding of each one's share), see the plan in the kernels.
+    s.n_splits = static_cast<int32_t>(4 * want);   // kept for reference; the device divides the steps itself
+    // Partial results: the kernels write one per workgroup and one more per (sequence, KV head, row group) at most (the
+    // work distribution in octopus_decode.hpp); the workspace has had room for four times as many as below from the start,
+    // and its documented size stays.
     s.max_items = static_cast<int32_t>(std::min<int64_t>(256 * 8 + groups, groups * std::max<int64_t>(max_steps, 1)));
     return s;
 }
@@ -310,7 +311,7 @@ Workspace make_workspace(const octopus_plan_t &plan, const DecodeShape &s) {
     const size_t ml_bytes = up(partials * 2 * sizeof(float));
     w.part_acc_off = w.part_ml_off + ml_bytes;
     const size_t acc_bytes = up(partials * static_cast<size_t>(plan.head_dim) * sizeof(float));
-    w.plan_off = w.part_acc_off + acc_bytes;
+    w.plan_off = w.part_acc_off + acc_bytes;      // (not used any more: kept in the documented size)
     const size_t plan_bytes = up((static_cast<size_t>(s.n_seq) + 5) * sizeof(int32_t));
     w.q2_off = w.plan_off + plan_bytes;   // second rotation of the queries (QJL residual only)
     w.win_ml_off = w.q2_off + up(rows * static_cast<size_t>(plan.head_dim) * sizeof(float));
@@ -541,6 +542,21 @@ struct WindowArgs {
 };
 }  // namespace
 
+static void set_queries(DecodeShape *s, const void *q, int32_t q_dtype, const uint8_t *signs, const uint8_t *signs2, float scale) {
+    s->q = q;
+    s->q_is_bf16 = q_dtype == OCTOPUS_DTYPE_BF16 ? 1 : 0;
+    s->signs = signs;
+    s->signs2 = signs2;
+    s->scale = scale;
+}
+
+// Whether the kernel that serves a call rotates its queries itself; else a kernel before it does.  matrix_kernel: the
+// kernel over bf16 values or the matrix-core kernel over quantised values (the vector-unit kernels read the rotated
+// queries through scalar loads, the many-row kernel from a layout of its own).
+static bool rotates_in_kernel(const octopus_plan_t &plan, bool many_rows, bool matrix_kernel) {
+    return !many_rows && matrix_kernel && joint_plan(plan);
+}
+
 static int attn_decode(const octopus_codebooks_t *cb, const void *q, int32_t q_dtype, int32_t n_seq,
                        int32_t n_q_heads, int32_t n_kv_heads, int32_t n_q, const uint8_t *signs, const void *cache,
                        int64_t t_capacity, const void *v, int32_t v_dtype, const int32_t *seq_lens, int64_t max_len,
@@ -586,8 +602,9 @@ static int attn_decode(const octopus_codebooks_t *cb, const void *q, int32_t q_d
     const int32_t vq_mfma = with_vq && scores_out == nullptr
                                 ? vq_mfma_available(cb->plan, vq_mfma_rows(n_q * (n_q_heads / n_kv_heads)), v_bits, v_group)
                                 : 0;
-    const DecodeShape s = make_decode_shape(cb->plan, n_seq, n_q_heads, n_kv_heads, n_q, max_len, t_capacity, many_rows,
-                                            rows_cap, vq_mfma);
+    DecodeShape s = make_decode_shape(cb->plan, n_seq, n_q_heads, n_kv_heads, n_q, max_len, t_capacity, many_rows, rows_cap,
+                                      vq_mfma);
+    set_queries(&s, q, q_dtype, signs, signs2, scale);
     const Workspace w = make_workspace(cb->plan, s);
     // every entry point asks for the one documented size, whatever its own kernel needs (the static scratch
     // has been checked against the need of the kernels it serves)
@@ -600,19 +617,19 @@ static int attn_decode(const octopus_codebooks_t *cb, const void *q, int32_t q_d
     float *part_ml = reinterpret_cast<float *>(base + w.part_ml_off);
     float *part_acc = reinterpret_cast<float *>(base + w.part_acc_off);
     float *q2 = with_qjl ? reinterpret_cast<float *>(base + w.q2_off) : nullptr;
-    int32_t *work_plan = many_rows ? nullptr : reinterpret_cast<int32_t *>(base + w.plan_off);
-    int err = launch_rotate_queries(cb->plan, q, q_dtype, signs, s, scale, q_rot, seq_lens, work_plan, signs2, q2,
-                                    stream);
+    int err = 0;
+    if (!rotates_in_kernel(cb->plan, many_rows, with_vq ? vq_mfma > 0 : v_dtype == OCTOPUS_DTYPE_BF16))
+        err = launch_rotate_queries(cb->plan, q, q_dtype, signs, s, scale, q_rot, seq_lens, nullptr, signs2, q2, stream);
     if (err == 0 && ev_before != nullptr) err = record_event(ev_before, stream);
     if (err == 0) {
         if (with_qjl)
-            err = launch_decode_qjl(*cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, work_plan,
+            err = launch_decode_qjl(*cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, nullptr,
                                     stream);
         else if (with_vq)
             err = launch_decode_vq(*cb, s, q_rot, cache, v, v_bits, v_group, seq_lens, part_ml, part_acc, scores_out,
-                                   work_plan, stream);
+                                   nullptr, stream);
         else
-            err = launch_decode(*cb, s, q_rot, cache, v, v_dtype, seq_lens, part_ml, part_acc, scores_out, work_plan,
+            err = launch_decode(*cb, s, q_rot, cache, v, v_dtype, seq_lens, part_ml, part_acc, scores_out, nullptr,
                                 stream);
     }
     if (err == 0 && ev_after != nullptr) err = record_event(ev_after, stream);
@@ -623,7 +640,7 @@ static int attn_decode(const octopus_codebooks_t *cb, const void *q, int32_t q_d
         err = launch_window(cb->plan, s, q, q_dtype, win->k_window, win->k_dtype, win->w_capacity, win->win_lens, v,
                             v_dtype, seq_lens, scale, win_ml, win_acc, scores_out, stream);
     }
-    if (err == 0) err = launch_merge(cb->plan, s, part_ml, part_acc, work_plan, out, win_ml, win_acc, stream);
+    if (err == 0) err = launch_merge(cb->plan, s, part_ml, part_acc, seq_lens, out, win_ml, win_acc, stream);
     return err == 0 ? OCTOPUS_OK : OCTOPUS_EHIP;
 }
 
@@ -866,8 +883,9 @@ static int attn_decode_paged(const octopus_codebooks_t *cb, const void *q, int32
         vq_waves = vq_mfma_available(cb->plan, vq_mfma_rows(n_q * (n_q_heads / n_kv_heads)), v_bits, v_group);
         if (vq_waves <= 0) return OCTOPUS_EUNSUPPORTED;
     }
-    const DecodeShape s = make_decode_shape(cb->plan, n_seq, n_q_heads, n_kv_heads, n_q, max_len, reach, many_rows,
-                                            rows_cap, vq_waves);
+    DecodeShape s = make_decode_shape(cb->plan, n_seq, n_q_heads, n_kv_heads, n_q, max_len, reach, many_rows, rows_cap,
+                                      vq_waves);
+    set_queries(&s, q, q_dtype, signs, with_qjl ? signs2 : nullptr, scale);
     const Workspace w = make_workspace(cb->plan, s);
     const size_t required = std::max(w.total, octopus_attn_decode_workspace(cb, n_seq, n_q_heads, n_kv_heads, n_q, max_len));
     if (workspace == nullptr || !aligned(workspace, 256) || workspace_bytes < required) return OCTOPUS_EWORKSPACE;
@@ -875,21 +893,21 @@ static int attn_decode_paged(const octopus_codebooks_t *cb, const void *q, int32
     float *q_rot = reinterpret_cast<float *>(base + w.q_rot_off);
     float *part_ml = reinterpret_cast<float *>(base + w.part_ml_off);
     float *part_acc = reinterpret_cast<float *>(base + w.part_acc_off);
-    int32_t *work_plan = many_rows ? nullptr : reinterpret_cast<int32_t *>(base + w.plan_off);
     float *q2 = with_qjl ? reinterpret_cast<float *>(base + w.q2_off) : nullptr;
     const PageTable pt{block_table, max_pages_per_seq, n_pages};
-    int err = launch_rotate_queries(cb->plan, q, q_dtype, signs, s, scale, q_rot, seq_lens, work_plan,
-                                    with_qjl ? signs2 : nullptr, q2, stream);
+    int err = 0;
+    if (!rotates_in_kernel(cb->plan, many_rows, true))
+        err = launch_rotate_queries(cb->plan, q, q_dtype, signs, s, scale, q_rot, seq_lens, nullptr, s.signs2, q2, stream);
     if (err == 0 && ev_before != nullptr) err = record_event(ev_before, stream);
     if (err == 0) {
         if (v_bits != 0)
             err = launch_decode_vq(*cb, s, q_rot, k_pool, v_pool, v_bits, v_group, seq_lens, part_ml, part_acc, nullptr,
-                                   work_plan, stream, pt);
+                                   nullptr, stream, pt);
         else if (with_qjl)
             err = launch_decode_paged_qjl(*cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc,
-                                          work_plan, stream);
+                                          nullptr, stream);
         else
-            err = launch_decode_paged(*cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, work_plan, stream);
+            err = launch_decode_paged(*cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, nullptr, stream);
     }
     if (err == 0 && ev_after != nullptr) err = record_event(ev_after, stream);
     float *win_ml = nullptr, *win_acc = nullptr;
@@ -900,7 +918,7 @@ static int attn_decode_paged(const octopus_codebooks_t *cb, const void *q, int32
         err = launch_window(cb->plan, s, q, q_dtype, win->k_window, win->k_dtype, win->w_capacity, win->win_lens, v_pool,
                             OCTOPUS_DTYPE_BF16, seq_lens, scale, win_ml, win_acc, nullptr, stream, pt);
     }
-    if (err == 0) err = launch_merge(cb->plan, s, part_ml, part_acc, work_plan, out, win_ml, win_acc, stream);
+    if (err == 0) err = launch_merge(cb->plan, s, part_ml, part_acc, seq_lens, out, win_ml, win_acc, stream);
     return err == 0 ? OCTOPUS_OK : OCTOPUS_EHIP;
 }
 

@@ -37,12 +37,25 @@ struct DecodeShape {
     int32_t rows_per_pass;  // query rows one workgroup scores per key (1, 2, 4 or 8; 128 or 256: many-row kernel)
     int32_t n_row_groups;   // ceil(rows_per_kv / rows_per_pass)
     int32_t n_splits;       // wavefronts (workgroups of the many-row kernel) sharing the tiles of one (sequence, KV head, row group)
-    int32_t max_items;      // bound of the work items the device cuts (row groups of at most 8)
+    int32_t max_items;      // what the partials' part of the workspace is sized for (row groups of at most 8)
     int32_t max_len;        // host-side bound of the sequence lengths
     int32_t item_waves;     // wavefronts of the workgroup that share a work item (4; 8: matrix-core kernel over quantised values up to d = 128 where its LDS fits)
     int32_t tiles_per_step; // 64-token tiles a wavefront takes per step (2 up to d = 128, else 1; 1: that kernel)
     int64_t t_capacity;
+    // the call's queries, for the kernels that rotate the rows of their row group themselves (rotates_in_kernel)
+    const void *q;
+    const uint8_t *signs, *signs2;   // signs2: second rotation of the QJL residual, or NULL
+    float scale;
+    int32_t q_is_bf16;
 };
+
+// Plans whose every class has a joint table (2 b_dir + b_nrm <= 10) score on the matrix cores where the kernel over bf16
+// values or the matrix-core kernel over quantised values serves the call; those kernels rotate the queries themselves.
+inline bool joint_plan(const octopus_plan_t &p) {
+    for (int c = 0; c < p.n_class; ++c)
+        if (2 * p.b_dir[c] + p.b_nrm[c] > 10) return false;
+    return true;
+}
 
 // Paged cache: logical 64-token tile j of sequence s lives in page table[s * stride + j] of a pool of n_pages
 // pages; table NULL: the contiguous cache.
@@ -68,9 +81,8 @@ int vq_mfma_available(const octopus_plan_t &plan, int32_t rows_per_pass, int32_t
 Workspace make_workspace(const octopus_plan_t &plan, const DecodeShape &s);
 
 // Kernel launchers (defined in the .hip files).  Each returns a hipError_t cast to int.
-// `work_plan`: device array the rotation kernel fills with the work items of the split-K kernel (NULL with
-// the many-row kernel, whose blocks are split on the host).  `q2` (NULL: not wanted): the queries rotated a second time
-// with `signs2` for the QJL residual, [padded row][head_dim].
+// `q2` (NULL: not wanted): the queries rotated a second time with `signs2` for the QJL residual, [padded row][head_dim].
+// (`work_plan`: not used; part of the launchers' signatures.)
 int launch_rotate_queries(const octopus_plan_t &plan, const void *q, int q_dtype, const uint8_t *signs,
                           const DecodeShape &s, float scale, float *q_rot, const int32_t *seq_lens,
                           int32_t *work_plan, const uint8_t *signs2, float *q2, void *stream);
@@ -85,7 +97,7 @@ int launch_decode_qjl(const octopus_codebooks_t &cb, const DecodeShape &s, const
 int qjl_rows_cap(const octopus_plan_t &plan);
 // win_ml / win_acc: the partial of a native-precision window per output row, or NULL
 int launch_merge(const octopus_plan_t &plan, const DecodeShape &s, const float *part_ml, const float *part_acc,
-                 const int32_t *work_plan, float *out, const float *win_ml, const float *win_acc, void *stream);
+                 const int32_t *seq_lens, float *out, const float *win_ml, const float *win_acc, void *stream);
 // Attention partial (m, l, acc) per output row over the native-precision window that follows the
 // compressed tokens of each sequence; pt: the value rows lie in pages (s.t_capacity = what the table addresses).
 int launch_window(const octopus_plan_t &plan, const DecodeShape &s, const void *q, int q_dtype, const void *k_win,
