@@ -3,6 +3,8 @@
 #ifndef OCTOPUS_DECODE_HPP_
 #define OCTOPUS_DECODE_HPP_
 
+#include <cstddef>
+
 #include "octopus_device.hpp"
 
 namespace octopus {
@@ -129,20 +131,29 @@ __device__ __forceinline__ uint4 split_triplet(float x, float y, float z) {
     return make_uint4(hx | (hy << 16), hz, lx | (ly << 16), lz);
 }
 
-// The joint table of a class with its entries in that form (same size and addressing as the fp32 table).
+// The joint table of a class with its entries in that form (same size and addressing as the fp32 table).  A thread takes
+// a direction with all its norm codes (or, with fewer directions than threads, a share of them).  Neighbouring threads
+// start with different norm codes and copies, so that the 16-byte writes of a wavefront spread over all banks (the entries
+// of neighbouring directions lie 256 bytes apart).
 template <int BD, int BN>
 __device__ __forceinline__ void build_joint_table_mx(float4 *table, const float *c_xi, const float *c_rho, int tid,
                                                      int nthreads) {
     using T = JointTable<BD, BN>;
-    constexpr int K = 1 << BD;
+    constexpr int K = 1 << BD, M = 1 << BN;
     uint4 *out = reinterpret_cast<uint4 *>(table);
-    for (int e = tid; e < T::ENTRIES; e += nthreads) {
-        const int dir = e >> BN, nrm = e & ((1 << BN) - 1);
+    const int per = nthreads / (K * K) > 1 ? (nthreads / (K * K) < M ? nthreads / (K * K) : M) : 1;   // threads per direction
+    const int part = tid % per;
+#pragma unroll 1
+    for (int dir = tid / per; dir < K * K; dir += nthreads / per) {
         const float4 n = oct_decode(c_xi[dir & (K - 1)], c_xi[dir >> BD]);
-        const float rho = c_rho[nrm];
-        const uint4 val = split_triplet(rho * n.x, rho * n.y, rho * n.z);
+#pragma unroll 1
+        for (int q = part; q < M; q += per) {
+            const int nrm = (q + dir / T::REP) & (M - 1);
+            const float rho = c_rho[nrm];
+            const uint4 val = split_triplet(rho * n.x, rho * n.y, rho * n.z);
 #pragma unroll
-        for (int r = 0; r < T::REP; ++r) out[e * T::REP + r] = val;
+            for (int r = 0; r < T::REP; ++r) out[(dir * M + nrm) * T::REP + ((r + dir) & (T::REP - 1))] = val;
+        }
     }
 }
 
@@ -159,18 +170,46 @@ struct DecodeTables {
     float4 dir1[P::NCLASS == 2 ? dir_table_float4s<(P::BD1 > 0 ? P::BD1 : 1), (P::BN1 > 0 ? P::BN1 : 1)>() : 1];
     __attribute__((aligned(16))) float rho0[J0 ? 4 : RhoTable<P::BN0>::FLOATS];
     __attribute__((aligned(16))) float rho1[P::NCLASS == 2 && !J1 ? RhoTable<(P::BN1 > 0 ? P::BN1 : 1)>::FLOATS : 4];
-    float c_xi[2][kMaxLevels];
-    float c_rho[2][kMaxLevels];
+    float c_xi[2][1 << (P::BD0 > P::BD1 ? P::BD0 : P::BD1)];
+    float c_rho[2][P::BN0 > 1 || P::BN1 > 1 ? 1 << (P::BN0 > P::BN1 ? P::BN0 : P::BN1) : 2];
 };
 
 // Plans whose every class has a joint table (all up to 3 bits per coordinate) can score on the matrix cores.
 template <class P>
 constexpr bool mx_scores() { return DecodeTables<P>::J0 && (P::NCLASS == 1 || DecodeTables<P>::J1); }
 
+// Centroids of the levels that plan P has, from the kernel's first argument (a DeviceBooks) to LDS: one level per lane,
+// requested at the kernel's start and stored when the tables are built.  (Reading them one by one with compile-time indices
+// took sixty instructions; straight-line code that runs once costs the fetch of its instructions, which in a kernel this
+// size is more than their execution.)
+template <class P>
+struct BookLevels {
+    static constexpr int NX = sizeof(DecodeTables<P>::c_xi[0]) / 4, NR = sizeof(DecodeTables<P>::c_rho[0]) / 4;
+    static_assert(NX <= kWave && NR <= kWave, "a level per lane");
+    float xi[P::NCLASS], rho[P::NCLASS];
+    __device__ __forceinline__ void load(int lane) {
+        typedef const float __attribute__((address_space(4))) *arg_t;
+        arg_t arg = (arg_t)__builtin_amdgcn_kernarg_segment_ptr();
+#pragma unroll
+        for (int c = 0; c < P::NCLASS; ++c) {   // (kMaxLevels levels each: every lane reads one)
+            xi[c] = arg[offsetof(DeviceBooks, c_xi) / 4 + c * kMaxLevels + lane];
+            rho[c] = arg[offsetof(DeviceBooks, c_rho) / 4 + c * kMaxLevels + lane];
+        }
+    }
+    __device__ __forceinline__ void store(DecodeTables<P> &tb, int tid) const {
+#pragma unroll
+        for (int c = 0; c < P::NCLASS; ++c) {
+            if (tid < NX) tb.c_xi[c][tid] = xi[c];
+            if (tid < NR) tb.c_rho[c][tid] = rho[c];
+        }
+    }
+};
+
 // MX: joint tables hold bf16 hi / lo operands (the matrix-core score pass) instead of fp32 vectors.
 template <class P, bool MX = false>
-__device__ __forceinline__ void build_tables(DecodeTables<P> &tb, const DeviceBooks &books, int tid, int nthreads) {
-    if (tid < kWave) copy_books<P>(books, tb.c_xi, tb.c_rho);
+__device__ __forceinline__ void build_tables(DecodeTables<P> &tb, const BookLevels<P> &levels, int tid, int nthreads) {
+    static_assert(kMaxLevels == kWave, "one level per lane");
+    levels.store(tb, tid);
     __syncthreads();
     if constexpr (MX) {
         static_assert(mx_scores<P>(), "matrix-core scores need joint tables");
@@ -212,10 +251,11 @@ __device__ __forceinline__ void build_tables(DecodeTables<P> &tb, const DeviceBo
 // equal lengths (16 x 32768): 213.4 -> 211.7 us.
 constexpr int kDecodeWorkgroups = 256;   // one per compute unit
 
+// (tiles_per_step: 1 or 2)
 __device__ __forceinline__ int steps_of(int len, int max_len, int tiles_per_step) {
-    const int l = min(max(len, 0), max_len);
-    const int tiles = (l + kWave - 1) / kWave;
-    return (tiles + tiles_per_step - 1) / tiles_per_step;
+    const uint32_t l = static_cast<uint32_t>(min(max(len, 0), max_len));
+    const uint32_t tiles = (l + kWave - 1) / kWave;
+    return static_cast<int>(tiles_per_step == 2 ? (tiles + 1) / 2 : tiles);
 }
 
 // Inclusive sum over the wavefront's lanes.
@@ -234,19 +274,22 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
     return v;
 }
 
-__device__ __forceinline__ uint64_t divide(uint64_t a, uint64_t b) {
-    if (((a | b) >> 32) == 0) return static_cast<uint32_t>(a) / static_cast<uint32_t>(b);
-    return a / b;
+// floor(a / b) of whole numbers below 2^53 with a / b < 2^31: the quotient in double precision is never rounded up to a
+// whole number it does not reach (it would have to be within 2^-53 of it, relatively, and is 1 / b away at least).
+// (A 64-bit division by integer instructions is over a hundred of them.)
+__device__ __forceinline__ uint32_t divide(uint64_t a, uint64_t b) {
+    return static_cast<uint32_t>(static_cast<double>(a) / static_cast<double>(b));
 }
 
 // Workgroups that share `total` steps, the first step of workgroup b, and the workgroup that has step x.
 __device__ __forceinline__ int span_workgroups(uint64_t total, int item_waves) {
-    const uint64_t full = (total + item_waves - 1) / static_cast<uint32_t>(item_waves);
-    return static_cast<int>(full < static_cast<uint64_t>(kDecodeWorkgroups) ? full : kDecodeWorkgroups);
+    return total >= static_cast<uint64_t>(kDecodeWorkgroups) * item_waves
+               ? kDecodeWorkgroups
+               : static_cast<int>((static_cast<uint32_t>(total) + item_waves - 1) / static_cast<uint32_t>(item_waves));
 }
 __device__ __forceinline__ uint64_t span_first(uint64_t total, int n_wg, int b) {
     return n_wg == kDecodeWorkgroups ? (total * static_cast<uint32_t>(b)) / kDecodeWorkgroups
-                                     : divide(total * static_cast<uint32_t>(b), static_cast<uint32_t>(n_wg));
+                                     : static_cast<uint64_t>(divide(total * static_cast<uint32_t>(b), static_cast<uint32_t>(n_wg)));
 }
 __device__ __forceinline__ int span_owner(uint64_t total, int n_wg, uint64_t x) {
     return static_cast<int>(divide((x + 1) * static_cast<uint32_t>(n_wg) - 1, total));
@@ -259,6 +302,8 @@ struct WaveWork {
 };
 
 // The share of one workgroup and where it stands in it.  Sequences are looked at 64 at a time, one per lane.
+// TPS, NW: tiles per step and wavefronts per workgroup of the kernel (the shape's tiles_per_step and item_waves).
+template <int TPS, int NW>
 struct WorkSpan {
     int chunk;               // first sequence of the 64
     int lane_len;            // length of sequence chunk + lane
@@ -269,7 +314,7 @@ struct WorkSpan {
     __device__ __forceinline__ void look(const DecodeShape &shp, const int32_t *seq_lens, int lane) {
         const int s = chunk + lane;
         lane_len = s < shp.n_seq ? min(max(seq_lens[s], 0), shp.max_len) : 0;
-        lane_sum = wave_scan(static_cast<uint32_t>(steps_of(lane_len, shp.max_len, shp.tiles_per_step)));
+        lane_sum = wave_scan(static_cast<uint32_t>(steps_of(lane_len, shp.max_len, TPS)));
     }
     __device__ __forceinline__ uint32_t chunk_sum() const {
         return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lane_sum), kWave - 1));
@@ -285,7 +330,7 @@ struct WorkSpan {
         chunk = 0;
         before = 0;
         if (shp.n_seq > kWave) look(shp, seq_lens, lane);
-        const int b = static_cast<int>(blockIdx.x), n_wg = span_workgroups(total, shp.item_waves);
+        const int b = static_cast<int>(blockIdx.x), n_wg = span_workgroups(total, NW);
         pos = b < n_wg ? span_first(total, n_wg, b) : 0;
         end = b < n_wg ? span_first(total, n_wg, b + 1) : 0;
     }
@@ -301,27 +346,31 @@ struct WorkSpan {
         const int l = __ffsll(static_cast<unsigned long long>(__ballot((before + lane_sum) * G > pos))) - 1;
         const int len = __builtin_amdgcn_readlane(lane_len, l);
         const uint32_t sum = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lane_sum), l));
-        const int n_steps = steps_of(len, shp.max_len, shp.tiles_per_step);   // > 0: the sequence holds step pos
+        const int n_steps = steps_of(len, shp.max_len, TPS);   // > 0: the sequence holds step pos
         const uint64_t first = (before + sum - static_cast<uint32_t>(n_steps)) * G;
-        const uint64_t local = pos - first, gis = divide(local, static_cast<uint32_t>(n_steps));
-        const uint64_t stop = first + (gis + 1) * static_cast<uint32_t>(n_steps);
+        const uint64_t local = pos - first;
+        const int g = __builtin_amdgcn_readfirstlane(static_cast<int>(divide(local, static_cast<uint32_t>(n_steps))));
+        const uint64_t group_first = static_cast<uint64_t>(static_cast<uint32_t>(g)) * static_cast<uint32_t>(n_steps);
+        const uint64_t stop = first + group_first + static_cast<uint32_t>(n_steps);
         const uint64_t seg_end = stop < end ? stop : end;
-        const int begin = static_cast<int>(local - gis * static_cast<uint32_t>(n_steps));
-        const int g = static_cast<int>(gis);
+        const int begin = static_cast<int>(local - group_first);
         ww->seq = chunk + l;
-        ww->grp = g % shp.n_row_groups;
-        ww->kvh = g / shp.n_row_groups;
+        ww->grp = 0;
+        ww->kvh = g;
+        if (shp.n_row_groups > 1) {
+            ww->kvh = g / shp.n_row_groups;
+            ww->grp = g - ww->kvh * shp.n_row_groups;
+        }
         ww->group_id = static_cast<int64_t>(ww->seq) * static_cast<int64_t>(G) + g;
         ww->slot = static_cast<int64_t>(blockIdx.x) + ww->group_id;
         ww->pair = static_cast<int64_t>(ww->seq) * shp.n_kv_heads + ww->kvh;
         ww->len = len;
-        ww->n_tiles = (len + kWave - 1) / kWave;
+        ww->n_tiles = static_cast<int>((static_cast<uint32_t>(len) + kWave - 1) / kWave);
         ww->step_end = begin + static_cast<int>(seg_end - pos);
         ww->step_begin = begin + wave;
-        ww->step_stride = shp.item_waves;
-        ww->step_last = ww->step_begin + (ww->step_begin < ww->step_end
-                                              ? (ww->step_end - 1 - ww->step_begin) / ww->step_stride
-                                              : 0) * ww->step_stride;
+        ww->step_stride = NW;
+        const int more = max(ww->step_end - 1 - ww->step_begin, 0);
+        ww->step_last = ww->step_begin + more / NW * NW;
         pos = seg_end;
         return true;
     }
@@ -332,22 +381,25 @@ struct WorkSpan {
 template <int D, int RG, int NW>
 __device__ __forceinline__ void merge_waves(const DecodeShape &shp, const WaveWork &ww, const float *acc, int acc_stride,
                                             const float *ml, int ml_stride, float *part_ml, float *part_acc, int tid) {
-    for (int e = tid; e < RG * D; e += NW * kWave) {
-        const int r = e / D, c = e % D;
+#pragma unroll 1
+    for (int e = tid; e < RG * D / 4; e += NW * kWave) {
+        const int r = e / (D / 4);
         if (ww.grp * RG + r >= shp.rows_per_kv) continue;
         float m = -INFINITY;
 #pragma unroll
         for (int w = 0; w < NW; ++w) m = fmaxf(m, ml[w * ml_stride + 2 * r]);
-        float a = 0.0f, l = 0.0f;
+        float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        float l = 0.0f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
             const float mw = ml[w * ml_stride + 2 * r];
             const float f = mw == -INFINITY ? 0.0f : exp2_raw((mw - m) * kLog2e);
-            a = fmaf(f, acc[w * acc_stride + e], a);
+            const float4 x = reinterpret_cast<const float4 *>(acc + w * acc_stride)[e];
+            a.x = fmaf(f, x.x, a.x); a.y = fmaf(f, x.y, a.y); a.z = fmaf(f, x.z, a.z); a.w = fmaf(f, x.w, a.w);
             l = fmaf(f, ml[w * ml_stride + 2 * r + 1], l);
         }
-        part_acc[ww.slot * (RG * D) + e] = a;
-        if (c == 0) {
+        reinterpret_cast<float4 *>(part_acc + ww.slot * (RG * D))[e] = a;
+        if (e % (D / 4) == 0) {
             part_ml[(ww.slot * RG + r) * 2] = m;
             part_ml[(ww.slot * RG + r) * 2 + 1] = l;
         }
@@ -399,14 +451,14 @@ __device__ __forceinline__ void transform_row(int lane, float (&x)[D / kWave]) {
         }
     }
     // ... then over the lane bits: the element with the bit clear takes a + b, the other a - b
-#pragma unroll
-    for (int m = 1; m < kWave; m <<= 1) {
+    static_for<0, 6>([&](auto bb) {
+        constexpr int m = 1 << decltype(bb)::value;
 #pragma unroll
         for (int j = 0; j < EPL; ++j) {
-            const float other = __shfl_xor(x[j], m, kWave);
-            x[j] = (lane & m) ? other - x[j] : x[j] + other;
+            const float other = lane_xor<m>(x[j], lane);
+            x[j] = other + ((lane & m) ? -x[j] : x[j]);
         }
-    }
+    });
 }
 
 template <int D>
@@ -626,108 +678,239 @@ __device__ __forceinline__ void tile_scores(const uint32_t (&w)[KPL][P::NWORDS],
     });
 }
 
-// Byte offset, in the joint table of its class, of the entry of triplet I of the record `w` for this lane.
-template <class P, int I>
-__device__ __forceinline__ uint32_t joint_offset(const uint32_t (&w)[P::NWORDS], int lane) {
-    constexpr int bn = P::bnrm(I), bd = P::bdir(I);
-    using JT = JointTable<bd, bn>;
-    constexpr int nb = P::nrm_bit(I), db = P::dir_bit(I);
-    if constexpr (JT::BYTE_CODES && (nb & 31) + bn <= 32) {
-        const uint32_t dl = __builtin_amdgcn_perm(w[db >> 5], lane_part<JT::REP>(lane),
-                                                  0x0c0c0000u | ((4u + ((db & 31) >> 3)) << 8));
-        uint32_t nrm, off;
-        asm("v_bfe_u32 %0, %1, %2, %3" : "=v"(nrm) : "v"(w[nb >> 5]), "n"(nb & 31), "n"(bn));
-        asm("v_lshl_or_b32 %0, %1, %2, %3" : "=v"(off) : "v"(nrm), "n"(JT::NS), "v"(dl));
-        return off;
-    } else {
-        return (field<db, 2 * bd>(w) << JT::CS) | (field<nb, bn>(w) << JT::NS) | lane_part<JT::REP>(lane);
+// ---- D2-D4 on the matrix cores ------------------------------------------------------------------------
+// Once the table entry of a triplet is in hand, its contribution to the scores is a product of (x, y, z) of the query
+// rows with (x, y, z) of the entry.  v_mfma_f32_16x16x32_bf16 takes 16 keys x 16 operand rows x 32 slots: lane (n, g) =
+// (l % 16, l / 16) supplies 8 slots of key n, and a table entry is 8 slots: the leading parts of (x, y, z, 0) and their
+// remainders.  So the four lane groups supply four triplets of the same 16 keys: lane group g takes the triplets of
+// quarter g of each class, of the keys of all four blocks of 16 keys of the tile one after the other.
+//   * fp32 accuracy from bf16 pairs: entry = e_hi + e_lo, q = q_hi + q_lo.  The operand rows hold q_hi (twice: against e_hi
+//     and e_lo) and q_lo (twice) of every query row, so one instruction covers all four products for up to 8 rows.
+//   * records arrive one key per lane; a quarter's code bits are cut out of the record with funnel shifts and moved to the
+//     lanes that look them up by exchanges of lane rows (a 4 x 4 transpose per register: block of keys <-> quarter).
+//   * in the accumulators of a block the rows of a key lie in lane groups [hi, lo, hi, lo] (up to four rows) or
+//     [hi 0-3, hi 4-7, lo 0-3, lo 4-7]; a few more exchanges add hi and lo and leave every lane with its own key's scores.
+// Bound by the issue of vector instructions and LDS reads of one wavefront per SIMD: per tile and 43 triplets this is 44
+// instructions of ~17 cycles whatever the rows, 44 lookups and 11 operand reads, where a 4 x 4 x 4 product per triplet and
+// four rows took 129 (258 for eight rows) of ~12 cycles, 43 lookups and 43 (86) operand reads.  Long contexts wait for
+// memory either way; eight rows per KV head gain (4 x 16384 tokens, d = 256, b = 3: 91 -> 67 us with the work split; 8 x
+// 16384, d = 128, b = 1: 74 -> 59).
+template <class P>
+struct MxSteps {
+    static constexpr int NS0 = (P::NT0 + 3) / 4, NS1 = (P::NT1 + 3) / 4;   // triplets per quarter of each class
+    static constexpr int N = NS0 + NS1;
+};
+
+// Query operands of a segment, in LDS: entry (step j, lane group g, operand row m) = the 4 slots (x, y, z, 0) that row m
+// has for the triplet lane group g looks up in step j (zeros past the class's last triplet and past the query rows).
+template <class P, int RG>
+struct QueryOperands {
+    static constexpr int ROWS = RG <= 4 ? 8 : 16;
+    uint2 e[MxSteps<P>::N][4][ROWS];
+};
+
+template <class P, int RG>
+__device__ __forceinline__ void build_query_operands(uint2 *dst, const float (*rows)[P::QS], int tid, int nthreads) {
+    using M = MxSteps<P>;
+    constexpr int ROWS = QueryOperands<P, RG>::ROWS;
+#pragma unroll 1
+    for (int e = tid; e < M::N * 4 * ROWS; e += nthreads) {
+        const int m = e % ROWS, g = (e / ROWS) % 4, j = e / (4 * ROWS);
+        const int r = m % (ROWS / 2), in = j < M::NS0 ? g * M::NS0 + j : g * M::NS1 + (j - M::NS0);
+        const int i = j < M::NS0 ? in : P::NT0 + in;
+        float x = 0.0f, y = 0.0f, z = 0.0f;
+        if (r < RG && in < (j < M::NS0 ? P::NT0 : P::NT1)) {
+            x = rows[r][3 * i];
+            y = rows[r][3 * i + 1];
+            z = rows[r][3 * i + 2];
+        }
+        const uint4 s = split_triplet(x, y, z);
+        dst[e] = m < ROWS / 2 ? make_uint2(s.x, s.y) : make_uint2(s.z, s.w);
     }
 }
 
-// ---- D2-D4 on the matrix cores ------------------------------------------------------------------------
-// Once the table entry of a triplet is in hand, its contribution to the scores of RG query rows is a dense
-// 4 x 4 x 4 product per group of four keys: rows x (x, y, z, 0) times (x, y, z, 0) x keys.
-// v_mfma_f32_4x4x4_16b_bf16 multiplies 16 such blocks at once: lane l supplies row l % 4 of A and column
-// l % 4 of B of block l / 4 (four bf16 each) and receives column l % 4 of D, register v = row v.  With
-// A = the rotated queries (row l % 4; the same in every block) and B = the table entry of lane l's own key,
-// lane l ends up with the scores of ITS key for four query rows: the layout the softmax below expects, with
-// no cross-lane traffic.  fp32 accuracy comes from bf16 pairs: q = q_hi + q_lo, entry = e_hi + e_lo, and
-// three products per triplet (hi hi, lo hi, hi lo; the dropped lo lo term is below 2^-16 of the product),
-// accumulated in fp32 by the instruction.
-//
-// Query operands of a segment, staged in LDS by the workgroup: entry (triplet i, row r) = split_triplet of
-// (q_rot[r][3 i], q_rot[r][3 i + 1], q_rot[r][3 i + 2]); rows are padded to a multiple of four with zeros.
-template <class P, int RG>
-struct QueryOperands {
-    static constexpr int ROWS = RG <= 4 ? 4 : 8;
-    uint4 e[P::NTRI][ROWS];
+// 32 bits of a record from bit POS on (zeros past its end).
+template <int POS, int NW>
+__device__ __forceinline__ uint32_t record_bits(const uint32_t (&w)[NW]) {
+    constexpr int wi = POS >> 5, sh = POS & 31;
+    if constexpr (wi >= NW) return 0u;
+    else if constexpr (sh == 0) return w[wi];
+    else if constexpr (wi + 1 >= NW) return w[wi] >> sh;
+    else return __builtin_amdgcn_alignbit(w[wi + 1], w[wi], sh);
+}
+
+// x[s] of lane group b -> x[b] of lane group s.
+__device__ __forceinline__ void transpose_groups(uint32_t (&x)[4]) {
+    auto s16 = [](uint32_t &a, uint32_t &b) {
+        const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+        a = r[0];
+        b = r[1];
+    };
+    auto s32 = [](uint32_t &a, uint32_t &b) {
+        const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+        a = r[0];
+        b = r[1];
+    };
+    s16(x[0], x[1]);
+    s16(x[2], x[3]);
+    s32(x[0], x[2]);
+    s32(x[1], x[3]);
+}
+
+// The code bits of one class that a lane looks up, for the four keys 16 b + n of a tile: dir[word][block] holds the
+// direction codes of its quarter, nrm[word][block] the norm codes.
+template <class P, int C, bool LEAN>
+struct MxCodes {
+    static constexpr int BD = C ? P::BD1 : P::BD0, BN = C ? P::BN1 : P::BN0;
+    static constexpr int NS = C ? MxSteps<P>::NS1 : MxSteps<P>::NS0;
+    static constexpr int ND = (NS * 2 * BD + 31) / 32, NN = (NS * BN + 31) / 32;
+    using JT = JointTable<(BD > 0 ? BD : 1), (BN > 0 ? BN : 1)>;
+    // Direction codes of whole bytes and two-bit norm codes (4 + 4 + 2 bits): the norm bits are kept in four shifted
+    // copies, so that bits 6 and 7 of a byte of one of them are the code; one byte permute brings the two codes of a
+    // triplet together and one and-or cuts and adds the lane part, instead of permute, bit-field extract and shift-or.
+    // (LEAN: kernels short of registers do without the copies)
+    static constexpr bool PAIRED = !LEAN && JT::BYTE_CODES && BN == 2 && JT::NS == 6;
+    static constexpr int NV = PAIRED ? 4 * NN : NN;
+    uint32_t dir[ND > 0 ? ND : 1][4], nrm[NV > 0 ? NV : 1][4];
+
+    __device__ __forceinline__ void cut(const uint32_t (&w)[P::NWORDS]) {
+        constexpr int db = C ? P::DIR1_BIT : P::DIR0_BIT, nb = C ? P::NRM1_BIT : P::NRM0_BIT;
+        static_for<0, ND>([&](auto tt) {
+            constexpr int t = decltype(tt)::value;
+            static_for<0, 4>([&](auto gg) {
+                constexpr int g = decltype(gg)::value;
+                dir[t][g] = record_bits<db + g * NS * 2 * BD + 32 * t, P::NWORDS>(w);
+            });
+            transpose_groups(dir[t]);
+        });
+        static_for<0, NN>([&](auto tt) {
+            constexpr int t = decltype(tt)::value;
+            uint32_t x[4];
+            static_for<0, 4>([&](auto gg) {
+                constexpr int g = decltype(gg)::value;
+                x[g] = record_bits<nb + g * NS * BN + 32 * t, P::NWORDS>(w);
+            });
+            transpose_groups(x);
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                if constexpr (PAIRED) {
+                    nrm[4 * t][b] = x[b] << 6;
+                    nrm[4 * t + 1][b] = x[b] << 4;
+                    nrm[4 * t + 2][b] = x[b] << 2;
+                    nrm[4 * t + 3][b] = x[b];
+                } else {
+                    nrm[t][b] = x[b];
+                }
+            }
+        });
+    }
+    // byte offset of the table entry of triplet J of the quarter of key block b
+    template <int J>
+    __device__ __forceinline__ uint32_t offset(int b, uint32_t lane_bits) const {
+        if constexpr (PAIRED) {
+            constexpr uint32_t sel = 0x0c0c0000u | (static_cast<uint32_t>(4 + J % 4) << 8) | static_cast<uint32_t>((J % 16) / 4);
+            const uint32_t both = __builtin_amdgcn_perm(dir[J / 4][b], nrm[4 * (J / 16) + J % 4][b], sel);
+            uint32_t off;
+            asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(off) : "v"(both), "s"(0xffc0u), "v"(lane_bits));
+            return off;
+        } else {
+            constexpr int dp = J * 2 * BD, np = J * BN;
+            uint32_t d[ND > 0 ? ND : 1], n[NN > 0 ? NN : 1];
+#pragma unroll
+            for (int t = 0; t < ND; ++t) d[t] = dir[t][b];
+#pragma unroll
+            for (int t = 0; t < NN; ++t) n[t] = nrm[t][b];
+            return (field_clamped<dp, 2 * BD>(d) << JT::CS) | (field_clamped<np, BN>(n) << JT::NS) | lane_bits;
+        }
+    }
 };
 
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef float mx_f32x4_t __attribute__((ext_vector_type(4)));
+// All operands come from LDS, so the hardware counter of outstanding LDS reads is exact and the lookups of a unit (one
+// step of one tile: four lookups; LEAN: half of one) can be issued AHEAD units before its products.  `hook` is called once
+// per unit, after the requests and before the products (see tile_scores).
+template <class P, int KPL, bool LEAN>
+constexpr int mx_units() { return MxSteps<P>::N * KPL * (LEAN ? 2 : 1); }
 
-// All operands come from LDS (no scalar loads in the pass), so the hardware counter of outstanding LDS reads
-// is exact and the reads of a triplet can be issued LA triplets before its products.  `hook` as in
-// tile_scores, called every 8 / RG triplets.
-// LOOKAHEAD: triplets requested ahead of their products (4 hides the LDS latency for a wavefront that has its
-// SIMD to itself; a kernel with two wavefronts per SIMD and registers to spare for neither asks for less).
-template <class P, int RG, int KPL, class Hook = NoChunkHook, int LOOKAHEAD = 4>
+template <class P, int RG, int KPL, class Hook = NoChunkHook, int AHEAD = 2, bool LEAN = false>
 __device__ __forceinline__ void tile_scores_mx(const uint32_t (&w)[KPL][P::NWORDS], const QueryOperands<P, RG> &qop,
                                                const DecodeTables<P> &tb, int lane, float (&s)[KPL][RG],
                                                const Hook &hook = Hook{}) {
-    constexpr int CT = 8 / RG;
-    constexpr int NSET = QueryOperands<P, RG>::ROWS / 4;
-    constexpr int LA = P::NTRI < LOOKAHEAD ? P::NTRI : LOOKAHEAD;   // triplets requested ahead
+    using M = MxSteps<P>;
+    typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+    typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+    constexpr int NU = mx_units<P, KPL, LEAN>();
+    constexpr int BPU = LEAN ? 2 : 4;   // key blocks per unit
+    constexpr int LA = NU - 1 < AHEAD ? NU - 1 : AHEAD;
     constexpr int NB = LA + 1;
-    uint4 ev[NB][KPL], qv[NB][NSET];
-    mx_f32x4_t d_main[KPL][NSET], d_cross[KPL][NSET];
+    constexpr int ROWS = QueryOperands<P, RG>::ROWS;
+    MxCodes<P, 0, LEAN> c0[KPL];
+    MxCodes<P, 1, LEAN> c1[P::NCLASS == 2 ? KPL : 1];
+#pragma unroll
+    for (int k = 0; k < KPL; ++k) c0[k].cut(w[k]);
+    if constexpr (P::NCLASS == 2) {
+#pragma unroll
+        for (int k = 0; k < KPL; ++k) c1[k].cut(w[k]);
+    }
+    union Op { uint4 u; bf16x8_t b; };
+    Op ev[NB][BPU];
+    uint2 qv[2];
+    f32x4_t acc[KPL][4];
 #pragma unroll
     for (int k = 0; k < KPL; ++k)
 #pragma unroll
-        for (int h = 0; h < NSET; ++h) {
-            d_main[k][h] = mx_f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-            d_cross[k][h] = mx_f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int b = 0; b < 4; ++b) acc[k][b] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    const uint2 *q_lane = &qop.e[0][lane >> 4][lane & (ROWS - 1)];
+    const uint32_t lane0 = lane_part<JointTable<P::BD0, P::BN0>::REP>(lane);
+    const uint32_t lane1 = P::NCLASS == 2 ? lane_part<JointTable<(P::BD1 > 0 ? P::BD1 : 1), (P::BN1 > 0 ? P::BN1 : 1)>::REP>(lane) : 0u;
+    // units of a step: its tiles in order, (LEAN) each in two halves
+    constexpr int UPS = KPL * (4 / BPU);
+    auto request = [&](auto uu) __attribute__((always_inline)) {
+        constexpr int u = decltype(uu)::value, j = u / UPS, k = u % UPS / (4 / BPU), b0 = u % (4 / BPU) * BPU;
+        if constexpr (u % UPS == 0) qv[j & 1] = q_lane[j * 4 * ROWS];
+#pragma unroll
+        for (int bb = 0; bb < BPU; ++bb) {
+            const int b = b0 + bb;
+            if constexpr (j < M::NS0)
+                ev[u % NB][bb].u = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(tb.dir0) +
+                                                                   c0[k].template offset<j>(b, lane0));
+            else
+                ev[u % NB][bb].u = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(tb.dir1) +
+                                                                   c1[P::NCLASS == 2 ? k : 0].template offset<j - M::NS0>(b, lane1));
         }
-    const char *q_lane = reinterpret_cast<const char *>(&qop.e[0][0]) + (lane & 3) * 16;
-    auto request = [&](auto ii) __attribute__((always_inline)) {
-        constexpr int i = decltype(ii)::value;
-        constexpr int slot = i % NB;
-        constexpr int c = P::cls(i);
-#pragma unroll
-        for (int k = 0; k < KPL; ++k)
-            ev[slot][k] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(c ? tb.dir1 : tb.dir0) +
-                                                           joint_offset<P, i>(w[k], lane));
-#pragma unroll
-        for (int h = 0; h < NSET; ++h)
-            qv[slot][h] = *reinterpret_cast<const uint4 *>(q_lane + (i * QueryOperands<P, RG>::ROWS + 4 * h) * 16);
     };
     static_for<0, LA>(request);
-    static_for<0, P::NTRI>([&](auto ii) {
-        constexpr int i = decltype(ii)::value;
-        constexpr int slot = i % NB;
-        if constexpr (i + LA < P::NTRI) request(std::integral_constant<int, i + LA>{});
-        if constexpr (i % CT == 0) hook(std::integral_constant<int, i / CT>{});
+    Op qa;
+    qa.u = make_uint4(0u, 0u, 0u, 0u);
+    static_for<0, NU>([&](auto uu) {
+        constexpr int u = decltype(uu)::value, j = u / UPS, k = u % UPS / (4 / BPU), b0 = u % (4 / BPU) * BPU;
+        if constexpr (u % UPS == 0) qa.u = make_uint4(qv[j & 1].x, qv[j & 1].y, qv[j & 1].x, qv[j & 1].y);
+        if constexpr (u + LA < NU) request(std::integral_constant<int, u + LA>{});
+        hook(uu);
 #pragma unroll
-        for (int h = 0; h < NSET; ++h) {
-            union { uint32_t u[2]; s16x4_t v; } q_hi, q_lo;
-            q_hi.u[0] = qv[slot][h].x; q_hi.u[1] = qv[slot][h].y;
-            q_lo.u[0] = qv[slot][h].z; q_lo.u[1] = qv[slot][h].w;
-#pragma unroll
-            for (int k = 0; k < KPL; ++k) {
-                union { uint32_t u[2]; s16x4_t v; } e_hi, e_lo;
-                e_hi.u[0] = ev[slot][k].x; e_hi.u[1] = ev[slot][k].y;
-                e_lo.u[0] = ev[slot][k].z; e_lo.u[1] = ev[slot][k].w;
-                d_main[k][h] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(q_hi.v, e_hi.v, d_main[k][h], 0, 0, 0);
-                d_cross[k][h] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(q_lo.v, e_hi.v, d_cross[k][h], 0, 0, 0);
-                d_cross[k][h] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(q_hi.v, e_lo.v, d_cross[k][h], 0, 0, 0);
-            }
-        }
+        for (int bb = 0; bb < BPU; ++bb)
+            acc[k][b0 + bb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa.b, ev[u % NB][bb].b, acc[k][b0 + bb], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
     });
 #pragma unroll
     for (int k = 0; k < KPL; ++k)
 #pragma unroll
-        for (int r = 0; r < RG; ++r) s[k][r] = d_main[k][r / 4][r % 4] + d_cross[k][r / 4][r % 4];
+        for (int i = 0; i < 4; ++i) {
+            float x0 = acc[k][0][i], x1 = acc[k][1][i], x2 = acc[k][2][i], x3 = acc[k][3][i];
+            if constexpr (RG <= 4) {
+                if (i >= RG) continue;
+                swap16(x0, x1);            // x0: hi of blocks 0, 1, 0, 1; x1: lo of the same
+                swap16(x2, x3);
+                const float a = x0 + x1, b = x2 + x3;
+                s[k][i < RG ? i : 0] = lane < 32 ? a : b;
+            } else {
+                swap32(x0, x2);            // x0: hi of blocks 0 (rows 0-3, 4-7) and 2, x2: lo of the same
+                swap32(x1, x3);
+                float a = x0 + x2, b = x1 + x3;
+                swap16(a, b);              // a: rows 0-3 of blocks 0 .. 3, b: rows 4-7
+                s[k][i] = a;
+                s[k][RG > 4 ? 4 + i : 0] = b;
+            }
+        }
 }
 
 template <int RG>
@@ -840,13 +1023,14 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
     constexpr int TQ = kWave * (D / 8 + 2);  // side-car bytes per tile
     // static, so that table addresses are compile-time constants that fold into the LDS instructions
     constexpr bool MX = mx_scores<P>();    // scores on the matrix cores (every plan up to 3 bits per coordinate)
+    constexpr bool LEAN = QJL || RG == 8 || P::NCLASS == 2;  // fewer registers for the score pass where it would spill
     __shared__ DecodeSmemMfma<P, KPL> sm;
     using QO = QjlOperands<D, RG>;
     __shared__ __attribute__((aligned(16))) uint4 qjl_store[QJL ? sizeof(QO) / 16 : 1];
-    __shared__ __attribute__((aligned(16))) uint4 qop_store[MX ? P::NTRI * QueryOperands<P, RG>::ROWS : 1];
+    __shared__ __attribute__((aligned(16))) uint2 qop_store[MX ? sizeof(QueryOperands<P, RG>) / 8 : 1];
     const QueryOperands<P, RG> &qop = *reinterpret_cast<const QueryOperands<P, RG> *>(&qop_store[0]);
     // the wavefronts' results at the end of a segment; at its start the rotated queries lie there (MX)
-    __shared__ float seg_acc[kDecodeWaves][RG][D];
+    __shared__ __attribute__((aligned(16))) float seg_acc[kDecodeWaves][RG][D];
     __shared__ float seg_ml[kDecodeWaves][RG][2];
     static_assert(P::QS + D <= kDecodeWaves * D, "both rotations fit");
     float (*q_rows)[P::QS] = reinterpret_cast<float (*)[P::QS]>(&seg_acc[0][0][0]);
@@ -854,7 +1038,9 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, kept in a scalar register
-    WorkSpan span;
+    BookLevels<P> levels;
+    levels.load(lane);
+    WorkSpan<KPL, kDecodeWaves> span;
     span.open(shp, seq_lens, lane);
     if (span.pos >= span.end) return;   // (whole workgroup, before any barrier)
     // The tables are built inside the segment loop, after the first segment's first loads have been issued:
@@ -1159,7 +1345,7 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
         asm volatile("" : "+s"(q_off));
         if constexpr (AHEAD) {
             // chunk c runs pieces [c NPIECE / NCH, (c + 1) NPIECE / NCH) and reads the A operands of chunk c + 1's
-            constexpr int NCH = score_chunks<P, RG>();
+            constexpr int NCH = MX ? mx_units<P, KPL, LEAN>() : score_chunks<P, RG>();
             uint4 pa_bits[NPIECE];
             static_for<0, NPIECE / NCH>([&](auto pp) { pa_bits[decltype(pp)::value] = pv_operand(decltype(pp)::value / CW); });
             auto pv_in_chunk = [&](auto cc) __attribute__((always_inline)) {
@@ -1173,7 +1359,7 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
                     if constexpr (pi % CW == CW - 1) load_values(v_cur[(pi / CW) / 2], pi / CW, vr[pi / CW]);
                 });
             };
-            if constexpr (MX) tile_scores_mx<P, RG, KPL>(w, qop, sm.tb, lane, s, pv_in_chunk);
+            if constexpr (MX) tile_scores_mx<P, RG, KPL, decltype(pv_in_chunk), 2, LEAN>(w, qop, sm.tb, lane, s, pv_in_chunk);
             else tile_scores<P, RG, KPL>(w, qg + q_off, sm.tb, lane, s, pv_in_chunk);
             // the probabilities of the previous step have been read: the new ones may overwrite them
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1231,7 +1417,10 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
             if constexpr (RP == 4) {
                 a = i < RG ? alpha[i < RG ? i : 0] : 1.0f;
             } else {
-                a = (g4 & 1) ? alpha[4 + i] : alpha[i];
+                // (copies: a choice between the array's elements themselves keeps it in memory, which the compiler puts in
+                // LDS and addresses through the dispatch packet -- in host memory, 15 us away for the last workgroups)
+                const float lower = alpha[i], upper = alpha[RG > 4 ? 4 + i : 0];
+                a = (g4 & 1) ? upper : lower;
             }
 #pragma unroll
             for (int c = 0; c < CPL; ++c) acc[c][i] *= a;
@@ -1290,6 +1479,7 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
             }
         }
         // (the rows of the operand that hold no probabilities stay zero)
+#pragma unroll 1
         for (int e = lane; e < 16 * PROW / 8; e += kWave) reinterpret_cast<uint4 *>(&sm.pbuf[wave][0][0])[e] = make_uint4(0u, 0u, 0u, 0u);
         if constexpr (AHEAD) {
             // The first step's P.V pieces multiply zeros by zeros.  The zero values come from loads through an empty descriptor, which move nothing: the wavefront
@@ -1301,7 +1491,7 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
             for (int ks = 0; ks < KS; ++ks) load_values(v_none, ks, vr[ks]);
         }
         if (!tables_built) {   // workgroup-uniform
-            build_tables<P, MX>(sm.tb, books, tid, kDecodeWaves * kWave);
+            build_tables<P, MX>(sm.tb, levels, tid, kDecodeWaves * kWave);
             tables_built = true;
         }
         // The segment's rotated queries as matrix-core operands.  Every wavefront has left the step loop of the previous
@@ -1309,22 +1499,12 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
         if constexpr (MX) {
             sq.store(shp, ww, wave, lane, q_rows, QJL ? q2_rows : nullptr);
             __syncthreads();
-            constexpr int ROWS = QueryOperands<P, RG>::ROWS;
-            uint4 *dst = reinterpret_cast<uint4 *>(&qop_store[0]);
-            for (int e = tid; e < P::NTRI * ROWS; e += kDecodeWaves * kWave) {
-                const int i = e / ROWS, r = e % ROWS;
-                float x = 0.0f, y = 0.0f, z = 0.0f;
-                if (r < RG) {
-                    x = q_rows[r][3 * i];
-                    y = q_rows[r][3 * i + 1];
-                    z = q_rows[r][3 * i + 2];
-                }
-                dst[e] = split_triplet(x, y, z);
-            }
+            build_query_operands<P, RG>(&qop_store[0], q_rows, tid, kDecodeWaves * kWave);
         }
         if constexpr (QJL) {   // ... and the A operands of the residual's correction
             const float *q2s = MX ? &q2_rows[0][0] : q2 + ww.group_id * (RG * D);
             constexpr int ENTRIES = QO::SETS * QO::STEPS * 64;
+#pragma unroll 1
             for (int e = tid; e < ENTRIES; e += kDecodeWaves * kWave) {
                 const int m = e % 16, g = (e / 16) % 4, st = (e / 64) % QO::STEPS, set = e / (64 * QO::STEPS);
                 // query row and part (0 leading, 1 and 2 the remainders) of operand row m
@@ -1358,10 +1538,17 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
         for (int c = 0; c < CPL; ++c)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float tot = acc[c][i] + __shfl_down(acc[c][i], RP * 4, kWave);
-                const int r = 4 * g4 + i;
-                if (r < RG) seg_acc[wave][r][(c / (LANEB / 2)) * (8 * LANEB) + n16 * (LANEB / 2) + c % (LANEB / 2)] = tot;
+                float hi = acc[c][i], lo = acc[c][i];
+                if constexpr (RP == 4) swap16(hi, lo); else swap32(hi, lo);   // lo: in the lane groups of the hi parts
+                acc[c][i] += lo;
             }
+        if (g4 < RP / 4) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int c = 0; c < CPL; ++c)
+                    if (i < RG) seg_acc[wave][4 * g4 + i][(c / (LANEB / 2)) * (8 * LANEB) + n16 * (LANEB / 2) + c % (LANEB / 2)] = acc[c][i];
+        }
 #pragma unroll
         for (int r = 0; r < RG; ++r) {
             const float l = wave_sum(l_lane[r]);
@@ -1383,7 +1570,7 @@ template <class P, int RG>
 struct DecodeSmemValu {
     DecodeTables<P> tb;
     float pbuf[kDecodeWaves][kWave][RG];
-    float seg_acc[kDecodeWaves][RG][P::D];   // the wavefronts' results at the end of a segment
+    __attribute__((aligned(16))) float seg_acc[kDecodeWaves][RG][P::D];   // the wavefronts' results at the end of a segment
     float seg_ml[kDecodeWaves][RG][2];
 };
 
@@ -1404,10 +1591,12 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) void decode_kernel_valu(
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    WorkSpan span;
+    BookLevels<P> levels;
+    levels.load(lane);
+    WorkSpan<TPS, kDecodeWaves> span;
     span.open(shp, seq_lens, lane);
     if (span.pos >= span.end) return;   // (whole workgroup, before any barrier)
-    build_tables<P>(sm.tb, books, tid, kDecodeWaves * kWave);
+    build_tables<P>(sm.tb, levels, tid, kDecodeWaves * kWave);
     const int rl = lane % LPR, ko = lane / LPR;
     WaveWork ww;
     while (span.next(shp, seq_lens, wave, lane, &ww)) {
@@ -1460,6 +1649,24 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) void decode_kernel_valu(
                 q_meta[i] = *reinterpret_cast<const float2 *>(row + code_bytes + ((rl * 8) / v_group) * 8);
             }
         }
+        // fp32 values: a lane's rows of the tile in batches of VB row loads, the first batch on its way during the scores
+        // (one load at a time, each waited for, was most of the kernel: one head over 4096 tokens, 16 -> 14 us with the loads of 16 rows in flight).  Rows past
+        // the last token are re-reads of it, replaced by zeros when they are used.
+        constexpr int VIT = kWave / KPL;                      // rows per lane and tile
+        constexpr int VBATCH = VQ ? 1 : (VIT < 16 ? VIT : 16);
+        float4 vbuf[VBATCH][2];
+        auto request_rows = [&](int i0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < VBATCH; ++i) {
+                const int64_t vrow = v_row0 + t0 + min((i0 + i) * KPL + ko, n_valid - 1);
+                vbuf[i][0] = v[vrow * (D / 4) + 2 * rl];
+                vbuf[i][1] = v[vrow * (D / 4) + 2 * rl + 1];
+            }
+        };
+        if constexpr (!VQ) {
+            request_rows(0);
+            asm volatile("" ::: "memory");   // (or the loads are moved to their use)
+        }
         float s1[1][RG];
         float (&s)[RG] = s1[0];
         int q_off = 0;
@@ -1502,16 +1709,19 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) void decode_kernel_valu(
                 }
             }
         } else {
-            for (int kb = 0; kb < n_valid; kb += KPL) {
-                const int key = kb + ko;
-                if (key < n_valid) {
+#pragma unroll
+            for (int i0 = 0; i0 < VIT; i0 += VBATCH) {
+                if (i0 > 0) request_rows(i0);
+#pragma unroll
+                for (int i = 0; i < VBATCH; ++i) {
+                    const int key = (i0 + i) * KPL + ko;
                     float pv[RG];
 #pragma unroll
                     for (int r = 0; r < RG; ++r) pv[r] = sm.pbuf[wave][key][r];
-                    const int64_t vrow = v_row0 + t0 + key;
-                    const float4 a = v[vrow * (D / 4) + 2 * rl];
-                    const float4 b = v[vrow * (D / 4) + 2 * rl + 1];
-                    const float vals[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+                    const float4 a = vbuf[i][0], b = vbuf[i][1];
+                    const bool in = key < n_valid;
+                    const float vals[8] = {in ? a.x : 0.0f, in ? a.y : 0.0f, in ? a.z : 0.0f, in ? a.w : 0.0f,
+                                           in ? b.x : 0.0f, in ? b.y : 0.0f, in ? b.z : 0.0f, in ? b.w : 0.0f};
 #pragma unroll
                     for (int r = 0; r < RG; ++r)
 #pragma unroll
@@ -1691,6 +1901,10 @@ int launch_decode_mfma_rg(const octopus_codebooks_t &cb, const DecodeShape &s, c
     return static_cast<int>(hipGetLastError());
 }
 
+// Query rows of the smallest row group the host shapes a call for (least_rows in octopus_host.cpp).
+template <class P>
+constexpr int least_rows_built() { return mx_scores<P>() || P::D > 128 ? 1 : (P::D == 128 ? 4 : 2); }
+
 // Paged pools (bf16 values, row groups of at most 8 rows).
 template <class P, int RG>
 int launch_decode_paged_rg(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *k_pool,
@@ -1709,16 +1923,17 @@ int launch_decode_paged_plan(const octopus_codebooks_t &cb, const DecodeShape &s
                              const void *k_pool, const void *v_pool, const PageTable &pt, const int32_t *seq_lens,
                              float *part_ml, float *part_acc, hipStream_t stream) {
     switch (s.rows_per_pass) {
-        case 1: return launch_decode_paged_rg<P, 1>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream);
-        case 2: return launch_decode_paged_rg<P, 2>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream);
+        case 1: if constexpr (least_rows_built<P>() <= 1) return launch_decode_paged_rg<P, 1>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream); break;
+        case 2: if constexpr (least_rows_built<P>() <= 2) return launch_decode_paged_rg<P, 2>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream); break;
         case 4: return launch_decode_paged_rg<P, 4>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream);
         case 8: return launch_decode_paged_rg<P, 8>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream);
         case 128:
         case 256:   // the many-row kernel (d <= 128), which takes the page table as an argument
             if constexpr (P::D <= 128) return launch_decode_mq<P>(cb, s, q_rot, k_pool, v_pool, seq_lens, part_ml, part_acc, stream, pt);
             return static_cast<int>(hipErrorInvalidValue);
-        default: return static_cast<int>(hipErrorInvalidValue);
+        default: break;
     }
+    return static_cast<int>(hipErrorInvalidValue);   // (a row group smaller than the least one)
 }
 
 // Paged pools with the QJL side-car in pages as well (a pool of [page][KV head] side-car tiles).
@@ -1741,12 +1956,13 @@ int launch_decode_paged_qjl_plan(const octopus_codebooks_t &cb, const DecodeShap
                                  const PageTable &pt, const int32_t *seq_lens, float *part_ml, float *part_acc,
                                  hipStream_t stream) {
     switch (s.rows_per_pass) {
-        case 1: return launch_decode_paged_qjl_rg<P, 1>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream);
-        case 2: return launch_decode_paged_qjl_rg<P, 2>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream);
+        case 1: if constexpr (least_rows_built<P>() <= 1) return launch_decode_paged_qjl_rg<P, 1>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream); break;
+        case 2: if constexpr (least_rows_built<P>() <= 2) return launch_decode_paged_qjl_rg<P, 2>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream); break;
         case 4: return launch_decode_paged_qjl_rg<P, 4>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream);
         case 8: return launch_decode_paged_qjl_rg<P, 8>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream);
-        default: return static_cast<int>(hipErrorInvalidValue);
+        default: break;
     }
+    return static_cast<int>(hipErrorInvalidValue);
 }
 
 template <class P, bool SCORES>
@@ -1845,12 +2061,13 @@ int launch_decode_qjl_plan(const octopus_codebooks_t &cb, const DecodeShape &s, 
                            const int32_t *seq_lens, float *part_ml, float *part_acc, float *scores_out,
                            hipStream_t stream) {
     switch (s.rows_per_pass) {
-        case 1: return launch_decode_qjl_rg<P, 1>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream);
-        case 2: return launch_decode_qjl_rg<P, 2>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream);
+        case 1: if constexpr (least_rows_built<P>() <= 1) return launch_decode_qjl_rg<P, 1>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream); break;
+        case 2: if constexpr (least_rows_built<P>() <= 2) return launch_decode_qjl_rg<P, 2>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream); break;
         case 4: return launch_decode_qjl_rg<P, 4>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream);
         case 8: return launch_decode_qjl_rg<P, 8>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream);
-        default: return static_cast<int>(hipErrorInvalidValue);
+        default: break;
     }
+    return static_cast<int>(hipErrorInvalidValue);
 }
 
 }  // namespace octopus

@@ -116,6 +116,8 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
     constexpr int STEP_BYTES = Gm::STEP_BYTES;
     constexpr int TILEB = P::GRANULES * kWave * 16;  // bytes per cache tile
     constexpr bool MX = mx_scores<P>();
+    constexpr bool LEAN = NWV > 4;   // fewer registers for the score pass: 256 with two wavefronts per SIMD
+    constexpr int LOOKAHEAD = NWV > 4 ? 1 : 2;
     // bf16 of 2^VB + code: exponent 127 + VB, the code in the top VB bits of the 7-bit mantissa
     constexpr float BIAS = static_cast<float>(1 << VB);
     constexpr int CODE_POS = 7 - VB;
@@ -123,7 +125,7 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
     constexpr uint32_t CODE_BASE = (static_cast<uint32_t>(127 + VB) << 7) * 0x00010001u;
     constexpr int KS = 2 * KPL;
     __shared__ DecodeSmemVq<P, RG, VB, VG> sm;
-    __shared__ __attribute__((aligned(16))) uint4 qop_store[MX ? P::NTRI * QueryOperands<P, RG>::ROWS : 1];
+    __shared__ __attribute__((aligned(16))) uint2 qop_store[MX ? sizeof(QueryOperands<P, RG>) / 8 : 1];
     const QueryOperands<P, RG> &qop = *reinterpret_cast<const QueryOperands<P, RG> *>(&qop_store[0]);
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -133,7 +135,9 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
     static_assert(RG * P::QS * 4 <= sizeof(sm.xs), "rotated queries fit");
     static_assert(RG * D * 4 <= STEP_BYTES && 2 * RG <= Gm::ZP, "a wavefront's results fit");
     float (*q_rows)[P::QS] = reinterpret_cast<float (*)[P::QS]>(&sm.xs[0][0][0][0][0]);
-    WorkSpan span;
+    BookLevels<P> levels;
+    levels.load(lane);
+    WorkSpan<KPL, NWV> span;
     span.open(shp, seq_lens, lane);
     if (span.pos >= span.end) return;   // (whole workgroup, before any barrier)
     bool tables_built = false;
@@ -358,7 +362,7 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
         asm volatile("" : "+s"(q_off));
         // D2-D4 with the B operands of D6 built alongside: piece i is requested in chunk i (NCH - 1) / NPB of
         // the pass and built in the chunk the next piece is requested in (the last one in the last chunk)
-        constexpr int NCH = score_chunks<P, RG>();
+        constexpr int NCH = MX ? mx_units<P, KPL, LEAN>() : score_chunks<P, RG>();
         static_assert(NCH > NPB, "a chunk of the score pass per operand piece");
         auto build_in_chunk = [&](auto cc) __attribute__((always_inline)) {
             constexpr int ci = decltype(cc)::value;
@@ -372,7 +376,7 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
                 if constexpr (pi * (NCH - 1) / NPB == ci) raw_request(pp);
             });
         };
-        if constexpr (MX) tile_scores_mx<P, RG, KPL, decltype(build_in_chunk), (NWV > 4 ? 2 : 4)>(w, qop, sm.tb, lane, s, build_in_chunk);
+        if constexpr (MX) tile_scores_mx<P, RG, KPL, decltype(build_in_chunk), LOOKAHEAD, LEAN>(w, qop, sm.tb, lane, s, build_in_chunk);
         else tile_scores<P, RG, KPL>(w, qg + q_off, sm.tb, lane, s, build_in_chunk);
 #pragma unroll
         for (int k = 0; k < KPL; ++k) {
@@ -418,7 +422,10 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
             for (int i = 0; i < 4; ++i) {
                 float a;
                 if constexpr (RP == 4) a = alpha[i];
-                else a = (g4 & 1) ? alpha[4 + i] : alpha[i];
+                else {   // (copies: a choice between the array's elements keeps it in memory, see decode_kernel_mfma)
+                    const float lower = alpha[i], upper = alpha[RG > 4 ? 4 + i : 0];
+                    a = (g4 & 1) ? upper : lower;
+                }
 #pragma unroll
                 for (int c = 0; c < CPL; ++c)
 #pragma unroll
@@ -469,7 +476,7 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
         if (any) load_records(ww.step_begin, slot_first, w);
         load_rows(ww.step_begin, slot_first, any, rows);
         if (!tables_built) {   // workgroup-uniform
-            build_tables<P, MX>(sm.tb, books, tid, NWV * kWave);
+            build_tables<P, MX>(sm.tb, levels, tid, NWV * kWave);
             tables_built = true;
         }
         // The segment's rotated queries as matrix-core operands.  Every wavefront is past the previous segment's merge (the
@@ -477,18 +484,7 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
         if constexpr (MX) {
             sq.store(shp, ww, wave, lane, q_rows, nullptr);
             __syncthreads();
-            constexpr int ROWS = QueryOperands<P, RG>::ROWS;
-            uint4 *dst = reinterpret_cast<uint4 *>(&qop_store[0]);
-            for (int e = tid; e < P::NTRI * ROWS; e += NWV * kWave) {
-                const int i = e / ROWS, r = e % ROWS;
-                float x = 0.0f, y = 0.0f, z = 0.0f;
-                if (r < RG) {
-                    x = q_rows[r][3 * i];
-                    y = q_rows[r][3 * i + 1];
-                    z = q_rows[r][3 * i + 2];
-                }
-                dst[e] = split_triplet(x, y, z);
-            }
+            build_query_operands<P, RG>(&qop_store[0], q_rows, tid, NWV * kWave);
             __syncthreads();
         }
         for (int step = ww.step_begin; step < ww.step_end; step += ww.step_stride) process_step(step);
@@ -518,7 +514,10 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
                 float tot = 0.0f;
 #pragma unroll
                 for (int hh = 0; hh < NA; ++hh) {
-                    const float t = acc[c][hh][i] + __shfl_down(acc[c][hh][i], RP * 4, kWave);
+                    // the leading-part and remainder rows lie 16 (RP = 4) or 32 lanes apart
+                    float hi = acc[c][hh][i], lo = acc[c][hh][i];
+                    if constexpr (RP == 4) swap16(hi, lo); else swap32(hi, lo);
+                    const float t = acc[c][hh][i] + lo;
                     tot = a_sel == hh ? t : tot;
                 }
                 const int r = RP == 4 ? i : 4 * g4 + i;

@@ -115,8 +115,8 @@ __device__ __forceinline__ void build_dir_lut(float4 *lut, const float *c_xi, in
 // Kernel-argument centroids to LDS with compile-time indices (every lane stores the same values).  Only the
 // levels that plan P has are copied: the arrays are sized for the largest plan, and each level costs the
 // copying wavefront a move and an LDS store while the rest of the workgroup waits.
-template <class P>
-__device__ __forceinline__ void copy_books(const DeviceBooks &books, float (*c_xi)[kMaxLevels], float (*c_rho)[kMaxLevels]) {
+template <class P, int NX, int NR>
+__device__ __forceinline__ void copy_books(const DeviceBooks &books, float (*c_xi)[NX], float (*c_rho)[NR]) {
     constexpr int two = P::NCLASS == 2 ? 1 : 0;
     constexpr int n_xi[2] = {1 << P::BD0, two << (P::BD1 > 0 ? P::BD1 : 0)};
     // (at least two norm levels, so that the first boundary of a class is a number whatever its bit width)
@@ -152,9 +152,18 @@ __device__ __forceinline__ float wave_max(float v) {
 }
 
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
+    auto take = [](float x, auto ctrl, auto rows) __attribute__((always_inline)) {   // 0 where no lane is read
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, decltype(rows)::value,
+                                                          0xf, false));
+    };
+    using std::integral_constant;
+    v += take(v, integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});   // row_shr:1, 2, 4, 8
+    v += take(v, integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+    v += take(v, integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+    v += take(v, integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+    v += take(v, integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});   // row_bcast:15 into rows 1 and 3
+    v += take(v, integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});   // row_bcast:31 into rows 2 and 3
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
 // Rows of 16 lanes exchanged between two registers: swap16 trades the odd rows of a for the even rows of b
@@ -168,6 +177,25 @@ __device__ __forceinline__ void swap32(float &a, float &b) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     a = __uint_as_float(r[0]);
     b = __uint_as_float(r[1]);
+}
+
+// The value of lane (l ^ M), without LDS traffic (a shuffle through LDS takes over a hundred cycles, these about ten).
+template <int M>
+__device__ __forceinline__ float lane_xor(float x, int lane) {
+    static_assert(M == 1 || M == 2 || M == 4 || M == 8 || M == 16 || M == 32, "one bit of the lane index");
+    if constexpr (M == 1) return dpp_take<0xB1, 0xf>(x);        // quad permute [1, 0, 3, 2]
+    else if constexpr (M == 2) return dpp_take<0x4E, 0xf>(x);   // quad permute [2, 3, 0, 1]
+    else if constexpr (M == 4) {
+        // lanes 0-3 and 8-11 of each row from four lanes above, the others from four lanes below
+        const int v = __float_as_int(x);
+        const int up = __builtin_amdgcn_update_dpp(v, v, 0x104, 0xf, 0x5, false);
+        return __int_as_float(__builtin_amdgcn_update_dpp(up, v, 0x114, 0xf, 0xa, false));
+    } else if constexpr (M == 8) return dpp_take<0x128, 0xf>(x);   // row rotate by 8
+    else {
+        float a = x, b = x;
+        if constexpr (M == 16) swap16(a, b); else swap32(a, b);   // a: the lower of each pair of rows twice, b: the upper
+        return (lane & M) ? a : b;
+    }
 }
 
 }  // namespace octopus

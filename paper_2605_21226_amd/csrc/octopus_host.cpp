@@ -222,7 +222,7 @@ bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 
 DecodeShape make_decode_shape(const octopus_plan_t &plan, int32_t n_seq, int32_t n_q_heads, int32_t n_kv_heads,
                               int32_t n_q, int64_t max_len, int64_t t_capacity, bool many_rows, int32_t rows_cap,
-                              int32_t vq_mfma_waves) {
+                              int32_t vq_mfma_waves, int32_t rows_min) {
     DecodeShape s{};
     s.n_seq = n_seq;
     s.n_q_heads = n_q_heads;
@@ -263,7 +263,7 @@ DecodeShape make_decode_shape(const octopus_plan_t &plan, int32_t n_seq, int32_t
     // Query rows scored per key by one workgroup: the power of two covering rows_per_kv, at most 8
     // (fewer with the QJL residual).  Rows beyond rows_per_kv in the last group are zero queries whose
     // results are not stored.
-    s.rows_per_pass = 1;
+    s.rows_per_pass = rows_min;
     while (s.rows_per_pass < s.rows_per_kv && s.rows_per_pass < rows_cap) s.rows_per_pass *= 2;
     if (vq_mfma_waves > 0) {
         // The matrix-core kernel over quantised values: row groups of 4 or 8; up to d = 128 two wavefronts per
@@ -550,6 +550,17 @@ static void set_queries(DecodeShape *s, const void *q, int32_t q_dtype, const ui
     s->scale = scale;
 }
 
+// Query rows of the smallest row group of the kernels over bf16 values.  Plans without joint tables (4 bits) score on the
+// vector units, a group of 8 / rows triplets at a time: with one row a chunk is eight triplets of two keys, which spills;
+// four rows (some of them zero queries) are faster than one or two (8 x 16384 tokens, 8 KV heads, d = 128, one / two query
+// heads per KV head: 80 / 74 us, as four 71 / 71; one with the QJL residual: 142, as four 78).  At d = 64 one row is served
+// as two (46 us, as two 44), with the residual as four (one 56, two 59, four 51); at d = 256, one key per lane, nothing spills and a row more costs its
+// arithmetic (two rows 77 us, as four 89).
+static int32_t least_rows(const octopus_plan_t &plan, bool many_rows, bool bf16_values, bool with_qjl) {
+    if (many_rows || !bf16_values || joint_plan(plan) || plan.head_dim > 128) return 1;
+    return plan.head_dim == 128 || with_qjl ? 4 : 2;
+}
+
 // Whether the kernel that serves a call rotates its queries itself; else a kernel before it does.  matrix_kernel: the
 // kernel over bf16 values or the matrix-core kernel over quantised values (the vector-unit kernels read the rotated
 // queries through scalar loads, the many-row kernel from a layout of its own).
@@ -602,10 +613,16 @@ static int attn_decode(const octopus_codebooks_t *cb, const void *q, int32_t q_d
     const int32_t vq_mfma = with_vq && scores_out == nullptr
                                 ? vq_mfma_available(cb->plan, vq_mfma_rows(n_q * (n_q_heads / n_kv_heads)), v_bits, v_group)
                                 : 0;
+    int32_t rows_min = least_rows(cb->plan, many_rows, !with_vq && v_dtype == OCTOPUS_DTYPE_BF16, with_qjl);
     DecodeShape s = make_decode_shape(cb->plan, n_seq, n_q_heads, n_kv_heads, n_q, max_len, t_capacity, many_rows, rows_cap,
-                                      vq_mfma);
+                                      vq_mfma, rows_min);
+    Workspace w = make_workspace(cb->plan, s);
+    if (static_scratch_call && w.total > static_cast<size_t>(OCTOPUS_STATIC_SCRATCH_BYTES)) {
+        // (the static array is checked against the need of the smallest row group)
+        s = make_decode_shape(cb->plan, n_seq, n_q_heads, n_kv_heads, n_q, max_len, t_capacity, many_rows, rows_cap, vq_mfma);
+        w = make_workspace(cb->plan, s);
+    }
     set_queries(&s, q, q_dtype, signs, signs2, scale);
-    const Workspace w = make_workspace(cb->plan, s);
     // every entry point asks for the one documented size, whatever its own kernel needs (the static scratch
     // has been checked against the need of the kernels it serves)
     const size_t required = static_scratch_call ? w.total
@@ -884,7 +901,7 @@ static int attn_decode_paged(const octopus_codebooks_t *cb, const void *q, int32
         if (vq_waves <= 0) return OCTOPUS_EUNSUPPORTED;
     }
     DecodeShape s = make_decode_shape(cb->plan, n_seq, n_q_heads, n_kv_heads, n_q, max_len, reach, many_rows, rows_cap,
-                                      vq_waves);
+                                      vq_waves, least_rows(cb->plan, many_rows, v_bits == 0, with_qjl));
     set_queries(&s, q, q_dtype, signs, with_qjl ? signs2 : nullptr, scale);
     const Workspace w = make_workspace(cb->plan, s);
     const size_t required = std::max(w.total, octopus_attn_decode_workspace(cb, n_seq, n_q_heads, n_kv_heads, n_q, max_len));
