@@ -64,9 +64,15 @@ struct DecodeSmemVqN {
     __attribute__((aligned(16))) unsigned char stage[Gm::NWV][Gm::STEP_BYTES];
 };
 
+// Whether NW wavefronts fit 160 KB of LDS.  The count is that of 64 codebook levels per table and class and of query
+// operands of 16 bytes per (triplet, row), both smaller by now: which shapes have a kernel is part of the interface (over
+// pages the others are refused), and the one that would fit in addition spills hundreds of bytes per lane.
 template <class P, int RG, int VB, int VG, int NW>
 constexpr bool vq_lds_fits_n() {
-    return sizeof(DecodeSmemVqN<P, RG, VB, VG, NW>) + (mx_scores<P>() ? sizeof(QueryOperands<P, RG>) : 16) + 64 <= 160 * 1024;
+    using T = DecodeTables<P>;
+    constexpr size_t levels = 4 * kMaxLevels * sizeof(float) - sizeof(T::c_xi) - sizeof(T::c_rho);
+    constexpr size_t operands = mx_scores<P>() ? P::NTRI * (RG <= 4 ? 4 : 8) * 16 : 16;
+    return sizeof(DecodeSmemVqN<P, RG, VB, VG, NW>) + levels + operands + 64 <= 160 * 1024;
 }
 
 // Wavefronts per workgroup: two per SIMD up to d = 128 (each within 256 registers), whose different phases --
