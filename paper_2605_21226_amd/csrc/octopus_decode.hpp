@@ -1829,14 +1829,16 @@ __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, const flo
     float m = -INFINITY;
     for (int j = lane; j < n_part; j += kWave) m = fmaxf(m, part_ml[(prow0 + static_cast<int64_t>(j) * pstride) * 2]);
     m = wave_max(m);
-    if (win_ml != nullptr) m = fmaxf(m, win_ml[orow * 2]);
+    // the many-row kernel's maxima are in units of log2, the others' and the window's in natural ones
+    const float unit = shp.rows_per_pass >= 128 ? 1.0f : kLog2e;
+    const float m_win = win_ml != nullptr ? win_ml[orow * 2] * (kLog2e / unit) : -INFINITY;
+    m = fmaxf(m, m_win);
     float a[CPT];
 #pragma unroll
     for (int c = 0; c < CPT; ++c) a[c] = 0.0f;
     float l = 0.0f;
     if (win_ml != nullptr) {
-        const float mw = win_ml[orow * 2];
-        const float f = (mw == -INFINITY) ? 0.0f : exp2_raw((mw - m) * kLog2e);
+        const float f = (m_win == -INFINITY) ? 0.0f : exp2_raw((m_win - m) * unit);
         if (lane == 0) l = f * win_ml[orow * 2 + 1];
 #pragma unroll
         for (int c = 0; c < CPT; ++c) a[c] = f * win_acc[orow * D + c * kWave + lane];
@@ -1846,7 +1848,7 @@ __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, const flo
         float f = 0.0f;
         if (j < n_part) {
             const float2 ml = *reinterpret_cast<const float2 *>(part_ml + (prow0 + static_cast<int64_t>(j) * pstride) * 2);
-            f = (ml.x == -INFINITY) ? 0.0f : exp2_raw((ml.x - m) * kLog2e);
+            f = (ml.x == -INFINITY) ? 0.0f : exp2_raw((ml.x - m) * unit);
             l += f * ml.y;
         }
         __syncthreads();

@@ -25,9 +25,14 @@
 
 namespace octopus {
 
-// Query rows per workgroup: 32 per wavefront, NW = 4 wavefronts (128 rows) or, at d = 64 where the
-// registers allow two wavefronts per SIMD, NW = 8 (256 rows).  The keys of a tile are decoded once per
-// workgroup, so more rows mean less decoding; the host picks 256 when there are rows enough to fill them.
+// Query rows per workgroup: 32 per wavefront, NW = 4 wavefronts (128 rows) or NW = 8 (256 rows, two wavefronts per SIMD
+// within 256 registers each).  The keys of a tile are decoded once per workgroup, so more rows mean less decoding; the host
+// picks 256 when there are rows enough to fill them.
+// What bounds it (cycles of a tile, timestamps, 8 wavefronts, d = 64, b = 4): first product 1050, softmax 1660, second
+// product 820, staging 1060 - 1400, barrier up to 700, of 5400.  A 32x32x16 product takes 32 cycles of the matrix core and
+// keeps the vector units of its SIMD from issuing for about 16 of them, so two wavefronts' 2 x 40 products and 2 x (about 30
+// exponentials at quarter rate and 250 other vector instructions) per tile add up to some 4400 cycles of issue: the way down
+// is fewer vector instructions per score.
 
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 constexpr int kXcds = 8;   // accelerator dies of the chip; consecutive workgroups go to consecutive dies
@@ -47,7 +52,7 @@ struct MqSmem {
 };
 
 template <class P, int NW>
-__global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D <= 64 ? 2 : 1))) void decode_kernel_mq(DeviceBooks books, DecodeShape shp,
+__global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D <= 64 || NW == 8 ? 2 : 1))) void decode_kernel_mq(DeviceBooks books, DecodeShape shp,
                                                          const float *__restrict__ q_rot,
                                                          const uint4 *__restrict__ cache,
                                                          const uint16_t *__restrict__ v,
@@ -109,7 +114,8 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
     for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const float a = qg[(16 * kk + 8 * h + 2 * e) * ROWS], b = qg[(16 * kk + 8 * h + 2 * e + 1) * ROWS];
+            // (in units of log2: the scores come out as exponents of two)
+            const float a = qg[(16 * kk + 8 * h + 2 * e) * ROWS] * kLog2e, b = qg[(16 * kk + 8 * h + 2 * e + 1) * ROWS] * kLog2e;
             const uint32_t ab = __float_as_uint(a), bb = __float_as_uint(b);
             qh[kk].u[e] = __builtin_amdgcn_perm(bb, ab, 0x07060302u);
             const float al = a - __uint_as_float(ab & 0xffff0000u), bl = b - __uint_as_float(bb & 0xffff0000u);
@@ -222,7 +228,15 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
         }
     };
 
-    float m_run = -INFINITY, l_run = 0.0f;
+    // The row's reference exponent: probabilities are 2^(score - m_ref).  Its negative is what the first product's
+    // accumulators start from, so the scores arrive with the subtraction done; it is moved (and everything summed so far
+    // rescaled) only when a score exceeds it by more than kHeadroom, which after the first tile is rare: a probability may
+    // then be up to 2^kHeadroom, which floating point does not mind.
+    constexpr float kHeadroom = 8.0f;
+    float m_ref = 0.0f, l_run = 0.0f;
+    f32x16_t c_ref;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) c_ref[e] = 0.0f;
     f32x16_t oacc[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
@@ -251,8 +265,7 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
         f32x16_t sacc[2];
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb) {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) sacc[mb][e] = 0.0f;
+            sacc[mb] = c_ref;
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) {
                 BF8 ah, al;
@@ -278,33 +291,46 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sacc[mb][e]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
-        const float m_new = fmaxf(m_run, mx);
-        const float alpha = exp2_raw((m_run - m_new) * kLog2e);
-        m_run = m_new;
-        const float m_log2 = -m_new * kLog2e;     // p = 2^(s log2(e) - m log2(e)): one fma per score
+            for (int e = mb == 0 ? 1 : 0; e < 16; e += 2) mx = fmaxf(fmaxf(mx, sacc[mb][e]), sacc[mb][e + 1 < 16 ? e + 1 : e]);
+        {
+            float other = mx, own = mx;
+            swap32(own, other);                    // the row's other half of the tile is in lane ^ 32
+            mx = fmaxf(own, other);
+        }
+        const bool first = tile == tile_begin;
+        if (first || __ballot(mx > kHeadroom) != 0) {
+            const float delta = first ? mx : fmaxf(mx, 0.0f);
+            m_ref += delta;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) c_ref[e] = -m_ref;
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) sacc[mb][e] -= delta;
+            if (!first) {
+                const float alpha = exp2_raw(-delta);
+                l_run *= alpha;
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) oacc[nb][e] *= alpha;
+            }
+        }
         float psum = 0.0f;
         BF8 ph[4], pl[4];   // per group of 16 keys: the 8 k-slots of this lane, hi and lo
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
             for (int e = 0; e < 16; e += 2) {
-                const float p0 = exp2_raw(fmaf(sacc[mb][e], kLog2e, m_log2)), p1 = exp2_raw(fmaf(sacc[mb][e + 1], kLog2e, m_log2));
+                const float p0 = exp2_raw(sacc[mb][e]), p1 = exp2_raw(sacc[mb][e + 1]);
                 psum += p0 + p1;
+                // (the remainders as v_dot2_f32_bf16 of the packed pair with (-1, 0): one instruction instead of two, and slower)
                 const uint32_t b0 = __float_as_uint(p0), b1 = __float_as_uint(p1);
                 const float l0 = p0 - __uint_as_float(b0 & 0xffff0000u), l1 = p1 - __uint_as_float(b1 & 0xffff0000u);
                 ph[2 * mb + e / 8].u[(e % 8) / 2] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
                 pl[2 * mb + e / 8].u[(e % 8) / 2] = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
             }
-        l_run = fmaf(l_run, alpha, psum);
-        // the running maxima stop moving after the first tiles: skip the rescale when no row of the wave needs it
-        if (__ballot(alpha != 1.0f) != 0) {
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) oacc[nb][e] *= alpha;
-        }
+        l_run += psum;
         // O^T += V^T P^T
 #pragma unroll
         for (int g16 = 0; g16 < 4; ++g16)
@@ -338,7 +364,7 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
                     make_float4(oacc[nb][4 * q4], oacc[nb][4 * q4 + 1], oacc[nb][4 * q4 + 2], oacc[nb][4 * q4 + 3]);
         const float l = l_run + __shfl_xor(l_run, 32, kWave);
         if (h == 0) {
-            part_ml[prow * 2] = m_run;
+            part_ml[prow * 2] = tile_begin < tile_end ? m_ref : -INFINITY;   // in units of log2
             part_ml[prow * 2 + 1] = l;
         }
     }
@@ -359,8 +385,7 @@ int launch_decode_mq(const octopus_codebooks_t &cb, const DecodeShape &s, const 
     if (s.rows_per_pass == 128) {
         go(decode_kernel_mq<P, 4>, 4);
     } else if (s.rows_per_pass == 256) {
-        if constexpr (P::D <= 64) go(decode_kernel_mq<P, 8>, 8);
-        else return static_cast<int>(hipErrorInvalidValue);
+        go(decode_kernel_mq<P, 8>, 8);
     } else {
         return static_cast<int>(hipErrorInvalidValue);
     }

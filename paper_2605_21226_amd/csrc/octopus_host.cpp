@@ -222,7 +222,7 @@ bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 
 DecodeShape make_decode_shape(const octopus_plan_t &plan, int32_t n_seq, int32_t n_q_heads, int32_t n_kv_heads,
                               int32_t n_q, int64_t max_len, int64_t t_capacity, bool many_rows, int32_t rows_cap,
-                              int32_t vq_mfma_waves, int32_t rows_min) {
+                              int32_t vq_mfma_waves, int32_t rows_min, bool wide_rows) {
     DecodeShape s{};
     s.n_seq = n_seq;
     s.n_q_heads = n_q_heads;
@@ -237,9 +237,10 @@ DecodeShape make_decode_shape(const octopus_plan_t &plan, int32_t n_seq, int32_t
     const int64_t len = std::max<int64_t>(max_len, 1);
     if (many_rows) {
         // Matrix-core kernel for many query rows: blocks of 128 rows (4 wavefronts), or of 256 rows (8
-        // wavefronts) at d = 64 when there are rows enough; one workgroup per (block, split).  A compute unit
-        // runs 8 of these wavefronts at d = 64 and 4 at d = 128.
-        s.rows_per_pass = (plan.head_dim <= 64 && s.rows_per_kv >= 192) ? 256 : 128;
+        // wavefronts) when there are rows enough; one workgroup per (block, split).  A compute unit runs 8 of these
+        // wavefronts, or 4 with blocks of 128 rows at d = 128.  The blocks of 256 at d = 128 (wide_rows) came later than the
+        // documented workspace size, which stays that of blocks of 128: see many_rows_at_128.
+        s.rows_per_pass = (plan.head_dim <= 64 ? s.rows_per_kv >= 192 : wide_rows) ? 256 : 128;
         s.n_row_groups = (s.rows_per_kv + s.rows_per_pass - 1) / s.rows_per_pass;
         const int64_t groups = static_cast<int64_t>(n_seq) * n_kv_heads * s.n_row_groups;
         const int64_t max_tiles = (len + OCTOPUS_TILE - 1) / OCTOPUS_TILE;
@@ -568,6 +569,25 @@ static bool rotates_in_kernel(const octopus_plan_t &plan, bool many_rows, bool m
     return !many_rows && matrix_kernel && joint_plan(plan);
 }
 
+// Many query rows at d = 128, more than one block of 128: blocks of 256 rows, two wavefronts per SIMD, each key decoded for
+// twice the rows (one sequence of 15877 tokens, 8 KV heads, 2036 rows each: kernel 470 -> 330 us; with blocks of 128 the
+// one wavefront per SIMD spent 3000 of a tile's 7800 cycles decoding keys with its matrix core idle).  Their workspace has
+// to fit the documented size: fewer splits until it does, and if it never does the shape stays as it is.
+static void many_rows_at_128(const octopus_codebooks_t *cb, int64_t max_len, DecodeShape *s, Workspace *w) {
+    if (cb->plan.head_dim != 128 || s->rows_per_kv <= 128) return;
+    DecodeShape wide = make_decode_shape(cb->plan, s->n_seq, s->n_q_heads, s->n_kv_heads, s->n_q, max_len, s->t_capacity, true, 8, 0,
+                                         1, true);
+    const size_t limit = plain_decode_workspace(cb, s->n_seq, s->n_q_heads, s->n_kv_heads, s->n_q, max_len);
+    Workspace ww = make_workspace(cb->plan, wide);
+    while (ww.total > limit && wide.n_splits > 1) {
+        --wide.n_splits;
+        ww = make_workspace(cb->plan, wide);
+    }
+    if (ww.total > limit) return;
+    *s = wide;
+    *w = ww;
+}
+
 static int attn_decode(const octopus_codebooks_t *cb, const void *q, int32_t q_dtype, int32_t n_seq,
                        int32_t n_q_heads, int32_t n_kv_heads, int32_t n_q, const uint8_t *signs, const void *cache,
                        int64_t t_capacity, const void *v, int32_t v_dtype, const int32_t *seq_lens, int64_t max_len,
@@ -622,6 +642,7 @@ static int attn_decode(const octopus_codebooks_t *cb, const void *q, int32_t q_d
         s = make_decode_shape(cb->plan, n_seq, n_q_heads, n_kv_heads, n_q, max_len, t_capacity, many_rows, rows_cap, vq_mfma);
         w = make_workspace(cb->plan, s);
     }
+    if (many_rows) many_rows_at_128(cb, max_len, &s, &w);
     set_queries(&s, q, q_dtype, signs, signs2, scale);
     // every entry point asks for the one documented size, whatever its own kernel needs (the static scratch
     // has been checked against the need of the kernels it serves)
@@ -902,8 +923,9 @@ static int attn_decode_paged(const octopus_codebooks_t *cb, const void *q, int32
     }
     DecodeShape s = make_decode_shape(cb->plan, n_seq, n_q_heads, n_kv_heads, n_q, max_len, reach, many_rows, rows_cap,
                                       vq_waves, least_rows(cb->plan, many_rows, v_bits == 0, with_qjl));
+    Workspace w = make_workspace(cb->plan, s);
+    if (many_rows) many_rows_at_128(cb, max_len, &s, &w);
     set_queries(&s, q, q_dtype, signs, with_qjl ? signs2 : nullptr, scale);
-    const Workspace w = make_workspace(cb->plan, s);
     const size_t required = std::max(w.total, octopus_attn_decode_workspace(cb, n_seq, n_q_heads, n_kv_heads, n_q, max_len));
     if (workspace == nullptr || !aligned(workspace, 256) || workspace_bytes < required) return OCTOPUS_EWORKSPACE;
     char *base = static_cast<char *>(workspace);

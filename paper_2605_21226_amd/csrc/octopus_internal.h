@@ -72,7 +72,7 @@ struct Workspace {
 
 DecodeShape make_decode_shape(const octopus_plan_t &plan, int32_t n_seq, int32_t n_q_heads, int32_t n_kv_heads,
                               int32_t n_q, int64_t max_len, int64_t t_capacity, bool many_rows, int32_t rows_cap = 8,
-                              int32_t vq_mfma_waves = 0, int32_t rows_min = 1);
+                              int32_t vq_mfma_waves = 0, int32_t rows_min = 1, bool wide_rows = false);
 // Row group the matrix-core kernel over quantised values would serve a call with (4 or 8 query rows), and
 // whether such a kernel is built for the plan and value format (octopus_common.hip).
 inline int32_t vq_mfma_rows(int32_t rows_per_kv) { return rows_per_kv <= 4 ? 4 : 8; }

@@ -1,0 +1,24 @@
+"""GPU parity of the many-row kernel where its blocks change: one row more than a block of 128 or 256, several blocks, rows
+that leave most of the last block empty, and sequences of one tile, one key more, and many tiles over several splits (the
+running reference of a row moves between tiles, is different in every split, and may lie far above a tile's scores).  Bar
+and oracle as in test_gpu_parity.py."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from test_gpu_parity import run_decode_case  # noqa: E402
+
+
+@pytest.mark.parametrize("d,bits", [(64, 4), (64, 1.5), (128, 3), (128, 4)])
+@pytest.mark.parametrize("n_q,lens", [(128, [64]), (129, [65, 1]), (192, [1000]), (257, [640, 0, 63])])
+def test_decode_many_rows_blocks(d, bits, n_q, lens):
+    run_decode_case(d, bits, len(lens), 1, 1, n_q, lens, "bf16", seed=int(d + n_q), want_scores=False)
+
+
+def test_decode_many_rows_several_splits():
+    run_decode_case(128, 3, 1, 2, 2, 140, [5000], "bf16", seed=11, want_scores=False)
+
