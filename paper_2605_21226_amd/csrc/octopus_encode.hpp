@@ -3,6 +3,8 @@
 #ifndef OCTOPUS_ENCODE_HPP_
 #define OCTOPUS_ENCODE_HPP_
 
+#include <cstddef>
+
 #include "octopus_device.hpp"
 
 namespace octopus {
@@ -61,7 +63,7 @@ constexpr int encode_threads() { return encode_waves<P>() * kWave; }
 template <class P, bool QJL = false>
 struct EncodeSmem {
     float u[3 * P::NTRI][kURow];           // rotated coordinates [coordinate][key]
-    uint32_t rec[P::NWORDS][kWave];        // packed records [word][key]
+    __attribute__((aligned(16))) uint32_t rec[P::NWORDS][kWave];   // packed records [word][key]
     static constexpr int REP = encode_table_rep<P::D, (P::BD0 > P::BD1 ? P::BD0 : P::BD1)>();
     static constexpr int CREP = encode_cell_rep<P::D>();
     float4 lut0[quadrant_entries(P::BD0) * REP];
@@ -128,18 +130,30 @@ __device__ __forceinline__ float4 dir_lookup(const float4 *lut, uint32_t code, i
     return n;
 }
 
-template <int BD, int REP>
-__device__ __forceinline__ void build_seed_grid(float2 *cell, float *bnd, const float *c_xi, int tid, int nthreads) {
+// Two phases with a barrier between them: the cell of every boundary, one boundary per thread; then, per cell, how many
+// boundaries lie in lower ones, four cells of boundaries per LDS read.  (Computing every boundary and its cell anew for
+// every cell was 1900 cycles of a workgroup's start at 4-bit directions and 3900 at 5-bit ones.)
+template <int BD>
+__device__ __forceinline__ void build_boundaries(float *bnd, int *bnd_cell, const float *c_xi, int tid) {
     using G = SeedGrid<BD>;
-    for (int k = tid; k <= kMaxLevels; k += nthreads)
-        bnd[k] = (k < G::K - 1) ? 0.5f * (c_xi[k] + c_xi[k + 1]) : INFINITY;
+    if (tid <= kMaxLevels) {
+        const float b = tid < G::K - 1 ? 0.5f * (c_xi[min(tid, G::K - 1)] + c_xi[min(tid + 1, G::K - 1)]) : INFINITY;
+        bnd[tid] = b;
+        if (tid < kMaxLevels) bnd_cell[tid] = tid < G::K - 1 ? G::cell_of(b) : G::NCELL;
+    }
+}
+template <int BD, int REP>
+__device__ __forceinline__ void build_seed_grid(float2 *cell, const float *bnd, const int *bnd_cell, int tid, int nthreads) {
+    using G = SeedGrid<BD>;
+#pragma unroll 1
     for (int c = tid; c < G::NCELL; c += nthreads) {
         int below = 0;
-        for (int k = 0; k < G::K - 1; ++k) {
-            const float b = 0.5f * (c_xi[k] + c_xi[k + 1]);
-            below += (G::cell_of(b) < c) ? 1 : 0;
+#pragma unroll
+        for (int k = 0; k < G::K; k += 4) {   // (entries past the last boundary are in no lower cell; at least four exist)
+            const int4 at = *reinterpret_cast<const int4 *>(bnd_cell + k);
+            below += (at.x < c ? 1 : 0) + (at.y < c ? 1 : 0) + (at.z < c ? 1 : 0) + (at.w < c ? 1 : 0);
         }
-        const float first = (below < G::K - 1) ? 0.5f * (c_xi[below] + c_xi[below + 1]) : INFINITY;
+        const float first = bnd[below];       // +inf past the last one
 #pragma unroll
         for (int r = 0; r < REP; ++r) cell[c * REP + r] = make_float2(__int_as_float(below), first);
     }
@@ -396,16 +410,39 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
     };
     // the first tile's rows are requested before the tables are built, so that they arrive meanwhile
     fetch_tile(first_tile);
+    // The codebooks' levels, one per lane, from the kernel's first argument and in flight with the rows: copied by
+    // constant index they are a scalar load and a straight line of moves per level, 2000 cycles before the first table.
+    // Together with the two phases of the tables below, at d = 128 and 8 KV heads: one key appended and decoded against
+    // 24.4 -> 24.2 us, 3001 keys and values of a prompt at 4 bits 18.6 -> 18.4 us; the same where tiles are many.
+    float book_xi[P::NCLASS], book_rho[P::NCLASS];
+    {
+        typedef const float __attribute__((address_space(4))) *arg_t;
+        arg_t arg = (arg_t)__builtin_amdgcn_kernarg_segment_ptr();
+#pragma unroll
+        for (int c = 0; c < P::NCLASS; ++c) {
+            book_xi[c] = arg[offsetof(DeviceBooks, c_xi) / 4 + c * kMaxLevels + lane];
+            book_rho[c] = arg[offsetof(DeviceBooks, c_rho) / 4 + c * kMaxLevels + lane];
+        }
+    }
 
     // tables
-    if (wave == 0) copy_books<P>(books, sm.c_xi, sm.c_rho);
-    __syncthreads();
-    build_encode_lut<P::BD0, REP>(sm.lut0, sm.nbx0, sm.nby0, sm.c_xi[0], tid, NT);
-    build_seed_grid<P::BD0, CREP>(sm.cell0, sm.bnd_xi[0], sm.c_xi[0], tid, NT);
-    if constexpr (P::NCLASS == 2) {
-        build_encode_lut<P::BD1, REP>(sm.lut1, sm.nbx1, sm.nby1, sm.c_xi[1], tid, NT);
-        build_seed_grid<P::BD1, CREP>(sm.cell1, sm.bnd_xi[1], sm.c_xi[1], tid, NT);
+    if (wave == 0) {
+        static_assert(kMaxLevels == kWave, "a level per lane");
+#pragma unroll
+        for (int c = 0; c < P::NCLASS; ++c) {
+            sm.c_xi[c][lane] = book_xi[c];
+            sm.c_rho[c][lane] = book_rho[c];
+        }
     }
+    __syncthreads();
+    int *bnd_cell = reinterpret_cast<int *>(&sm.rec[0][0]);   // (no record is being built yet)
+    build_boundaries<P::BD0>(sm.bnd_xi[0], bnd_cell, sm.c_xi[0], tid);
+    if constexpr (P::NCLASS == 2) build_boundaries<P::BD1>(sm.bnd_xi[1], bnd_cell + kMaxLevels, sm.c_xi[1], tid);
+    build_encode_lut<P::BD0, REP>(sm.lut0, sm.nbx0, sm.nby0, sm.c_xi[0], tid, NT);
+    if constexpr (P::NCLASS == 2) build_encode_lut<P::BD1, REP>(sm.lut1, sm.nbx1, sm.nby1, sm.c_xi[1], tid, NT);
+    __syncthreads();
+    build_seed_grid<P::BD0, CREP>(sm.cell0, sm.bnd_xi[0], bnd_cell, tid, NT);
+    if constexpr (P::NCLASS == 2) build_seed_grid<P::BD1, CREP>(sm.cell1, sm.bnd_xi[1], bnd_cell + kMaxLevels, tid, NT);
     if (tid < 2 * kMaxLevels) {
         const int c = tid / kMaxLevels, k = tid % kMaxLevels;
         const int levels = 1 << (c ? (P::BN1 > 0 ? P::BN1 : 1) : P::BN0);
