@@ -573,6 +573,13 @@ static bool rotates_in_kernel(const octopus_plan_t &plan, bool many_rows, bool m
 // twice the rows (one sequence of 15877 tokens, 8 KV heads, 2036 rows each: kernel 470 -> 330 us; with blocks of 128 the
 // one wavefront per SIMD spent 3000 of a tile's 7800 cycles decoding keys with its matrix core idle).  Their workspace has
 // to fit the documented size: fewer splits until it does, and if it never does the shape stays as it is.
+// They pay where a compute unit then walks fewer tiles one after the other (rounds of workgroups x tiles per split); a tile
+// of 256 rows takes 1.2 - 1.3 times one of 128, so where the chip is not full either way blocks of 128 on twice the compute
+// units are faster.  Calls with blocks of 128 / 256, tiles in a row n / w: 59 rows x 4 heads, 4245 tokens (17 / 17) 79.8 /
+// 85.8 us, 64 x 8, one KV head, 16384 (18 / 20) 80.6 / 96.7, 256 x 4, 1500 (24 / 24) 113 / 122; 72 x 8, 15396 (41 / 25)
+// 164 / 132, 900 x 4, one KV head, 20000 (38 / 19) 219 / 181, 160 x 1, 30000 (30 / 17) 129 / 92, 512 x 4, 4096 (32 / 16)
+// 153 / 122.  At a ratio of 5 / 4 either may win: 1000 x 4, two KV heads, 6000 at 4 bits (24 / 19) 117 / 122, 200 x 1, 20480
+// (20 / 16) 94.5 / 88.5; the line is at 4 / 3.
 static void many_rows_at_128(const octopus_codebooks_t *cb, int64_t max_len, DecodeShape *s, Workspace *w) {
     if (cb->plan.head_dim != 128 || s->rows_per_kv <= 128) return;
     DecodeShape wide = make_decode_shape(cb->plan, s->n_seq, s->n_q_heads, s->n_kv_heads, s->n_q, max_len, s->t_capacity, true, 8, 0,
@@ -584,6 +591,12 @@ static void many_rows_at_128(const octopus_codebooks_t *cb, int64_t max_len, Dec
         ww = make_workspace(cb->plan, wide);
     }
     if (ww.total > limit) return;
+    const int64_t tiles = (std::max<int64_t>(max_len, 1) + OCTOPUS_TILE - 1) / OCTOPUS_TILE;
+    auto in_a_row = [&](const DecodeShape &x) {
+        const int64_t wgs = static_cast<int64_t>(x.n_seq) * x.n_kv_heads * x.n_row_groups * x.n_splits;
+        return (wgs + 255) / 256 * ((tiles + x.n_splits - 1) / x.n_splits);
+    };
+    if (4 * in_a_row(wide) > 3 * in_a_row(*s)) return;
     *s = wide;
     *w = ww;
 }

@@ -22,3 +22,9 @@ def test_decode_many_rows_blocks(d, bits, n_q, lens):
 def test_decode_many_rows_several_splits():
     run_decode_case(128, 3, 1, 2, 2, 140, [5000], "bf16", seed=11, want_scores=False)
 
+
+# d = 128 takes blocks of 256 rows only where they leave fewer tiles to walk in a row: 288 workgroups of 128 rows against 144
+# of 256 (the last of which has 129 rows); 16 splits against 25
+@pytest.mark.parametrize("n_seq,n_kv,n_q,lens", [(9, 8, 385, [130, 64, 65, 0, 1, 129, 128, 2, 63]), (1, 8, 130, [25600])])
+def test_decode_many_rows_blocks_of_256_at_128(n_seq, n_kv, n_q, lens):
+    run_decode_case(128, 3, n_seq, n_kv, n_kv, n_q, lens, "bf16", seed=n_q, want_scores=False)
