@@ -1302,7 +1302,7 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
     // swapping roles, so that no register copies (and no full memory wait in front of them) carry the
     // prefetched records over.
     auto process_step = [&](int step, const uint32_t (&w)[KPL][P::NWORDS], uint32_t (&w_next)[KPL][P::NWORDS],
-                            const uint32_t (&sc)[KPL][4 * QO::WPL + 1], uint32_t (&sc_next)[KPL][4 * QO::WPL + 1])
+                            uint32_t (&sc)[KPL][4 * QO::WPL + 1], uint32_t (&sc_next)[KPL][4 * QO::WPL + 1])
                             __attribute__((always_inline)) {
         const int t0 = step * (KPL * kWave);
         const int n_valid = min(KPL * kWave, ww.len - t0);
@@ -1321,17 +1321,24 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
             else v_cur[k] = values_of(step, true);
         }
         if constexpr (!AHEAD) {   // d = 256: the registers hold one step's values only while it is worked on
+            // ... and its side-car, asked for before them: held across the previous step it made the residual kernels spill,
+            // as did the wide form of the score pass (4 x 16384 tokens, 8 KV heads: b = 3, one row 98 -> 69 us, four rows
+            // 103 -> 74; b = 2.5, eight rows 129 -> 83)
+            if constexpr (QJL) {
+                if constexpr (PAGED) load_sidecar_at(slot_cur, sc);
+                else load_sidecar(step, sc);
+            }
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) load_values(v_cur[ks / 2], ks, vr[ks]);
         }
         if constexpr (PAGED) {
             load_records_at(slot_nxt, w_next);
-            if constexpr (QJL) load_sidecar_at(slot_nxt, sc_next);
+            if constexpr (QJL && AHEAD) load_sidecar_at(slot_nxt, sc_next);
 #pragma unroll
             for (int k = 0; k < KPL; ++k) slot_cur[k] = slot_nxt[k];
         } else {
             load_records(step_nx, w_next);
-            if constexpr (QJL) load_sidecar(min(step + ww.step_stride, ww.step_last), sc_next);
+            if constexpr (QJL && AHEAD) load_sidecar(min(step + ww.step_stride, ww.step_last), sc_next);
         }
         // The loads above feed the NEXT step, which sits behind a branch in the unrolled loop; without this
         // barrier the compiler sinks them into that branch, i.e. to the top of the step that uses them, and
@@ -1365,7 +1372,7 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             __builtin_amdgcn_wave_barrier();
         } else {
-            if constexpr (MX) tile_scores_mx<P, RG, KPL>(w, qop, sm.tb, lane, s);
+            if constexpr (MX) tile_scores_mx<P, RG, KPL, NoChunkHook, 2, QJL>(w, qop, sm.tb, lane, s);
             else tile_scores<P, RG, KPL>(w, qg + q_off, sm.tb, lane, s);
         }
 #pragma unroll
@@ -1472,10 +1479,10 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
                 page_ids(min(ww.step_begin + ww.step_stride, ww.step_last), page_nxt);
                 page_slots(page_first, slot_cur);
                 load_records_at(slot_cur, w_a);
-                if constexpr (QJL) load_sidecar_at(slot_cur, sc_a);
+                if constexpr (QJL && AHEAD) load_sidecar_at(slot_cur, sc_a);
             } else {
                 load_records(ww.step_begin, w_a);
-                if constexpr (QJL) load_sidecar(ww.step_begin, sc_a);
+                if constexpr (QJL && AHEAD) load_sidecar(ww.step_begin, sc_a);
             }
         }
         // (the rows of the operand that hold no probabilities stay zero)

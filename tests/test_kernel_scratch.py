@@ -1,0 +1,38 @@
+"""Kernels whose inner loops have to stay in registers, by what the compiler reports of the built library: scratch memory per
+lane.  A change that makes them spill costs tens of per cent and no parity test sees it."""
+import os
+import re
+
+import pytest
+
+pytest.importorskip("msgpack")
+
+from kernel_resources import kernels  # noqa: E402
+from paper_2605_21226_amd import binding  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def library():
+    if not os.path.exists(binding.LIB_PATH):
+        pytest.skip("liboctopus.so is not built")
+    return kernels(binding.LIB_PATH)
+
+
+def _decode(library, d, scores, qjl):
+    """{((b_dir, b_nrm, b_dir, b_nrm), query rows, paged): scratch bytes per lane} of decode_kernel_mfma."""
+    pat = re.compile(rf"18decode_kernel_mfmaINS_5PlanTILi{d}ELi(\d)ELi(\d)ELi(\d)ELi(\d)EEELi(\d)ELb{scores:d}ELb{qjl:d}ELb(\d)E")
+    found = {}
+    for name, k in library.items():
+        m = pat.search(name)
+        if m:
+            n = [int(x) for x in m.groups()]
+            found[(tuple(n[:4]), n[4], n[5])] = k[".private_segment_fixed_size"]
+    return found
+
+
+def test_residual_kernels_at_256_do_not_spill(library):
+    """Five bit widths (4 bits scores on the vector units), four row groups, contiguous and paged; 12 bytes are a lane's
+    three loop-invariant words."""
+    joint = {k: v for k, v in _decode(library, 256, True, True).items() if k[0][0] < 5}
+    assert len(joint) == 5 * 4 * 2
+    assert {k: v for k, v in joint.items() if v > 12} == {}
