@@ -237,10 +237,9 @@ __device__ __forceinline__ void build_tables(DecodeTables<P> &tb, const BookLeve
 
 // Work distribution of the split-K kernels.  The steps of the call (a step = tiles_per_step 64-token tiles) lie in a row:
 // sequences in order, the (KV head, row group) pairs of a sequence in order, the steps of a pair in order.  The row is
-// divided evenly over the workgroups (one per compute unit, fewer when there are not item_waves steps for each, so that a
-// short call has few partial results), and a workgroup walks its share as one SEGMENT per pair that it touches: all its
-// wavefronts together, interleaved (step_begin, step_begin + item_waves, ...), so that the workgroup streams through
-// memory front to back.  At the end of a segment the wavefronts' partial results are merged in LDS and one partial per
+// divided evenly over the workgroups (one per compute unit), and a workgroup walks its share as one SEGMENT per pair that it
+// touches: all its wavefronts together, interleaved (step_begin, step_begin + item_waves, ...), so that the workgroup streams
+// through memory front to back.  At the end of a segment the wavefronts' partial results are merged in LDS and one partial per
 // query row goes to memory, at slot (workgroup + pair), which no two segments share.  Every workgroup computes its
 // share from the sequence lengths by itself (one load and a scan of 64 lanes): nothing is planned by an earlier kernel and
 // nothing is handed out at run time.
@@ -249,7 +248,18 @@ __device__ __forceinline__ void build_tables(DecodeTables<P> &tb, const BookLeve
 // merge in LDS included): 24 sequences of 125 - 8000 tokens, 8 KV heads of 8 query rows, d = 128, paged, with a window:
 // 194 -> 146 us; 32 sequences of 1 k - 64 k, d = 256: 877 -> 830 us; one head, 4096 tokens, fp32: 28.6 -> 21.3 us;
 // equal lengths (16 x 32768): 213.4 -> 211.7 us.
+// A segment has a fixed cost (queries rotated, operands built, first loads, merge, four barriers) of the order of a round of
+// steps, which an even division does not see.  It serves calls of fewer pairs than workgroups with steps enough for all;
+//   * where there are no more BLOCKS of item_waves steps (the last one of a pair may have fewer) than workgroups, a block is
+//     a workgroup's: one step per wavefront and one segment per workgroup, whatever the lengths;
+//   * where there are as many pairs as workgroups or more, every pair counts kSegmentTiles more than its whole blocks, and
+//     only whole blocks are handed out.
+// Calls with every length divided evenly / as here, d = 128, b = 3, ragged (lengths of 1 / 64 of the longest and up): 32
+// sequences to 372 tokens, one KV head of eight rows 43.2 / 17.7 us, 64 to 500, 8 KV heads of four rows 50.5 / 25.8, 256 to 500
+// 156 / 84, 256 to 4000 358 / 239, the same over quantised values 371 / 225, 40 to 16000 162 / 135 (kSegmentTiles half or twice
+// as many: 239 - 247, 135 - 145; with eight wavefronts 222 - 258).  Where the division stays even, choosing costs 0.1 - 0.2 us.
 constexpr int kDecodeWorkgroups = 256;   // one per compute unit
+constexpr int kSegmentTiles = 8;         // what a segment's fixed cost is counted for (twice with eight wavefronts)
 
 // (tiles_per_step: 1 or 2)
 __device__ __forceinline__ int steps_of(int len, int max_len, int tiles_per_step) {
@@ -281,18 +291,56 @@ __device__ __forceinline__ uint32_t divide(uint64_t a, uint64_t b) {
     return static_cast<uint32_t>(static_cast<double>(a) / static_cast<double>(b));
 }
 
-// Workgroups that share `total` steps, the first step of workgroup b, and the workgroup that has step x.
-__device__ __forceinline__ int span_workgroups(uint64_t total, int item_waves) {
-    return total >= static_cast<uint64_t>(kDecodeWorkgroups) * item_waves
-               ? kDecodeWorkgroups
-               : static_cast<int>((static_cast<uint32_t>(total) + item_waves - 1) / static_cast<uint32_t>(item_waves));
-}
-__device__ __forceinline__ uint64_t span_first(uint64_t total, int n_wg, int b) {
-    return n_wg == kDecodeWorkgroups ? (total * static_cast<uint32_t>(b)) / kDecodeWorkgroups
-                                     : static_cast<uint64_t>(divide(total * static_cast<uint32_t>(b), static_cast<uint32_t>(n_wg)));
-}
-__device__ __forceinline__ int span_owner(uint64_t total, int n_wg, uint64_t x) {
-    return static_cast<int>(divide((x + 1) * static_cast<uint32_t>(n_wg) - 1, total));
+// How a call's steps are divided: in units, of which a pair has fixed() and then those of its quanta in order; a workgroup
+// takes the quanta whose first unit lies in its share.  (Quanta are never further apart than a share is long -- one unit, or
+// item_waves units of a total of item_waves kDecodeWorkgroups at least -- so the workgroups that have quanta of a pair are
+// consecutive.)  waves_log2, tps: log2 of the wavefronts per workgroup, tiles per step.
+enum : int { kDivideEvenly, kBlockEach, kPairsWeighed };
+struct Division {
+    int kind;
+    int waves_log2, tps;
+
+    // Most calls are known to be divided evenly by their steps alone (and code that runs costs its fetch here).
+    static __device__ __forceinline__ bool surely_even(const DecodeShape &shp, uint64_t steps, int waves_log2) {
+        return shp.pairs_fill == 0 && steps > static_cast<uint64_t>(kDecodeWorkgroups) << waves_log2;
+    }
+    // Steps and (non-empty) pairs of the call.  The blocks are at most a block's rest per pair more than the steps alone
+    // make; where this bound is past the workgroups and the blocks are not, the even division is close to whole blocks.
+    __device__ __forceinline__ void set(uint64_t steps, uint64_t pairs) {
+        kind = pairs >= static_cast<uint64_t>(kDecodeWorkgroups) ? kPairsWeighed : kDivideEvenly;
+        if (steps + (pairs << waves_log2) - pairs <= static_cast<uint64_t>(kDecodeWorkgroups) << waves_log2) kind = kBlockEach;
+    }
+    __device__ __forceinline__ uint32_t fixed() const {
+        return kind == kPairsWeighed ? static_cast<uint32_t>((waves_log2 == 3 ? 2 * kSegmentTiles : kSegmentTiles) / tps) : 0u;
+    }
+    __device__ __forceinline__ int steps_log2() const { return kind == kDivideEvenly ? 0 : waves_log2; }   // steps per quantum
+    __device__ __forceinline__ int units_log2() const { return kind == kPairsWeighed ? waves_log2 : 0; }   // units per quantum
+    __device__ __forceinline__ uint32_t quanta(uint32_t steps) const { return (steps + (1u << steps_log2()) - 1u) >> steps_log2(); }
+    __device__ __forceinline__ uint32_t units(uint32_t steps) const {
+        return steps > 0u ? fixed() + (quanta(steps) << units_log2()) : 0u;
+    }
+    // quanta of a pair that begin before its unit x
+    __device__ __forceinline__ uint32_t quanta_before(uint32_t x) const {
+        return x > fixed() ? (x - fixed() + (1u << units_log2()) - 1u) >> units_log2() : 0u;
+    }
+    // the share of workgroup b, and the workgroup that has unit x
+    __device__ __forceinline__ void share(uint64_t total, int b, uint64_t *pos, uint64_t *end) const {
+        if (__builtin_expect(kind == kBlockEach, 0)) {   // (at most as many units as workgroups)
+            *pos = min(static_cast<uint32_t>(b), static_cast<uint32_t>(total));
+            *end = min(static_cast<uint32_t>(b) + 1u, static_cast<uint32_t>(total));
+        } else {
+            const uint64_t t = total * static_cast<uint32_t>(b);
+            *pos = t / kDecodeWorkgroups;
+            *end = (t + total) / kDecodeWorkgroups;
+        }
+    }
+    __device__ __forceinline__ int owner(uint64_t total, uint64_t x) const {
+        return kind == kBlockEach ? static_cast<int>(x) : static_cast<int>(divide((x + 1) * kDecodeWorkgroups - 1, total));
+    }
+};
+
+__device__ __forceinline__ uint32_t last_lane(uint32_t x) {
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(x), kWave - 1));
 }
 
 struct WaveWork {
@@ -307,53 +355,78 @@ template <int TPS, int NW>
 struct WorkSpan {
     int chunk;               // first sequence of the 64
     int lane_len;            // length of sequence chunk + lane
-    uint32_t lane_sum;       // steps per pair of sequences chunk .. chunk + lane
-    uint64_t before;         // steps per pair of the sequences before chunk
-    uint64_t pos, end;       // the workgroup's steps that are left
+    uint32_t lane_sum;       // units per pair of sequences chunk .. chunk + lane
+    uint64_t before;         // units per pair of the sequences before chunk
+    uint64_t pos, end;       // the workgroup's units that are left
+    Division div{kDivideEvenly, NW == 8 ? 3 : 2, TPS};
 
-    __device__ __forceinline__ void look(const DecodeShape &shp, const int32_t *seq_lens, int lane) {
+    static_assert(NW == 4 || NW == 8, "waves_log2");
+    __device__ __forceinline__ uint32_t read(const DecodeShape &shp, const int32_t *seq_lens, int lane) {
         const int s = chunk + lane;
-        lane_len = s < shp.n_seq ? min(max(seq_lens[s], 0), shp.max_len) : 0;
-        lane_sum = wave_scan(static_cast<uint32_t>(steps_of(lane_len, shp.max_len, TPS)));
+        const int len = seq_lens[min(s, shp.n_seq - 1)];
+        lane_len = s < shp.n_seq ? min(max(len, 0), shp.max_len) : 0;
+        return static_cast<uint32_t>(steps_of(lane_len, shp.max_len, TPS));
     }
-    __device__ __forceinline__ uint32_t chunk_sum() const {
-        return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lane_sum), kWave - 1));
+    __device__ __forceinline__ void look(const DecodeShape &shp, const int32_t *seq_lens, int lane) {
+        lane_sum = wave_scan(div.units(read(shp, seq_lens, lane)));
     }
+    __device__ __forceinline__ uint32_t chunk_sum() const { return last_lane(lane_sum); }
     __device__ __forceinline__ void open(const DecodeShape &shp, const int32_t *seq_lens, int lane) {
         const uint64_t G = static_cast<uint64_t>(shp.n_kv_heads) * shp.n_row_groups;
-        uint64_t total = 0;
-        for (chunk = 0; chunk < shp.n_seq; chunk += kWave) {
-            look(shp, seq_lens, lane);
-            total += chunk_sum();
-        }
-        total *= G;
         chunk = 0;
         before = 0;
-        if (shp.n_seq > kWave) look(shp, seq_lens, lane);
-        const int b = static_cast<int>(blockIdx.x), n_wg = span_workgroups(total, NW);
-        pos = b < n_wg ? span_first(total, n_wg, b) : 0;
-        end = b < n_wg ? span_first(total, n_wg, b + 1) : 0;
+        uint32_t st = read(shp, seq_lens, lane);
+        lane_sum = wave_scan(st);
+        uint64_t total = chunk_sum();
+        if (__builtin_expect(shp.n_seq > kWave, 0)) {
+            for (chunk = kWave; chunk < shp.n_seq; chunk += kWave) total += last_lane(wave_scan(read(shp, seq_lens, lane)));
+            chunk = 0;
+            st = read(shp, seq_lens, lane);
+        }
+        total *= G;
+        if (__builtin_expect(!Division::surely_even(shp, total, div.waves_log2), 0)) {
+            uint64_t pairs = __popcll(__ballot(st > 0u));
+            for (chunk = kWave; chunk < shp.n_seq; chunk += kWave) pairs += __popcll(__ballot(read(shp, seq_lens, lane) > 0u));
+            div.set(total, pairs * G);
+            if (div.kind != kDivideEvenly) {
+                lane_sum = wave_scan(div.units(st));
+                total = chunk_sum();
+                for (chunk = kWave; chunk < shp.n_seq; chunk += kWave) total += last_lane(wave_scan(div.units(read(shp, seq_lens, lane))));
+                total *= G;
+            }
+            chunk = 0;
+            if (shp.n_seq > kWave) read(shp, seq_lens, lane);   // (lane_len)
+        }
+        div.share(total, static_cast<int>(blockIdx.x), &pos, &end);
     }
     // The next segment (wave-uniform) and this wavefront's part of it; false when the share is done.
     __device__ __forceinline__ bool next(const DecodeShape &shp, const int32_t *seq_lens, int wave, int lane, WaveWork *ww) {
-        if (pos >= end) return false;
         const uint64_t G = static_cast<uint64_t>(shp.n_kv_heads) * shp.n_row_groups;
-        while ((before + chunk_sum()) * G <= pos) {   // (more than 64 sequences; a later one holds step pos, so it ends)
-            before += chunk_sum();
-            chunk += kWave;
-            look(shp, seq_lens, lane);
-        }
-        const int l = __ffsll(static_cast<unsigned long long>(__ballot((before + lane_sum) * G > pos))) - 1;
-        const int len = __builtin_amdgcn_readlane(lane_len, l);
-        const uint32_t sum = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lane_sum), l));
-        const int n_steps = steps_of(len, shp.max_len, TPS);   // > 0: the sequence holds step pos
-        const uint64_t first = (before + sum - static_cast<uint32_t>(n_steps)) * G;
-        const uint64_t local = pos - first;
-        const int g = __builtin_amdgcn_readfirstlane(static_cast<int>(divide(local, static_cast<uint32_t>(n_steps))));
-        const uint64_t group_first = static_cast<uint64_t>(static_cast<uint32_t>(g)) * static_cast<uint32_t>(n_steps);
-        const uint64_t stop = first + group_first + static_cast<uint32_t>(n_steps);
-        const uint64_t seg_end = stop < end ? stop : end;
-        const int begin = static_cast<int>(local - group_first);
+        int l, len, n_steps, g;
+        uint32_t lo, hi;
+        do {
+            if (pos >= end) return false;
+            while ((before + chunk_sum()) * G <= pos) {   // (more than 64 sequences; a later one holds unit pos, so it ends)
+                before += chunk_sum();
+                chunk += kWave;
+                look(shp, seq_lens, lane);
+            }
+            l = __ffsll(static_cast<unsigned long long>(__ballot((before + lane_sum) * G > pos))) - 1;
+            len = __builtin_amdgcn_readlane(lane_len, l);
+            const uint32_t sum = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lane_sum), l));
+            n_steps = steps_of(len, shp.max_len, TPS);   // > 0: the sequence holds unit pos
+            const uint32_t n_units = div.units(static_cast<uint32_t>(n_steps));
+            const uint64_t first = (before + sum - n_units) * G;
+            const uint64_t local = pos - first;
+            g = __builtin_amdgcn_readfirstlane(static_cast<int>(divide(local, n_units)));
+            const uint64_t group_first = static_cast<uint64_t>(static_cast<uint32_t>(g)) * n_units;
+            const uint64_t stop = first + group_first + n_units;
+            const uint64_t seg_end = stop < end ? stop : end;
+            lo = div.quanta_before(static_cast<uint32_t>(local - group_first));
+            hi = div.quanta_before(static_cast<uint32_t>(seg_end - first - group_first));
+            pos = seg_end;
+        } while (lo >= hi);   // (none of the pair's quanta begins in this share)
+        const int begin = static_cast<int>(lo << div.steps_log2());
         ww->seq = chunk + l;
         ww->grp = 0;
         ww->kvh = g;
@@ -366,12 +439,11 @@ struct WorkSpan {
         ww->pair = static_cast<int64_t>(ww->seq) * shp.n_kv_heads + ww->kvh;
         ww->len = len;
         ww->n_tiles = static_cast<int>((static_cast<uint32_t>(len) + kWave - 1) / kWave);
-        ww->step_end = begin + static_cast<int>(seg_end - pos);
+        ww->step_end = min(static_cast<int>(hi << div.steps_log2()), n_steps);
         ww->step_begin = begin + wave;
         ww->step_stride = NW;
         const int more = max(ww->step_end - 1 - ww->step_begin, 0);
         ww->step_last = ww->step_begin + more / NW * NW;
-        pos = seg_end;
         return true;
     }
 };
@@ -1778,10 +1850,14 @@ __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, const flo
     constexpr int UN = 8;           // partial rows in flight per lane
     __shared__ float wgt[kWave];
     const int lane = threadIdx.x;
-    const int64_t orow = blockIdx.x;  // (seq, qi, head)
-    const int head = static_cast<int>(orow % shp.n_q_heads);
-    const int qi = static_cast<int>((orow / shp.n_q_heads) % shp.n_q);
-    const int seq = static_cast<int>(orow / (static_cast<int64_t>(shp.n_q_heads) * shp.n_q));
+    int lens = seq_lens[min(lane, shp.n_seq - 1)];   // asked for before anything is computed
+    // (a launch has fewer than 2^32 threads, so a row's index fits 32 bits; divided as 64 bits it is 300 instructions)
+    const uint32_t urow = blockIdx.x;  // (seq, qi, head)
+    const int64_t orow = urow;
+    const int head = static_cast<int>(urow % static_cast<uint32_t>(shp.n_q_heads));
+    const uint32_t query = urow / static_cast<uint32_t>(shp.n_q_heads);
+    const int qi = static_cast<int>(query % static_cast<uint32_t>(shp.n_q));
+    const int seq = static_cast<int>(query / static_cast<uint32_t>(shp.n_q));
     const int kvh = head / shp.heads_per_kv;
     const int row = qi * shp.heads_per_kv + head % shp.heads_per_kv;
     const int grp = row / shp.rows_per_pass, r = row % shp.rows_per_pass;
@@ -1797,28 +1873,49 @@ __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, const flo
         pstride = 1;
     } else {
         const uint64_t G = static_cast<uint64_t>(shp.n_kv_heads) * shp.n_row_groups;
-        uint64_t total = 0, first = 0;
-        int own = 0;
-        for (int s0 = 0; s0 < shp.n_seq; s0 += kWave) {
-            const int s = s0 + lane;
-            const int st = s < shp.n_seq ? steps_of(seq_lens[s], shp.max_len, shp.tiles_per_step) : 0;
-            const uint32_t sum = wave_scan(static_cast<uint32_t>(st));
+        uint64_t total = 0, before = 0;
+        uint32_t st = 0, own = 0;   // steps of sequence s0 + lane, and of this row's
+        auto read = [&](int s0) {
+            if (s0 > 0 || shp.n_seq > kWave) lens = seq_lens[min(s0 + lane, shp.n_seq - 1)];
+            st = s0 + lane < shp.n_seq ? static_cast<uint32_t>(steps_of(lens, shp.max_len, shp.tiles_per_step)) : 0u;
+        };
+        auto add = [&](int s0, uint32_t x) {   // x: per lane, of sequences s0 ..
+            const uint32_t sum = wave_scan(x);
             if (seq >= s0 && seq < s0 + kWave) {
-                own = __builtin_amdgcn_readlane(st, seq - s0);
-                first = total + static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sum), seq - s0)) -
-                        static_cast<uint32_t>(own);
+                own = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(st), seq - s0));
+                before = total + static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sum - x), seq - s0));
             }
-            total += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sum), kWave - 1));
+            total += last_lane(sum);
+        };
+        for (int s0 = 0; s0 < shp.n_seq; s0 += kWave) {
+            read(s0);
+            add(s0, st);
         }
         total *= G;
+        Division div{kDivideEvenly, shp.item_waves == 8 ? 3 : 2, shp.tiles_per_step};
+        if (__builtin_expect(!Division::surely_even(shp, total, div.waves_log2), 0)) {
+            uint64_t pairs = 0;
+            for (int s0 = 0; s0 < shp.n_seq; s0 += kWave) {
+                read(s0);
+                pairs += __popcll(__ballot(st > 0u));
+            }
+            div.set(total, pairs * G);
+            if (div.kind != kDivideEvenly) {
+                total = 0;
+                for (int s0 = 0; s0 < shp.n_seq; s0 += kWave) {
+                    read(s0);
+                    add(s0, div.units(st));
+                }
+                total *= G;
+            }
+        }
         const int g = kvh * shp.n_row_groups + grp;
-        first = first * G + static_cast<uint64_t>(g) * static_cast<uint32_t>(own);
-        const int n_wg = span_workgroups(total, shp.item_waves);
+        const uint64_t first = before * G + static_cast<uint64_t>(g) * div.units(own) + div.fixed();   // the pair's first quantum
         n_part = 0;
         int wg = 0;
-        if (own > 0) {
-            wg = span_owner(total, n_wg, first);
-            n_part = span_owner(total, n_wg, first + static_cast<uint32_t>(own) - 1) - wg + 1;
+        if (own > 0u) {
+            wg = div.owner(total, first);
+            n_part = div.owner(total, first + ((div.quanta(own) - 1u) << div.units_log2())) - wg + 1;
         }
         prow0 = (wg + static_cast<int64_t>(seq) * static_cast<int64_t>(G) + g) * shp.rows_per_pass + r;
         pstride = shp.rows_per_pass;

@@ -289,6 +289,7 @@ DecodeShape make_decode_shape(const octopus_plan_t &plan, int32_t n_seq, int32_t
     // Partial results: the kernels write one per workgroup and one more per (sequence, KV head, row group) at most (the
     // work distribution in octopus_decode.hpp); the workspace has had room for four times as many as below from the start,
     // and its documented size stays.
+    s.pairs_fill = groups >= 256 ? 1 : 0;
     s.max_items = static_cast<int32_t>(std::min<int64_t>(256 * 8 + groups, groups * std::max<int64_t>(max_steps, 1)));
     return s;
 }

@@ -47,6 +47,7 @@ struct DecodeShape {
     const uint8_t *signs, *signs2;   // signs2: second rotation of the QJL residual, or NULL
     float scale;
     int32_t q_is_bf16;
+    int32_t pairs_fill;     // there may be as many (sequence, KV head, row group) pairs with tokens as workgroups (256)
 };
 
 // Plans whose every class has a joint table (2 b_dir + b_nrm <= 10) score on the matrix cores where the kernel over bf16
