@@ -10,6 +10,7 @@ torch = pytest.importorskip("torch")
 if not torch.cuda.is_available():
     pytest.skip("no GPU", allow_module_level=True)
 
+from test_gpu_paged import run_paged_decode_case, run_paged_hybrid_case  # noqa: E402
 from test_gpu_parity import run_decode_case  # noqa: E402
 
 
@@ -28,3 +29,22 @@ def test_decode_many_rows_several_splits():
 @pytest.mark.parametrize("n_seq,n_kv,n_q,lens", [(9, 8, 385, [130, 64, 65, 0, 1, 129, 128, 2, 63]), (1, 8, 130, [25600])])
 def test_decode_many_rows_blocks_of_256_at_128(n_seq, n_kv, n_q, lens):
     run_decode_case(128, 3, n_seq, n_kv, n_kv, n_q, lens, "bf16", seed=n_q, want_scores=False)
+
+
+# ... at every bit width (a wavefront stages 16 coordinates of a key: triplets straddle two of them, and at the two-class
+# widths the boundary between the classes falls inside one's share), over pages, and with a window merged in
+WIDE_LENS = [130, 64, 65, 0, 1, 129, 128, 2, 63]
+
+
+@pytest.mark.parametrize("bits", [1, 1.5, 2, 2.5, 4])
+def test_decode_many_rows_blocks_of_256_at_128_every_width(bits):
+    run_decode_case(128, bits, 9, 8, 8, 385, WIDE_LENS, "bf16", seed=int(500 + 10 * bits), want_scores=False)
+
+
+@pytest.mark.parametrize("bits", [1, 2.5, 3, 4])
+def test_decode_many_rows_blocks_of_256_at_128_paged(bits):
+    run_paged_decode_case(128, bits, 9, 8, 8, 385, WIDE_LENS, seed=int(600 + 10 * bits))
+
+
+def test_decode_many_rows_blocks_of_256_at_128_paged_with_window():
+    run_paged_hybrid_case(128, 3, 9, 8, 8, 385, WIDE_LENS, [32, 5, 0, 7, 32, 1, 16, 31, 2], 32, "bf16", seed=700)

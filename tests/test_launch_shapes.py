@@ -1,0 +1,53 @@
+"""Which block of query rows the host picks, on the CPU: the calls of the GPU tests of the 256-row blocks at head dimension 128
+do take them, and the shapes that are faster with blocks of 128 rows keep those."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = next((c for c in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", shutil.which("hipcc")) if c and os.path.exists(c)), None)
+
+WIDE = (9, 8, 8, 385, 130)       # the shape test_gpu_many_rows.py runs at every width, contiguous and paged
+
+
+@pytest.fixture(scope="module")
+def shapes(tmp_path_factory):
+    if HIPCC is None:
+        pytest.skip("hipcc not found")
+    exe = str(tmp_path_factory.mktemp("host") / "shape_driver")
+    csrc = os.path.join(ROOT, "paper_2605_21226_amd", "csrc")
+    res = subprocess.run([HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", "-x", "hip", "-I" + os.path.join(ROOT, "include"),
+                          "-I" + csrc, "-Wno-unused-command-line-argument", os.path.join(csrc, "octopus_host.cpp"),
+                          os.path.join(ROOT, "tests", "host", "shape_driver.cpp"), "-o", exe],
+                         capture_output=True, text=True, timeout=600)
+    assert res.returncode == 0, res.stderr[-4000:]
+
+    def ask(paged, d, bits, n_seq, n_qh, n_kv, n_q, max_len):
+        args = [str(x) for x in (int(paged), d, bits, n_seq, n_qh, n_kv, n_q, max_len)]
+        res = subprocess.run([exe] + args, capture_output=True, text=True, timeout=60)
+        assert res.returncode == 0, res.stdout + res.stderr
+        return tuple(int(x) for x in res.stdout.split())
+    return ask
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("bits", [1, 1.5, 2, 2.5, 3, 4])
+def test_calls_with_blocks_of_256_rows(shapes, bits, paged):
+    assert shapes(paged, 128, bits, *WIDE)[0] == 256
+    assert shapes(paged, 128, bits, 1, 8, 8, 130, 25600)[0] == 256
+    assert shapes(paged, 64, bits, 1, 1, 1, 192, 1000)[0] == 256
+
+
+def test_calls_with_blocks_of_128_rows(shapes):
+    for n_seq, n_qh, n_kv, n_q, max_len in [(1, 4, 1, 59, 4245), (1, 8, 1, 64, 16384), (2, 1, 1, 128, 64), (1, 2, 2, 140, 5000)]:
+        assert shapes(False, 128, 3, n_seq, n_qh, n_kv, n_q, max_len)[0] == 128
+    assert shapes(False, 64, 3, 1, 1, 1, 191, 1000)[0] == 128
+
+
+def test_row_groups_of_plans_without_joint_tables(shapes):
+    """At 4 bits small groups are padded up to d = 128: the row group is part of what the GPU tests of it run."""
+    assert [shapes(False, 128, 4, 2, 2 * r, 2, 1, 700)[0] for r in (1, 2, 4, 8)] == [4, 4, 4, 8]
+    assert [shapes(False, 64, 4, 2, 2 * r, 2, 1, 700)[0] for r in (1, 2, 4, 8)] == [2, 2, 4, 8]
+    assert [shapes(False, 256, 4, 2, 2 * r, 2, 1, 700)[0] for r in (1, 2, 4, 8)] == [1, 2, 4, 8]
