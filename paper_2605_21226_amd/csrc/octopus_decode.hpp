@@ -617,9 +617,12 @@ struct SegmentQueries {
 template <int REP>
 __device__ __forceinline__ uint32_t lane_part(int lane) { return (static_cast<uint32_t>(lane) & (REP - 1)) << 4; }
 
-// Chunks of the score pass: 8 / RG triplets each.
-template <class P, int RG>
-constexpr int score_chunks() { return (P::NTRI + 8 / RG - 1) / (8 / RG); }
+// Triplets per chunk of the score pass, and chunks: 8 / RG, but four of one row and two keys (eight of them spill: one query
+// row, 4 bits, d = 64, 8 x 16384 tokens, 8 KV heads 45 us, with the residual 56; four: 42 and 49).
+template <int RG, int KPL>
+constexpr int score_triplets() { return RG == 1 && KPL == 2 ? 4 : 8 / RG; }
+template <class P, int RG, int KPL>
+constexpr int score_chunks() { return (P::NTRI + score_triplets<RG, KPL>() - 1) / score_triplets<RG, KPL>(); }
 
 struct NoChunkHook {
     template <class C>
@@ -634,8 +637,8 @@ template <class P, int RG, int KPL, class Hook = NoChunkHook>
 __device__ __forceinline__ void tile_scores(const uint32_t (&w)[KPL][P::NWORDS], const float *__restrict__ qg,
                                             const DecodeTables<P> &tb, int lane, float (&s)[KPL][RG],
                                             const Hook &hook = Hook{}) {
-    constexpr int CT = 8 / RG;                       // triplets per chunk
-    constexpr int NCHUNK = score_chunks<P, RG>();
+    constexpr int CT = score_triplets<RG, KPL>();    // triplets per chunk
+    constexpr int NCHUNK = score_chunks<P, RG, KPL>();
     constexpr int QC = CT * 3 * RG;                  // query floats per chunk
 #pragma unroll
     for (int k = 0; k < KPL; ++k)
@@ -1424,7 +1427,7 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
         asm volatile("" : "+s"(q_off));
         if constexpr (AHEAD) {
             // chunk c runs pieces [c NPIECE / NCH, (c + 1) NPIECE / NCH) and reads the A operands of chunk c + 1's
-            constexpr int NCH = MX ? mx_units<P, KPL, LEAN>() : score_chunks<P, RG>();
+            constexpr int NCH = MX ? mx_units<P, KPL, LEAN>() : score_chunks<P, RG, KPL>();
             uint4 pa_bits[NPIECE];
             static_for<0, NPIECE / NCH>([&](auto pp) { pa_bits[decltype(pp)::value] = pv_operand(decltype(pp)::value / CW); });
             auto pv_in_chunk = [&](auto cc) __attribute__((always_inline)) {
@@ -2007,9 +2010,12 @@ int launch_decode_mfma_rg(const octopus_codebooks_t &cb, const DecodeShape &s, c
     return static_cast<int>(hipGetLastError());
 }
 
-// Query rows of the smallest row group the host shapes a call for (least_rows in octopus_host.cpp).
-template <class P>
-constexpr int least_rows_built() { return mx_scores<P>() || P::D > 128 ? 1 : (P::D == 128 ? 4 : 2); }
+// Row groups of one and two rows that the host shapes a call for (least_rows in octopus_host.cpp); those of four and eight
+// are built for every plan.
+template <class P, bool QJL = false>
+constexpr bool row_group_built(int rows) {
+    return rows >= 4 || mx_scores<P>() || P::D > 128 || (P::D == 64 && (rows == 1 || !QJL));
+}
 
 // Paged pools (bf16 values, row groups of at most 8 rows).
 template <class P, int RG>
@@ -2029,8 +2035,8 @@ int launch_decode_paged_plan(const octopus_codebooks_t &cb, const DecodeShape &s
                              const void *k_pool, const void *v_pool, const PageTable &pt, const int32_t *seq_lens,
                              float *part_ml, float *part_acc, hipStream_t stream) {
     switch (s.rows_per_pass) {
-        case 1: if constexpr (least_rows_built<P>() <= 1) return launch_decode_paged_rg<P, 1>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream); break;
-        case 2: if constexpr (least_rows_built<P>() <= 2) return launch_decode_paged_rg<P, 2>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream); break;
+        case 1: if constexpr (row_group_built<P>(1)) return launch_decode_paged_rg<P, 1>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream); break;
+        case 2: if constexpr (row_group_built<P>(2)) return launch_decode_paged_rg<P, 2>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream); break;
         case 4: return launch_decode_paged_rg<P, 4>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream);
         case 8: return launch_decode_paged_rg<P, 8>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream);
         case 128:
@@ -2039,7 +2045,7 @@ int launch_decode_paged_plan(const octopus_codebooks_t &cb, const DecodeShape &s
             return static_cast<int>(hipErrorInvalidValue);
         default: break;
     }
-    return static_cast<int>(hipErrorInvalidValue);   // (a row group smaller than the least one)
+    return static_cast<int>(hipErrorInvalidValue);   // (a row group that is not built)
 }
 
 // Paged pools with the QJL side-car in pages as well (a pool of [page][KV head] side-car tiles).
@@ -2062,8 +2068,8 @@ int launch_decode_paged_qjl_plan(const octopus_codebooks_t &cb, const DecodeShap
                                  const PageTable &pt, const int32_t *seq_lens, float *part_ml, float *part_acc,
                                  hipStream_t stream) {
     switch (s.rows_per_pass) {
-        case 1: if constexpr (least_rows_built<P>() <= 1) return launch_decode_paged_qjl_rg<P, 1>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream); break;
-        case 2: if constexpr (least_rows_built<P>() <= 2) return launch_decode_paged_qjl_rg<P, 2>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream); break;
+        case 1: if constexpr (row_group_built<P, true>(1)) return launch_decode_paged_qjl_rg<P, 1>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream); break;
+        case 2: if constexpr (row_group_built<P, true>(2)) return launch_decode_paged_qjl_rg<P, 2>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream); break;
         case 4: return launch_decode_paged_qjl_rg<P, 4>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream);
         case 8: return launch_decode_paged_qjl_rg<P, 8>(cb, s, q_rot, k_pool, qjl_pool, q2, v_pool, pt, seq_lens, part_ml, part_acc, stream);
         default: break;
@@ -2167,8 +2173,8 @@ int launch_decode_qjl_plan(const octopus_codebooks_t &cb, const DecodeShape &s, 
                            const int32_t *seq_lens, float *part_ml, float *part_acc, float *scores_out,
                            hipStream_t stream) {
     switch (s.rows_per_pass) {
-        case 1: if constexpr (least_rows_built<P>() <= 1) return launch_decode_qjl_rg<P, 1>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream); break;
-        case 2: if constexpr (least_rows_built<P>() <= 2) return launch_decode_qjl_rg<P, 2>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream); break;
+        case 1: if constexpr (row_group_built<P, true>(1)) return launch_decode_qjl_rg<P, 1>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream); break;
+        case 2: if constexpr (row_group_built<P, true>(2)) return launch_decode_qjl_rg<P, 2>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream); break;
         case 4: return launch_decode_qjl_rg<P, 4>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream);
         case 8: return launch_decode_qjl_rg<P, 8>(cb, s, q_rot, cache, qjl, q2, v, seq_lens, part_ml, part_acc, scores_out, stream);
         default: break;

@@ -368,7 +368,7 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
         asm volatile("" : "+s"(q_off));
         // D2-D4 with the B operands of D6 built alongside: piece i is requested in chunk i (NCH - 1) / NPB of
         // the pass and built in the chunk the next piece is requested in (the last one in the last chunk)
-        constexpr int NCH = MX ? mx_units<P, KPL, LEAN>() : score_chunks<P, RG>();
+        constexpr int NCH = MX ? mx_units<P, KPL, LEAN>() : score_chunks<P, RG, KPL>();
         static_assert(NCH > NPB, "a chunk of the score pass per operand piece");
         auto build_in_chunk = [&](auto cc) __attribute__((always_inline)) {
             constexpr int ci = decltype(cc)::value;

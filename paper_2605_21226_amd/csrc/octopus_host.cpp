@@ -553,14 +553,14 @@ static void set_queries(DecodeShape *s, const void *q, int32_t q_dtype, const ui
 }
 
 // Query rows of the smallest row group of the kernels over bf16 values.  Plans without joint tables (4 bits) score on the
-// vector units, a group of 8 / rows triplets at a time: with one row a chunk is eight triplets of two keys, which spills;
-// four rows (some of them zero queries) are faster than one or two (8 x 16384 tokens, 8 KV heads, d = 128, one / two query
-// heads per KV head: 80 / 74 us, as four 71 / 71; one with the QJL residual: 142, as four 78).  At d = 64 one row is served
-// as two (46 us, as two 44), with the residual as four (one 56, two 59, four 51); at d = 256, one key per lane, nothing spills and a row more costs its
-// arithmetic (two rows 77 us, as four 89).
-static int32_t least_rows(const octopus_plan_t &plan, bool many_rows, bool bf16_values, bool with_qjl) {
+// vector units, a chunk of triplets at a time.  At d = 128 four rows (some of them zero queries) are faster than one or two, whose
+// chunks spill (8 x 16384 tokens, 8 KV heads, one / two query heads per KV head: 80 / 74 us, as four 71 / 71; one with the
+// QJL residual: 142, as four 78).  At d = 64 one row stays one (43 us as two, 42; with the residual 51 as four, 49) and two stay
+// two (43), but with the residual two are served as four (57 as two, 51); at d = 256, one key per lane, nothing spills and a
+// row more costs its arithmetic (two rows 77 us, as four 89).
+static int32_t least_rows(const octopus_plan_t &plan, bool many_rows, bool bf16_values, bool with_qjl, int32_t rows_per_kv) {
     if (many_rows || !bf16_values || joint_plan(plan) || plan.head_dim > 128) return 1;
-    return plan.head_dim == 128 || with_qjl ? 4 : 2;
+    return plan.head_dim == 128 || (with_qjl && rows_per_kv > 1) ? 4 : 1;
 }
 
 // Whether the kernel that serves a call rotates its queries itself; else a kernel before it does.  matrix_kernel: the
@@ -647,7 +647,8 @@ static int attn_decode(const octopus_codebooks_t *cb, const void *q, int32_t q_d
     const int32_t vq_mfma = with_vq && scores_out == nullptr
                                 ? vq_mfma_available(cb->plan, vq_mfma_rows(n_q * (n_q_heads / n_kv_heads)), v_bits, v_group)
                                 : 0;
-    int32_t rows_min = least_rows(cb->plan, many_rows, !with_vq && v_dtype == OCTOPUS_DTYPE_BF16, with_qjl);
+    int32_t rows_min = least_rows(cb->plan, many_rows, !with_vq && v_dtype == OCTOPUS_DTYPE_BF16, with_qjl,
+                                  n_q * (n_q_heads / n_kv_heads));
     DecodeShape s = make_decode_shape(cb->plan, n_seq, n_q_heads, n_kv_heads, n_q, max_len, t_capacity, many_rows, rows_cap,
                                       vq_mfma, rows_min);
     Workspace w = make_workspace(cb->plan, s);
@@ -936,7 +937,7 @@ static int attn_decode_paged(const octopus_codebooks_t *cb, const void *q, int32
         if (vq_waves <= 0) return OCTOPUS_EUNSUPPORTED;
     }
     DecodeShape s = make_decode_shape(cb->plan, n_seq, n_q_heads, n_kv_heads, n_q, max_len, reach, many_rows, rows_cap,
-                                      vq_waves, least_rows(cb->plan, many_rows, v_bits == 0, with_qjl));
+                                      vq_waves, least_rows(cb->plan, many_rows, v_bits == 0, with_qjl, n_q * (n_q_heads / n_kv_heads)));
     Workspace w = make_workspace(cb->plan, s);
     if (many_rows) many_rows_at_128(cb, max_len, &s, &w);
     set_queries(&s, q, q_dtype, signs, with_qjl ? signs2 : nullptr, scale);

@@ -47,7 +47,7 @@ def test_calls_with_blocks_of_128_rows(shapes):
 
 
 def test_row_groups_of_plans_without_joint_tables(shapes):
-    """At 4 bits small groups are padded up to d = 128: the row group is part of what the GPU tests of it run."""
+    """At 4 bits small groups are padded at d = 128: the row group is part of what the GPU tests of it run."""
     assert [shapes(False, 128, 4, 2, 2 * r, 2, 1, 700)[0] for r in (1, 2, 4, 8)] == [4, 4, 4, 8]
-    assert [shapes(False, 64, 4, 2, 2 * r, 2, 1, 700)[0] for r in (1, 2, 4, 8)] == [2, 2, 4, 8]
+    assert [shapes(False, 64, 4, 2, 2 * r, 2, 1, 700)[0] for r in (1, 2, 4, 8)] == [1, 2, 4, 8]
     assert [shapes(False, 256, 4, 2, 2 * r, 2, 1, 700)[0] for r in (1, 2, 4, 8)] == [1, 2, 4, 8]
