@@ -207,10 +207,8 @@ struct BookLevels {
 
 // MX: joint tables hold bf16 hi / lo operands (the matrix-core score pass) instead of fp32 vectors.
 template <class P, bool MX = false>
-__device__ __forceinline__ void build_tables(DecodeTables<P> &tb, const BookLevels<P> &levels, int tid, int nthreads) {
-    static_assert(kMaxLevels == kWave, "one level per lane");
-    levels.store(tb, tid);
-    __syncthreads();
+__device__ __forceinline__ void build_tables(DecodeTables<P> &tb, int tid, int nthreads) {
+    __syncthreads();   // (the levels are in place)
     if constexpr (MX) {
         static_assert(mx_scores<P>(), "matrix-core scores need joint tables");
         build_joint_table_mx<P::BD0, P::BN0>(tb.dir0, tb.c_xi[0], tb.c_rho[0], tid, nthreads);
@@ -404,6 +402,9 @@ struct WorkSpan {
         const uint64_t G = static_cast<uint64_t>(shp.n_kv_heads) * shp.n_row_groups;
         int l, len, n_steps, g;
         uint32_t lo, hi;
+        // (the compiler computes what depends on the kind once and keeps it in registers across the segment's steps, which spills)
+        Division div = this->div;
+        asm volatile("" : "+s"(div.kind));
         do {
             if (pos >= end) return false;
             while ((before + chunk_sum()) * G <= pos) {   // (more than 64 sequences; a later one holds unit pos, so it ends)
@@ -1098,7 +1099,8 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
     constexpr int TQ = kWave * (D / 8 + 2);  // side-car bytes per tile
     // static, so that table addresses are compile-time constants that fold into the LDS instructions
     constexpr bool MX = mx_scores<P>();    // scores on the matrix cores (every plan up to 3 bits per coordinate)
-    constexpr bool LEAN = QJL || RG == 8 || P::NCLASS == 2;  // fewer registers for the score pass where it would spill
+    // fewer registers for the score pass where it would spill (one row, 3 bits, 16 x 32768 tokens, 8 KV heads, spilling 231 us, so 203)
+    constexpr bool LEAN = QJL || RG == 8 || RG == 1 || P::NCLASS == 2;
     __shared__ DecodeSmemMfma<P, KPL> sm;
     using QO = QjlOperands<D, RG>;
     __shared__ __attribute__((aligned(16))) uint4 qjl_store[QJL ? sizeof(QO) / 16 : 1];
@@ -1118,6 +1120,7 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
     WorkSpan<KPL, kDecodeWaves> span;
     span.open(shp, seq_lens, lane);
     if (span.pos >= span.end) return;   // (whole workgroup, before any barrier)
+    levels.store(sm.tb, tid);           // (kept in registers until the tables are built they are live through the steps)
     // The tables are built inside the segment loop, after the first segment's first loads have been issued:
     // those do not depend on the tables, and their latency covers the build.
     bool tables_built = false;
@@ -1573,7 +1576,7 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
             for (int ks = 0; ks < KS; ++ks) load_values(v_none, ks, vr[ks]);
         }
         if (!tables_built) {   // workgroup-uniform
-            build_tables<P, MX>(sm.tb, levels, tid, kDecodeWaves * kWave);
+            build_tables<P, MX>(sm.tb, tid, kDecodeWaves * kWave);
             tables_built = true;
         }
         // The segment's rotated queries as matrix-core operands.  Every wavefront has left the step loop of the previous
@@ -1678,7 +1681,8 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) void decode_kernel_valu(
     WorkSpan<TPS, kDecodeWaves> span;
     span.open(shp, seq_lens, lane);
     if (span.pos >= span.end) return;   // (whole workgroup, before any barrier)
-    build_tables<P>(sm.tb, levels, tid, kDecodeWaves * kWave);
+    levels.store(sm.tb, tid);           // (kept in registers until the tables are built they are live through the steps)
+    build_tables<P>(sm.tb, tid, kDecodeWaves * kWave);
     const int rl = lane % LPR, ko = lane / LPR;
     WaveWork ww;
     while (span.next(shp, seq_lens, wave, lane, &ww)) {

@@ -122,7 +122,12 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
     constexpr int STEP_BYTES = Gm::STEP_BYTES;
     constexpr int TILEB = P::GRANULES * kWave * 16;  // bytes per cache tile
     constexpr bool MX = mx_scores<P>();
-    constexpr bool LEAN = NWV > 4;   // fewer registers for the score pass: 256 with two wavefronts per SIMD
+    // Fewer registers for the score pass: with two wavefronts per SIMD (256 each), and with one where that is no slower: at 3
+    // bits the wide form saves two instructions of a lookup's four (d = 256, values at 2 / 3 bits in groups of 32, 8 x 16384
+    // tokens, 8 KV heads x 4: wide 91 / 96 us, so 93 / 99), other widths spill less or not at all (b = 2, 8 rows, 4 bits 402 ->
+    // 380; b = 2, 3 bits 107 -> 99; d = 128, b = 1, 8 rows, groups of 16 549 -> 413).  d = 256 in groups of 16 spills
+    // hundreds of bytes either way and is faster wide (338 / 372 at b = 1, 362 / 382 at 1.5).
+    constexpr bool LEAN = NWV > 4 || (!(P::NCLASS == 1 && P::BD0 == 4 && P::BN0 == 2) && (D <= 128 || VG == 32));
     constexpr int LOOKAHEAD = NWV > 4 ? 1 : 2;
     // bf16 of 2^VB + code: exponent 127 + VB, the code in the top VB bits of the 7-bit mantissa
     constexpr float BIAS = static_cast<float>(1 << VB);
@@ -146,6 +151,7 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
     WorkSpan<KPL, NWV> span;
     span.open(shp, seq_lens, lane);
     if (span.pos >= span.end) return;   // (whole workgroup, before any barrier)
+    levels.store(sm.tb, tid);           // (kept in registers until the tables are built they are live through the steps)
     bool tables_built = false;
     WaveWork ww;
     const float *qg = q_rot;
@@ -482,7 +488,7 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
         if (any) load_records(ww.step_begin, slot_first, w);
         load_rows(ww.step_begin, slot_first, any, rows);
         if (!tables_built) {   // workgroup-uniform
-            build_tables<P, MX>(sm.tb, levels, tid, NWV * kWave);
+            build_tables<P, MX>(sm.tb, tid, NWV * kWave);
             tables_built = true;
         }
         // The segment's rotated queries as matrix-core operands.  Every wavefront is past the previous segment's merge (the

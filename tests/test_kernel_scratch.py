@@ -36,3 +36,11 @@ def test_residual_kernels_at_256_do_not_spill(library):
     joint = {k: v for k, v in _decode(library, 256, True, True).items() if k[0][0] < 5}
     assert len(joint) == 5 * 4 * 2
     assert {k: v for k, v in joint.items() if v > 12} == {}
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_kernels_without_residual_do_not_spill(library, d):
+    """Every plan with joint tables (two direction codes and a norm code of at most ten bits), one to eight query rows."""
+    joint = {k: v for k, v in _decode(library, d, False, False).items() if all(2 * k[0][c] + k[0][c + 1] <= 10 for c in (0, 2))}
+    assert len(joint) >= 5 * 4 * 2
+    assert {k: v for k, v in joint.items() if v} == {}
