@@ -239,8 +239,8 @@ int octopus_attn_decode(const octopus_codebooks_t *cb,
                         void *stream);
 
 /* For callers that cannot allocate device memory -- code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc: octopus_attn_decode without the workspace arguments.  The rotated queries,
- * the split-K partials and the work plan live in a static device array inside the library,
+ * harnesses that forbid hipMalloc: octopus_attn_decode without the workspace arguments.  The rotated queries and
+ * the split-K partials live in a static device array inside the library,
  * OCTOPUS_STATIC_SCRATCH_BYTES bytes on every GPU the library runs on, held until the process ends.  The
  * call allocates and frees nothing (the array's device address is looked up on the first call on a device).
  *   Limit: shapes whose octopus_attn_decode_workspace(...) exceeds OCTOPUS_STATIC_SCRATCH_BYTES are refused
@@ -503,8 +503,10 @@ const char *octopus_strerror(int code);
  * octopus_profile_events: the next decode-attention call made by this thread (octopus_attn_decode, its _static,
  * _qjl, _vq and _hybrid forms, octopus_attn_decode_paged and its _hybrid, _vq and _qjl forms) records the HIP events `before` and `after` (hipEvent_t
  * passed as void*, caller-owned, created with timing enabled) on the call's stream immediately before and after
- * the launch of its fused decode kernel, i.e. around Alg. 2 proper without the query rotation and the split
- * merge.  The handles are per thread and are forgotten by that call whether it succeeds or not; NULL, NULL
+ * the launch of its fused decode kernel, i.e. around Alg. 2 proper without the split merge.  The query rotation is
+ * inside where that kernel does it itself (plans up to 3 bits per coordinate, row groups of at most 8, bf16 values
+ * or quantised values on the matrix cores); where a launch of its own does it,
+ * it is outside.  The handles are per thread and are forgotten by that call whether it succeeds or not; NULL, NULL
  * cancels.  Returns OCTOPUS_OK, or OCTOPUS_EINVAL if only one of the two is NULL. */
 int octopus_profile_events(void *before, void *after);
 

@@ -768,7 +768,7 @@ __device__ __forceinline__ void tile_scores(const uint32_t (&w)[KPL][P::NWORDS],
 //     [hi 0-3, hi 4-7, lo 0-3, lo 4-7]; a few more exchanges add hi and lo and leave every lane with its own key's scores.
 // Bound by the issue of vector instructions and LDS reads of one wavefront per SIMD: per tile and 43 triplets this is 44
 // instructions of ~17 cycles whatever the rows, 44 lookups and 11 operand reads, where a 4 x 4 x 4 product per triplet and
-// four rows took 129 (258 for eight rows) of ~12 cycles, 43 lookups and 43 (86) operand reads.  Long contexts wait for
+// four rows took 129 (258 for eight rows) of ~15 cycles, 43 lookups and 43 (86) operand reads.  Long contexts wait for
 // memory either way; eight rows per KV head gain (4 x 16384 tokens, d = 256, b = 3: 91 -> 67 us with the work split; 8 x
 // 16384, d = 128, b = 1: 74 -> 59).
 template <class P>
@@ -2092,7 +2092,7 @@ int launch_decode_mfma_plan(const octopus_codebooks_t &cb, const DecodeShape &s,
         case 4: return launch_decode_mfma_rg<P, 4, SCORES>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, stream);
         case 8: return launch_decode_mfma_rg<P, 8, SCORES>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, stream);
         case 128:
-        case 256:   // the many-row kernel: 256 rows per workgroup at d = 64, 128 at d = 128
+        case 256:   // the many-row kernel: rows per workgroup
             if constexpr (P::D <= 128 && !SCORES)
                 return launch_decode_mq<P>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, stream);
             return static_cast<int>(hipErrorInvalidValue);

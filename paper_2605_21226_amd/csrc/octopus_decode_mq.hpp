@@ -1,12 +1,12 @@
 // Decode attention for many query rows per KV head (a chunk of queries against the whole cache, e.g. the
 // 3600 queries of a video frame): Alg. 2 with the roles of a dense attention kernel.  Here the work per
 // key is a dense contraction over hundreds of rows, so both products run on the matrix cores; the keys
-// are still decoded on the fly from the packed records, once per 128 query rows, into an LDS tile and
-// never reach memory.
+// are still decoded on the fly from the packed records, once per block of 128 or 256 query rows, into an LDS
+// tile and never reach memory.
 //
-// A workgroup of 4 wavefronts owns 128 query rows of one (sequence, KV head) (32 per wavefront) and a
-// range of 64-token tiles.  Per tile:
-//   * stage (all 256 threads, one tile ahead, double-buffered LDS): lane = key; the record is unpacked,
+// A workgroup of 4 or 8 wavefronts owns 128 or 256 query rows of one (sequence, KV head) (32 per wavefront)
+// and a range of 64-token tiles.  Per tile:
+//   * stage (all wavefronts, one tile ahead, double-buffered LDS): lane = key; the record is unpacked,
 //     gamma * rho^ * n^ is looked up and multiplied, split into two bf16 numbers (hi = upper 16 bits,
 //     lo = the rest) and written to the key tile [key][coordinate]; the values of the tile are written
 //     transposed [channel][key];
@@ -27,7 +27,7 @@ namespace octopus {
 
 // Query rows per workgroup: 32 per wavefront, NW = 4 wavefronts (128 rows) or NW = 8 (256 rows, two wavefronts per SIMD
 // within 256 registers each).  The keys of a tile are decoded once per workgroup, so more rows mean less decoding; the host
-// picks 256 when there are rows enough to fill them.
+// picks 256 at d = 64 from 192 rows on, at d = 128 where a compute unit then walks fewer tiles in a row (many_rows_at_128).
 // What bounds it (cycles of a tile, timestamps, 8 wavefronts, d = 64, b = 4): first product 1050, softmax 1660, second
 // product 820, staging 1060 - 1400, barrier up to 700, of 5400.  A 32x32x16 product takes 32 cycles of the matrix core and
 // keeps the vector units of its SIMD from issuing for about 16 of them, so two wavefronts' 2 x 40 products and 2 x (about 30
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
 
     // ---- staging: global -> registers -> LDS tile ---------------------------------------------------
     uint32_t w[P::NWORDS];          // this lane's record of the tile being staged
-    uint4 vp[VP];                   // its value pieces: key `lane`, channels 8 (wave + 4 i) .. + 8
+    uint4 vp[VP];                   // its value pieces: key `lane`, channels 8 (wave + NW i) .. + 8
     auto load_tile = [&](int tile) {
         typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
         typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
     // of a wavefront and were a third of this kernel's time.)
     auto stage_block = [&](auto ww, int buf) __attribute__((always_inline)) {
         constexpr int wv = decltype(ww)::value;
-        constexpr int CW = D / NW;                      // coordinates per wave: 8 (d = 64) or 32 (d = 128)
+        constexpr int CW = D / NW;                      // coordinates per wave: D / 4 or D / 8 (8, 16 or 32)
         constexpr int T_LO = (wv * CW) / 3, T_HI = ((wv + 1) * CW - 1) / 3;
         constexpr int NT = T_HI - T_LO + 1;
         float val[3 * NT];

@@ -261,8 +261,8 @@ DecodeShape make_decode_shape(const octopus_plan_t &plan, int32_t n_seq, int32_t
         s.n_splits = static_cast<int32_t>(best);
         return s;
     }
-    // Query rows scored per key by one workgroup: the power of two covering rows_per_kv, at most 8
-    // (fewer with the QJL residual).  Rows beyond rows_per_kv in the last group are zero queries whose
+    // Query rows scored per key by one workgroup: the power of two covering rows_per_kv, at most 8 and at least
+    // rows_min.  Rows beyond rows_per_kv in the last group are zero queries whose
     // results are not stored.
     s.rows_per_pass = rows_min;
     while (s.rows_per_pass < s.rows_per_kv && s.rows_per_pass < rows_cap) s.rows_per_pass *= 2;
@@ -274,18 +274,10 @@ DecodeShape make_decode_shape(const octopus_plan_t &plan, int32_t n_seq, int32_t
         s.item_waves = vq_mfma_waves;
     }
     s.n_row_groups = (s.rows_per_kv + s.rows_per_pass - 1) / s.rows_per_pass;
-    // Split-K sizing: one wavefront per split.  The decode kernel runs one wavefront per SIMD, 256
-    // compute units x 4 at once; the steps (128 keys up to d = 128, 64 keys at d = 256) of each
-    // (sequence, KV head, row group) are divided over as many splits as fill those slots once, so that
-    // all wavefronts start together and end together.
+    // The kernels divide the steps (128 keys up to d = 128, 64 keys at d = 256) over the workgroups themselves.
     const int64_t groups = static_cast<int64_t>(n_seq) * n_kv_heads * s.n_row_groups;
     const int64_t step_keys = OCTOPUS_TILE * s.tiles_per_step;
     const int64_t max_steps = (len + step_keys - 1) / step_keys;
-    const int64_t slots = 256 * 4;
-    // workgroups of 4 wavefronts: splits come in fours
-    int64_t want = (slots / 4 + groups / 2) / groups;
-    want = std::max<int64_t>(1, std::min<int64_t>(want, (max_steps + 3) / 4));
-    s.n_splits = static_cast<int32_t>(4 * want);   // kept for reference; the device divides the steps itself
     // Partial results: the kernels write one per workgroup and one more per (sequence, KV head, row group) at most (the
     // work distribution in octopus_decode.hpp); the workspace has had room for four times as many as below from the start,
     // and its documented size stays.
@@ -505,7 +497,8 @@ int octopus_vq_on_matrix_cores(const octopus_codebooks_t *cb, int32_t n_q_heads,
     return vq_mfma_available(cb->plan, vq_mfma_rows(n_q * (n_q_heads / n_kv_heads)), v_bits, v_group) > 0 ? 1 : 0;
 }
 
-// Workspace of a decode call without quantised values (what octopus_attn_decode_static has to fit).
+// Workspace of a decode call without quantised values (what octopus_attn_decode_static has to fit); the QJL residual
+// has the row groups of the plain call.
 static size_t plain_decode_workspace(const octopus_codebooks_t *cb, int32_t n_seq, int32_t n_q_heads,
                                      int32_t n_kv_heads, int32_t n_q, int64_t max_len) {
     const DecodeShape s = make_decode_shape(cb->plan, n_seq, n_q_heads, n_kv_heads, n_q, max_len, 0, false);
@@ -513,12 +506,6 @@ static size_t plain_decode_workspace(const octopus_codebooks_t *cb, int32_t n_se
     if (many_rows_shape(cb->plan, n_q_heads, n_kv_heads, n_q)) {   // the larger of the two kernels' needs
         const DecodeShape m = make_decode_shape(cb->plan, n_seq, n_q_heads, n_kv_heads, n_q, max_len, 0, true);
         total = std::max(total, make_workspace(cb->plan, m).total);
-    }
-    // ... and of the kernel with the QJL residual, which serves smaller row groups
-    const int cap = qjl_rows_cap(cb->plan);
-    if (cap > 0) {
-        const DecodeShape j = make_decode_shape(cb->plan, n_seq, n_q_heads, n_kv_heads, n_q, max_len, 0, false, cap);
-        total = std::max(total, make_workspace(cb->plan, j).total);
     }
     return total;
 }
@@ -754,8 +741,8 @@ int octopus_attn_decode_static(const octopus_codebooks_t *cb, const void *q, int
     int err = OCTOPUS_OK;
     void *ws = static_scratch(&err);
     if (ws == nullptr) return err;
-    // nothing in the scratch has to start at zero: the first kernel of the call writes the work plan and its
-    // counter, and every partial result that the merge reads is written by the call's own main kernel
+    // nothing in the scratch has to start at zero: every rotated query and every partial result that a kernel reads
+    // is written by an earlier kernel of the call
     return attn_decode(cb, q, q_dtype, n_seq, n_q_heads, n_kv_heads, n_q, signs, cache, t_capacity, v, v_dtype,
                        seq_lens, max_len, scale, out, scores_out, ws, OCTOPUS_STATIC_SCRATCH_BYTES, stream, false,
                        nullptr, nullptr, 0, 0, nullptr, true);

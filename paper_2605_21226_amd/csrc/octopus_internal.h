@@ -36,10 +36,10 @@ struct DecodeShape {
     int32_t rows_per_kv;    // n_q * heads_per_kv query rows sharing one KV head
     int32_t rows_per_pass;  // query rows one workgroup scores per key (1, 2, 4 or 8; 128 or 256: many-row kernel)
     int32_t n_row_groups;   // ceil(rows_per_kv / rows_per_pass)
-    int32_t n_splits;       // wavefronts (workgroups of the many-row kernel) sharing the tiles of one (sequence, KV head, row group)
+    int32_t n_splits;       // many-row kernel: workgroups sharing the tiles of one (sequence, KV head, row group)
     int32_t max_items;      // what the partials' part of the workspace is sized for (row groups of at most 8)
     int32_t max_len;        // host-side bound of the sequence lengths
-    int32_t item_waves;     // wavefronts of the workgroup that share a work item (4; 8: matrix-core kernel over quantised values up to d = 128 where its LDS fits)
+    int32_t item_waves;     // wavefronts of the workgroup, which share a segment (4; 8: matrix-core kernel over quantised values up to d = 128 where its LDS fits)
     int32_t tiles_per_step; // 64-token tiles a wavefront takes per step (2 up to d = 128, else 1; 1: that kernel)
     int64_t t_capacity;
     // the call's queries, for the kernels that rotate the rows of their row group themselves (rotates_in_kernel)
@@ -83,7 +83,8 @@ Workspace make_workspace(const octopus_plan_t &plan, const DecodeShape &s);
 
 // Kernel launchers (defined in the .hip files).  Each returns a hipError_t cast to int.
 // `q2` (NULL: not wanted): the queries rotated a second time with `signs2` for the QJL residual, [padded row][head_dim].
-// (`work_plan`: not used; part of the launchers' signatures.)
+// (`work_plan`, and the rotation's `seq_lens`: not used; part of the launchers' signatures, which the host-side test drivers
+// stub.)
 int launch_rotate_queries(const octopus_plan_t &plan, const void *q, int q_dtype, const uint8_t *signs,
                           const DecodeShape &s, float scale, float *q_rot, const int32_t *seq_lens,
                           int32_t *work_plan, const uint8_t *signs2, float *q2, void *stream);
