@@ -413,7 +413,7 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
     // The codebooks' levels, one per lane, from the kernel's first argument and in flight with the rows: copied by
     // constant index they are a scalar load and a straight line of moves per level, 2000 cycles before the first table.
     // Together with the two phases of the tables below, at d = 128 and 8 KV heads: one key appended and decoded against
-    // 24.4 -> 24.2 us, 3001 keys and values of a prompt at 4 bits 18.6 -> 18.4 us; the same where tiles are many.
+    // 24.4 -> 24.2 us; 3001 keys and values of a prompt at 4 bits (18.4 us) and long prefills the same within the noise.
     float book_xi[P::NCLASS], book_rho[P::NCLASS];
     {
         typedef const float __attribute__((address_space(4))) *arg_t;
