@@ -78,9 +78,9 @@ constexpr bool vq_lds_fits_n() {
 // Wavefronts per workgroup: two per SIMD up to d = 128 (each within 256 registers), whose different phases --
 // vector work, matrix-core work, LDS traffic -- the hardware overlaps, where the LDS of eight wavefronts fits (each
 // has its own staging buffer and probability rows) and the step loop fits 256 registers: up to 8 accumulator tiles
-// (what the kernel spills then, up to 60 bytes per lane, is stored and read outside the loop; with 16 tiles the loop spills, and one wavefront per SIMD with 512 registers is faster: row groups of eight at d = 128
-// 0.42 -> 0.33 ms, groups of 16 channels 0.30 -> 0.24 ms on the Llama-shaped batch); else, and at d = 256, one per
-// SIMD.
+// (what the kernel spills then, up to 60 bytes per lane, is stored and read outside the loop; with 16 tiles the loop
+// spills, and one wavefront per SIMD with 512 registers is faster: row groups of eight at d = 128 0.42 -> 0.33 ms,
+// groups of 16 channels 0.30 -> 0.24 ms on the Llama-shaped batch); else, and at d = 256, one per SIMD.
 template <class P, int RG, int VB, int VG>
 constexpr int vq_waves() {
     using G8 = VqGeometryN<P, RG, VB, VG, 8>;
