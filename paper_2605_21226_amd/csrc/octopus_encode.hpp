@@ -1,5 +1,6 @@
 // Online key encoder (Alg. 1 with the local 3x3 candidate set): a workgroup of 4 or 8 wavefronts takes one to
-// eight consecutive 64-token cache tiles of one (sequence, KV head), one after the other.
+// eight consecutive 64-token cache tiles of one (sequence, KV head), one after the other.  With the library's own
+// direction codebooks the winner of the nine candidates is found among four (CornerGrid).
 #ifndef OCTOPUS_ENCODE_HPP_
 #define OCTOPUS_ENCODE_HPP_
 
@@ -33,6 +34,32 @@ struct SeedGrid {
     }
 };
 
+// CORNERS.  The winner of Alg. 1's nine candidates is one of four for every Lloyd-Max direction codebook this library
+// builds (corner_levels; other codebooks take the nine): with |xi| and |eta| in the place of xi and eta, the four corners of
+// the bracket between two neighbouring positive levels on either axis (below the second level: the first bracket, above
+// the last but one: the last), in the quadrant that the signs of the key's x and y name.  Why: on a face of the octahedron the
+// point is a linear function of (xi, eta), so a candidate that loses to one corner at every vertex of a convex piece of the
+// square loses on all of it.  Cut by the brackets, by the seeds and by the face, every piece has such a corner for each
+// other candidate, by at least 2.9e-6 of the triplet's norm (the rounding errors of two scores stay below 1e-6) where |p_x|
+// and |p_y| are above near_axis().  Next to an axis two mirrored candidates tie, and the first of the nine wins: a
+// wavefront with such a key in it (one in 300; zero and non-finite keys as well) also looks at the nine.
+// Equal scores of two corners are decided in the order of Alg. 1's loop, which runs towards the axis where the
+// coordinate is negative.  Signs cost nothing (the products take |x| and |y|), the corners lie at constant offsets from the
+// first one, so there is no table of neighbours: 4 lookups a triplet instead of 15, 71 vector instructions instead of 115.
+//
+// The bracket is found as the seed is, through a grid, here of 2^b_dir cells over [0, 1] (no cell holds two levels: the
+// least gap between neighbours is 1.8 cells) and one more cell for an |xi| that rounds to a few ulp beyond 1.  Cell entry
+// {K / 2 + j, level}: the bracket is j + (level < |xi|); a cell without a level, or whose level ends no bracket, has
+// level = +inf.
+template <int BD>
+struct CornerGrid {
+    static constexpr int K = 1 << BD, H = K / 2;
+    static constexpr int NCELL = K + 1;
+    __device__ static __forceinline__ int cell_of(float x) { return static_cast<int>(x * static_cast<float>(K)); }
+    // the margins next to an axis shrink with the levels: 2 |p_x| times the first level, and less where z < 0
+    static constexpr float near_axis() { return BD <= 3 ? 1e-5f : 1.25e-6f * K; }
+};
+
 // The direction table holds ONE QUADRANT of the code grid: a Lloyd-Max codebook of the symmetric marginal is
 // antisymmetric (C_xi[K - 1 - j] = -C_xi[j], checked on the host), and Oct^-1(-xi, eta) is Oct^-1(xi, eta) with
 // its first component negated, bit for bit (likewise eta and the second component).  Entry (fx, fy), fx, fy <
@@ -46,8 +73,6 @@ struct SeedGrid {
 // workgroups still fit a compute unit at 3 bits per coordinate.  The seed grid keeps two copies up to d = 128.
 template <int D, int BD = 1>
 constexpr int encode_table_rep() { return (D <= 128 && BD <= 5) ? 8 : (D <= 128 || BD <= 3 ? 4 : 2); }
-template <int D>
-constexpr int encode_cell_rep() { return D <= 128 ? 2 : 1; }
 constexpr int quadrant_entries(int bd) { return bd <= 1 ? 1 : (1 << (2 * (bd - 1))); }
 
 // Wavefronts per workgroup.  LDS (the rotated tile, above all) decides how many workgroups a compute unit holds:
@@ -60,73 +85,88 @@ constexpr int encode_waves() { return P::D >= 128 ? 8 : 4; }
 template <class P>
 constexpr int encode_threads() { return encode_waves<P>() * kWave; }
 
-template <class P, bool QJL = false>
+// float2 entries of a class's grid (rep: its copies, lane l reads copy l mod rep) and of a neighbour table.
+constexpr int grid_cells(int bd, bool corners, int rep) { return bd < 1 ? 1 : (corners ? (1 << bd) + 1 : 8 * (1 << bd)) * rep; }
+constexpr int axis_entries(int bd, bool corners) { return bd < 1 || corners ? 1 : (1 << bd) * 3; }
+template <class P, bool QJL, bool CORNERS>
 struct EncodeSmem {
     float u[3 * P::NTRI][kURow];           // rotated coordinates [coordinate][key]
     __attribute__((aligned(16))) uint32_t rec[P::NWORDS][kWave];   // packed records [word][key]
     static constexpr int REP = encode_table_rep<P::D, (P::BD0 > P::BD1 ? P::BD0 : P::BD1)>();
-    static constexpr int CREP = encode_cell_rep<P::D>();
+    static constexpr int CREP = (CORNERS ? 8 : 2) / (P::D <= 128 ? 1 : 2);   // copies of the grid
+    static constexpr int NX = P::BD0 > 2 || P::BD1 > 2 ? 1 << (P::BD0 > P::BD1 ? P::BD0 : P::BD1) : 4;
+    static constexpr int NR = 1 << (P::BN0 > P::BN1 ? P::BN0 : P::BN1);
     float4 lut0[quadrant_entries(P::BD0) * REP];
     float4 lut1[P::NCLASS == 2 ? quadrant_entries(P::BD1) * REP : 1];
-    float2 cell0[SeedGrid<P::BD0>::NCELL * CREP];
-    float2 cell1[P::NCLASS == 2 ? SeedGrid<(P::BD1 > 0 ? P::BD1 : 1)>::NCELL * CREP : 1];
+    float2 cell0[grid_cells(P::BD0, CORNERS, CREP)];
+    float2 cell1[grid_cells(P::BD1, CORNERS, CREP)];
     // neighbours of a seed index j on the x and on the y axis, [j][dx + 1]: {+-1 (the sign the key's coordinate
     // takes), byte offset of the candidate's row / column in the quadrant table}
-    float2 nbx0[(1 << P::BD0) * 3], nby0[(1 << P::BD0) * 3];
-    float2 nbx1[P::NCLASS == 2 ? (1 << P::BD1) * 3 : 1], nby1[P::NCLASS == 2 ? (1 << P::BD1) * 3 : 1];
-    float c_xi[2][kMaxLevels];
-    float c_rho[2][kMaxLevels];
-    float bnd_xi[2][kMaxLevels + 1];       // boundaries, +inf padded
-    float bnd_rho[2][kMaxLevels];
+    float2 nbx0[axis_entries(P::BD0, CORNERS)], nby0[axis_entries(P::BD0, CORNERS)];
+    float2 nbx1[axis_entries(P::BD1, CORNERS)], nby1[axis_entries(P::BD1, CORNERS)];
+    float c_xi[P::NCLASS][NX];
+    float c_rho[P::NCLASS][NR];
+    float bnd_xi[P::NCLASS][NX];           // boundaries, +inf padded
+    float bnd_rho[P::NCLASS][NR];
     float sumsq[kWave];                    // squared norm of each key of the tile, then its scale factor 1 / (gamma sqrt(d))
     float res_sq[QJL ? encode_waves<P>() : 1][QJL ? kWave : 1];   // QJL side-car: squared residual norm, partial per wavefront
 };
 
 // Wavefronts per SIMD that the LDS footprint allows (160 KB per compute unit, 4 SIMDs): the register budget the
 // kernel is compiled for, so that registers never cost a workgroup that LDS has room for.
-template <class P, bool QJL>
+template <class P, bool QJL, bool CORNERS>
 constexpr int encode_waves_per_simd() {
-    constexpr int groups = static_cast<int>((160 * 1024) / sizeof(EncodeSmem<P, QJL>));
+    constexpr int groups = static_cast<int>((160 * 1024) / sizeof(EncodeSmem<P, QJL, CORNERS>));
     constexpr int waves = (groups < 1 ? 1 : groups) * encode_waves<P>() / 4;
     return waves > 6 ? 6 : waves;   // (the kernel does not fit the 64 registers of 8 wavefronts per SIMD)
 }
 
-template <int BD, int REP>
-__device__ __forceinline__ void build_encode_lut(float4 *lut, float2 *nbx, float2 *nby, const float *c_xi, int tid,
-                                                 int nthreads) {
-    constexpr int K = 1 << BD, H = BD <= 1 ? 1 : K / 2;
+// Entry (fx, fy) of the quadrant: the levels counted from the outermost negative one (FIRST 0), or for CORNERS from
+// the least positive one (FIRST K / 2).
+template <int BD, int REP, int FIRST>
+__device__ __forceinline__ void build_quadrant(float4 *lut, const float *c_xi, int tid, int nthreads) {
+    constexpr int H = BD <= 1 ? 1 : 1 << (BD - 1);
     // (with fewer entries than threads, nthreads / (H * H) threads share an entry: each computes it once and
     // writes its share of the copies)
     constexpr int Q = H * H;
     if (Q >= nthreads) {
         for (int e = tid; e < Q; e += nthreads) {
-            const float4 n = oct_decode(c_xi[e % H], c_xi[e / H]);
+            const float4 n = oct_decode(c_xi[FIRST + e % H], c_xi[FIRST + e / H]);
 #pragma unroll
             for (int r = 0; r < REP; ++r) lut[e * REP + r] = n;
         }
     } else {
         const int per_entry = nthreads / Q, e = tid % Q;
-        const float4 n = oct_decode(c_xi[e % H], c_xi[e / H]);
+        const float4 n = oct_decode(c_xi[FIRST + e % H], c_xi[FIRST + e / H]);
         for (int r = tid / Q; r < REP; r += per_entry) lut[e * REP + r] = n;
     }
-    for (int e = tid; e < 3 * K; e += nthreads) {
-        const int j = min(max(e / 3 + e % 3 - 1, 0), K - 1);   // the clamped neighbour (Alg. 1's window at the rim)
-        const int f = min(j, K - 1 - j);
-        const float sign = j >= H && K > 1 ? -1.0f : 1.0f;
-        nbx[e] = make_float2(sign, __uint_as_float(static_cast<uint32_t>(f * REP * 16)));
-        nby[e] = make_float2(sign, __uint_as_float(static_cast<uint32_t>(f * H * REP * 16)));
+}
+
+template <int BD, int REP, bool CORNERS>
+__device__ __forceinline__ void build_encode_lut(float4 *lut, float2 *nbx, float2 *nby, const float *c_xi, int tid,
+                                                 int nthreads) {
+    constexpr int K = 1 << BD, H = BD <= 1 ? 1 : K / 2;
+    build_quadrant<BD, REP, CORNERS ? K / 2 : 0>(lut, c_xi, tid, nthreads);
+    if constexpr (!CORNERS) {
+        for (int e = tid; e < 3 * K; e += nthreads) {
+            const int j = min(max(e / 3 + e % 3 - 1, 0), K - 1);   // the clamped neighbour (Alg. 1's window at the rim)
+            const int f = min(j, K - 1 - j);
+            const float sign = j >= H && K > 1 ? -1.0f : 1.0f;
+            nbx[e] = make_float2(sign, __uint_as_float(static_cast<uint32_t>(f * REP * 16)));
+            nby[e] = make_float2(sign, __uint_as_float(static_cast<uint32_t>(f * H * REP * 16)));
+        }
     }
 }
 
 // Oct^-1 of the centroids of a direction code, from the quadrant table.
-template <int BD, int REP>
+template <int BD, int REP, bool CORNERS = false>
 __device__ __forceinline__ float4 dir_lookup(const float4 *lut, uint32_t code, int lane) {
     constexpr int K = 1 << BD, H = BD <= 1 ? 1 : K / 2;
     const int jx = static_cast<int>(code & (K - 1)), jy = static_cast<int>(code >> BD);
-    const int fx = min(jx, K - 1 - jx), fy = min(jy, K - 1 - jy);
+    const int fx = CORNERS ? max(jx, K - 1 - jx) - H : min(jx, K - 1 - jx), fy = CORNERS ? max(jy, K - 1 - jy) - H : min(jy, K - 1 - jy);
     float4 n = lut[(fx + fy * H) * REP + (lane & (REP - 1))];
-    if (jx >= H) n.x = -n.x;
-    if (jy >= H) n.y = -n.y;
+    if ((jx >= H) != CORNERS) n.x = -n.x;
+    if ((jy >= H) != CORNERS) n.y = -n.y;
     return n;
 }
 
@@ -136,10 +176,10 @@ __device__ __forceinline__ float4 dir_lookup(const float4 *lut, uint32_t code, i
 template <int BD>
 __device__ __forceinline__ void build_boundaries(float *bnd, int *bnd_cell, const float *c_xi, int tid) {
     using G = SeedGrid<BD>;
-    if (tid <= kMaxLevels) {
+    if (tid < (G::K > 4 ? G::K : 4)) {
         const float b = tid < G::K - 1 ? 0.5f * (c_xi[min(tid, G::K - 1)] + c_xi[min(tid + 1, G::K - 1)]) : INFINITY;
         bnd[tid] = b;
-        if (tid < kMaxLevels) bnd_cell[tid] = tid < G::K - 1 ? G::cell_of(b) : G::NCELL;
+        if (bnd_cell != nullptr) bnd_cell[tid] = tid < G::K - 1 ? G::cell_of(b) : G::NCELL;
     }
 }
 template <int BD, int REP>
@@ -156,6 +196,31 @@ __device__ __forceinline__ void build_seed_grid(float2 *cell, const float *bnd, 
         const float first = bnd[below];       // +inf past the last one
 #pragma unroll
         for (int r = 0; r < REP; ++r) cell[c * REP + r] = make_float2(__int_as_float(below), first);
+    }
+}
+
+// CornerGrid's cells: the cell of every level that separates two brackets (the positive ones but the first and the last),
+// one level per thread, then, per cell, how many of them lie in lower ones.
+template <int BD>
+__device__ __forceinline__ void build_level_cells(int *level_cell, const float *c_xi, int tid) {
+    using G = CornerGrid<BD>;
+    if (tid < kMaxLevels) level_cell[tid] = tid < G::H - 2 ? G::cell_of(c_xi[G::H + 1 + min(tid, G::H - 2)]) : G::NCELL;
+}
+template <int BD, int REP>
+__device__ __forceinline__ void build_corner_grid(float2 *cell, const float *c_xi, const int *level_cell, int tid, int nthreads) {
+    using G = CornerGrid<BD>;
+#pragma unroll 1
+    for (int c = tid; c < G::NCELL; c += nthreads) {
+        int below = 0;
+#pragma unroll
+        for (int k = 0; k < G::H; k += 4) {   // (entries past the last such level are in no lower cell; four exist)
+            const int4 at = *reinterpret_cast<const int4 *>(level_cell + k);
+            below += (at.x < c ? 1 : 0) + (at.y < c ? 1 : 0) + (at.z < c ? 1 : 0) + (at.w < c ? 1 : 0);
+        }
+        const float level = level_cell[below] == c ? c_xi[G::H + 1 + below] : INFINITY;
+        const float2 entry = make_float2(__int_as_float(G::H + below), level);
+#pragma unroll
+        for (int r = 0; r < REP; ++r) cell[c * REP + r] = entry;
     }
 }
 
@@ -273,6 +338,102 @@ __device__ __forceinline__ void encode_triplet(float x, float y, float z, const 
     *nrm_index = static_cast<uint32_t>(r);
 }
 
+// The same triplet with the four corners of its bracket as candidates; `valid`: the key is one that is stored (the others
+// are zeros, which would send every wavefront of a short append through the nine candidates); `pads`: how many of the
+// triplet's coordinates lie past the head dimension (y, z: zero).
+template <int BD, int BN, int REP, int CREP>
+__device__ __forceinline__ void encode_triplet_corners(float x, float y, float z, const float4 *lut, const float2 *cell,
+                                                       const float *bnd_xi, const float *bnd_rho, int lane, bool valid, int pads,
+                                                       uint32_t *dir_field, uint32_t *nrm_index) {
+    using G = CornerGrid<BD>;
+    constexpr int K = G::K, H = G::H, M = 1 << BN;
+    // Eq. (oct-encode), as in encode_triplet
+    const float l1 = fabsf(x) + fabsf(y) + fabsf(z);
+    const float l1c = fmaxf(l1, kEps);
+    float inv = __builtin_amdgcn_rcpf(l1c);
+    inv = fmaf(fmaf(-l1c, inv, 1.0f), inv, inv);
+    const float px = x * inv, py = y * inv;
+    const int neg_x = __float_as_int(x) >> 31, neg_y = __float_as_int(y) >> 31;   // 0 or -1
+    float best;
+    uint32_t best_code;
+    int jx = H, jy = H;   // K / 2 + bracket
+    const char *base = reinterpret_cast<const char *>(lut + (lane & (REP - 1)));
+    if constexpr (H == 1) {   // one level on either side: the signs are the code
+        const float4 n = *reinterpret_cast<const float4 *>(base);
+        best = fmaf(z, n.z, fmaf(fabsf(y), n.y, fabsf(x) * n.x));
+        best_code = static_cast<uint32_t>((1 + neg_x) | ((1 + neg_y) << BD));
+    } else {
+        const float xi = z < 0.0f ? 1.0f - fabsf(py) : fabsf(px), eta = z < 0.0f ? 1.0f - fabsf(px) : fabsf(py);
+        const float2 ex = cell[G::cell_of(xi) * CREP + (lane & (CREP - 1))];
+        const float2 ey = cell[G::cell_of(eta) * CREP + (lane & (CREP - 1))];
+        jx = __float_as_int(ex.x) + (ex.y < xi ? 1 : 0);
+        jy = __float_as_int(ey.x) + (ey.y < eta ? 1 : 0);
+        asm("" : "+v"(jx), "+v"(jy));   // (else the compare is kept apart and added a second time below)
+        const char *at = base + (jx * REP + jy * (H * REP)) * 16 - (H * REP + H * H * REP) * 16;
+        float sc[4];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const float4 n = *reinterpret_cast<const float4 *>(at + (a * REP + b * (H * REP)) * 16);
+                sc[2 * a + b] = fmaf(z, n.z, fmaf(fabsf(y), n.y, fabsf(x) * n.x));
+            }
+        // The upper end wins where its score is larger, or equal and the axis runs the other way.  A pair's larger score is
+        // positive wherever it matters (the winner's angle to the key is far below 90 degrees), and then floats compare
+        // as integers.
+        const float row0 = fmaxf(sc[0], sc[1]), row1 = fmaxf(sc[2], sc[3]);
+        best = fmaxf(row0, row1);
+        const bool up_x = __float_as_int(row1) - neg_x > __float_as_int(row0);
+        const float lower = up_x ? sc[2] : sc[0], upper = up_x ? sc[3] : sc[1];
+        const bool up_y = __float_as_int(upper) - neg_y > __float_as_int(lower);
+        // K / 2 + level on the positive side of an axis, its complement on the negative one
+        const uint32_t code = static_cast<uint32_t>((jx + (up_x ? 1 : 0)) | ((jy + (up_y ? 1 : 0)) << BD));
+        const uint32_t flip = (static_cast<uint32_t>(neg_x) & (K - 1)) | (static_cast<uint32_t>(neg_y) & ~(K - 1u));
+        best_code = (code ^ flip) & (K * K - 1u);
+    }
+    // next to an axis, below the divisor's clamp, or not a number: the nine candidates around the seed
+    if (valid && !(fminf(fminf(fabsf(px), fabsf(py)), l1 * (G::near_axis() / kEps)) > G::near_axis())) {
+        if (pads > 1) y = 0.0f;   // (zero times a scale factor that is not a number)
+        if (pads > 0) z = 0.0f;
+        const float l1x = fmaxf(fabsf(x) + fabsf(y) + fabsf(z), kEps);
+        float invx = __builtin_amdgcn_rcpf(l1x);
+        invx = fmaf(fmaf(-l1x, invx, 1.0f), invx, invx);
+        const float qx = x * invx, qy = y * invx;
+        float xi = qx, eta = qy;
+        if (z < 0.0f) {
+            const float fx = 1.0f - fabsf(qy), fy = 1.0f - fabsf(qx);
+            xi = (qx >= 0.0f) ? fx : -fx;
+            eta = (qy >= 0.0f) ? fy : -fy;
+        }
+        // the seed (boundaries strictly below the coordinate) from the bracket: one boundary lies inside it
+        auto seed = [&](float v, int j) __attribute__((always_inline)) {
+            const float b = bnd_xi[H == 1 ? 1 : j];   // (one boundary in all, zero: the entry behind it is +inf)
+            const int h = v > 0.0f ? j + (b < v ? 1 : 0) : j + (b <= -v ? 1 : 0);
+            return v > 0.0f ? h : (v <= 0.0f ? K - 1 - h : 0);   // (not a number: the first)
+        };
+        const int sx = seed(xi, jx), sy = seed(eta, jy);
+        best = -INFINITY;
+        best_code = static_cast<uint32_t>(min(sx + 1, K - 1) | (min(sy + 1, K - 1) << BD));   // (no candidate is a number)
+#pragma clang loop unroll(disable)
+        for (int dx = -1; dx <= 1; ++dx) {
+            const int cx = min(max(sx + dx, 0), K - 1);
+#pragma unroll
+            for (int dy = -1; dy <= 1; ++dy) {
+                const uint32_t code = static_cast<uint32_t>(cx | (min(max(sy + dy, 0), K - 1) << BD));
+                const float4 n = dir_lookup<BD, REP, true>(lut, code, lane);
+                const float s = fmaf(z, n.z, fmaf(y, n.y, x * n.x));
+                if (s > best) { best = s; best_code = code; }
+            }
+        }
+    }
+    // (thresholds lie in [0, 1), checked with the levels: no clamp of the score)
+    int r = 0;
+#pragma unroll
+    for (int k = 0; k < M - 1; ++k) r += (bnd_rho[k] < best) ? 1 : 0;
+    *dir_field = best_code;
+    *nrm_index = static_cast<uint32_t>(r);
+}
+
 // The encoder-only rounding variants of App. E (same bitstream, same decoder); `mode` as in octopus.h:
 // 0 seed only (Alg. 1 with the window {(0,0)}), 1 local 3x3, 2 full K x K grid, 3 three independent
 // nearest-centroid rounds (the norm code from rho_i itself), 4 local 2x2 (the seed and its upper neighbour).
@@ -327,11 +488,24 @@ __device__ __forceinline__ void encode_triplet_any(float x, float y, float z, co
     *nrm_index = static_cast<uint32_t>(r);
 }
 
-__device__ __forceinline__ void or_bits(uint32_t (*rec)[kWave], int key, int bitpos, int nbits, uint32_t v) {
-    const int wi = bitpos >> 5, sh = bitpos & 31;
-    atomicOr(&rec[wi][key], v << sh);
-    if (sh + nbits > 32) atomicOr(&rec[wi + 1][key], v >> (32 - sh));
-}
+// Consecutive fields of one stream of a key's record, gathered in a register and OR-ed into LDS a word at a time (the first and
+// the last word of a wavefront's share are also its neighbours').  Bit positions are wave-uniform.
+struct FieldWriter {
+    uint32_t acc = 0u;
+    int bit;   // position of the next field, from the start of the record
+    __device__ __forceinline__ void put(uint32_t (*rec)[kWave], int key, int nbits, uint32_t v) {
+        const int sh = bit & 31;
+        acc |= v << sh;
+        if (sh + nbits >= 32) {
+            atomicOr(&rec[bit >> 5][key], acc);
+            acc = sh + nbits > 32 ? v >> (32 - sh) : 0u;
+        }
+        bit += nbits;
+    }
+    __device__ __forceinline__ void finish(uint32_t (*rec)[kWave], int key) const {
+        if (bit & 31) atomicOr(&rec[bit >> 5][key], acc);
+    }
+};
 
 // Consecutive cache tiles one workgroup takes, its tables built once for all of them: eight where that still leaves
 // the launch several workgroups per place on the chip (a long prefill: the tables cost a fifth of a tile's time),
@@ -348,9 +522,17 @@ inline int encode_tiles_per_group(int tiles, int n_kv_heads, int n_seq) {
 // transform follows, and the signs of its output (bit set = negative) plus ||r|| as fp16 are stored per
 // key: per tile of 64 tokens [d/32 words][64 keys] uint32, then [64 keys] fp16.
 // ANY: the rounding mode is the run-time argument `mode` (the default encoder is built without it).
-template <class P, bool BF16, bool QJL, bool ANY = false>
+// CORNERS: four candidates per triplet (CornerGrid).
+//
+// Bound: the vector units (the nine-candidate form: LDS as well).  With four candidates, the transform's first three
+// stages in the load phase and the others in one pass through LDS instead of two, the scale factor applied by the triplets and
+// the fields of a record gathered in registers: 16 x 32768 tokens x 8 KV heads at d = 128, b = 3 923 -> 563 us (4.5 -> 7.4 G
+// keys/s); 4 sequences at b = 2 / b = 4 241 -> 152 / 293 -> 202; d = 256, 4 x 16384 x 8, b = 2.5 / 4 353 -> 224 / 480 -> 324;
+// d = 64, 8 x 32768 x 8, b = 3 252 -> 159; with the residual at d = 256 299 -> 162; 3001 keys of one sequence x 8 at b = 4
+// 14.3 -> 11.5.
+template <class P, bool BF16, bool QJL, bool ANY = false, bool CORNERS = false>
 __global__ __launch_bounds__(encode_threads<P>())
-__attribute__((amdgpu_waves_per_eu(encode_waves_per_simd<P, QJL>(), encode_waves_per_simd<P, QJL>())))
+__attribute__((amdgpu_waves_per_eu(encode_waves_per_simd<P, QJL, CORNERS>(), encode_waves_per_simd<P, QJL, CORNERS>())))
 void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
                                                       int64_t stride_seq, int64_t stride_tok, int64_t stride_head,
                                                       int32_t n_new, const uint8_t *__restrict__ signs,
@@ -363,9 +545,10 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
     constexpr int LPR = D / 8;        // threads per key row in the load phase
     constexpr int NWV = encode_waves<P>(), NT = encode_threads<P>();
     constexpr int RPP = NT / LPR;     // key rows per load pass
-    constexpr int REP = EncodeSmem<P, QJL>::REP, CREP = EncodeSmem<P, QJL>::CREP;
+    using Smem = EncodeSmem<P, QJL, CORNERS>;
+    constexpr int REP = Smem::REP, CREP = Smem::CREP;
     // static, so that table addresses are compile-time constants that fold into the LDS instructions
-    __shared__ EncodeSmem<P, QJL> sm;
+    __shared__ Smem sm;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept in a scalar register
@@ -378,6 +561,9 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
     const int64_t head_base = seq * stride_seq + kvh * stride_head;
     const int col = (tid % LPR) * 8;
     const uint32_t sbits = signs[kvh * (D / 8) + col / 8];
+    uint32_t flip[4];   // the sign bits of a thread's eight coordinates, two bf16 to a word
+#pragma unroll
+    for (int w = 0; w < 4; ++w) flip[w] = ((sbits >> (2 * w)) & 1u) << 15 | ((sbits >> (2 * w + 1)) & 1u) << 31;
     uint4 *region = cache + (static_cast<int64_t>(seq) * n_kv_heads + kvh) * (t_capacity * P::GRANULES);
 
     // A tile's key rows as loaded: 8 coordinates per thread and pass (bf16: one 16-byte word; fp32: two);
@@ -430,21 +616,30 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
         static_assert(kMaxLevels == kWave, "a level per lane");
 #pragma unroll
         for (int c = 0; c < P::NCLASS; ++c) {
-            sm.c_xi[c][lane] = book_xi[c];
-            sm.c_rho[c][lane] = book_rho[c];
+            if (lane < Smem::NX) sm.c_xi[c][lane] = book_xi[c];
+            if (lane < Smem::NR) sm.c_rho[c][lane] = book_rho[c];
         }
     }
     __syncthreads();
     int *bnd_cell = reinterpret_cast<int *>(&sm.rec[0][0]);   // (no record is being built yet)
-    build_boundaries<P::BD0>(sm.bnd_xi[0], bnd_cell, sm.c_xi[0], tid);
-    if constexpr (P::NCLASS == 2) build_boundaries<P::BD1>(sm.bnd_xi[1], bnd_cell + kMaxLevels, sm.c_xi[1], tid);
-    build_encode_lut<P::BD0, REP>(sm.lut0, sm.nbx0, sm.nby0, sm.c_xi[0], tid, NT);
-    if constexpr (P::NCLASS == 2) build_encode_lut<P::BD1, REP>(sm.lut1, sm.nbx1, sm.nby1, sm.c_xi[1], tid, NT);
+    build_boundaries<P::BD0>(sm.bnd_xi[0], CORNERS ? nullptr : bnd_cell, sm.c_xi[0], tid);
+    if constexpr (P::NCLASS == 2) build_boundaries<P::BD1>(sm.bnd_xi[1], CORNERS ? nullptr : bnd_cell + kMaxLevels, sm.c_xi[1], tid);
+    if constexpr (CORNERS) {   // (the grid is over the levels; the boundaries serve the keys next to an axis)
+        build_level_cells<P::BD0>(bnd_cell, sm.c_xi[0], tid);
+        if constexpr (P::NCLASS == 2) build_level_cells<P::BD1>(bnd_cell + kMaxLevels, sm.c_xi[1], tid);
+    }
+    build_encode_lut<P::BD0, REP, CORNERS>(sm.lut0, sm.nbx0, sm.nby0, sm.c_xi[0], tid, NT);
+    if constexpr (P::NCLASS == 2) build_encode_lut<P::BD1, REP, CORNERS>(sm.lut1, sm.nbx1, sm.nby1, sm.c_xi[1], tid, NT);
     __syncthreads();
-    build_seed_grid<P::BD0, CREP>(sm.cell0, sm.bnd_xi[0], bnd_cell, tid, NT);
-    if constexpr (P::NCLASS == 2) build_seed_grid<P::BD1, CREP>(sm.cell1, sm.bnd_xi[1], bnd_cell + kMaxLevels, tid, NT);
-    if (tid < 2 * kMaxLevels) {
-        const int c = tid / kMaxLevels, k = tid % kMaxLevels;
+    if constexpr (CORNERS) {
+        build_corner_grid<P::BD0, CREP>(sm.cell0, sm.c_xi[0], bnd_cell, tid, NT);
+        if constexpr (P::NCLASS == 2) build_corner_grid<P::BD1, CREP>(sm.cell1, sm.c_xi[1], bnd_cell + kMaxLevels, tid, NT);
+    } else {
+        build_seed_grid<P::BD0, CREP>(sm.cell0, sm.bnd_xi[0], bnd_cell, tid, NT);
+        if constexpr (P::NCLASS == 2) build_seed_grid<P::BD1, CREP>(sm.cell1, sm.bnd_xi[1], bnd_cell + kMaxLevels, tid, NT);
+    }
+    if (tid < P::NCLASS * Smem::NR) {
+        const int c = tid / Smem::NR, k = tid % Smem::NR;
         const int levels = 1 << (c ? (P::BN1 > 0 ? P::BN1 : 1) : P::BN0);
         sm.bnd_rho[c][k] = (k < levels - 1) ? 0.5f * (sm.c_rho[c][k] + sm.c_rho[c][k + 1]) : INFINITY;
     }
@@ -468,7 +663,8 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
             const int key = pass * RPP + tid / LPR;
             float x[8];
             if constexpr (BF16) {
-                const uint4 r = raw[pass][0];
+                const uint4 k = raw[pass][0];
+                const uint4 r = make_uint4(k.x ^ flip[0], k.y ^ flip[1], k.z ^ flip[2], k.w ^ flip[3]);
                 x[0] = bf16_lo(r.x); x[1] = bf16_hi(r.x); x[2] = bf16_lo(r.y); x[3] = bf16_hi(r.y);
                 x[4] = bf16_lo(r.z); x[5] = bf16_hi(r.z); x[6] = bf16_lo(r.w); x[7] = bf16_hi(r.w);
             } else {
@@ -482,40 +678,35 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
             for (int e = 0; e < 8; ++e) ss = fmaf(x[e], x[e], ss);
             ss = row_sum<LPR>(ss);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) sm.u[col + e][key] = ((sbits >> e) & 1u) ? -x[e] : x[e];
+            for (int e = 0; e < 8; ++e) x[e] = !BF16 && ((sbits >> e) & 1u) ? -x[e] : x[e];
+            butterflies<8>(x);   // E3, the first three stages: a thread holds eight coordinates of its row
+#pragma unroll
+            for (int e = 0; e < 8; ++e) sm.u[col + e][key] = x[e];
             if (tid % LPR == 0) sm.sumsq[key] = ss;
         }
         if (tg + 1 < tiles_per_group) fetch_tile(tile + 1);
         __syncthreads();
 
-        // E3: Walsh-Hadamard transform, one key per lane, two radix passes through LDS
+        // E3: the other stages of the Walsh-Hadamard transform, one key per lane, in one pass through LDS.  The triplets take
+        // the coordinates unscaled and multiply by the key's scale factor themselves.
         {
-            constexpr int R2 = D / 16;
+            constexpr int R = D / 8;
             // the norm of every key, once per key: by one wavefront, 64 keys at a time (the load phase has 4 to 32
             // lanes per key, and a square root and a division cost as much there for one active lane as for 64); the
-            // scale factor replaces the sum of squares in LDS and is read by all after the barrier between the passes
+            // scale factor replaces the sum of squares in LDS
             if (wave == NWV - 1) {
                 const float gamma = sqrtf(sm.sumsq[lane]);
-                sm.rec[0][lane] = __float_as_uint(gamma);
+                // (the sign of a NaN among bf16 keys may have been flipped)
+                sm.rec[0][lane] = __float_as_uint(gamma) & (BF16 ? 0x7fffffffu : 0xffffffffu);
                 sm.sumsq[lane] = (1.0f / fmaxf(gamma, kEps)) * inv_sqrt_dim<D>();
             }
-            for (int g = wave; g < D / 16; g += NWV) {
-                float x[16];
+            for (int lo = wave; lo < 8; lo += NWV) {
+                float x[R];
 #pragma unroll
-                for (int e = 0; e < 16; ++e) x[e] = sm.u[g * 16 + e][lane];
-                butterflies<16>(x);
+                for (int e = 0; e < R; ++e) x[e] = sm.u[e * 8 + lo][lane];
+                butterflies<R>(x);
 #pragma unroll
-                for (int e = 0; e < 16; ++e) sm.u[g * 16 + e][lane] = x[e];
-            }
-            __syncthreads();
-            const float norm = sm.sumsq[lane];
-            for (int lo = wave; lo < 16; lo += NWV) {
-                float x[R2];
-#pragma unroll
-                for (int e = 0; e < R2; ++e) x[e] = sm.u[e * 16 + lo][lane];
-                butterflies<R2>(x);
-#pragma unroll
-                for (int e = 0; e < R2; ++e) sm.u[e * 16 + lo][lane] = x[e] * norm;
+                for (int e = 0; e < R; ++e) sm.u[e * 8 + lo][lane] = x[e];
             }
             __syncthreads();
         }
@@ -539,9 +730,18 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
                 for (int k = 0; k < (1 << P::BN1) - 1; ++k) thr1_reg[k] = sm.bnd_rho[1][k];
             }
             const float *thr0 = THR0_REG ? thr0_reg : sm.bnd_rho[0];
-            const float *thr1 = THR1_REG ? thr1_reg : sm.bnd_rho[1];
-            for (int i = wave * CHUNK; i < i_end; ++i) {
-                const float x = sm.u[3 * i][lane], y = sm.u[3 * i + 1][lane], z = sm.u[3 * i + 2][lane];
+            const float *thr1 = THR1_REG ? thr1_reg : sm.bnd_rho[P::NCLASS - 1];
+            const float norm = sm.sumsq[lane];
+            const bool valid = tile * kWave + lane >= tok_lo && tile * kWave + lane < tok_hi;
+            FieldWriter dir, nrm;
+            const int i_first = wave * CHUNK;
+            dir.bit = (P::NCLASS == 1 || i_first < P::NT0) ? P::DIR0_BIT + i_first * 2 * P::BD0 : P::DIR1_BIT + (i_first - P::NT0) * 2 * P::BD1;
+            nrm.bit = (P::NCLASS == 1 || i_first < P::NT0) ? P::NRM0_BIT + i_first * P::BN0 : P::NRM1_BIT + (i_first - P::NT0) * P::BN1;
+            for (int i = i_first; i < i_end; ++i) {
+                // (coordinates past the head dimension are zero: the scale factor of a key that is not finite is left out there)
+                float x = sm.u[3 * i][lane] * norm, y = sm.u[3 * i + 1][lane] * (CORNERS || 3 * i + 1 < D ? norm : 1.0f),
+                      z = sm.u[3 * i + 2][lane] * (CORNERS || 3 * i + 2 < D ? norm : 1.0f);
+                asm("" : "+v"(x), "+v"(y), "+v"(z));   // (the rounded products: none is to be fused into a later sum)
                 uint32_t dir_field, nrm_index;
                 float4 nhat;
                 float rho;
@@ -549,23 +749,35 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
                     if constexpr (ANY)
                         encode_triplet_any<P::BD0, P::BN0, REP, CREP>(x, y, z, sm.lut0, sm.cell0, sm.bnd_xi[0],
                                                                       sm.bnd_rho[0], lane, mode, &dir_field, &nrm_index);
+                    else if constexpr (CORNERS)
+                        encode_triplet_corners<P::BD0, P::BN0, REP, CREP>(x, y, z, sm.lut0, sm.cell0, sm.bnd_xi[0], thr0, lane,
+                                                                          valid, 3 * i + 3 - D, &dir_field, &nrm_index);
                     else
                         encode_triplet<P::BD0, P::BN0, REP, CREP>(x, y, z, sm.lut0, sm.cell0, sm.nbx0, sm.nby0,
                                                                   sm.bnd_xi[0], thr0, lane, &dir_field, &nrm_index);
-                    or_bits(sm.rec, lane, P::DIR0_BIT + i * 2 * P::BD0, 2 * P::BD0, dir_field);
-                    or_bits(sm.rec, lane, P::NRM0_BIT + i * P::BN0, P::BN0, nrm_index);
-                    if constexpr (QJL) { nhat = dir_lookup<P::BD0, REP>(sm.lut0, dir_field, lane); rho = sm.c_rho[0][nrm_index]; }
+                    dir.put(sm.rec, lane, 2 * P::BD0, dir_field);
+                    nrm.put(sm.rec, lane, P::BN0, nrm_index);
+                    if constexpr (QJL) { nhat = dir_lookup<P::BD0, REP, CORNERS>(sm.lut0, dir_field, lane); rho = sm.c_rho[0][nrm_index]; }
                 } else {
                     if constexpr (P::NCLASS == 2) {
                         if constexpr (ANY)
                             encode_triplet_any<P::BD1, P::BN1, REP, CREP>(x, y, z, sm.lut1, sm.cell1, sm.bnd_xi[1],
                                                                           sm.bnd_rho[1], lane, mode, &dir_field, &nrm_index);
+                        else if constexpr (CORNERS)
+                            encode_triplet_corners<P::BD1, P::BN1, REP, CREP>(x, y, z, sm.lut1, sm.cell1, sm.bnd_xi[1], thr1, lane,
+                                                                              valid, 3 * i + 3 - D, &dir_field, &nrm_index);
                         else
                             encode_triplet<P::BD1, P::BN1, REP, CREP>(x, y, z, sm.lut1, sm.cell1, sm.nbx1, sm.nby1,
                                                                       sm.bnd_xi[1], thr1, lane, &dir_field, &nrm_index);
-                        or_bits(sm.rec, lane, P::DIR1_BIT + (i - P::NT0) * 2 * P::BD1, 2 * P::BD1, dir_field);
-                        or_bits(sm.rec, lane, P::NRM1_BIT + (i - P::NT0) * P::BN1, P::BN1, nrm_index);
-                        if constexpr (QJL) { nhat = dir_lookup<P::BD1, REP>(sm.lut1, dir_field, lane); rho = sm.c_rho[1][nrm_index]; }
+                        if (i == P::NT0 && i > i_first) {   // the second class has its own streams
+                            dir.finish(sm.rec, lane);
+                            nrm.finish(sm.rec, lane);
+                            dir = FieldWriter{0u, P::DIR1_BIT};
+                            nrm = FieldWriter{0u, P::NRM1_BIT};
+                        }
+                        dir.put(sm.rec, lane, 2 * P::BD1, dir_field);
+                        nrm.put(sm.rec, lane, P::BN1, nrm_index);
+                        if constexpr (QJL) { nhat = dir_lookup<P::BD1, REP, CORNERS>(sm.lut1, dir_field, lane); rho = sm.c_rho[1][nrm_index]; }
                     }
                 }
                 if constexpr (QJL) {
@@ -577,6 +789,8 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
                     if (3 * i + 2 < D) { sm.u[3 * i + 2][lane] = r2; rsq = fmaf(r2, r2, rsq); }
                 }
             }
+            dir.finish(sm.rec, lane);
+            nrm.finish(sm.rec, lane);
             if constexpr (QJL) sm.res_sq[wave][lane] = rsq;
         }
         __syncthreads();
@@ -668,7 +882,14 @@ int launch_encode_plan(const octopus_codebooks_t &cb, const void *keys, int key_
                            signs, static_cast<uint4 *>(cache), t_capacity, start_pos, n_kv_heads, signs2,
                            static_cast<unsigned char *>(qjl), 1, pt, tpg);
     };
-    if (qjl != nullptr) {
+    // (four candidates per triplet where the winner is known to be among them, else nine)
+    if (corner_levels(cb)) {
+        if (qjl != nullptr) {
+            if (bf16) go(encode_kernel<P, true, true, false, true>); else go(encode_kernel<P, false, true, false, true>);
+        } else {
+            if (bf16) go(encode_kernel<P, true, false, false, true>); else go(encode_kernel<P, false, false, false, true>);
+        }
+    } else if (qjl != nullptr) {
         if (bf16) go(encode_kernel<P, true, true>); else go(encode_kernel<P, false, true>);
     } else {
         if (bf16) go(encode_kernel<P, true, false>); else go(encode_kernel<P, false, false>);

@@ -316,6 +316,33 @@ Workspace make_workspace(const octopus_plan_t &plan, const DecodeShape &s) {
     return w;
 }
 
+// Upper halves of the Lloyd-Max codebooks of Eq. (oct-marginal) for 1, 3, 4 and 5 direction bits, as
+// octopus_build_codebooks builds them (the lower halves are their negatives).  For these levels the winner of Alg. 1's nine
+// candidates lies among four, by margins three times the encoder's rounding errors (tests/test_encoder_corners.py checks
+// the levels and the margins); a level may differ in its last two bits.
+bool corner_levels(const octopus_codebooks_t &cb) {
+    static const float k1[] = {0.5f};
+    static const float k3[] = {0.143009439f, 0.383984327f, 0.616015673f, 0.856990576f};
+    static const float k4[] = {0.0721566528f, 0.20219183f, 0.323773116f, 0.441563517f,
+                               0.558436453f, 0.676226854f, 0.79780817f, 0.927843332f};
+    static const float k5[] = {0.0361604691f, 0.104518041f, 0.169686973f, 0.232398972f, 0.293326497f, 0.353058338f,
+                               0.412073106f, 0.470726699f, 0.529273331f, 0.587926924f, 0.646941662f, 0.706673503f,
+                               0.767601013f, 0.830313027f, 0.895481944f, 0.963839531f};
+    for (int c = 0; c < cb.plan.n_class; ++c) {
+        const int bd = cb.plan.b_dir[c];
+        const float *levels = bd == 1 ? k1 : (bd == 3 ? k3 : (bd == 4 ? k4 : (bd == 5 ? k5 : nullptr)));
+        if (levels == nullptr) return false;
+        const int half = 1 << (bd - 1);
+        for (int k = 0; k < half; ++k)
+            if (!(std::fabs(cb.c_xi[c][half + k] - levels[k]) <= 2.4e-7f * levels[k]) ||
+                !(cb.c_xi[c][half - 1 - k] == -cb.c_xi[c][half + k]))
+                return false;
+        for (int k = 0; k < (1 << cb.plan.b_nrm[c]); ++k)   // the encoder leaves out the clamp of the norm to [0, 1]
+            if (!(cb.c_rho[c][k] >= 0.0f && cb.c_rho[c][k] < 1.0f)) return false;
+    }
+    return true;
+}
+
 }  // namespace octopus
 
 using namespace octopus;

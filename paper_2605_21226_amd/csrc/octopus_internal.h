@@ -147,6 +147,10 @@ int launch_probe_read(const void *data, int64_t bytes, int nontemporal, int n_bl
 // hipEventRecord(event, stream); returns a hipError_t cast to int.
 int record_event(void *event, void *stream);
 
+// True when every class's direction levels are those of the library's own codebook (to 2^-22 of a level) and its norm
+// levels lie in [0, 1): the encoder then looks at four candidates per triplet instead of nine.
+bool corner_levels(const octopus_codebooks_t &cb);
+
 // True when every kernel family is instantiated for this plan (the six built bit widths of each head dimension).
 bool plan_supported(const octopus_plan_t &plan);
 // True for the extra (b_dir, b_nrm) pairs of the App. D sweep: plain encoder (local 3x3) and split-K decode over

@@ -1,0 +1,150 @@
+"""The encoder looks at four candidates per triplet where the winner of Alg. 1's nine is known to be among them: for the
+library's own direction levels.  Here that claim is checked for every piece of the square, in 64 bits, and the levels the
+library takes it for; on the GPU the four-candidate kernels are compared with the nine-candidate ones code for code."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from paper_2605_21226_amd import binding, layout
+
+torch = pytest.importorskip("torch")
+
+
+def _books(bd):
+    return binding.octopus_build_codebooks(128, {1: 1, 3: 2, 4: 3, 5: 4}[bd])
+
+
+def _corner_levels(cb):
+    fn = getattr(binding.load(), "_ZN7octopus13corner_levelsERK17octopus_codebooks")
+    fn.restype = ctypes.c_bool
+    return fn(ctypes.byref(cb))
+
+
+def _unit(xi, eta):
+    r = 1 - np.abs(xi) - np.abs(eta)
+    a = np.where(r < 0, np.where(xi >= 0, 1, -1) * (1 - np.abs(eta)), xi)
+    b = np.where(r < 0, np.where(eta >= 0, 1, -1) * (1 - np.abs(xi)), eta)
+    return np.stack([a, b, r], -1) / np.sqrt(a * a + b * b + r * r)[..., None]
+
+
+def _clip(poly, f):
+    """The part of a convex polygon where the linear function f is not negative."""
+    out = []
+    for a, b in zip(poly, poly[1:] + poly[:1]):
+        fa, fb = f(a), f(b)
+        if fa >= 0:
+            out.append(a)
+        if (fa > 0 > fb) or (fa < 0 < fb):
+            out.append(a + fa / (fa - fb) * (b - a))
+    return out
+
+
+@pytest.mark.parametrize("bd,near_axis", [(1, 1e-5), (3, 1e-5), (4, 2e-5), (5, 4e-5)])
+def test_the_winner_is_one_of_four(bd, near_axis):
+    """Bound: two scores of a unit triplet are off by at most 3 roundings of 2^-24 each plus 3 * 2^-24 of either table entry,
+    and the point by 3e-7 in xi and eta (levels up to 0.6 apart): under 1e-6 together.  Every candidate outside the four has
+    to lose to one of them by 2.5e-6 on the whole of a piece (the difference is linear there: its vertices decide)."""
+    k, half = 1 << bd, 1 << (bd - 1)
+    c = np.array(_books(bd).c_xi[0][:k], dtype=np.float64)
+    n = _unit(c[:, None] + 0 * c, c[None, :] + 0 * c[:, None])
+    mids = 0.5 * (c[1:] + c[:-1])
+    edges = [0.0] + list(c[half + 1:k - 1]) + [1.0]
+    checked, least = 0, np.inf
+
+    def pieces(j):
+        cuts = [edges[j]] + [m for m in mids if edges[j] < m < edges[j + 1]] + [edges[j + 1]]
+        return zip(cuts[:-1], cuts[1:])
+    for jx in range(len(edges) - 1):
+        for jy in range(len(edges) - 1):
+            corners = {(half + jx + a, half + jy + b) for a in (0, 1) for b in (0, 1)} if half > 1 else {(1, 1)}
+            for x0, x1 in pieces(jx):
+                for y0, y1 in pieces(jy):
+                    sx, sy = np.searchsorted(mids, [0.5 * (x0 + x1), 0.5 * (y0 + y1)])
+                    nine = {(min(max(sx + a, 0), k - 1), min(max(sy + b, 0), k - 1)) for a in (-1, 0, 1) for b in (-1, 0, 1)}
+                    assert corners <= nine
+                    rect = [np.array(p) for p in ((x0, y0), (x1, y0), (x1, y1), (x0, y1))]
+                    for upper in (True, False):
+                        poly = _clip(rect, (lambda v: 1 - v[0] - v[1]) if upper else (lambda v: v[0] + v[1] - 1))
+                        for f in ([lambda v: v[0] - near_axis, lambda v: v[1] - near_axis] if upper else
+                                  [lambda v: 1 - v[1] - near_axis, lambda v: 1 - v[0] - near_axis]):
+                            poly = _clip(poly, f)
+                        if not poly:
+                            continue
+                        pts = np.array([[v[0], v[1], 1 - v[0] - v[1]] if upper else [1 - v[1], 1 - v[0], 1 - v[0] - v[1]]
+                                        for v in poly])
+                        pts /= np.linalg.norm(pts, axis=1, keepdims=True)
+                        for e in nine - corners:
+                            least = min(least, max((pts @ (n[t] - n[e])).min() for t in corners))
+                            checked += 1
+    print(f"{checked} candidates, least margin {least:.3g}")
+    assert checked and least >= 2.5e-6
+    # the grid over [0, 1] that finds the bracket holds at most one level per cell
+    cells = np.floor(c[half:] * k).astype(int)
+    assert np.all(np.diff(cells) > 0)
+
+
+def test_levels_the_four_candidates_are_taken_for():
+    for d in (64, 128, 256):
+        for bits in (1, 1.5, 2, 2.5, 3, 4):
+            assert _corner_levels(binding.octopus_build_codebooks(d, bits))
+    cb = _books(4)
+    cb.c_xi[0][9] *= 1.000001
+    assert not _corner_levels(cb)            # one level moved
+    cb.c_xi[0][6] *= 1.000001
+    assert not _corner_levels(cb)            # both sides moved
+    cb = _books(4)
+    cb.c_rho[0][3] = 1.0
+    assert not _corner_levels(cb)            # a norm level outside [0, 1)
+    assert not _corner_levels(binding.octopus_build_codebooks_pair(128, 2, 2))
+
+
+def _special_keys(n, n_kv, d, gen):
+    """Random keys with rows of zeros, one-hot and two-hot rows, constant rows, signs, half zeros, small integers, tiny and huge
+    norms, NaN and infinity between them."""
+    k = torch.randn((1, n, n_kv, d), generator=gen)
+    k[0, 1::16] = 0
+    k[0, 2::16] = 0
+    for t in range(2, n, 16):
+        k[0, t, :, (t * 7) % d] = 1.5
+    k[0, 3::16] = 0
+    for t in range(3, n, 16):
+        k[0, t, :, (t * 5) % d] = 1.0
+        k[0, t, :, (t * 3 + 1) % d] = -1.0
+    k[0, 4::16] *= 1e-25
+    k[0, 5::16] *= 1e25
+    k[0, 6::16] = 1.0
+    k[0, 7::64, :, 3] = float("nan")
+    k[0, 23::64, :, 3] = float("inf")
+    k[0, 8::16] = torch.sign(k[0, 8::16])
+    k[0, 9::16, :, ::2] = 0
+    k[0, 10::16] = torch.round(k[0, 10::16])
+    k[0, 11::16, :, :d // 2] = k[0, 11::16, :, d // 2:].clone()
+    return k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("d,bits", [(64, 1), (128, 1.5), (256, 2), (64, 2.5), (128, 3), (64, 4), (256, 4)])
+def test_four_candidates_give_the_codes_of_nine(d, bits, dtype):
+    """The same keys with the library's codebooks and with the top norm level raised to 1 (nine candidates): norms and direction
+    codes agree bit for bit."""
+    n, n_kv, start = 531, 2, 13
+    gen = torch.Generator().manual_seed(17)
+    keys = _special_keys(n, n_kv, d, gen).to("cuda", dtype)
+    signs = torch.randint(0, 256, (n_kv, d // 8), generator=gen, dtype=torch.uint8).cuda()
+    cap = (n + start + 63) // 64 * 64
+    at = torch.tensor([start], dtype=torch.int32, device="cuda")
+    codes = []
+    for nine in (False, True):
+        cb = binding.octopus_build_codebooks(d, bits)
+        if nine:
+            for c in range(cb.plan.n_class):
+                cb.c_rho[c][(1 << cb.plan.b_nrm[c]) - 1] = 1.0
+        assert _corner_levels(cb) != nine
+        cache = torch.zeros(binding.octopus_cache_bytes(cb, 1, n_kv, cap), dtype=torch.uint8, device="cuda")
+        binding.octopus_encode(cb, keys, signs, cache, cap, at)
+        torch.cuda.synchronize()
+        rec, _ = layout.cache_to_records(cache.cpu().numpy(), 1, n_kv, cap, cb.plan.granules, cb.plan.record_bytes)
+        codes.append(rec[..., :4 + cb.plan.dir_bytes])
+    assert np.array_equal(codes[0], codes[1])
