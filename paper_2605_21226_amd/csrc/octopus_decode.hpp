@@ -247,15 +247,23 @@ __device__ __forceinline__ void build_tables(DecodeTables<P> &tb, int tid, int n
 // 194 -> 146 us; 32 sequences of 1 k - 64 k, d = 256: 877 -> 830 us; one head, 4096 tokens, fp32: 28.6 -> 21.3 us;
 // equal lengths (16 x 32768): 213.4 -> 211.7 us.
 // A segment has a fixed cost (queries rotated, operands built, first loads, merge, four barriers) of the order of a round of
-// steps, which an even division does not see.  It serves calls of fewer pairs than workgroups with steps enough for all;
+// steps, which an even division does not see.  It serves calls of fewer pairs than workgroups, of much the same length and with
+// steps enough for all;
 //   * where there are no more BLOCKS of item_waves steps (the last one of a pair may have fewer) than workgroups, a block is
 //     a workgroup's: one step per wavefront and one segment per workgroup, whatever the lengths;
-//   * where there are as many pairs as workgroups or more, every pair counts kSegmentTiles more than its whole blocks, and
-//     only whole blocks are handed out.
+//   * where there are as many pairs as workgroups or more, or some are short beside the others (short_pairs), every pair counts
+//     kSegmentTiles more than its whole blocks, and only whole blocks are handed out.  Divided evenly, the pairs of a few short
+//     sequences are one workgroup's segments: of 24 ragged sequences to 8000 tokens the worst has ten, of which each costs as much
+//     as a round of steps.
+// Fewer pairs than workgroups, ragged (1 / 64 of the longest and up), d = 128, b = 3, evenly / weighed: 24 sequences to 8000, 8 KV
+// heads of eight rows 104 / 56.5 us (over quantised values, four rows 95 / 50; fp32 values 198 / 114), 100 to 5000, 2 KV heads
+// 62 / 41, 16 to 30000, 4 KV heads 67 / 59.5, one of 60000 and eight of 300 58 / 39; 16 of half to full 12000 equal.  Pairs of equal
+// length stay evenly divided: weighed, 24 x 1024 28 / 24 but 28 x 1100 28.3 / 29.5, 16 x 1500 20.7 / 22, 24 x 4096 52 / 53.  Longer than
+// four shares, a cut pair costs little either way.  24 x 512 with blocks counted exactly: 26.4 / 19.3.
 // Calls with every length divided evenly / as here, d = 128, b = 3, ragged (lengths of 1 / 64 of the longest and up): 32
 // sequences to 372 tokens, one KV head of eight rows 43.2 / 17.7 us, 64 to 500, 8 KV heads of four rows 50.5 / 25.8, 256 to 500
 // 156 / 84, 256 to 4000 358 / 239, the same over quantised values 371 / 225, 40 to 16000 162 / 135 (kSegmentTiles half or twice
-// as many: 239 - 247, 135 - 145; with eight wavefronts 222 - 258).  Where the division stays even, choosing costs 0.1 - 0.2 us.
+// as many: 239 - 247, 135 - 145; with eight wavefronts 222 - 258).  Where the division stays even, choosing costs 0.1 - 0.2 us, in calls of few steps 0.1 - 0.4.
 constexpr int kDecodeWorkgroups = 256;   // one per compute unit
 constexpr int kSegmentTiles = 8;         // what a segment's fixed cost is counted for (twice with eight wavefronts)
 
@@ -298,15 +306,40 @@ struct Division {
     int kind;
     int waves_log2, tps;
 
-    // Most calls are known to be divided evenly by their steps alone (and code that runs costs its fetch here).
-    static __device__ __forceinline__ bool surely_even(const DecodeShape &shp, uint64_t steps, int waves_log2) {
-        return shp.pairs_fill == 0 && steps > static_cast<uint64_t>(kDecodeWorkgroups) << waves_log2;
+    // Sequences whose pairs are under three quarters of the mean pair and shorter than four even shares (st: the steps of this
+    // lane's sequence, sum and total: of all sequences and pairs, present: sequences with tokens).
+    static __device__ __forceinline__ uint64_t short_pairs(uint32_t st, uint64_t sum, uint64_t total, uint32_t present) {
+        const float shares = static_cast<float>(total) * (4.0f / kDecodeWorkgroups), mean = 0.75f * static_cast<float>(sum);
+        const float x = static_cast<float>(st);
+        return __ballot(st > 0u && x < shares && x * static_cast<float>(present) < mean);
     }
-    // Steps and (non-empty) pairs of the call.  The blocks are at most a block's rest per pair more than the steps alone
-    // make; where this bound is past the workgroups and the blocks are not, the even division is close to whole blocks.
-    __device__ __forceinline__ void set(uint64_t steps, uint64_t pairs) {
-        kind = pairs >= static_cast<uint64_t>(kDecodeWorkgroups) ? kPairsWeighed : kDivideEvenly;
-        if (steps + (pairs << waves_log2) - pairs <= static_cast<uint64_t>(kDecodeWorkgroups) << waves_log2) kind = kBlockEach;
+    static __device__ __forceinline__ uint32_t with_tokens(uint32_t st) { return __popcll(__ballot(st > 0u)); }
+    // Most calls are known to be divided evenly by their steps alone (and code that runs costs its fetch here).
+    static __device__ __forceinline__ bool surely_even(const DecodeShape &shp, uint32_t st, uint64_t sum, uint64_t total, int waves_log2) {
+        return shp.pairs_fill == 0 && shp.n_seq <= kWave && total > static_cast<uint64_t>(kDecodeWorkgroups) << waves_log2 &&
+               short_pairs(st, sum, total, with_tokens(st)) == 0u;
+    }
+    // The kind, from the steps of all sequences and pairs; steps_at(s0): the steps of sequence s0 + lane (0: none).
+    template <class Steps>
+    __device__ __forceinline__ void set(const DecodeShape &shp, uint64_t sum, const Steps &steps_at) {
+        const uint64_t G = static_cast<uint64_t>(shp.n_kv_heads) * shp.n_row_groups, total = sum * G;
+        constexpr uint64_t kWgs = kDecodeWorkgroups;
+        uint32_t present = 0;
+        for (int s0 = 0; s0 < shp.n_seq; s0 += kWave) present += with_tokens(steps_at(s0));
+        const uint64_t pairs = present * G;
+        kind = kBlockEach;
+        if (total + (pairs << waves_log2) - pairs <= kWgs << waves_log2) return;   // (blocks have at most a rest per pair more)
+        if (total <= kWgs << waves_log2) {   // (else the blocks are more than the workgroups)
+            uint64_t blocks = 0;
+            for (int s0 = 0; s0 < shp.n_seq; s0 += kWave)
+                blocks += static_cast<uint32_t>(__builtin_amdgcn_readlane(
+                    static_cast<int>(wave_scan((steps_at(s0) + (1u << waves_log2) - 1u) >> waves_log2)), kWave - 1));
+            if (blocks * G <= kWgs) return;
+        }
+        kind = pairs >= kWgs ? kPairsWeighed : kDivideEvenly;
+        if (pairs < kWgs)
+            for (int s0 = 0; s0 < shp.n_seq; s0 += kWave)
+                if (short_pairs(steps_at(s0), sum, total, present) != 0u) kind = kPairsWeighed;
     }
     __device__ __forceinline__ uint32_t fixed() const {
         return kind == kPairsWeighed ? static_cast<uint32_t>((waves_log2 == 3 ? 2 * kSegmentTiles : kSegmentTiles) / tps) : 0u;
@@ -381,11 +414,14 @@ struct WorkSpan {
             chunk = 0;
             st = read(shp, seq_lens, lane);
         }
+        const uint64_t sum = total;
         total *= G;
-        if (__builtin_expect(!Division::surely_even(shp, total, div.waves_log2), 0)) {
-            uint64_t pairs = __popcll(__ballot(st > 0u));
-            for (chunk = kWave; chunk < shp.n_seq; chunk += kWave) pairs += __popcll(__ballot(read(shp, seq_lens, lane) > 0u));
-            div.set(total, pairs * G);
+        if (__builtin_expect(!Division::surely_even(shp, st, sum, total, div.waves_log2), 0)) {
+            div.set(shp, sum, [&](int s0) __attribute__((always_inline)) {
+                if (s0 == 0) return st;
+                chunk = s0;
+                return read(shp, seq_lens, lane);
+            });
             if (div.kind != kDivideEvenly) {
                 lane_sum = wave_scan(div.units(st));
                 total = chunk_sum();
@@ -1899,15 +1935,11 @@ __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, const flo
             read(s0);
             add(s0, st);
         }
+        const uint64_t sum = total;
         total *= G;
         Division div{kDivideEvenly, shp.item_waves == 8 ? 3 : 2, shp.tiles_per_step};
-        if (__builtin_expect(!Division::surely_even(shp, total, div.waves_log2), 0)) {
-            uint64_t pairs = 0;
-            for (int s0 = 0; s0 < shp.n_seq; s0 += kWave) {
-                read(s0);
-                pairs += __popcll(__ballot(st > 0u));
-            }
-            div.set(total, pairs * G);
+        if (__builtin_expect(!Division::surely_even(shp, st, sum, total, div.waves_log2), 0)) {
+            div.set(shp, sum, [&](int s0) __attribute__((always_inline)) { read(s0); return st; });
             if (div.kind != kDivideEvenly) {
                 total = 0;
                 for (int s0 = 0; s0 < shp.n_seq; s0 += kWave) {
