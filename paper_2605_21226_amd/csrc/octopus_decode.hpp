@@ -872,7 +872,7 @@ __device__ __forceinline__ void transpose_groups(uint32_t (&x)[4]) {
 
 // The code bits of one class that a lane looks up, for the four keys 16 b + n of a tile: dir[word][block] holds the
 // direction codes of its quarter, nrm[word][block] the norm codes.
-template <class P, int C, bool LEAN>
+template <class P, int C, bool COPIES>
 struct MxCodes {
     static constexpr int BD = C ? P::BD1 : P::BD0, BN = C ? P::BN1 : P::BN0;
     static constexpr int NS = C ? MxSteps<P>::NS1 : MxSteps<P>::NS0;
@@ -881,8 +881,8 @@ struct MxCodes {
     // Direction codes of whole bytes and two-bit norm codes (4 + 4 + 2 bits): the norm bits are kept in four shifted
     // copies, so that bits 6 and 7 of a byte of one of them are the code; one byte permute brings the two codes of a
     // triplet together and one and-or cuts and adds the lane part, instead of permute, bit-field extract and shift-or.
-    // (LEAN: kernels short of registers do without the copies)
-    static constexpr bool PAIRED = !LEAN && JT::BYTE_CODES && BN == 2 && JT::NS == 6;
+    // (COPIES false: kernels short of registers do without them)
+    static constexpr bool PAIRED = COPIES && JT::BYTE_CODES && BN == 2 && JT::NS == 6;
     static constexpr int NV = PAIRED ? 4 * NN : NN;
     uint32_t dir[ND > 0 ? ND : 1][4], nrm[NV > 0 ? NV : 1][4];
 
@@ -944,7 +944,7 @@ struct MxCodes {
 template <class P, int KPL, bool LEAN>
 constexpr int mx_units() { return MxSteps<P>::N * KPL * (LEAN ? 2 : 1); }
 
-template <class P, int RG, int KPL, class Hook = NoChunkHook, int AHEAD = 2, bool LEAN = false>
+template <class P, int RG, int KPL, class Hook = NoChunkHook, int AHEAD = 2, bool LEAN = false, bool COPIES = !LEAN>
 __device__ __forceinline__ void tile_scores_mx(const uint32_t (&w)[KPL][P::NWORDS], const QueryOperands<P, RG> &qop,
                                                const DecodeTables<P> &tb, int lane, float (&s)[KPL][RG],
                                                const Hook &hook = Hook{}) {
@@ -956,8 +956,8 @@ __device__ __forceinline__ void tile_scores_mx(const uint32_t (&w)[KPL][P::NWORD
     constexpr int LA = NU - 1 < AHEAD ? NU - 1 : AHEAD;
     constexpr int NB = LA + 1;
     constexpr int ROWS = QueryOperands<P, RG>::ROWS;
-    MxCodes<P, 0, LEAN> c0[KPL];
-    MxCodes<P, 1, LEAN> c1[P::NCLASS == 2 ? KPL : 1];
+    MxCodes<P, 0, COPIES> c0[KPL];
+    MxCodes<P, 1, COPIES> c1[P::NCLASS == 2 ? KPL : 1];
 #pragma unroll
     for (int k = 0; k < KPL; ++k) c0[k].cut(w[k]);
     if constexpr (P::NCLASS == 2) {
@@ -1137,6 +1137,7 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
     // static, so that table addresses are compile-time constants that fold into the LDS instructions
     constexpr bool MX = mx_scores<P>();    // scores on the matrix cores (every plan up to 3 bits per coordinate)
     // fewer registers for the score pass where it would spill (one row, 3 bits, 16 x 32768 tokens, 8 KV heads, spilling 231 us, so 203)
+    // (eight rows without the residual keep the two-instruction lookups: 16 x 1500 tokens 22.5 -> 22.2, 16 x 32768 208.4 -> 207.8)
     constexpr bool LEAN = QJL || RG == 8 || RG == 1 || P::NCLASS == 2;
     __shared__ DecodeSmemMfma<P, KPL> sm;
     using QO = QjlOperands<D, RG>;
@@ -1481,7 +1482,7 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
                     if constexpr (pi % CW == CW - 1) load_values(v_cur[(pi / CW) / 2], pi / CW, vr[pi / CW]);
                 });
             };
-            if constexpr (MX) tile_scores_mx<P, RG, KPL, decltype(pv_in_chunk), 2, LEAN>(w, qop, sm.tb, lane, s, pv_in_chunk);
+            if constexpr (MX) tile_scores_mx<P, RG, KPL, decltype(pv_in_chunk), 2, LEAN, !LEAN || (RG == 8 && !QJL)>(w, qop, sm.tb, lane, s, pv_in_chunk);
             else tile_scores<P, RG, KPL>(w, qg + q_off, sm.tb, lane, s, pv_in_chunk);
             // the probabilities of the previous step have been read: the new ones may overwrite them
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1511,13 +1512,17 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
             }
         }
         // D5: online softmax, one running maximum per row for the whole wave
-        float alpha[RG];
+        float alpha[RG], mx[RG];
 #pragma unroll
         for (int r = 0; r < RG; ++r) {
-            float mx = s[0][r];
+            mx[r] = s[0][r];
 #pragma unroll
-            for (int k = 1; k < KPL; ++k) mx = fmaxf(mx, s[k][r]);
-            const float m_new = fmaxf(m_run[r], wave_max(mx));
+            for (int k = 1; k < KPL; ++k) mx[r] = fmaxf(mx[r], s[k][r]);
+        }
+        wave_max_of(mx);
+#pragma unroll
+        for (int r = 0; r < RG; ++r) {
+            const float m_new = fmaxf(m_run[r], mx[r]);
             alpha[r] = exp2_raw((m_run[r] - m_new) * kLog2e);
             m_run[r] = m_new;
             float psum = 0.0f;
@@ -1800,10 +1805,13 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) void decode_kernel_valu(
 #pragma unroll
         for (int r = 0; r < RG; ++r) s[r] = valid ? s[r] * gamma : -INFINITY;
         if (scores_out != nullptr && valid) store_scores<RG>(shp, ww, scores_out, t0 + lane, s);
-        float alpha[RG];
+        float alpha[RG], mx[RG];
+#pragma unroll
+        for (int r = 0; r < RG; ++r) mx[r] = s[r];
+        wave_max_of(mx);
 #pragma unroll
         for (int r = 0; r < RG; ++r) {
-            const float m_new = fmaxf(m_run[r], wave_max(s[r]));
+            const float m_new = fmaxf(m_run[r], mx[r]);
             alpha[r] = exp2_raw((m_run[r] - m_new) * kLog2e);
             m_run[r] = m_new;
             const float p = exp2_raw((s[r] - m_new) * kLog2e);

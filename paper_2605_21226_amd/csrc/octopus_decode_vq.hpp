@@ -129,6 +129,10 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
     // hundreds of bytes either way and is faster wide (338 / 372 at b = 1, 362 / 382 at 1.5).
     constexpr bool LEAN = NWV > 4 || (!(P::NCLASS == 1 && P::BD0 == 4 && P::BN0 == 2) && (D <= 128 || VG == 32));
     constexpr int LOOKAHEAD = NWV > 4 ? 1 : 2;
+    // ... but a lookup of two instructions instead of four (MxCodes::PAIRED) also where two wavefronts share a SIMD: its 12 registers
+    // cost no more than what is stored outside the step loop (Llama-shaped batch, values at 3 / 2 bits in groups of 32: 142.6 ->
+    // 138.7, 135.8 -> 126.3 us; d = 64 85.9 -> 79.3).
+    constexpr bool COPIES = !LEAN || NWV > 4;
     // bf16 of 2^VB + code: exponent 127 + VB, the code in the top VB bits of the 7-bit mantissa
     constexpr float BIAS = static_cast<float>(1 << VB);
     constexpr int CODE_POS = 7 - VB;
@@ -388,7 +392,7 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
                 if constexpr (pi * (NCH - 1) / NPB == ci) raw_request(pp);
             });
         };
-        if constexpr (MX) tile_scores_mx<P, RG, KPL, decltype(build_in_chunk), LOOKAHEAD, LEAN>(w, qop, sm.tb, lane, s, build_in_chunk);
+        if constexpr (MX) tile_scores_mx<P, RG, KPL, decltype(build_in_chunk), LOOKAHEAD, LEAN, COPIES>(w, qop, sm.tb, lane, s, build_in_chunk);
         else tile_scores<P, RG, KPL>(w, qg + q_off, sm.tb, lane, s, build_in_chunk);
 #pragma unroll
         for (int k = 0; k < KPL; ++k) {
@@ -403,13 +407,17 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
         float2 sz[KPL][G];
         load_meta(sz);
         // D5: online softmax, one running maximum per row for the whole wave; s becomes the probabilities
-        float alpha[RG];
+        float alpha[RG], mx[RG];
 #pragma unroll
         for (int r = 0; r < RG; ++r) {
-            float mx = s[0][r];
+            mx[r] = s[0][r];
 #pragma unroll
-            for (int k = 1; k < KPL; ++k) mx = fmaxf(mx, s[k][r]);
-            const float m_new = fmaxf(m_run[r], wave_max(mx));
+            for (int k = 1; k < KPL; ++k) mx[r] = fmaxf(mx[r], s[k][r]);
+        }
+        wave_max_of(mx);
+#pragma unroll
+        for (int r = 0; r < RG; ++r) {
+            const float m_new = fmaxf(m_run[r], mx[r]);
             alpha[r] = exp2_raw((m_run[r] - m_new) * kLog2e);
             m_run[r] = m_new;
             float psum = 0.0f;
