@@ -866,6 +866,202 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
     }
 }
 
+// One triplet without tables, for the append kernel below: the brackets by comparison with every level, the four corners
+// (next to an axis: the nine candidates) by Oct^-1 of their levels, which is what the tables hold.
+template <int BD, int BN>
+__device__ __forceinline__ void encode_triplet_alone(float x, float y, float z, const float *c_xi, const float *c_rho,
+                                                     uint32_t *dir_field, uint32_t *nrm_index) {
+    using G = CornerGrid<BD>;
+    constexpr int K = G::K, H = G::H, M = 1 << BN;
+    const float l1 = fabsf(x) + fabsf(y) + fabsf(z);
+    const float l1c = fmaxf(l1, kEps);
+    float inv = __builtin_amdgcn_rcpf(l1c);
+    inv = fmaf(fmaf(-l1c, inv, 1.0f), inv, inv);
+    const float px = x * inv, py = y * inv;
+    const int neg_x = __float_as_int(x) >> 31, neg_y = __float_as_int(y) >> 31;   // 0 or -1
+    float best;
+    uint32_t best_code;
+    if (fminf(fminf(fabsf(px), fabsf(py)), l1 * (G::near_axis() / kEps)) > G::near_axis()) {
+        const float xi = z < 0.0f ? 1.0f - fabsf(py) : fabsf(px), eta = z < 0.0f ? 1.0f - fabsf(px) : fabsf(py);
+        int jx = H, jy = H;   // K / 2 + bracket
+#pragma unroll
+        for (int k = 1; k < H - 1; ++k) {
+            const float level = c_xi[H + k];
+            jx += level < xi ? 1 : 0;
+            jy += level < eta ? 1 : 0;
+        }
+        constexpr int ENDS = H > 1 ? 2 : 1;
+        float sc[4];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                if (a >= ENDS || b >= ENDS) { sc[2 * a + b] = -INFINITY; continue; }
+                const float4 n = oct_decode(c_xi[jx + a], c_xi[jy + b]);
+                sc[2 * a + b] = fmaf(z, n.z, fmaf(fabsf(y), n.y, fabsf(x) * n.x));
+            }
+        const float row0 = fmaxf(sc[0], sc[1]), row1 = fmaxf(sc[2], sc[3]);
+        best = fmaxf(row0, row1);
+        const bool up_x = H > 1 && __float_as_int(row1) - neg_x > __float_as_int(row0);
+        const float lower = up_x ? sc[2] : sc[0], upper = up_x ? sc[3] : sc[1];
+        const bool up_y = H > 1 && __float_as_int(upper) - neg_y > __float_as_int(lower);
+        const uint32_t code = static_cast<uint32_t>((jx + (up_x ? 1 : 0)) | ((jy + (up_y ? 1 : 0)) << BD));
+        const uint32_t flip = (static_cast<uint32_t>(neg_x) & (K - 1)) | (static_cast<uint32_t>(neg_y) & ~(K - 1u));
+        best_code = (code ^ flip) & (K * K - 1u);
+    } else {
+        float xi = px, eta = py;
+        if (z < 0.0f) {
+            const float fx = 1.0f - fabsf(py), fy = 1.0f - fabsf(px);
+            xi = (px >= 0.0f) ? fx : -fx;
+            eta = (py >= 0.0f) ? fy : -fy;
+        }
+        int jx = 0, jy = 0;   // boundaries strictly below
+#pragma clang loop unroll(disable)
+        for (int k = 0; k < K - 1; ++k) {
+            const float b = 0.5f * (c_xi[k] + c_xi[k + 1]);
+            jx += b < xi ? 1 : 0;
+            jy += b < eta ? 1 : 0;
+        }
+        best = -INFINITY;
+        best_code = static_cast<uint32_t>(min(jx + 1, K - 1) | (min(jy + 1, K - 1) << BD));   // (no candidate is a number)
+#pragma clang loop unroll(disable)
+        for (int c = 0; c < 9; ++c) {
+            const int cx = min(max(jx + c / 3 - 1, 0), K - 1), cy = min(max(jy + c % 3 - 1, 0), K - 1);
+            const float4 n = oct_decode(c_xi[cx], c_xi[cy]);
+            const float s = fmaf(z, n.z, fmaf(y, n.y, x * n.x));
+            if (s > best) { best = s; best_code = static_cast<uint32_t>(cx | (cy << BD)); }
+        }
+    }
+    int r = 0;
+#pragma unroll
+    for (int k = 0; k < M - 1; ++k) r += (0.5f * (c_rho[k] + c_rho[k + 1]) < best) ? 1 : 0;
+    *dir_field = best_code;
+    *nrm_index = static_cast<uint32_t>(r);
+}
+
+// Few keys (a decode step appends one per sequence and KV head): one wavefront per key, a triplet per lane.  encode_kernel
+// spends 9 us on such a call whatever it holds, tables and a chain of six triplets per wavefront, each with its LDS round
+// trips; here nothing is built and every triplet is on its way at once.  Same codes bit for bit (the same operands in every
+// addition of the transform and of the norm).  Bound by that chain: load, norm, 7 stages,
+// triplet, store.
+template <class P, bool BF16>
+__global__ __launch_bounds__(kWave) void encode_few_kernel(DeviceBooks books, const void *__restrict__ keys, int64_t stride_seq,
+                                                           int64_t stride_tok, int64_t stride_head, int32_t n_new,
+                                                           const uint8_t *__restrict__ signs, uint4 *__restrict__ cache,
+                                                           int64_t t_capacity, const int32_t *__restrict__ start_pos,
+                                                           int32_t n_kv_heads, PageTable pt) {
+    constexpr int D = P::D, LPR = D / 8;
+    constexpr int NX = P::BD0 > 2 || P::BD1 > 2 ? 1 << (P::BD0 > P::BD1 ? P::BD0 : P::BD1) : 4;
+    constexpr int NR = 1 << (P::BN0 > P::BN1 ? P::BN0 : P::BN1);
+    __shared__ __attribute__((aligned(16))) float u[3 * P::NTRI + 16];
+    __shared__ __attribute__((aligned(16))) uint32_t rec[P::NWORDS + 4];
+    __shared__ float c_xi[P::NCLASS][NX], c_rho[P::NCLASS][NR];
+    const int lane = threadIdx.x;
+    const int kvh = blockIdx.y, seq = blockIdx.z;
+    const int64_t start = start_pos ? max(start_pos[seq], 0) : 0;
+    const int64_t tok = start + blockIdx.x;
+    if (blockIdx.x >= static_cast<uint32_t>(n_new) || tok >= t_capacity) return;
+    const int64_t tile = tok / kWave;
+    int page = 0;
+    if (pt.table != nullptr) page = pt.table[static_cast<int64_t>(seq) * pt.stride + tile];
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = 0.0f;
+    uint32_t sbits = 0u;
+    if (lane < LPR) {
+        sbits = signs[kvh * LPR + lane];
+        const int64_t off = seq * stride_seq + kvh * stride_head + static_cast<int64_t>(blockIdx.x) * stride_tok + lane * 8;
+        if constexpr (BF16) {
+            const uint4 r = *reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(keys) + off);
+            x[0] = bf16_lo(r.x); x[1] = bf16_hi(r.x); x[2] = bf16_lo(r.y); x[3] = bf16_hi(r.y);
+            x[4] = bf16_lo(r.z); x[5] = bf16_hi(r.z); x[6] = bf16_lo(r.w); x[7] = bf16_hi(r.w);
+        } else {
+            const float4 a = *reinterpret_cast<const float4 *>(static_cast<const float *>(keys) + off);
+            const float4 b = *reinterpret_cast<const float4 *>(static_cast<const float *>(keys) + off + 4);
+            x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < P::NCLASS; ++c) {   // (levels by lane; the arguments hold kMaxLevels of each)
+        typedef const float __attribute__((address_space(4))) *arg_t;
+        arg_t arg = (arg_t)__builtin_amdgcn_kernarg_segment_ptr();
+        const float xi = arg[offsetof(DeviceBooks, c_xi) / 4 + c * kMaxLevels + lane], rho = arg[offsetof(DeviceBooks, c_rho) / 4 + c * kMaxLevels + lane];
+        if (lane < NX) c_xi[c][lane] = xi;
+        if (lane < NR) c_rho[c][lane] = rho;
+    }
+    if (lane < P::NWORDS) rec[lane] = 0u;
+
+    // E1-E3: norm, sign flip, transform (eight coordinates per lane, then lane by lane)
+    float ss = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ss = fmaf(x[e], x[e], ss);
+    ss = row_sum<LPR>(ss);
+    const float gamma = sqrtf(__int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(ss))));
+    const float norm = (1.0f / fmaxf(gamma, kEps)) * inv_sqrt_dim<D>();
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = ((sbits >> e) & 1u) ? -x[e] : x[e];
+    butterflies<8>(x);
+    static_for<0, (D == 64 ? 3 : (D == 128 ? 4 : 5))>([&](auto bb) {
+        constexpr int m = 1 << decltype(bb)::value;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float other = lane_xor<m>(x[e], lane);
+            x[e] = (lane & m) ? other - x[e] : x[e] + other;
+        }
+    });
+    if (lane < LPR) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) u[lane * 8 + e] = x[e];
+    }
+    __syncthreads();
+
+    // E4-E8
+    for (int i = lane; i < P::NTRI; i += kWave) {
+        float a = u[3 * i] * norm, b = 3 * i + 1 < D ? u[3 * i + 1] * norm : 0.0f, c = 3 * i + 2 < D ? u[3 * i + 2] * norm : 0.0f;
+        asm("" : "+v"(a), "+v"(b), "+v"(c));   // (the rounded products: none is to be fused into a later sum)
+        uint32_t dir, nrm;
+        int dir_bit, nrm_bit, dir_bits, nrm_bits;
+        if (P::NCLASS == 1 || i < P::NT0) {
+            encode_triplet_alone<P::BD0, P::BN0>(a, b, c, c_xi[0], c_rho[0], &dir, &nrm);
+            dir_bits = 2 * P::BD0;
+            nrm_bits = P::BN0;
+            dir_bit = P::DIR0_BIT + i * dir_bits;
+            nrm_bit = P::NRM0_BIT + i * nrm_bits;
+        } else {
+            constexpr int BD1 = P::BD1 > 0 ? P::BD1 : 1, BN1 = P::BN1 > 0 ? P::BN1 : 1;
+            encode_triplet_alone<BD1, BN1>(a, b, c, c_xi[P::NCLASS - 1], c_rho[P::NCLASS - 1], &dir, &nrm);
+            dir_bits = 2 * BD1;
+            nrm_bits = BN1;
+            dir_bit = P::DIR1_BIT + (i - P::NT0) * dir_bits;
+            nrm_bit = P::NRM1_BIT + (i - P::NT0) * nrm_bits;
+        }
+        atomicOr(&rec[dir_bit >> 5], dir << (dir_bit & 31));
+        if ((dir_bit & 31) + dir_bits > 32) atomicOr(&rec[(dir_bit >> 5) + 1], dir >> (32 - (dir_bit & 31)));
+        atomicOr(&rec[nrm_bit >> 5], nrm << (nrm_bit & 31));
+        if ((nrm_bit & 31) + nrm_bits > 32) atomicOr(&rec[(nrm_bit >> 5) + 1], nrm >> (32 - (nrm_bit & 31)));
+    }
+    if (lane == 0) rec[0] = __float_as_uint(gamma) & (BF16 ? 0x7fffffffu : 0xffffffffu);   // (no field reaches into word 0)
+    __syncthreads();
+    if (lane < P::GRANULES) {
+        uint4 *dst = cache + (static_cast<int64_t>(seq) * n_kv_heads + kvh) * (t_capacity * P::GRANULES) + tile * (P::GRANULES * kWave);
+        if (pt.table != nullptr)
+            dst = cache + (static_cast<int64_t>(min(max(page, 0), pt.n_pages - 1)) * n_kv_heads + kvh) * (P::GRANULES * kWave);
+        typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+        const u32x4_t rec4 = {rec[4 * lane], rec[4 * lane + 1], rec[4 * lane + 2], rec[4 * lane + 3]};
+        __builtin_nontemporal_store(rec4, reinterpret_cast<u32x4_t *>(dst + lane * kWave + tok % kWave));
+    }
+}
+
+// Calls that encode_few_kernel serves: its time goes with the keys, encode_kernel's with the tiles they fall into.  A tile kernel /
+// this one, 8 KV heads: one key per sequence, 512 / 1024 / 2048 sequences, d = 128, b = 3 45.5 / 9.5, 87 / 13.9, 170 / 19.4 us
+// (d = 256, b = 4 159 / 21, 315 / 32, 626 / 54; d = 64, b = 2 23 / 11.7, 40 / 18, 76 / 31); four keys, 256 sequences, d = 128
+// 24.6 / 12.5 but d = 64, b = 2 13.9 / 18.5; 16 keys, 128 sequences 14.9 / 19.4.  In one sequence 512 keys are on a par (9 - 10 us) at
+// d = 128 and behind at d = 256 (13 / 20), 128 keys ahead everywhere; alone on the chip one key takes 4.4 us instead of 7.5.
+template <int D>
+bool few_keys(int64_t n_seq, int64_t n_kv_heads, int64_t n_new) {
+    return n_new <= (D >= 128 ? 4 : 2) || n_seq * n_kv_heads * n_new <= 1024;
+}
+
 template <class P>
 int launch_encode_plan(const octopus_codebooks_t &cb, const void *keys, int key_dtype, int64_t stride_seq,
                        int64_t stride_tok, int64_t stride_head, int32_t n_seq, int32_t n_kv_heads, int32_t n_new,
@@ -884,7 +1080,13 @@ int launch_encode_plan(const octopus_codebooks_t &cb, const void *keys, int key_
     };
     // (four candidates per triplet where the winner is known to be among them, else nine)
     if (corner_levels(cb)) {
-        if (qjl != nullptr) {
+        if (qjl == nullptr && few_keys<P::D>(n_seq, n_kv_heads, n_new)) {
+            auto few = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(n_new, n_kv_heads, n_seq), dim3(kWave), 0, stream, books, keys, stride_seq, stride_tok,
+                                   stride_head, n_new, signs, static_cast<uint4 *>(cache), t_capacity, start_pos, n_kv_heads, pt);
+            };
+            if (bf16) few(encode_few_kernel<P, true>); else few(encode_few_kernel<P, false>);
+        } else if (qjl != nullptr) {
             if (bf16) go(encode_kernel<P, true, true, false, true>); else go(encode_kernel<P, false, true, false, true>);
         } else {
             if (bf16) go(encode_kernel<P, true, false, false, true>); else go(encode_kernel<P, false, false, false, true>);

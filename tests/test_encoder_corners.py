@@ -148,3 +148,27 @@ def test_four_candidates_give_the_codes_of_nine(d, bits, dtype):
         rec, _ = layout.cache_to_records(cache.cpu().numpy(), 1, n_kv, cap, cb.plan.granules, cb.plan.record_bytes)
         codes.append(rec[..., :4 + cb.plan.dir_bytes])
     assert np.array_equal(codes[0], codes[1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("d,bits", [(64, 1), (64, 1.5), (64, 4), (128, 1), (128, 2), (128, 2.5), (128, 3), (128, 4), (256, 1.5), (256, 3), (256, 4)])
+def test_appended_keys_have_the_records_of_a_prefill(d, bits, dtype):
+    """One call over 300 tokens x 4 KV heads (tiles) and the same tokens one, two and seven at a time (a wavefront per key): the
+    same bytes, past the capacity nothing is written."""
+    n, n_kv, start = 300, 4, 13
+    gen = torch.Generator().manual_seed(19)
+    keys = _special_keys(n, n_kv, d, gen).to("cuda", dtype)
+    signs = torch.randint(0, 256, (n_kv, d // 8), generator=gen, dtype=torch.uint8).cuda()
+    cb = binding.octopus_build_codebooks(d, bits)
+    cap = (n + start + 63) // 64 * 64
+    caches = [torch.zeros(binding.octopus_cache_bytes(cb, 1, n_kv, cap), dtype=torch.uint8, device="cuda") for _ in range(2)]
+    binding.octopus_encode(cb, keys, signs, caches[0], cap, torch.tensor([start], dtype=torch.int32, device="cuda"))
+    t, sizes = 0, (1, 2, 7)
+    while t < n:
+        m = min(sizes[t % 3], n - t)
+        binding.octopus_encode(cb, keys[:, t:t + m], signs, caches[1], cap, torch.tensor([start + t], dtype=torch.int32, device="cuda"))
+        t += m
+    binding.octopus_encode(cb, keys[:, :2], signs, caches[1], cap, torch.tensor([cap], dtype=torch.int32, device="cuda"))
+    torch.cuda.synchronize()
+    assert torch.equal(caches[0], caches[1])
