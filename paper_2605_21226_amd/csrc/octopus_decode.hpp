@@ -256,7 +256,7 @@ __device__ __forceinline__ void build_tables(DecodeTables<P> &tb, int tid, int n
 //     sequences are one workgroup's segments: of 24 ragged sequences to 8000 tokens the worst has ten, of which each costs as much
 //     as a round of steps.
 // Fewer pairs than workgroups, ragged (1 / 64 of the longest and up), d = 128, b = 3, evenly / weighed: 24 sequences to 8000, 8 KV
-// heads of eight rows 104 / 56.5 us (over quantised values, four rows 95 / 50; fp32 values 198 / 114), 100 to 5000, 2 KV heads
+// heads of eight rows 104 / 56.5 us (over quantised values, four rows 95 / 50; fp32 values 174 / 116), 100 to 5000, 2 KV heads
 // 62 / 41, 16 to 30000, 4 KV heads 67 / 59.5, one of 60000 and eight of 300 58 / 39; 16 of half to full 12000 equal.  Pairs of equal
 // length stay evenly divided: weighed, 24 x 1024 28 / 24 but 28 x 1100 28.3 / 29.5, 16 x 1500 20.7 / 22, 24 x 4096 52 / 53.  Longer than
 // four shares, a cut pair costs little either way.  24 x 512 with blocks counted exactly: 26.4 / 19.3.
@@ -301,7 +301,7 @@ __device__ __forceinline__ uint32_t divide(uint64_t a, uint64_t b) {
 // takes the quanta whose first unit lies in its share.  (Quanta are never further apart than a share is long -- one unit, or
 // item_waves units of a total of item_waves kDecodeWorkgroups at least -- so the workgroups that have quanta of a pair are
 // consecutive.)  waves_log2, tps: log2 of the wavefronts per workgroup, tiles per step.
-enum : int { kDivideEvenly, kBlockEach, kPairsWeighed };
+enum : int { kDivideEvenly, kBlockEach, kPairsWeighed, kPairEach };
 struct Division {
     int kind;
     int waves_log2, tps;
@@ -344,7 +344,7 @@ struct Division {
     __device__ __forceinline__ uint32_t fixed() const {
         return kind == kPairsWeighed ? static_cast<uint32_t>((waves_log2 == 3 ? 2 * kSegmentTiles : kSegmentTiles) / tps) : 0u;
     }
-    __device__ __forceinline__ int steps_log2() const { return kind == kDivideEvenly ? 0 : waves_log2; }   // steps per quantum
+    __device__ __forceinline__ int steps_log2() const { return kind == kDivideEvenly ? 0 : (kind == kPairEach ? 30 : waves_log2); }   // steps per quantum
     __device__ __forceinline__ int units_log2() const { return kind == kPairsWeighed ? waves_log2 : 0; }   // units per quantum
     __device__ __forceinline__ uint32_t quanta(uint32_t steps) const { return (steps + (1u << steps_log2()) - 1u) >> steps_log2(); }
     __device__ __forceinline__ uint32_t units(uint32_t steps) const {
@@ -356,7 +356,7 @@ struct Division {
     }
     // the share of workgroup b, and the workgroup that has unit x
     __device__ __forceinline__ void share(uint64_t total, int b, uint64_t *pos, uint64_t *end) const {
-        if (__builtin_expect(kind == kBlockEach, 0)) {   // (at most as many units as workgroups)
+        if (__builtin_expect(kind == kBlockEach || kind == kPairEach, 0)) {   // (at most as many units as workgroups)
             *pos = min(static_cast<uint32_t>(b), static_cast<uint32_t>(total));
             *end = min(static_cast<uint32_t>(b) + 1u, static_cast<uint32_t>(total));
         } else {
@@ -416,8 +416,9 @@ struct WorkSpan {
         }
         const uint64_t sum = total;
         total *= G;
-        if (__builtin_expect(!Division::surely_even(shp, st, sum, total, div.waves_log2), 0)) {
-            div.set(shp, sum, [&](int s0) __attribute__((always_inline)) {
+        if (__builtin_expect(shp.out != nullptr || !Division::surely_even(shp, st, sum, total, div.waves_log2), 0)) {
+            if (shp.out != nullptr) div.kind = kPairEach;
+            else div.set(shp, sum, [&](int s0) __attribute__((always_inline)) {
                 if (s0 == 0) return st;
                 chunk = s0;
                 return read(shp, seq_lens, lane);
@@ -508,11 +509,34 @@ __device__ __forceinline__ void merge_waves(const DecodeShape &shp, const WaveWo
             a.x = fmaf(f, x.x, a.x); a.y = fmaf(f, x.y, a.y); a.z = fmaf(f, x.z, a.z); a.w = fmaf(f, x.w, a.w);
             l = fmaf(f, ml[w * ml_stride + 2 * r + 1], l);
         }
+        if (__builtin_expect(shp.out != nullptr, 0)) {   // all of the row: the output as well
+            const int row = ww.grp * RG + r, qi = row / shp.heads_per_kv, head = ww.kvh * shp.heads_per_kv + row % shp.heads_per_kv;
+            const int64_t orow = (static_cast<int64_t>(ww.seq) * shp.n_q + qi) * shp.n_q_heads + head;
+            const bool any = l > 0.0f;
+            reinterpret_cast<float4 *>(shp.out + orow * D)[e % (D / 4)] =
+                make_float4(any ? a.x / l : 0.0f, any ? a.y / l : 0.0f, any ? a.z / l : 0.0f, any ? a.w / l : 0.0f);
+        }
         reinterpret_cast<float4 *>(part_acc + ww.slot * (RG * D))[e] = a;
         if (e % (D / 4) == 0) {
             part_ml[(ww.slot * RG + r) * 2] = m;
             part_ml[(ww.slot * RG + r) * 2 + 1] = l;
         }
+    }
+}
+
+// Calls without a merge (shp.out): workgroup b writes the output rows of pair b, zeros, if the pair has no tokens.
+template <int D, int RG>
+__device__ __forceinline__ void zero_empty_pair(const DecodeShape &shp, const int32_t *seq_lens, int tid, int nthreads) {
+    const uint32_t b = blockIdx.x, per = static_cast<uint32_t>(shp.n_kv_heads * shp.n_row_groups);
+    const uint32_t seq = b / per;
+    if (seq >= static_cast<uint32_t>(shp.n_seq) || min(seq_lens[seq], shp.max_len) > 0) return;
+    const int g = static_cast<int>(b % per), kvh = g / shp.n_row_groups, grp = g % shp.n_row_groups;
+#pragma unroll 1
+    for (int e = tid; e < RG * D; e += nthreads) {
+        const int row = grp * RG + e / D;
+        if (row >= shp.rows_per_kv) continue;
+        const int qi = row / shp.heads_per_kv, head = kvh * shp.heads_per_kv + row % shp.heads_per_kv;
+        shp.out[((static_cast<int64_t>(seq) * shp.n_q + qi) * shp.n_q_heads + head) * D + e % D] = 0.0f;
     }
 }
 
@@ -1137,7 +1161,8 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
     // static, so that table addresses are compile-time constants that fold into the LDS instructions
     constexpr bool MX = mx_scores<P>();    // scores on the matrix cores (every plan up to 3 bits per coordinate)
     // fewer registers for the score pass where it would spill (one row, 3 bits, 16 x 32768 tokens, 8 KV heads, spilling 231 us, so 203)
-    // (eight rows without the residual keep the two-instruction lookups: 16 x 1500 tokens 22.5 -> 22.2, 16 x 32768 208.4 -> 207.8)
+    // (eight rows without the residual keep the two-instruction lookups: 16 x 1500 tokens 22.5 -> 22.2, 16 x 32768 208.4 -> 207.8;
+    // not at two classes, over pages they spill)
     constexpr bool LEAN = QJL || RG == 8 || RG == 1 || P::NCLASS == 2;
     __shared__ DecodeSmemMfma<P, KPL> sm;
     using QO = QjlOperands<D, RG>;
@@ -1157,6 +1182,7 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
     levels.load(lane);
     WorkSpan<KPL, kDecodeWaves> span;
     span.open(shp, seq_lens, lane);
+    if (__builtin_expect(shp.out != nullptr, 0)) zero_empty_pair<D, RG>(shp, seq_lens, tid, kDecodeWaves * kWave);
     if (span.pos >= span.end) return;   // (whole workgroup, before any barrier)
     levels.store(sm.tb, tid);           // (kept in registers until the tables are built they are live through the steps)
     // The tables are built inside the segment loop, after the first segment's first loads have been issued:
@@ -1482,7 +1508,7 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) __attribute__((amdgpu_waves_pe
                     if constexpr (pi % CW == CW - 1) load_values(v_cur[(pi / CW) / 2], pi / CW, vr[pi / CW]);
                 });
             };
-            if constexpr (MX) tile_scores_mx<P, RG, KPL, decltype(pv_in_chunk), 2, LEAN, !LEAN || (RG == 8 && !QJL)>(w, qop, sm.tb, lane, s, pv_in_chunk);
+            if constexpr (MX) tile_scores_mx<P, RG, KPL, decltype(pv_in_chunk), 2, LEAN, !LEAN || (RG == 8 && !QJL && P::NCLASS == 1)>(w, qop, sm.tb, lane, s, pv_in_chunk);
             else tile_scores<P, RG, KPL>(w, qg + q_off, sm.tb, lane, s, pv_in_chunk);
             // the probabilities of the previous step have been read: the new ones may overwrite them
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1712,7 +1738,6 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) void decode_kernel_valu(
     constexpr int D = P::D;
     constexpr int LPR = D / 8;          // lanes per value row (8 channels per lane)
     constexpr int KPL = kWave / LPR;    // value rows per wave-wide load
-    constexpr int TPS = decode_keys_per_lane<D>();  // tiles per step
     extern __shared__ __align__(16) unsigned char smem_raw[];
     DecodeSmemValu<P, RG> &sm = *reinterpret_cast<DecodeSmemValu<P, RG> *>(smem_raw);
 
@@ -1720,8 +1745,9 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) void decode_kernel_valu(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     BookLevels<P> levels;
     levels.load(lane);
-    WorkSpan<TPS, kDecodeWaves, false> span;   // (registers to spare)
+    WorkSpan<1, kDecodeWaves, false> span;   // (registers to spare)
     span.open(shp, seq_lens, lane);
+    if (__builtin_expect(shp.out != nullptr, 0)) zero_empty_pair<D, RG>(shp, seq_lens, tid, kDecodeWaves * kWave);
     if (span.pos >= span.end) return;   // (whole workgroup, before any barrier)
     levels.store(sm.tb, tid);           // (kept in registers until the tables are built they are live through the steps)
     build_tables<P>(sm.tb, tid, kDecodeWaves * kWave);
@@ -1741,10 +1767,10 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) void decode_kernel_valu(
         for (int c = 0; c < 8; ++c) acc[r][c] = 0.0f;
     }
 
-    // the splits are sized in steps of TPS tiles (shared with the bf16-value kernel); here a step is
-    // simply TPS tiles one after the other
-    for (int step = ww.step_begin; step < ww.step_end; step += ww.step_stride)
-    for (int tile = step * TPS; tile < min((step + 1) * TPS, ww.n_tiles); ++tile) {
+    // A step is a tile.  (Nothing of a tile waits for the one before but the running maximum, so two of them in a step, as in the
+    // kernel over bf16 values, only made a short call's longest chain twice as long: two / one, one head over 4096
+    // tokens 19.7 -> 17.8 us, 8 KV heads of four rows over 1000 26.7 -> 23.1, 2 x 9000 38.8 -> 35.5, 16 x 8192 133.9 -> 133.6.)
+    for (int tile = ww.step_begin; tile < ww.step_end; tile += ww.step_stride) {
         const int t0 = tile * kWave;
         const int n_valid = min(kWave, ww.len - t0);
         uint32_t w1[1][P::NWORDS];

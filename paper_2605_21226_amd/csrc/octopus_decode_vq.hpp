@@ -154,6 +154,7 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
     levels.load(lane);
     WorkSpan<KPL, NWV> span;
     span.open(shp, seq_lens, lane);
+    if (__builtin_expect(shp.out != nullptr, 0)) zero_empty_pair<D, RG>(shp, seq_lens, tid, NWV * kWave);
     if (span.pos >= span.end) return;   // (whole workgroup, before any barrier)
     levels.store(sm.tb, tid);           // (kept in registers until the tables are built they are live through the steps)
     bool tables_built = false;

@@ -595,6 +595,19 @@ static bool rotates_in_kernel(const octopus_plan_t &plan, bool many_rows, bool m
 // 164 / 132, 900 x 4, one KV head, 20000 (38 / 19) 219 / 181, 160 x 1, 30000 (30 / 17) 129 / 92, 512 x 4, 4096 (32 / 16)
 // 153 / 122.  At a ratio of 5 / 4 either may win: 1000 x 4, two KV heads, 6000 at 4 bits (24 / 19) 117 / 122, 200 x 1, 20480
 // (20 / 16) 94.5 / 88.5; the line is at 4 / 3.
+// Calls whose every (sequence, KV head, row group) is one workgroup's for a round of steps or two: the kernel writes the output
+// itself and no merge is launched.  Merged / direct, b = 3, four rows per KV head, 8 KV heads, one round: 1 x 400 tokens, d = 128
+// 15.4 / 11.6 us, 32 x 500 17.3 / 12.9 (values at 3 bits 18.6 / 14.7, residual 21.7 / 17.5), 32 x 250 over fp32 values 28.3 / 23.8, d = 256,
+// 32 x 250 19.4 / 14.4.  Two rounds: with more pairs than half the workgroups, 32 x 1000, 24.5 / 19.9 (residual 29.2 / 24.8); with fewer, where
+// merged every round is a workgroup's, 1 x 1000 15.6 / 14.7 (values at 3 bits 17.2 / 17.2, d = 256, 1 x 400 16.6 / 16.0), but with the
+// residual 19.9 / 20.6 and over fp32 values 26.3 / 30.0 (steps of two tiles then), whose steps are the longest.
+static bool direct_output(const DecodeShape &s, const float *out, bool with_window, bool long_steps) {
+    const int64_t round = static_cast<int64_t>(s.item_waves) * s.tiles_per_step * OCTOPUS_TILE;
+    const int64_t pairs = static_cast<int64_t>(s.n_seq) * s.n_kv_heads * s.n_row_groups;
+    return !with_window && s.rows_per_pass < 128 && pairs <= 256 && s.max_len <= (long_steps && 2 * pairs <= 256 ? 1 : 2) * round &&
+           aligned(out, 16);
+}
+
 static void many_rows_at_128(const octopus_codebooks_t *cb, int64_t max_len, DecodeShape *s, Workspace *w) {
     if (cb->plan.head_dim != 128 || s->rows_per_kv <= 128) return;
     DecodeShape wide = make_decode_shape(cb->plan, s->n_seq, s->n_q_heads, s->n_kv_heads, s->n_q, max_len, s->t_capacity, true, 8, 0,
@@ -672,7 +685,10 @@ static int attn_decode(const octopus_codebooks_t *cb, const void *q, int32_t q_d
         w = make_workspace(cb->plan, s);
     }
     if (many_rows) many_rows_at_128(cb, max_len, &s, &w);
+    const bool vector_kernel = with_vq ? vq_mfma == 0 : v_dtype != OCTOPUS_DTYPE_BF16;
+    if (vector_kernel) s.tiles_per_step = 1;   // (decode_kernel_valu; the workspace has room for either)
     set_queries(&s, q, q_dtype, signs, signs2, scale);
+    if (direct_output(s, out, win != nullptr, with_qjl || vector_kernel)) s.out = out;
     // every entry point asks for the one documented size, whatever its own kernel needs (the static scratch
     // has been checked against the need of the kernels it serves)
     const size_t required = static_scratch_call ? w.total
@@ -707,7 +723,7 @@ static int attn_decode(const octopus_codebooks_t *cb, const void *q, int32_t q_d
         err = launch_window(cb->plan, s, q, q_dtype, win->k_window, win->k_dtype, win->w_capacity, win->win_lens, v,
                             v_dtype, seq_lens, scale, win_ml, win_acc, scores_out, stream);
     }
-    if (err == 0) err = launch_merge(cb->plan, s, part_ml, part_acc, seq_lens, out, win_ml, win_acc, stream);
+    if (err == 0 && s.out == nullptr) err = launch_merge(cb->plan, s, part_ml, part_acc, seq_lens, out, win_ml, win_acc, stream);
     return err == 0 ? OCTOPUS_OK : OCTOPUS_EHIP;
 }
 
@@ -955,6 +971,7 @@ static int attn_decode_paged(const octopus_codebooks_t *cb, const void *q, int32
     Workspace w = make_workspace(cb->plan, s);
     if (many_rows) many_rows_at_128(cb, max_len, &s, &w);
     set_queries(&s, q, q_dtype, signs, with_qjl ? signs2 : nullptr, scale);
+    if (direct_output(s, out, win != nullptr, with_qjl)) s.out = out;   // (pages hold bf16 or quantised values)
     const size_t required = std::max(w.total, octopus_attn_decode_workspace(cb, n_seq, n_q_heads, n_kv_heads, n_q, max_len));
     if (workspace == nullptr || !aligned(workspace, 256) || workspace_bytes < required) return OCTOPUS_EWORKSPACE;
     char *base = static_cast<char *>(workspace);
@@ -986,7 +1003,7 @@ static int attn_decode_paged(const octopus_codebooks_t *cb, const void *q, int32
         err = launch_window(cb->plan, s, q, q_dtype, win->k_window, win->k_dtype, win->w_capacity, win->win_lens, v_pool,
                             OCTOPUS_DTYPE_BF16, seq_lens, scale, win_ml, win_acc, nullptr, stream, pt);
     }
-    if (err == 0) err = launch_merge(cb->plan, s, part_ml, part_acc, seq_lens, out, win_ml, win_acc, stream);
+    if (err == 0 && s.out == nullptr) err = launch_merge(cb->plan, s, part_ml, part_acc, seq_lens, out, win_ml, win_acc, stream);
     return err == 0 ? OCTOPUS_OK : OCTOPUS_EHIP;
 }
 

@@ -40,13 +40,14 @@ struct DecodeShape {
     int32_t max_items;      // what the partials' part of the workspace is sized for (row groups of at most 8)
     int32_t max_len;        // host-side bound of the sequence lengths
     int32_t item_waves;     // wavefronts of the workgroup, which share a segment (4; 8: matrix-core kernel over quantised values up to d = 128 where its LDS fits)
-    int32_t tiles_per_step; // 64-token tiles a wavefront takes per step (2 up to d = 128, else 1; 1: that kernel)
+    int32_t tiles_per_step; // 64-token tiles a wavefront takes per step (2 up to d = 128, else 1; 1: that kernel and decode_kernel_valu)
     int64_t t_capacity;
     // the call's queries, for the kernels that rotate the rows of their row group themselves (rotates_in_kernel)
     const void *q;
     const uint8_t *signs, *signs2;   // signs2: second rotation of the QJL residual, or NULL
     float scale;
     int32_t q_is_bf16;
+    float *out;             // the call's output where every pair is one workgroup's and no merge follows, or NULL (direct_output)
     int32_t pairs_fill;     // there may be as many (sequence, KV head, row group) pairs with tokens as workgroups (256)
 };
 

@@ -76,3 +76,44 @@ def test_short_call_gives_every_block_a_workgroup():
 ])
 def test_decode_division_with_short_pairs(n_kv, lens, dtype):
     run_decode_case(64, 3, len(lens), n_kv, n_kv, 1, lens, dtype, seed=len(lens), want_scores=False)
+
+
+# Calls of at most 256 (sequence, KV head, row group) pairs and one or two rounds of steps (1024 tokens; 512 at d = 256; over
+# fp32 values 256) write their output without a merge; one token or one pair more, and they don't.
+@pytest.mark.parametrize("d,bits,n_qh,n_kv,lens,dtype", [
+    (128, 3, 16, 2, [1024, 0, 1, 513, 512], "bf16"),
+    (128, 3, 16, 2, [1025, 0, 1, 513, 512], "bf16"),
+    (64, 4, 6, 2, [0, 1000, 129, 0], "bf16"),
+    (64, 2, 24, 1, [300, 0, 70], "bf16"),                  # three row groups
+    (256, 2.5, 4, 2, [512, 0, 257], "bf16"),
+    (128, 3, 8, 2, [256, 0, 65, 1], "fp32"),
+    (128, 3, 8, 2, [257, 0, 65, 1], "fp32"),
+    (64, 3, 8, 8, [int(x) for x in np.arange(32) * 13 % 200], "bf16"),
+    (64, 3, 8, 8, [int(x) for x in np.arange(33) * 13 % 200], "bf16"),
+    (64, 3, 2, 2, [0, 0, 0], "bf16"),
+])
+def test_decode_without_a_merge(d, bits, n_qh, n_kv, lens, dtype):
+    run_decode_case(d, bits, len(lens), n_qh, n_kv, 1, lens, dtype, seed=int(len(lens) + d), want_scores=False)
+
+
+def test_output_that_is_not_16_byte_aligned():
+    """The outputs of a short call into an aligned tensor and into one four bytes further: the same to rounding."""
+    from gpu_util import DEV
+    from paper_2605_21226_amd import binding
+    d, n_kv, rows, lens = 128, 2, 4, [300, 0, 77]
+    gen = torch.Generator().manual_seed(23)
+    cb = binding.octopus_build_codebooks(d, 3)
+    cache = torch.zeros(binding.octopus_cache_bytes(cb, 3, n_kv, 320), dtype=torch.uint8, device=DEV)
+    signs = torch.randint(0, 256, (n_kv, d // 8), generator=gen, dtype=torch.uint8).to(DEV)
+    binding.octopus_encode(cb, torch.randn((3, 300, n_kv, d), generator=gen).to(DEV, torch.bfloat16), signs, cache, 320)
+    v = torch.randn((3, n_kv, 320, d), generator=gen).to(DEV, torch.bfloat16)
+    q = torch.randn((3, 1, n_kv * rows, d), generator=gen).to(DEV, torch.bfloat16)
+    ws = torch.empty(binding.octopus_attn_decode_workspace(cb, 3, n_kv * rows, n_kv, 1, 300), dtype=torch.uint8, device=DEV)
+    n = 3 * n_kv * rows * d
+    outs = []
+    for shift in (0, 1):
+        out = torch.full((n + 4,), float("nan"), dtype=torch.float32, device=DEV)[shift:shift + n].view(3, 1, n_kv * rows, d)
+        binding.octopus_attn_decode(cb, q, signs, cache, 320, v, torch.tensor(lens, dtype=torch.int32, device=DEV), 300, 0.09, out, ws)
+        outs.append(out.cpu())
+    assert not outs[0][1].any() and torch.isfinite(outs[0]).all()
+    assert torch.allclose(outs[0], outs[1], rtol=1e-6, atol=1e-6)
