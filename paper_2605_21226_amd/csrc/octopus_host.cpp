@@ -600,7 +600,8 @@ static bool rotates_in_kernel(const octopus_plan_t &plan, bool many_rows, bool m
 // 15.4 / 11.6 us, 32 x 500 17.3 / 12.9 (values at 3 bits 18.6 / 14.7, residual 21.7 / 17.5), 32 x 250 over fp32 values 28.3 / 23.8, d = 256,
 // 32 x 250 19.4 / 14.4.  Two rounds: with more pairs than half the workgroups, 32 x 1000, 24.5 / 19.9 (residual 29.2 / 24.8); with fewer, where
 // merged every round is a workgroup's, 1 x 1000 15.6 / 14.7 (values at 3 bits 17.2 / 17.2, d = 256, 1 x 400 16.6 / 16.0), but with the
-// residual 19.9 / 20.6 and over fp32 values 26.3 / 30.0 (steps of two tiles then), whose steps are the longest.
+// residual 19.9 / 20.6, over fp32 values 26.3 / 30.0 (steps of two tiles then), plans without joint tables 24.1 / 25.3 (b = 4, 2 x 533,
+// 2 KV heads) and over quantised values with four wavefronts 26.2 / 28.3 (2 bits, eight rows, 1 x 423), whose steps are long.
 static bool direct_output(const DecodeShape &s, const float *out, bool with_window, bool long_steps) {
     const int64_t round = static_cast<int64_t>(s.item_waves) * s.tiles_per_step * OCTOPUS_TILE;
     const int64_t pairs = static_cast<int64_t>(s.n_seq) * s.n_kv_heads * s.n_row_groups;
@@ -688,7 +689,7 @@ static int attn_decode(const octopus_codebooks_t *cb, const void *q, int32_t q_d
     const bool vector_kernel = with_vq ? vq_mfma == 0 : v_dtype != OCTOPUS_DTYPE_BF16;
     if (vector_kernel) s.tiles_per_step = 1;   // (decode_kernel_valu; the workspace has room for either)
     set_queries(&s, q, q_dtype, signs, signs2, scale);
-    if (direct_output(s, out, win != nullptr, with_qjl || vector_kernel)) s.out = out;
+    if (direct_output(s, out, win != nullptr, with_qjl || vector_kernel || (with_vq && s.item_waves == 4) || !joint_plan(cb->plan))) s.out = out;
     // every entry point asks for the one documented size, whatever its own kernel needs (the static scratch
     // has been checked against the need of the kernels it serves)
     const size_t required = static_scratch_call ? w.total
@@ -971,7 +972,7 @@ static int attn_decode_paged(const octopus_codebooks_t *cb, const void *q, int32
     Workspace w = make_workspace(cb->plan, s);
     if (many_rows) many_rows_at_128(cb, max_len, &s, &w);
     set_queries(&s, q, q_dtype, signs, with_qjl ? signs2 : nullptr, scale);
-    if (direct_output(s, out, win != nullptr, with_qjl)) s.out = out;   // (pages hold bf16 or quantised values)
+    if (direct_output(s, out, win != nullptr, with_qjl || (v_bits != 0 && s.item_waves == 4) || !joint_plan(cb->plan))) s.out = out;   // (pages hold bf16 or quantised values)
     const size_t required = std::max(w.total, octopus_attn_decode_workspace(cb, n_seq, n_q_heads, n_kv_heads, n_q, max_len));
     if (workspace == nullptr || !aligned(workspace, 256) || workspace_bytes < required) return OCTOPUS_EWORKSPACE;
     char *base = static_cast<char *>(workspace);

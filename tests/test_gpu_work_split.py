@@ -83,7 +83,8 @@ def test_decode_division_with_short_pairs(n_kv, lens, dtype):
 @pytest.mark.parametrize("d,bits,n_qh,n_kv,lens,dtype", [
     (128, 3, 16, 2, [1024, 0, 1, 513, 512], "bf16"),
     (128, 3, 16, 2, [1025, 0, 1, 513, 512], "bf16"),
-    (64, 4, 6, 2, [0, 1000, 129, 0], "bf16"),
+    (64, 4, 6, 2, [0, 1000, 129, 0], "bf16"),              # (no joint tables: one round)
+    (64, 4, 6, 2, [0, 500, 129, 0], "bf16"),
     (64, 2, 24, 1, [300, 0, 70], "bf16"),                  # three row groups
     (256, 2.5, 4, 2, [512, 0, 257], "bf16"),
     (128, 3, 8, 2, [256, 0, 65, 1], "fp32"),
