@@ -258,8 +258,10 @@ __device__ __forceinline__ void build_tables(DecodeTables<P> &tb, int tid, int n
 // Fewer pairs than workgroups, ragged (1 / 64 of the longest and up), d = 128, b = 3, evenly / weighed: 24 sequences to 8000, 8 KV
 // heads of eight rows 104 / 56.5 us (over quantised values, four rows 95 / 50; fp32 values 174 / 116), 100 to 5000, 2 KV heads
 // 62 / 41, 16 to 30000, 4 KV heads 67 / 59.5, one of 60000 and eight of 300 58 / 39; 16 of half to full 12000 equal.  Pairs of equal
-// length stay evenly divided: weighed, 24 x 1024 28 / 24 but 28 x 1100 28.3 / 29.5, 16 x 1500 20.7 / 22, 24 x 4096 52 / 53.  Longer than
-// four shares, a cut pair costs little either way.  24 x 512 with blocks counted exactly: 26.4 / 19.3.
+// length stay evenly divided: weighed, 24 x 1024 28 / 24 but 28 x 1100 28.3 / 29.5, 16 x 1500 20.7 / 22, 24 x 4096 52 / 53; so do
+// pairs longer than a share, and calls of shares under three rounds, which whole blocks round up too much (evenly / weighed, 8 sequences
+// to 1326, 24 KV heads, d = 64 18.8 / 20.5; 2 to 8179 over 3-bit values, eight rows 40.5 / 49).  24 x 512 with blocks counted exactly:
+// 26.4 / 19.3.
 // Calls with every length divided evenly / as here, d = 128, b = 3, ragged (lengths of 1 / 64 of the longest and up): 32
 // sequences to 372 tokens, one KV head of eight rows 43.2 / 17.7 us, 64 to 500, 8 KV heads of four rows 50.5 / 25.8, 256 to 500
 // 156 / 84, 256 to 4000 358 / 239, the same over quantised values 371 / 225, 40 to 16000 162 / 135 (kSegmentTiles half or twice
@@ -306,24 +308,32 @@ struct Division {
     int kind;
     int waves_log2, tps;
 
-    // Sequences whose pairs are under three quarters of the mean pair and shorter than four even shares (st: the steps of this
-    // lane's sequence, sum and total: of all sequences and pairs, present: sequences with tokens).
-    static __device__ __forceinline__ uint64_t short_pairs(uint32_t st, uint64_t sum, uint64_t total, uint32_t present) {
-        const float shares = static_cast<float>(total) * (4.0f / kDecodeWorkgroups), mean = 0.75f * static_cast<float>(sum);
+    // Sequences whose pairs are under three quarters of the mean pair and shorter than an even share, where a share is at least
+    // three rounds of steps (st: the steps of this lane's sequence, sum and total: of all sequences and pairs, present: sequences
+    // with tokens).
+    static __device__ __forceinline__ uint64_t short_pairs(uint32_t st, uint64_t sum, uint64_t total, uint32_t present, int waves_log2) {
+        if (total < static_cast<uint64_t>(3 * kDecodeWorkgroups) << waves_log2) return 0u;
+        const float share = static_cast<float>(total) * (1.0f / kDecodeWorkgroups), mean = 0.75f * static_cast<float>(sum);
         const float x = static_cast<float>(st);
-        return __ballot(st > 0u && x < shares && x * static_cast<float>(present) < mean);
+        return __ballot(st > 0u && x < share && x * static_cast<float>(present) < mean);
     }
     static __device__ __forceinline__ uint32_t with_tokens(uint32_t st) { return __popcll(__ballot(st > 0u)); }
     // Most calls are known to be divided evenly by their steps alone (and code that runs costs its fetch here).
     static __device__ __forceinline__ bool surely_even(const DecodeShape &shp, uint32_t st, uint64_t sum, uint64_t total, int waves_log2) {
         return shp.pairs_fill == 0 && shp.n_seq <= kWave && total > static_cast<uint64_t>(kDecodeWorkgroups) << waves_log2 &&
-               short_pairs(st, sum, total, with_tokens(st)) == 0u;
+               short_pairs(st, sum, total, with_tokens(st), waves_log2) == 0u;
     }
     // The kind, from the steps of all sequences and pairs; steps_at(s0): the steps of sequence s0 + lane (0: none).
     template <class Steps>
     __device__ __forceinline__ void set(const DecodeShape &shp, uint64_t sum, const Steps &steps_at) {
         const uint64_t G = static_cast<uint64_t>(shp.n_kv_heads) * shp.n_row_groups, total = sum * G;
         constexpr uint64_t kWgs = kDecodeWorkgroups;
+        if (shp.n_seq == 1) {   // (as below, where a lone sequence is never short; without the scans)
+            const uint32_t n = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(steps_at(0))));
+            const uint64_t blocks = static_cast<uint64_t>((n + (1u << waves_log2) - 1u) >> waves_log2) * G;
+            kind = blocks <= kWgs ? kBlockEach : (G >= kWgs ? kPairsWeighed : kDivideEvenly);
+            return;
+        }
         uint32_t present = 0;
         for (int s0 = 0; s0 < shp.n_seq; s0 += kWave) present += with_tokens(steps_at(s0));
         const uint64_t pairs = present * G;
@@ -339,7 +349,7 @@ struct Division {
         kind = pairs >= kWgs ? kPairsWeighed : kDivideEvenly;
         if (pairs < kWgs)
             for (int s0 = 0; s0 < shp.n_seq; s0 += kWave)
-                if (short_pairs(steps_at(s0), sum, total, present) != 0u) kind = kPairsWeighed;
+                if (short_pairs(steps_at(s0), sum, total, present, waves_log2) != 0u) kind = kPairsWeighed;
     }
     __device__ __forceinline__ uint32_t fixed() const {
         return kind == kPairsWeighed ? static_cast<uint32_t>((waves_log2 == 3 ? 2 * kSegmentTiles : kSegmentTiles) / tps) : 0u;

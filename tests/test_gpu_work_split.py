@@ -73,6 +73,9 @@ def test_short_call_gives_every_block_a_workgroup():
     (2, [100] * 40 + [60000] + [64] * 25),                # ... and more than 64 sequences
     (8, [512] * 24),                                      # whole blocks, fewer than workgroups, the bound by rests past them
     (3, [30000, 14500, 1]),
+    (4, [60000, 37400, 832]),                             # shares of three rounds (d = 64, bf16: 512 tokens each)
+    (4, [60000, 37400, 768]),                             # ... and just under
+    (5, [70001]),
 ])
 def test_decode_division_with_short_pairs(n_kv, lens, dtype):
     run_decode_case(64, 3, len(lens), n_kv, n_kv, 1, lens, dtype, seed=len(lens), want_scores=False)
