@@ -107,7 +107,7 @@ struct EncodeSmem {
     float c_xi[P::NCLASS][NX];
     float c_rho[P::NCLASS][NR];
     float bnd_xi[P::NCLASS][NX];           // boundaries, +inf padded
-    float bnd_rho[P::NCLASS][NR];
+    __attribute__((aligned(16))) float bnd_rho[P::NCLASS][NR];   // (read four at a time where there are many)
     float sumsq[kWave];                    // squared norm of each key of the tile, then its scale factor 1 / (gamma sqrt(d))
     float res_sq[QJL ? encode_waves<P>() : 1][QJL ? kWave : 1];   // QJL side-car: squared residual norm, partial per wavefront
 };
@@ -488,22 +488,29 @@ __device__ __forceinline__ void encode_triplet_any(float x, float y, float z, co
     *nrm_index = static_cast<uint32_t>(r);
 }
 
-// Consecutive fields of one stream of a key's record, gathered in a register and OR-ed into LDS a word at a time (the first and
-// the last word of a wavefront's share are also its neighbours').  Bit positions are wave-uniform.
+// Consecutive fields of one stream of a key's record.  GATHER: gathered in a register and OR-ed into LDS a word at a time (the
+// first and the last word of a wavefront's share are also its neighbours'); else each is OR-ed into LDS as it comes.  Bit
+// positions are wave-uniform.
+template <bool GATHER>
 struct FieldWriter {
     uint32_t acc = 0u;
     int bit;   // position of the next field, from the start of the record
     __device__ __forceinline__ void put(uint32_t (*rec)[kWave], int key, int nbits, uint32_t v) {
         const int sh = bit & 31;
-        acc |= v << sh;
-        if (sh + nbits >= 32) {
-            atomicOr(&rec[bit >> 5][key], acc);
-            acc = sh + nbits > 32 ? v >> (32 - sh) : 0u;
+        if constexpr (GATHER) {
+            acc |= v << sh;
+            if (sh + nbits >= 32) {
+                atomicOr(&rec[bit >> 5][key], acc);
+                acc = sh + nbits > 32 ? v >> (32 - sh) : 0u;
+            }
+        } else {
+            atomicOr(&rec[bit >> 5][key], v << sh);
+            if (sh + nbits > 32) atomicOr(&rec[(bit >> 5) + 1][key], v >> (32 - sh));
         }
         bit += nbits;
     }
     __device__ __forceinline__ void finish(uint32_t (*rec)[kWave], int key) const {
-        if (bit & 31) atomicOr(&rec[bit >> 5][key], acc);
+        if (GATHER && (bit & 31)) atomicOr(&rec[bit >> 5][key], acc);
     }
 };
 
@@ -733,7 +740,11 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
             const float *thr1 = THR1_REG ? thr1_reg : sm.bnd_rho[P::NCLASS - 1];
             const float norm = sm.sumsq[lane];
             const bool valid = tile * kWave + lane >= tok_lo && tile * kWave + lane < tok_hi;
-            FieldWriter dir, nrm;
+            // (gathered fields cost registers: with nine candidates those of two classes up to d = 128 spill, and of 32 norm levels and
+            // more.  16 Ki keys x 8 KV heads over other codebooks, gathered / as they come: d = 128 at 1.5 bits, fp32 keys 73.9 / 64.2 us,
+            // at 2.5 bits 76.3 / 72.0, 2 + 6 bits 122 / 94 (bf16 keys); the other way round at 3 bits 61.8 / 64.4, at d = 256 89.1 / 93.0)
+            constexpr bool GATHER = CORNERS || ((P::NCLASS == 1 || D > 128) && P::BN0 < 5);
+            FieldWriter<GATHER> dir, nrm;
             const int i_first = wave * CHUNK;
             dir.bit = (P::NCLASS == 1 || i_first < P::NT0) ? P::DIR0_BIT + i_first * 2 * P::BD0 : P::DIR1_BIT + (i_first - P::NT0) * 2 * P::BD1;
             nrm.bit = (P::NCLASS == 1 || i_first < P::NT0) ? P::NRM0_BIT + i_first * P::BN0 : P::NRM1_BIT + (i_first - P::NT0) * P::BN1;
@@ -772,8 +783,8 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
                         if (i == P::NT0 && i > i_first) {   // the second class has its own streams
                             dir.finish(sm.rec, lane);
                             nrm.finish(sm.rec, lane);
-                            dir = FieldWriter{0u, P::DIR1_BIT};
-                            nrm = FieldWriter{0u, P::NRM1_BIT};
+                            dir = FieldWriter<GATHER>{0u, P::DIR1_BIT};
+                            nrm = FieldWriter<GATHER>{0u, P::NRM1_BIT};
                         }
                         dir.put(sm.rec, lane, 2 * P::BD1, dir_field);
                         nrm.put(sm.rec, lane, P::BN1, nrm_index);

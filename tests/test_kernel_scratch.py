@@ -44,3 +44,12 @@ def test_kernels_without_residual_do_not_spill(library, d):
     joint = {k: v for k, v in _decode(library, d, False, False).items() if all(2 * k[0][c] + k[0][c + 1] <= 10 for c in (0, 2))}
     assert len(joint) >= 5 * 4 * 2
     assert {k: v for k, v in joint.items() if v} == {}
+
+
+def test_encoders_do_not_spill(library):
+    """encode_kernel with four and with nine candidates, every rounding variant and pair, and the append kernel.  The pair of 3 + 5 bits
+    over fp32 keys keeps three words of a lane outside its loops."""
+    found = {name: k[".private_segment_fixed_size"] for name, k in library.items() if re.search(r"1[37]encode_(few_)?kernel", name)}
+    assert sum("encode_few_kernel" in n for n in found) == 18 * 2 and len(found) == 36 + 200
+    words = re.compile(r"13encode_kernelINS_5PlanTILi128ELi3ELi5ELi0ELi0EEELb0ELb0ELb0ELb0E")
+    assert {n: v for n, v in found.items() if v > (12 if words.search(n) else 0)} == {}
