@@ -90,6 +90,7 @@ __global__ __launch_bounds__(kWave) void window_kernel(DecodeShape shp, const vo
         auto request_values = [&](int jb) __attribute__((always_inline)) {   // (rows past the chunk's end: its last one)
 #pragma unroll
             for (int u = 0; u < VB; ++u) {
+                if (u % 8 == 0 && jb + u >= nj) break;   // (uniform)
                 const int j = min(jb + u, nj - 1);
                 const int64_t row = (j < split ? first : second) + j;
                 if constexpr (v_is_bf16 && CPT == 1) {
@@ -139,14 +140,23 @@ __global__ __launch_bounds__(kWave) void window_kernel(DecodeShape shp, const vo
         for (int c = 0; c < CPT; ++c) acc[c] *= alpha;
         for (int jb = 0; jb < nj; jb += VB) {
             if (jb > 0) request_values(jb);
-#pragma unroll
-            for (int u = 0; u < VB; ++u) {
-                const float wj = jb + u < nj ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p), jb + u)) : 0.0f;
+            auto add = [&](int u) __attribute__((always_inline)) {
+                const float wj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p), jb + u));
 #pragma unroll
                 for (int c = 0; c < CPT; ++c) {
                     const uint32_t word = x[u][v_is_bf16 ? c / 2 : c];
                     const float val = !v_is_bf16 ? __uint_as_float(word) : ((c & 1) ? bf16_hi(word) : bf16_lo(word));
                     acc[c] = fmaf(wj, val, acc[c]);
+                }
+            };
+            if (jb + VB <= nj) {
+#pragma unroll
+                for (int u = 0; u < VB; ++u) add(u);
+            } else {   // (rows past the end stay out: at weight zero an infinity in the last row would count again, as 0 * inf)
+#pragma unroll
+                for (int u = 0; u < VB - 1; ++u) {
+                    if (jb + u >= nj) break;
+                    add(u);
                 }
             }
         }

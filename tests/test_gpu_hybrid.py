@@ -117,3 +117,30 @@ def test_hybrid_window_clipped_at_capacity():
                                        vals[0, 0, :64].astype(np.float64), 0.1)
     for j in range(2):
         check_out(out.cpu().numpy()[0, 0, j], ref_o[j])
+
+
+@pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "bf16"), (256, "bf16"), (128, "fp32")])
+@pytest.mark.parametrize("w", [1, 8, 16, 24, 33, 64, 72])
+def test_infinity_in_the_last_value_row_of_a_window(d, dtype, w):
+    """Its channel is infinite (a weight of at least exp(-60) times infinity), the others are what they are without it: rows that
+    a batch of value rows has too many do not count."""
+    gen = torch.Generator().manual_seed(w)
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    cb = binding.octopus_build_codebooks(d, 3)
+    signs = torch.randint(0, 256, (1, d // 8), generator=gen, dtype=torch.uint8).to(DEV)
+    cache = torch.zeros(binding.octopus_cache_bytes(cb, 1, 1, 256), dtype=torch.uint8, device=DEV)
+    binding.octopus_encode(cb, torch.randn((1, 100, 1, d), generator=gen).to(DEV, t), signs, cache, 256)
+    v = torch.randn((1, 1, 256, d), generator=gen).to(DEV, t)
+    k_win = torch.randn((1, 1, 80, d), generator=gen).to(DEV, t)
+    q = torch.randn((1, 1, 2, d), generator=gen).to(DEV, t)
+    lens, win = (torch.tensor([n], dtype=torch.int32, device=DEV) for n in (100, w))
+    ws = torch.empty(binding.octopus_attn_decode_workspace(cb, 1, 2, 1, 1, 100), dtype=torch.uint8, device=DEV)
+    outs = []
+    for x in (1.0, float("inf")):
+        v[0, 0, 100 + w - 1, 5] = x
+        out = torch.zeros((1, 1, 2, d), device=DEV)
+        binding.octopus_attn_decode_hybrid(cb, q, signs, cache, 256, v, lens, 100, k_win, win, 0.1, out, ws)
+        outs.append(out.cpu().numpy()[0, 0])
+    assert np.all(np.isposinf(outs[1][:, 5])) and np.all(np.isfinite(outs[0]))
+    others = np.arange(d) != 5
+    assert np.array_equal(outs[0][:, others], outs[1][:, others])
