@@ -246,10 +246,13 @@ __device__ __forceinline__ float row_sum(float v) {
     static_assert(LPR == 8 || LPR == 16 || LPR == 32, "lanes per key row");
     v += lane_permute<0xB1>(v);    // quad permute [1, 0, 3, 2]
     v += lane_permute<0x4E>(v);    // quad permute [2, 3, 0, 1]
-    v += lane_permute<0x141>(v);   // mirror within each 8 lanes
-    if constexpr (LPR >= 16) v += lane_permute<0x140>(v);   // mirror within each 16 lanes
-    if constexpr (LPR >= 32) v += __shfl_xor(v, 16, kWave);
-    return v;
+    if constexpr (LPR >= 16) v += lane_permute<0x141>(v);   // mirror within each 8 lanes
+    if constexpr (LPR >= 32) v += lane_permute<0x140>(v);   // mirror within each 16 lanes
+    // (the last addition in the order written, not as one instruction with the permute, which takes it
+    // the other way round: of several NaNs in a key the same one is its norm in every kernel)
+    float other = LPR == 8 ? lane_permute<0x141>(v) : (LPR == 16 ? lane_permute<0x140>(v) : __shfl_xor(v, 16, kWave));
+    asm("" : "+v"(other));
+    return v + other;
 }
 
 template <int R>
@@ -665,6 +668,7 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
         for (int e = kWave + tid; e < P::NWORDS * kWave; e += NT) sm.rec[e / kWave][e % kWave] = 0u;
 
         // E1-E2: squared norm, sign flip
+        [[maybe_unused]] float rows_sum = 0.0f;
 #pragma unroll
         for (int pass = 0; pass < NPASS; ++pass) {
             const int key = pass * RPP + tid / LPR;
@@ -690,6 +694,29 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
 #pragma unroll
             for (int e = 0; e < 8; ++e) sm.u[col + e][key] = x[e];
             if (tid % LPR == 0) sm.sumsq[key] = ss;
+            if constexpr (BF16) rows_sum += ss;
+        }
+        // Rows that are not a number: their sum again, of the values before their signs were flipped, as a NaN's own sign is stored
+        // (all lanes of a row are here).
+        if constexpr (BF16) {
+            if (__builtin_expect((__float_as_uint(rows_sum) & 0x7fffffffu) > 0x7f800000u, 0)) {
+#pragma unroll 1
+                for (int pass = 0; pass < NPASS; ++pass) {
+                    uint4 k = raw[0][0];
+#pragma unroll
+                    for (int other = 1; other < NPASS; ++other)
+                        if (pass == other) k = raw[other][0];
+                    const uint32_t w[4] = {k.x, k.y, k.z, k.w};
+                    float ss = 0.0f;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float v = e & 1 ? bf16_hi(w[e / 2]) : bf16_lo(w[e / 2]);
+                        ss = fmaf(v, v, ss);
+                    }
+                    ss = row_sum<LPR>(ss);
+                    if (tid % LPR == 0) sm.sumsq[pass * RPP + tid / LPR] = ss;
+                }
+            }
         }
         if (tg + 1 < tiles_per_group) fetch_tile(tile + 1);
         __syncthreads();
@@ -703,8 +730,7 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
             // scale factor replaces the sum of squares in LDS
             if (wave == NWV - 1) {
                 const float gamma = sqrtf(sm.sumsq[lane]);
-                // (the sign of a NaN among bf16 keys may have been flipped)
-                sm.rec[0][lane] = __float_as_uint(gamma) & (BF16 ? 0x7fffffffu : 0xffffffffu);
+                sm.rec[0][lane] = __float_as_uint(gamma);
                 sm.sumsq[lane] = (1.0f / fmaxf(gamma, kEps)) * inv_sqrt_dim<D>();
             }
             for (int lo = wave; lo < 8; lo += NWV) {
@@ -1051,7 +1077,7 @@ __global__ __launch_bounds__(kWave) void encode_few_kernel(DeviceBooks books, co
         atomicOr(&rec[nrm_bit >> 5], nrm << (nrm_bit & 31));
         if ((nrm_bit & 31) + nrm_bits > 32) atomicOr(&rec[(nrm_bit >> 5) + 1], nrm >> (32 - (nrm_bit & 31)));
     }
-    if (lane == 0) rec[0] = __float_as_uint(gamma) & (BF16 ? 0x7fffffffu : 0xffffffffu);   // (no field reaches into word 0)
+    if (lane == 0) rec[0] = __float_as_uint(gamma);   // (no field reaches into word 0)
     __syncthreads();
     if (lane < P::GRANULES) {
         uint4 *dst = cache + (static_cast<int64_t>(seq) * n_kv_heads + kvh) * (t_capacity * P::GRANULES) + tile * (P::GRANULES * kWave);

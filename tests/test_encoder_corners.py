@@ -172,3 +172,43 @@ def test_appended_keys_have_the_records_of_a_prefill(d, bits, dtype):
     binding.octopus_encode(cb, keys[:, :2], signs, caches[1], cap, torch.tensor([cap], dtype=torch.int32, device="cuda"))
     torch.cuda.synchronize()
     assert torch.equal(caches[0], caches[1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("d,bits", [(64, 3), (128, 1.5), (128, 4), (256, 2.5)])
+def test_norm_of_a_key_with_nans(d, bits, dtype):
+    """A key with one NaN: its norm is that NaN, sign and payload, quieted, from the tile kernel with four and with nine candidates
+    and from the append kernel.  Several NaNs: the same one everywhere."""
+    n, n_kv = 300, 4
+    gen = torch.Generator().manual_seed(29)
+    keys = torch.randn((1, n, n_kv, d), generator=gen).to(dtype)
+    if dtype == torch.bfloat16:
+        nans, raw, quiet = [0x7FC0, 0xFFC0, 0x7FC5, 0xFFC3, 0x7F81, 0xFF82], keys.view(torch.int16), lambda x: (x | 0x40) << 16
+    else:
+        nans, raw, quiet = [0x7FC00000, 0xFFC00000, 0x7FC12345, 0xFFC54321, 0x7F800001, 0xFF812345], keys.view(torch.int32), lambda x: x | 0x400000
+    top = 1 << (15 if dtype == torch.bfloat16 else 31)
+    expected = np.zeros((n_kv, n), dtype=np.uint32)
+    for t in range(n):
+        for h in range(n_kv):
+            for j in range(1 if t % 2 else 3):
+                x = nans[(t // 2 + h + j) % 6]
+                raw[0, t, h, (13 * t + 37 * j + 5 * h) % d] = x - 2 * top if x >= top else x
+                expected[h, t] = quiet(x)
+    keys = keys.cuda()
+    signs = torch.randint(0, 256, (n_kv, d // 8), generator=gen, dtype=torch.uint8).cuda()
+    words = []
+    for nine, single in ((False, False), (True, False), (False, True)):
+        cb = binding.octopus_build_codebooks(d, bits)
+        if nine:
+            for c in range(cb.plan.n_class):
+                cb.c_rho[c][(1 << cb.plan.b_nrm[c]) - 1] = 1.0
+        cache = torch.zeros(binding.octopus_cache_bytes(cb, 1, n_kv, 320), dtype=torch.uint8, device="cuda")
+        for t in range(n if single else 1):
+            at = torch.tensor([t], dtype=torch.int32, device="cuda")
+            binding.octopus_encode(cb, keys[:, t:t + 1] if single else keys, signs, cache, 320, at)
+        torch.cuda.synchronize()
+        rec, _ = layout.cache_to_records(cache.cpu().numpy(), 1, n_kv, 320, cb.plan.granules, cb.plan.record_bytes)
+        words.append(np.ascontiguousarray(rec[0, :, :n, :4]).view(np.uint32)[..., 0])
+        assert np.array_equal(words[-1][:, 1::2], expected[:, 1::2])
+        assert np.array_equal(words[-1], words[0])

@@ -48,8 +48,10 @@ def test_kernels_without_residual_do_not_spill(library, d):
 
 def test_encoders_do_not_spill(library):
     """encode_kernel with four and with nine candidates, every rounding variant and pair, and the append kernel.  The pair of 3 + 5 bits
-    over fp32 keys keeps three words of a lane outside its loops."""
+    over fp32 keys keeps three words of a lane outside its loops, 1.5 bits at d = 256 with the residual and nine candidates two (97.1 us
+    of 16 Ki keys x 8 KV heads without them, 97.4 with)."""
     found = {name: k[".private_segment_fixed_size"] for name, k in library.items() if re.search(r"1[37]encode_(few_)?kernel", name)}
     assert sum("encode_few_kernel" in n for n in found) == 18 * 2 and len(found) == 36 + 200
-    words = re.compile(r"13encode_kernelINS_5PlanTILi128ELi3ELi5ELi0ELi0EEELb0ELb0ELb0ELb0E")
-    assert {n: v for n, v in found.items() if v > (12 if words.search(n) else 0)} == {}
+    words = {"13encode_kernelINS_5PlanTILi128ELi3ELi5ELi0ELi0EEELb0ELb0ELb0ELb0E": 12,
+             "13encode_kernelINS_5PlanTILi256ELi3ELi1ELi1ELi1EEELb1ELb1ELb0ELb0E": 8}
+    assert {n: v for n, v in found.items() if v > max([b for part, b in words.items() if part in n], default=0)} == {}
