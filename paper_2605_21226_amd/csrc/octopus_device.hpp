@@ -154,42 +154,35 @@ __device__ __forceinline__ float wave_max(float v) {
 // The same for several values at once, one instruction per stage and value: the permute is part of the maximum (lanes whose
 // source does not exist or whose row is masked off keep what they have), where the compiler makes a move, a
 // canonicalisation and a maximum of it (18 of 24 instructions per value; 16 x 32768 tokens over 3-bit values, four / eight rows 148 ->
-// 142.6 / 240 -> 216 us, eight rows of 4-bit keys at d = 64 53.4 -> 51).  A permute reads a register two instructions after
-// it was written at the earliest, which the compiler does not see to here: four values are each other's distance, fewer take
-// waits, and the waits before and after are tied to the values (else they are moved away from them).
-template <int N>
-__device__ __forceinline__ void two_waits(float (&x)[N]) {
-    static_assert(N == 1 || N == 2 || N == 4 || N == 8, "values at once");
-    if constexpr (N == 1) asm volatile("s_nop 1" : "+v"(x[0]));
-    else if constexpr (N == 2) asm volatile("s_nop 1" : "+v"(x[0]), "+v"(x[1]));
-    else if constexpr (N == 4) asm volatile("s_nop 1" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
-    else asm volatile("s_nop 1" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]));
-}
-template <int STAGE, int N>
-__device__ __forceinline__ void max_stage(float (&x)[N]) {
-    if constexpr (STAGE == 0 || N < 4) two_waits(x);
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        if constexpr (STAGE == 0) asm volatile("v_max_f32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf" : "+v"(x[i]));
-        else if constexpr (STAGE == 1) asm volatile("v_max_f32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf" : "+v"(x[i]));
-        else if constexpr (STAGE == 2) asm volatile("v_max_f32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf" : "+v"(x[i]));
-        else if constexpr (STAGE == 3) asm volatile("v_max_f32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf" : "+v"(x[i]));
-        else if constexpr (STAGE == 4) asm volatile("v_max_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf" : "+v"(x[i]));
-        else asm volatile("v_max_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf" : "+v"(x[i]));
-    }
-}
+// 142.6 / 240 -> 216 us, eight rows of 4-bit keys at d = 64 53.4 -> 51).  A permute reads a register two wait states after
+// it was written at the earliest, and the compiler puts no waits around inline assembly: all stages are ONE statement, so that
+// nothing (a copy, a reload) can come between them.  Four values are each other's distance, fewer take waits; the waits at
+// the ends are for what comes before and for the lane reads after (tests/test_wave_max_waits.py reads them in the built library).
+#define OCTOPUS_MAX_OF(I, CTRL) "v_max_f32_dpp %" #I ", %" #I ", %" #I " " CTRL "\n"
+#define OCTOPUS_MAX_OF_1(CTRL) OCTOPUS_MAX_OF(0, CTRL) "s_nop 1\n"
+#define OCTOPUS_MAX_OF_2(CTRL) OCTOPUS_MAX_OF(0, CTRL) OCTOPUS_MAX_OF(1, CTRL) "s_nop 0\n"
+#define OCTOPUS_MAX_OF_4(CTRL) OCTOPUS_MAX_OF(0, CTRL) OCTOPUS_MAX_OF(1, CTRL) OCTOPUS_MAX_OF(2, CTRL) OCTOPUS_MAX_OF(3, CTRL)
+#define OCTOPUS_MAX_OF_8(CTRL) OCTOPUS_MAX_OF_4(CTRL) OCTOPUS_MAX_OF(4, CTRL) OCTOPUS_MAX_OF(5, CTRL) OCTOPUS_MAX_OF(6, CTRL) OCTOPUS_MAX_OF(7, CTRL)
+#define OCTOPUS_MAX_STAGES(STAGE)                                                                                \
+    "s_nop 1\n" STAGE("row_shr:1 row_mask:0xf bank_mask:0xf") STAGE("row_shr:2 row_mask:0xf bank_mask:0xf")      \
+    STAGE("row_shr:4 row_mask:0xf bank_mask:0xf") STAGE("row_shr:8 row_mask:0xf bank_mask:0xf")                  \
+    STAGE("row_bcast:15 row_mask:0xa bank_mask:0xf") STAGE("row_bcast:31 row_mask:0xc bank_mask:0xf") "s_nop 1"
 template <int N>
 __device__ __forceinline__ void wave_max_of(float (&x)[N]) {
-    max_stage<0>(x);
-    max_stage<1>(x);
-    max_stage<2>(x);
-    max_stage<3>(x);
-    max_stage<4>(x);
-    max_stage<5>(x);
-    two_waits(x);
+    static_assert(N == 1 || N == 2 || N == 4 || N == 8, "values at once");
+    if constexpr (N == 1) asm volatile(OCTOPUS_MAX_STAGES(OCTOPUS_MAX_OF_1) : "+v"(x[0]));
+    else if constexpr (N == 2) asm volatile(OCTOPUS_MAX_STAGES(OCTOPUS_MAX_OF_2) : "+v"(x[0]), "+v"(x[1]));
+    else if constexpr (N == 4) asm volatile(OCTOPUS_MAX_STAGES(OCTOPUS_MAX_OF_4) : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+    else asm volatile(OCTOPUS_MAX_STAGES(OCTOPUS_MAX_OF_8) : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]));
 #pragma unroll
     for (int i = 0; i < N; ++i) x[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x[i]), 63));
 }
+#undef OCTOPUS_MAX_OF
+#undef OCTOPUS_MAX_OF_1
+#undef OCTOPUS_MAX_OF_2
+#undef OCTOPUS_MAX_OF_4
+#undef OCTOPUS_MAX_OF_8
+#undef OCTOPUS_MAX_STAGES
 
 __device__ __forceinline__ float wave_sum(float v) {
     auto take = [](float x, auto ctrl, auto rows) __attribute__((always_inline)) {   // 0 where no lane is read
