@@ -519,12 +519,13 @@ __device__ __forceinline__ void merge_waves(const DecodeShape &shp, const WaveWo
             a.x = fmaf(f, x.x, a.x); a.y = fmaf(f, x.y, a.y); a.z = fmaf(f, x.z, a.z); a.w = fmaf(f, x.w, a.w);
             l = fmaf(f, ml[w * ml_stride + 2 * r + 1], l);
         }
-        if (__builtin_expect(shp.out != nullptr, 0)) {   // all of the row: the output as well
+        if (__builtin_expect(shp.out != nullptr, 0)) {   // all of the row: the output, and no partial, which nothing would read
             const int row = ww.grp * RG + r, qi = row / shp.heads_per_kv, head = ww.kvh * shp.heads_per_kv + row % shp.heads_per_kv;
             const int64_t orow = (static_cast<int64_t>(ww.seq) * shp.n_q + qi) * shp.n_q_heads + head;
             const bool any = l > 0.0f;
             reinterpret_cast<float4 *>(shp.out + orow * D)[e % (D / 4)] =
                 make_float4(any ? a.x / l : 0.0f, any ? a.y / l : 0.0f, any ? a.z / l : 0.0f, any ? a.w / l : 0.0f);
+            continue;
         }
         reinterpret_cast<float4 *>(part_acc + ww.slot * (RG * D))[e] = a;
         if (e % (D / 4) == 0) {

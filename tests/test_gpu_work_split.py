@@ -45,7 +45,7 @@ def test_decode_division_by_blocks_and_past_it(n_seq, extra):
 
 def test_short_call_gives_every_block_a_workgroup():
     """32 short sequences, one KV head of eight rows: the partial results lie at slots (workgroup + pair), so the slots written
-    say which workgroups took part."""
+    say which workgroups took part.  (Into an output that is not 16-byte aligned: else the kernel writes it without partial results.)"""
     from gpu_util import DEV
     from paper_2605_21226_amd import binding
     d, rows, lens = 128, 8, [int(x) for x in 5 + np.arange(32) * 61 % 367]
@@ -54,7 +54,7 @@ def test_short_call_gives_every_block_a_workgroup():
     cache = torch.zeros(binding.octopus_cache_bytes(cb, 32, 1, 384), dtype=torch.uint8, device=DEV)
     v = torch.zeros((32, 1, 384, d), dtype=torch.bfloat16, device=DEV)
     q = torch.zeros((32, 1, rows, d), dtype=torch.bfloat16, device=DEV)
-    out = torch.zeros((32, 1, rows, d), dtype=torch.float32, device=DEV)
+    out = torch.zeros(32 * rows * d + 4, dtype=torch.float32, device=DEV)[1:-3].view(32, 1, rows, d)
     signs = torch.zeros(d // 8, dtype=torch.uint8, device=DEV)
     ws = torch.full((binding.octopus_attn_decode_workspace(cb, 32, rows, 1, 1, 384),), 255, dtype=torch.uint8, device=DEV)
     binding.octopus_attn_decode(cb, q, signs, cache, 384, v, torch.tensor(lens, dtype=torch.int32, device=DEV), 384, 0.1, out, ws)
@@ -116,8 +116,32 @@ def test_output_that_is_not_16_byte_aligned():
     n = 3 * n_kv * rows * d
     outs = []
     for shift in (0, 1):
+        ws.fill_(255)
         out = torch.full((n + 4,), float("nan"), dtype=torch.float32, device=DEV)[shift:shift + n].view(3, 1, n_kv * rows, d)
         binding.octopus_attn_decode(cb, q, signs, cache, 320, v, torch.tensor(lens, dtype=torch.int32, device=DEV), 300, 0.09, out, ws)
         outs.append(out.cpu())
+        assert bool((ws == 255).all()) == (shift == 0)   # no partial results where nothing reads them
     assert not outs[0][1].any() and torch.isfinite(outs[0]).all()
     assert torch.allclose(outs[0], outs[1], rtol=1e-6, atol=1e-6)
+
+
+# Many sequences, some of them empty, more than one per lane: up to 256 pairs by the decode kernel alone, 258 and 260 through the merge.
+RAGGED = [int(x) for x in (40 + np.arange(128) * 29 % 171) * (np.arange(128) % 5 > 0)]
+
+
+@pytest.mark.parametrize("n_seq,n_kv", [(128, 2), (100, 2), (65, 4)])
+def test_many_sequences_with_and_without_a_merge(n_seq, n_kv):
+    run_decode_case(64, 3, n_seq, n_kv, n_kv, 1, RAGGED[:n_seq], "bf16", seed=31 + n_seq, want_scores=False)
+
+
+@pytest.mark.parametrize("n_seq,n_kv", [(90, 2), (43, 6)])
+def test_many_sequences_over_pages_values_and_the_residual(n_seq, n_kv):
+    from test_gpu_paged import run_paged_decode_case, run_paged_qjl_decode_case, run_paged_vq_decode_case
+    from test_gpu_qjl import run_decode_qjl_case
+    from test_gpu_values import run_decode_vq_case
+    lens, n_qh = RAGGED[:n_seq], 4 * n_kv
+    run_paged_decode_case(64, 3, n_seq, n_qh, n_kv, 1, lens, seed=37)
+    run_decode_vq_case(64, 3, 3, 32, n_seq, n_qh, n_kv, 1, lens, seed=38, want_scores=False)
+    run_paged_vq_decode_case(64, 2, 2, 16, n_seq, n_qh, n_kv, 1, lens, seed=39)
+    run_decode_qjl_case(64, 3, n_seq, n_qh, n_kv, 1, lens, seed=40, want_scores=False)
+    run_paged_qjl_decode_case(64, 2, n_seq, n_qh, n_kv, 1, lens, seed=41)

@@ -24,8 +24,8 @@ def shapes(tmp_path_factory):
                          capture_output=True, text=True, timeout=600)
     assert res.returncode == 0, res.stderr[-4000:]
 
-    def ask(paged, d, bits, n_seq, n_qh, n_kv, n_q, max_len):
-        args = [str(x) for x in (int(paged), d, bits, n_seq, n_qh, n_kv, n_q, max_len)]
+    def ask(kind, d, bits, n_seq, n_qh, n_kv, n_q, max_len):
+        args = [str(x) for x in (int(kind), d, bits, n_seq, n_qh, n_kv, n_q, max_len)]
         res = subprocess.run([exe] + args, capture_output=True, text=True, timeout=60)
         assert res.returncode == 0, res.stdout + res.stderr
         return tuple(int(x) for x in res.stdout.split())
@@ -51,3 +51,31 @@ def test_row_groups_of_plans_without_joint_tables(shapes):
     assert [shapes(False, 128, 4, 2, 2 * r, 2, 1, 700)[0] for r in (1, 2, 4, 8)] == [4, 4, 4, 8]
     assert [shapes(False, 64, 4, 2, 2 * r, 2, 1, 700)[0] for r in (1, 2, 4, 8)] == [1, 2, 4, 8]
     assert [shapes(False, 256, 4, 2, 2 * r, 2, 1, 700)[0] for r in (1, 2, 4, 8)] == [1, 2, 4, 8]
+
+
+BF16, PAGED, FP32, VQ8, VQ4, QJL, WINDOW, SHIFTED, PAGED_VQ8, PAGED_QJL, PAGED_WINDOW = 0, 1, 2, 3, 4, 5, 6, 7, 13, 15, 16
+
+
+@pytest.mark.parametrize("kind,d,bits,round_tokens,long_steps", [
+    (BF16, 128, 3, 512, False), (PAGED, 128, 3, 512, False), (BF16, 64, 1.5, 512, False), (BF16, 256, 2.5, 256, False),
+    (VQ8, 128, 3, 512, False), (PAGED_VQ8, 64, 2, 512, False), (VQ4, 128, 3, 256, True), (FP32, 128, 3, 256, True),
+    (FP32, 256, 2, 256, True), (QJL, 128, 3, 512, True), (PAGED_QJL, 64, 2, 512, True), (BF16, 64, 4, 512, True), (PAGED, 128, 4, 512, True)])
+def test_which_calls_are_served_without_a_merge(shapes, kind, d, bits, round_tokens, long_steps):
+    """Up to two rounds of steps and 256 (sequence, KV head, row group) pairs; one round where steps are long and the pairs are at most
+    half the workgroups.  One token or one pair more, and the partial results are merged."""
+    few = 1 if long_steps else 2
+    # (eight query rows per KV head: one row group, whatever the kernel)
+    for n_seq, rounds in ((1, few), (64, few), (65, 2), (128, 2)):
+        assert shapes(kind, d, bits, n_seq, 16, 2, 1, rounds * round_tokens)[3] == 0
+        assert shapes(kind, d, bits, n_seq, 16, 2, 1, 64)[3] == 0
+        assert shapes(kind, d, bits, n_seq, 16, 2, 1, rounds * round_tokens + 1)[3] == 1
+    assert shapes(kind, d, bits, 129, 16, 2, 1, 64)[3] == 1
+    # 24 rows per KV head: three row groups, 252 and 258 pairs
+    assert [shapes(kind, d, bits, n, 48, 2, 1, 64)[1::2] for n in (42, 43)] == [(3, 0), (3, 1)]
+
+
+def test_calls_that_are_always_merged(shapes):
+    for kind in (WINDOW, PAGED_WINDOW, SHIFTED):
+        assert shapes(kind, 128, 3, 1, 8, 2, 1, 64)[3] == 1
+    for kind in (BF16, PAGED):
+        assert shapes(kind, 128, 3, 1, 8, 8, 130, 100)[3] == 1           # blocks of many query rows
