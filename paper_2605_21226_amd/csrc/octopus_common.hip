@@ -257,8 +257,11 @@ template <int D>
 static int merge_d(const DecodeShape &s, const float *part_ml, const float *part_acc, const int32_t *seq_lens,
                    float *out, const float *win_ml, const float *win_acc, hipStream_t stream) {
     const int64_t rows = static_cast<int64_t>(s.n_seq) * s.n_q * s.n_q_heads;
-    hipLaunchKernelGGL((merge_kernel<D>), dim3(static_cast<unsigned>(rows)), dim3(kWave), 0, stream, s, part_ml,
-                       part_acc, seq_lens, out, win_ml, win_acc);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(rows)), dim3(kWave), 0, stream, s, part_ml,
+                           part_acc, seq_lens, out, win_ml, win_acc);
+    };
+    if (s.two_round_blocks != 0) go(merge_kernel<D, true>); else go(merge_kernel<D, false>);
     return static_cast<int>(hipGetLastError());
 }
 

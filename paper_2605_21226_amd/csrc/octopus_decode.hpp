@@ -260,8 +260,12 @@ __device__ __forceinline__ void build_tables(DecodeTables<P> &tb, int tid, int n
 // 62 / 41, 16 to 30000, 4 KV heads 67 / 59.5, one of 60000 and eight of 300 58 / 39; 16 of half to full 12000 equal.  Pairs of equal
 // length stay evenly divided: weighed, 24 x 1024 28 / 24 but 28 x 1100 28.3 / 29.5, 16 x 1500 20.7 / 22, 24 x 4096 52 / 53; so do
 // pairs longer than a share, and calls of shares under three rounds, which whole blocks round up too much (evenly / weighed, 8 sequences
-// to 1326, 24 KV heads, d = 64 18.8 / 20.5; 2 to 8179 over 3-bit values, eight rows 40.5 / 49).  24 x 512 with blocks counted exactly:
-// 26.4 / 19.3.
+// to 1326, 24 KV heads, d = 64 18.8 / 20.5).  24 x 512 with blocks counted exactly: 26.4 / 19.3.
+// decode_kernel_valu, whose steps are one tile, goes by blocks of two rounds (each one segment) where its even shares are between
+// one round and two, or else a share that straddles two pairs costs a second segment.  Evenly / by blocks, 8 KV heads over fp32 values at
+// d = 128: 2 sequences to 8179, eight rows 50.3 / 41.5 us, four 35.7 / 31.4, one 25.5 / 25.7; five to 4000, four rows 39.0 / 30.8; 20
+// to 5000, 2 KV heads 36.4 / 30.4; eight rows over quantised values, 2 to 8179 48.6 / 40.3.  Equal pairs, a power of two of them, whose
+// even shares end where the pairs do, stay even (2 x 6000, eight rows 38.8 / 40.6, one row 23.3 / 24.5).
 // Calls with every length divided evenly / as here, d = 128, b = 3, ragged (lengths of 1 / 64 of the longest and up): 32
 // sequences to 372 tokens, one KV head of eight rows 43.2 / 17.7 us, 64 to 500, 8 KV heads of four rows 50.5 / 25.8, 256 to 500
 // 156 / 84, 256 to 4000 358 / 239, the same over quantised values 371 / 225, 40 to 16000 162 / 135 (kSegmentTiles half or twice
@@ -303,10 +307,10 @@ __device__ __forceinline__ uint32_t divide(uint64_t a, uint64_t b) {
 // takes the quanta whose first unit lies in its share.  (Quanta are never further apart than a share is long -- one unit, or
 // item_waves units of a total of item_waves kDecodeWorkgroups at least -- so the workgroups that have quanta of a pair are
 // consecutive.)  waves_log2, tps: log2 of the wavefronts per workgroup, tiles per step.
-enum : int { kDivideEvenly, kBlockEach, kPairsWeighed, kPairEach };
 struct Division {
     int kind;
     int waves_log2, tps;
+    int rounds_log2 = 0;   // kBlockEach: rounds of steps to a block
 
     // Sequences whose pairs are under three quarters of the mean pair and shorter than an even share, where a share is at least
     // three rounds of steps (st: the steps of this lane's sequence, sum and total: of all sequences and pairs, present: sequences
@@ -318,20 +322,35 @@ struct Division {
         return __ballot(st > 0u && x < share && x * static_cast<float>(present) < mean);
     }
     static __device__ __forceinline__ uint32_t with_tokens(uint32_t st) { return __popcll(__ballot(st > 0u)); }
+    static __device__ __forceinline__ uint64_t blocks_of(uint32_t st, int log2) {
+        return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(wave_scan((st + (1u << log2) - 1u) >> log2)), kWave - 1));
+    }
     // Most calls are known to be divided evenly by their steps alone (and code that runs costs its fetch here).
+    // TWO: shp.two_round_blocks may be set; calls of one to two rounds are then even where the pairs are equal and a power of two.
+    template <bool TWO>
     static __device__ __forceinline__ bool surely_even(const DecodeShape &shp, uint32_t st, uint64_t sum, uint64_t total, int waves_log2) {
-        return shp.pairs_fill == 0 && shp.n_seq <= kWave && total > static_cast<uint64_t>(kDecodeWorkgroups) << waves_log2 &&
-               short_pairs(st, sum, total, with_tokens(st), waves_log2) == 0u;
+        if (shp.pairs_fill != 0 || shp.n_seq > kWave || total <= static_cast<uint64_t>(kDecodeWorkgroups) << waves_log2) return false;
+        if (TWO && __builtin_expect(shp.two_round_blocks != 0 && total <= static_cast<uint64_t>(2 * kDecodeWorkgroups) << waves_log2, 0)) {
+            const uint32_t present = with_tokens(st), pairs = present * static_cast<uint32_t>(shp.n_kv_heads * shp.n_row_groups);
+            return (pairs & (pairs - 1u)) == 0u && __ballot(st > 0u && st * present != static_cast<uint32_t>(sum)) == 0u;
+        }
+        return short_pairs(st, sum, total, with_tokens(st), waves_log2) == 0u;
     }
     // The kind, from the steps of all sequences and pairs; steps_at(s0): the steps of sequence s0 + lane (0: none).
-    template <class Steps>
+    template <bool TWO, class Steps>
     __device__ __forceinline__ void set(const DecodeShape &shp, uint64_t sum, const Steps &steps_at) {
         const uint64_t G = static_cast<uint64_t>(shp.n_kv_heads) * shp.n_row_groups, total = sum * G;
         constexpr uint64_t kWgs = kDecodeWorkgroups;
+        const int two_log2 = waves_log2 + 1;
         if (shp.n_seq == 1) {   // (as below, where a lone sequence is never short; without the scans)
             const uint32_t n = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(steps_at(0))));
             const uint64_t blocks = static_cast<uint64_t>((n + (1u << waves_log2) - 1u) >> waves_log2) * G;
             kind = blocks <= kWgs ? kBlockEach : (G >= kWgs ? kPairsWeighed : kDivideEvenly);
+            if (TWO && __builtin_expect(shp.two_round_blocks != 0 && blocks > kWgs, 0) && ((n + (1u << two_log2) - 1u) >> two_log2) * G <= kWgs &&
+                (G & (G - 1)) != 0) {
+                kind = kBlockEach;
+                rounds_log2 = 1;
+            }
             return;
         }
         uint32_t present = 0;
@@ -341,10 +360,20 @@ struct Division {
         if (total + (pairs << waves_log2) - pairs <= kWgs << waves_log2) return;   // (blocks have at most a rest per pair more)
         if (total <= kWgs << waves_log2) {   // (else the blocks are more than the workgroups)
             uint64_t blocks = 0;
-            for (int s0 = 0; s0 < shp.n_seq; s0 += kWave)
-                blocks += static_cast<uint32_t>(__builtin_amdgcn_readlane(
-                    static_cast<int>(wave_scan((steps_at(s0) + (1u << waves_log2) - 1u) >> waves_log2)), kWave - 1));
+            for (int s0 = 0; s0 < shp.n_seq; s0 += kWave) blocks += blocks_of(steps_at(s0), waves_log2);
             if (blocks * G <= kWgs) return;
+        }
+        if (TWO && __builtin_expect(shp.two_round_blocks != 0 && total <= kWgs << two_log2, 0)) {
+            uint64_t blocks = 0, unequal = pairs & (pairs - 1);
+            for (int s0 = 0; s0 < shp.n_seq; s0 += kWave) {
+                const uint32_t st = steps_at(s0);
+                blocks += blocks_of(st, two_log2);
+                unequal |= __ballot(st > 0u && st * present != static_cast<uint32_t>(sum));   // (sum <= 2048 << 3 here)
+            }
+            if (blocks * G <= kWgs && unequal != 0u) {
+                rounds_log2 = 1;
+                return;
+            }
         }
         kind = pairs >= kWgs ? kPairsWeighed : kDivideEvenly;
         if (pairs < kWgs)
@@ -354,7 +383,7 @@ struct Division {
     __device__ __forceinline__ uint32_t fixed() const {
         return kind == kPairsWeighed ? static_cast<uint32_t>((waves_log2 == 3 ? 2 * kSegmentTiles : kSegmentTiles) / tps) : 0u;
     }
-    __device__ __forceinline__ int steps_log2() const { return kind == kDivideEvenly ? 0 : (kind == kPairEach ? 30 : waves_log2); }   // steps per quantum
+    __device__ __forceinline__ int steps_log2() const { return kind == kDivideEvenly ? 0 : (kind == kPairEach ? 30 : waves_log2 + rounds_log2); }   // steps per quantum
     __device__ __forceinline__ int units_log2() const { return kind == kPairsWeighed ? waves_log2 : 0; }   // units per quantum
     __device__ __forceinline__ uint32_t quanta(uint32_t steps) const { return (steps + (1u << steps_log2()) - 1u) >> steps_log2(); }
     __device__ __forceinline__ uint32_t units(uint32_t steps) const {
@@ -426,9 +455,9 @@ struct WorkSpan {
         }
         const uint64_t sum = total;
         total *= G;
-        if (__builtin_expect(shp.out != nullptr || !Division::surely_even(shp, st, sum, total, div.waves_log2), 0)) {
-            if (shp.out != nullptr) div.kind = kPairEach;
-            else div.set(shp, sum, [&](int s0) __attribute__((always_inline)) {
+        if (__builtin_expect(shp.kind_known != 0 || !Division::surely_even<!FRESH>(shp, st, sum, total, div.waves_log2), 0)) {
+            if (shp.kind_known != 0) div.kind = shp.kind_known;
+            else div.template set<!FRESH>(shp, sum, [&](int s0) __attribute__((always_inline)) {
                 if (s0 == 0) return st;
                 chunk = s0;
                 return read(shp, seq_lens, lane);
@@ -1928,7 +1957,8 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) void decode_kernel_valu(
 // A split without tokens has m = -inf, l = 0 and a zero accumulator, so it needs no special case.
 // Bound by latency (one load for the lengths, then the partials): with one partial per segment instead of four per item
 // of work, a long sequence has a quarter of the rows to read (one head over 4096 tokens: 11.6 us with 128 partials).
-template <int D>
+// TWO: the call may be divided into blocks of two rounds (shp.two_round_blocks).
+template <int D, bool TWO>
 __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, const float *__restrict__ part_ml,
                                                       const float *__restrict__ part_acc,
                                                       const int32_t *__restrict__ seq_lens, float *__restrict__ out,
@@ -1983,8 +2013,9 @@ __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, const flo
         const uint64_t sum = total;
         total *= G;
         Division div{kDivideEvenly, shp.item_waves == 8 ? 3 : 2, shp.tiles_per_step};
-        if (__builtin_expect(!Division::surely_even(shp, st, sum, total, div.waves_log2), 0)) {
-            div.set(shp, sum, [&](int s0) __attribute__((always_inline)) { read(s0); return st; });
+        if (__builtin_expect(shp.kind_known != 0 || !Division::surely_even<TWO>(shp, st, sum, total, div.waves_log2), 0)) {
+            if (shp.kind_known != 0) div.kind = shp.kind_known;
+            else div.template set<TWO>(shp, sum, [&](int s0) __attribute__((always_inline)) { read(s0); return st; });
             if (div.kind != kDivideEvenly) {
                 total = 0;
                 for (int s0 = 0; s0 < shp.n_seq; s0 += kWave) {

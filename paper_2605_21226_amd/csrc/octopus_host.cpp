@@ -584,6 +584,34 @@ static bool rotates_in_kernel(const octopus_plan_t &plan, bool many_rows, bool m
     return !many_rows && matrix_kernel && joint_plan(plan);
 }
 
+// Calls whose every (sequence, KV head, row group) is one workgroup's for a round of steps or two: the kernel writes the output
+// itself and no merge is launched.  Merged / direct, b = 3, four rows per KV head, 8 KV heads, one round: 1 x 400 tokens, d = 128
+// 15.4 / 11.6 us, 32 x 500 17.3 / 12.9 (values at 3 bits 18.6 / 14.7, residual 21.7 / 17.5), 32 x 250 over fp32 values 28.3 / 23.8, d = 256,
+// 32 x 250 19.4 / 14.4.  Two rounds: with more pairs than half the workgroups, 32 x 1000, 24.5 / 19.9 (residual 29.2 / 24.8); with fewer, where
+// merged every round is a workgroup's, 1 x 1000 16.5 / 15.4 (inputs that no cache holds 16.8 / 15.5; values at 3 bits 18.1 / 17.4, d = 256,
+// 1 x 400 17.7 / 16.8), but with the residual 20.8 / 20.8 (from memory 20.7 / 21.1), plans without joint tables 25.1 /
+// 25.8 and over quantised values with four wavefronts 26.2 / 28.3 (2 bits, eight rows, 1 x 423), whose steps are long; over fp32
+// values eight rows, 2 x 400 31.3 / 33.1, d = 256, 1 x 500 27.6 / 34.5, four rows, 1 x 512 23.4 / 23.0 (from memory 24.7 / 25.2).
+static bool direct_output(const DecodeShape &s, const float *out, bool with_window, bool long_steps) {
+    const int64_t round = static_cast<int64_t>(s.item_waves) * s.tiles_per_step * OCTOPUS_TILE;
+    const int64_t pairs = static_cast<int64_t>(s.n_seq) * s.n_kv_heads * s.n_row_groups;
+    return !with_window && s.rows_per_pass < 128 && pairs <= 256 && s.max_len <= (long_steps && 2 * pairs <= 256 ? 1 : 2) * round &&
+           aligned(out, 16);
+}
+
+// What is known of the division of a call's steps before its lengths are: one workgroup per pair (direct: the output is written
+// without a merge), or, where even sequences of max_len tokens have no more blocks of a round than there are workgroups, one per
+// block; the kernels then need not count (which costs 0.2 - 0.8 us of such a call: values at 3 bits, d = 64, 2 sequences to 2754 15.7 /
+// 15.4 us, the residual at d = 256, 8 x 430 27.9 / 27.0, 4 bits, 2 sequences to 533 24.8 / 24.3).
+static void set_division(DecodeShape *s, float *out, bool direct, bool vector_kernel, int32_t head_dim) {
+    const int64_t round = static_cast<int64_t>(s->item_waves) * s->tiles_per_step * OCTOPUS_TILE;
+    const int64_t pairs = static_cast<int64_t>(s->n_seq) * s->n_kv_heads * s->n_row_groups;
+    if (direct) s->out = out;
+    if (direct) s->kind_known = kPairEach;
+    else if (s->rows_per_pass < 128 && pairs * ((s->max_len + round - 1) / round) <= 256) s->kind_known = kBlockEach;
+    s->two_round_blocks = vector_kernel && head_dim <= 128 ? 1 : 0;
+}
+
 // Many query rows at d = 128, more than one block of 128: blocks of 256 rows, two wavefronts per SIMD, each key decoded for
 // twice the rows (one sequence of 15877 tokens, 8 KV heads, 2036 rows each: kernel 470 -> 330 us; with blocks of 128 the
 // one wavefront per SIMD spent 3000 of a tile's 7800 cycles decoding keys with its matrix core idle).  Their workspace has
@@ -595,20 +623,6 @@ static bool rotates_in_kernel(const octopus_plan_t &plan, bool many_rows, bool m
 // 164 / 132, 900 x 4, one KV head, 20000 (38 / 19) 219 / 181, 160 x 1, 30000 (30 / 17) 129 / 92, 512 x 4, 4096 (32 / 16)
 // 153 / 122.  At a ratio of 5 / 4 either may win: 1000 x 4, two KV heads, 6000 at 4 bits (24 / 19) 117 / 122, 200 x 1, 20480
 // (20 / 16) 94.5 / 88.5; the line is at 4 / 3.
-// Calls whose every (sequence, KV head, row group) is one workgroup's for a round of steps or two: the kernel writes the output
-// itself and no merge is launched.  Merged / direct, b = 3, four rows per KV head, 8 KV heads, one round: 1 x 400 tokens, d = 128
-// 15.4 / 11.6 us, 32 x 500 17.3 / 12.9 (values at 3 bits 18.6 / 14.7, residual 21.7 / 17.5), 32 x 250 over fp32 values 28.3 / 23.8, d = 256,
-// 32 x 250 19.4 / 14.4.  Two rounds: with more pairs than half the workgroups, 32 x 1000, 24.5 / 19.9 (residual 29.2 / 24.8); with fewer, where
-// merged every round is a workgroup's, 1 x 1000 15.6 / 14.7 (values at 3 bits 17.2 / 17.2, d = 256, 1 x 400 16.6 / 16.0), but with the
-// residual 19.9 / 20.6, over fp32 values 26.3 / 30.0 (steps of two tiles then), plans without joint tables 24.1 / 25.3 (b = 4, 2 x 533,
-// 2 KV heads) and over quantised values with four wavefronts 26.2 / 28.3 (2 bits, eight rows, 1 x 423), whose steps are long.
-static bool direct_output(const DecodeShape &s, const float *out, bool with_window, bool long_steps) {
-    const int64_t round = static_cast<int64_t>(s.item_waves) * s.tiles_per_step * OCTOPUS_TILE;
-    const int64_t pairs = static_cast<int64_t>(s.n_seq) * s.n_kv_heads * s.n_row_groups;
-    return !with_window && s.rows_per_pass < 128 && pairs <= 256 && s.max_len <= (long_steps && 2 * pairs <= 256 ? 1 : 2) * round &&
-           aligned(out, 16);
-}
-
 static void many_rows_at_128(const octopus_codebooks_t *cb, int64_t max_len, DecodeShape *s, Workspace *w) {
     if (cb->plan.head_dim != 128 || s->rows_per_kv <= 128) return;
     DecodeShape wide = make_decode_shape(cb->plan, s->n_seq, s->n_q_heads, s->n_kv_heads, s->n_q, max_len, s->t_capacity, true, 8, 0,
@@ -689,7 +703,8 @@ static int attn_decode(const octopus_codebooks_t *cb, const void *q, int32_t q_d
     const bool vector_kernel = with_vq ? vq_mfma == 0 : v_dtype != OCTOPUS_DTYPE_BF16;
     if (vector_kernel) s.tiles_per_step = 1;   // (decode_kernel_valu; the workspace has room for either)
     set_queries(&s, q, q_dtype, signs, signs2, scale);
-    if (direct_output(s, out, win != nullptr, with_qjl || vector_kernel || (with_vq && s.item_waves == 4) || !joint_plan(cb->plan))) s.out = out;
+    const bool direct = direct_output(s, out, win != nullptr, with_qjl || vector_kernel || (with_vq && s.item_waves == 4) || !joint_plan(cb->plan));
+    set_division(&s, out, direct, vector_kernel, cb->plan.head_dim);
     // every entry point asks for the one documented size, whatever its own kernel needs (the static scratch
     // has been checked against the need of the kernels it serves)
     const size_t required = static_scratch_call ? w.total
@@ -972,7 +987,8 @@ static int attn_decode_paged(const octopus_codebooks_t *cb, const void *q, int32
     Workspace w = make_workspace(cb->plan, s);
     if (many_rows) many_rows_at_128(cb, max_len, &s, &w);
     set_queries(&s, q, q_dtype, signs, with_qjl ? signs2 : nullptr, scale);
-    if (direct_output(s, out, win != nullptr, with_qjl || (v_bits != 0 && s.item_waves == 4) || !joint_plan(cb->plan))) s.out = out;   // (pages hold bf16 or quantised values)
+    const bool direct = direct_output(s, out, win != nullptr, with_qjl || (v_bits != 0 && s.item_waves == 4) || !joint_plan(cb->plan));
+    set_division(&s, out, direct, false, cb->plan.head_dim);   // (pages hold bf16 values, or quantised ones for the matrix-core kernel)
     const size_t required = std::max(w.total, octopus_attn_decode_workspace(cb, n_seq, n_q_heads, n_kv_heads, n_q, max_len));
     if (workspace == nullptr || !aligned(workspace, 256) || workspace_bytes < required) return OCTOPUS_EWORKSPACE;
     char *base = static_cast<char *>(workspace);

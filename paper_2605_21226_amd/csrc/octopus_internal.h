@@ -30,6 +30,9 @@ inline DeviceBooks device_books(const octopus_codebooks_t &cb) {
 // Floats per rotated query row in the workspace: 3 * n_tri rounded up to 4.
 inline int q_row_stride(int n_tri) { return (3 * n_tri + 3) & ~3; }
 
+// How the decode kernels divide a call's steps (octopus_decode.hpp).
+enum : int { kDivideEvenly, kBlockEach, kPairsWeighed, kPairEach };
+
 struct DecodeShape {
     int32_t n_seq, n_q_heads, n_kv_heads, n_q;
     int32_t heads_per_kv;   // n_q_heads / n_kv_heads
@@ -48,6 +51,8 @@ struct DecodeShape {
     float scale;
     int32_t q_is_bf16;
     float *out;             // the call's output where every pair is one workgroup's and no merge follows, or NULL (direct_output)
+    int32_t kind_known;     // kBlockEach or kPairEach where the host knows it whatever the lengths, else 0
+    int32_t two_round_blocks;   // calls of one to two rounds of steps per workgroup go by blocks of two rounds (Division::set)
     int32_t pairs_fill;     // there may be as many (sequence, KV head, row group) pairs with tokens as workgroups (256)
 };
 

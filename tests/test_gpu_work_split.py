@@ -145,3 +145,22 @@ def test_many_sequences_over_pages_values_and_the_residual(n_seq, n_kv):
     run_paged_vq_decode_case(64, 2, 2, 16, n_seq, n_qh, n_kv, 1, lens, seed=39)
     run_decode_qjl_case(64, 3, n_seq, n_qh, n_kv, 1, lens, seed=40, want_scores=False)
     run_paged_qjl_decode_case(64, 2, n_seq, n_qh, n_kv, 1, lens, seed=41)
+
+
+# The kernels that accumulate on the vector units, calls of one to two rounds of steps (256 tokens each) per workgroup: blocks of two
+# rounds, but an even division where the pairs are equal and a power of two.
+@pytest.mark.parametrize("n_kv,lens", [
+    (8, [6000, 4167, 0, 70]),
+    (5, [20000]),
+    (1, [40000] + [500] * 66),                            # more than 64 sequences
+    (8, [6000, 6000]),                                    # (even)
+    (4, [8192, 8192, 8192, 8191]),                        # ... and one token short of it: 256 blocks of two rounds
+    (4, [8192, 8192, 8192, 8193]),                        # one token too many
+])
+def test_decode_by_blocks_of_two_rounds(n_kv, lens):
+    run_decode_case(64, 3, len(lens), n_kv, n_kv, 1, lens, "fp32", seed=len(lens) + 7, want_scores=False)
+
+
+def test_quantised_values_by_blocks_of_two_rounds():
+    from test_gpu_values import run_decode_vq_case
+    run_decode_vq_case(64, 3, 3, 16, 2, 8, 8, 1, [6000, 4167], seed=43, want_scores=True)
