@@ -128,7 +128,11 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
     // 380; b = 2, 3 bits 107 -> 99; d = 128, b = 1, 8 rows, groups of 16 549 -> 413).  d = 256 in groups of 16 spills
     // hundreds of bytes either way and is faster wide (338 / 372 at b = 1, 362 / 382 at 1.5).
     constexpr bool LEAN = NWV > 4 || (!(P::NCLASS == 1 && P::BD0 == 4 && P::BN0 == 2) && (D <= 128 || VG == 32));
-    constexpr int LOOKAHEAD = NWV > 4 ? 1 : 2;
+    // The kernels that keep hundreds of bytes of a lane in scratch anyway look one lookup ahead and, at d = 256, read the step's scales
+    // after the softmax instead of before: 26 of them at 1 - 2 bits, 8 x 8192 tokens, 2.9 % faster on average (one by one 0.96 - 1.14;
+    // 4 bits in groups of 32, b = 1.5, eight rows 217 -> 195 us; 3 bits in groups of 16, four rows 208 -> 216).
+    constexpr bool HEAVY = NWV == 4 && ((D == 256 && VG == 16) || (RG == 8 && (D == 256 || VG == 16)));
+    constexpr int LOOKAHEAD = NWV > 4 || HEAVY ? 1 : 2;
     // ... but a lookup of two instructions instead of four (MxCodes::PAIRED) also where two wavefronts share a SIMD: its 12 registers
     // cost no more than what is stored outside the step loop (Llama-shaped batch, values at 3 / 2 bits in groups of 32: 142.6 ->
     // 138.7, 135.8 -> 126.3 us; d = 64 85.9 -> 79.3).
@@ -406,7 +410,7 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
         // scales and zero points of this lane's keys for the products below
         load_records(step_nx, slot_nx, w);
         float2 sz[KPL][G];
-        load_meta(sz);
+        if constexpr (!(HEAVY && D == 256)) load_meta(sz);
         // D5: online softmax, one running maximum per row for the whole wave; s becomes the probabilities
         float alpha[RG], mx[RG];
 #pragma unroll
@@ -429,6 +433,7 @@ __global__ __launch_bounds__((vq_waves<P, RG, VB, VG>() * kWave))
             }
             l_lane[r] = fmaf(l_lane[r], alpha[r], psum);
         }
+        if constexpr (HEAVY && D == 256) load_meta(sz);
         // the running sums are rescaled only when a row's maximum has moved (rare after a sequence's first steps)
         bool moved = false;
 #pragma unroll

@@ -55,3 +55,11 @@ def test_encoders_do_not_spill(library):
     words = {"13encode_kernelINS_5PlanTILi128ELi3ELi5ELi0ELi0EEELb0ELb0ELb0ELb0E": 12,
              "13encode_kernelINS_5PlanTILi256ELi3ELi1ELi1ELi1EEELb1ELb1ELb0ELb0E": 8}
     assert {n: v for n, v in found.items() if v > max([b for part, b in words.items() if part in n], default=0)} == {}
+
+
+def test_scratch_of_the_heaviest_kernels_over_quantised_values(library):
+    """Groups of 16, or eight rows, of 1 - 2 bit keys at d = 256 keep hundreds of bytes of a lane in scratch; together no more than
+    before the maxima over a wavefront were taken for all rows at once."""
+    pat = re.compile(r"decode_kernel_vq_mfmaINS_5PlanTILi256ELi[13]ELi1E\w*ELi(4ELi\dELi16|8ELi\dELi32)E")
+    found = [k[".private_segment_fixed_size"] for name, k in library.items() if pat.search(name)]
+    assert len(found) == 17 and sum(found) <= 10948
