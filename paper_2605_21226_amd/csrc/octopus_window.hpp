@@ -17,8 +17,8 @@ namespace octopus {
 // accumulates its D / 64 channels over the chunk's tokens.
 // Bound by latency and by the second-level cache (a window is a few kilobytes a row): the chunk's keys are asked for before the
 // lengths are known, whole rows per instruction, and handed to their lanes through LDS (16 bytes per lane and row of 64 rows each
-// fetched every cache line eight times: 13.3 us of 24 sequences x 64 heads x 32 tokens); the chunk's two pages as soon as the
-// lengths are there, and 32 value rows, a lane's channels in one load, before the scores are computed.
+// fetched every cache line eight times: 13.3 us of 24 sequences x 64 heads x 32 tokens, so 8.0); the chunk's two pages as soon as
+// the lengths are there, and up to 32 value rows, a lane's channels in one load, before the scores are computed.
 template <int D, bool k_is_bf16, bool v_is_bf16>
 __global__ __launch_bounds__(kWave) void window_kernel(DecodeShape shp, const void *__restrict__ q, int q_is_bf16,
                                                        const void *__restrict__ k_win,
