@@ -2090,11 +2090,20 @@ __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, const flo
                         x[u][c] = part_acc[(prow0 + static_cast<int64_t>(j0 + min(jj + u, nj - 1)) * pstride) * D +
                                            c * kWave + lane];
             }
-#pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                const float fj = (jj + u < nj) ? wgt[jj + u] : 0.0f;
+            auto take = [&](int u) __attribute__((always_inline)) {
+                const float fj = wgt[jj + u];
 #pragma unroll
                 for (int c = 0; c < CPT; ++c) a[c] = fmaf(fj, x[u][c], a[c]);
+            };
+            if (jj + UN <= nj) {
+#pragma unroll
+                for (int u = 0; u < UN; ++u) take(u);
+            } else {   // (partials past the last stay out: at weight zero an infinity in it would count again, as 0 * inf)
+#pragma unroll
+                for (int u = 0; u < UN - 1; ++u) {
+                    if (jj + u >= nj) break;
+                    take(u);
+                }
             }
         }
     }

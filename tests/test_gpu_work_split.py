@@ -164,3 +164,32 @@ def test_decode_by_blocks_of_two_rounds(n_kv, lens):
 def test_quantised_values_by_blocks_of_two_rounds():
     from test_gpu_values import run_decode_vq_case
     run_decode_vq_case(64, 3, 3, 16, 2, 8, 8, 1, [6000, 4167], seed=43, want_scores=True)
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("lens", [[300], [20000, 100], [5000, 3000, 70]])
+def test_infinity_in_the_last_value_row(d, lens):
+    """Its channel is infinite, the others are what they are without it: partial results that a batch of them has too many do not count.
+    (fp32 values: their weights are not split.)"""
+    from gpu_util import DEV
+    from paper_2605_21226_amd import binding
+    gen = torch.Generator().manual_seed(51)
+    n, n_kv, rows, top = len(lens), 2, 2, max(lens)
+    cap = (top + 63) // 64 * 64
+    cb = binding.octopus_build_codebooks(d, 3)
+    signs = torch.randint(0, 256, (n_kv, d // 8), generator=gen, dtype=torch.uint8).to(DEV)
+    cache = torch.zeros(binding.octopus_cache_bytes(cb, n, n_kv, cap), dtype=torch.uint8, device=DEV)
+    binding.octopus_encode(cb, torch.randn((n, top, n_kv, d), generator=gen).to(DEV), signs, cache, cap)
+    v = torch.randn((n, n_kv, cap, d), generator=gen).to(DEV)
+    q = torch.randn((n, 1, n_kv * rows, d), generator=gen).to(DEV)
+    ws = torch.empty(binding.octopus_attn_decode_workspace(cb, n, n_kv * rows, n_kv, 1, top), dtype=torch.uint8, device=DEV)
+    outs = []
+    for x in (1.0, float("inf")):
+        for s, length in enumerate(lens):
+            v[s, :, length - 1, 5] = x
+        out = torch.zeros((n, 1, n_kv * rows, d), device=DEV)
+        binding.octopus_attn_decode(cb, q, signs, cache, cap, v, torch.tensor(lens, dtype=torch.int32, device=DEV), top, 0.1, out, ws)
+        outs.append(out.cpu().numpy())
+    assert np.all(np.isposinf(outs[1][..., 5])) and np.all(np.isfinite(outs[0]))
+    others = np.arange(d) != 5
+    assert np.array_equal(outs[0][..., others], outs[1][..., others])
