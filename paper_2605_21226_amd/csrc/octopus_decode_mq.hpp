@@ -53,7 +53,6 @@ struct MqSmem {
 
 template <class P, int NW>
 __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D <= 64 || NW == 8 ? 2 : 1))) void decode_kernel_mq(DeviceBooks books, DecodeShape shp,
-                                                         const float *__restrict__ q_rot,
                                                          const uint4 *__restrict__ cache,
                                                          const uint16_t *__restrict__ v,
                                                          const int32_t *__restrict__ seq_lens,
@@ -75,25 +74,23 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, h = lane >> 5;
 
-    // tables (one copy: the lookups are a small part of this kernel)
-    if (tid < kWave) copy_books<P>(books, sm.c_xi, sm.c_rho);
-    __syncthreads();
-    build_dir_lut<P::BD0>(sm.dir0, sm.c_xi[0], tid, kWave * NW);
-    if constexpr (P::NCLASS == 2) build_dir_lut<P::BD1>(sm.dir1, sm.c_xi[1], tid, kWave * NW);
-
     // work: (sequence, KV head, block of ROWS rows, split) and the split's tiles.  The blocks of rows of one
-    // (sequence, KV head, split) read the same keys and values: they are given to ONE accelerator die (workgroup
-    // b runs on die b % 8, each with its own L2), next to each other in that die's sequence of workgroups, so
-    // that the tiles are fetched from memory once and not once per die.  Unit u = (pair, split) goes to die
-    // u % 8; the grid is padded to whole rounds of 8 units (the workgroups of units that do not exist leave).
-    const int64_t slot = blockIdx.x / kXcds;
-    const int64_t unit = (slot / shp.n_row_groups) * kXcds + blockIdx.x % kXcds;
-    const int64_t n_units = static_cast<int64_t>(shp.n_seq) * shp.n_kv_heads * shp.n_splits;
-    if (unit >= n_units) return;   // (whole workgroup, before any barrier)
-    const int split = static_cast<int>(unit % shp.n_splits);
-    const int64_t pair = unit / shp.n_splits;
-    const int64_t group_id = pair * shp.n_row_groups + slot % shp.n_row_groups;
-    const int seq = static_cast<int>(pair / shp.n_kv_heads);
+    // (sequence, KV head, split) read the same keys and values: they follow each other in the order of the work, and each
+    // accelerator die (workgroup b runs on die b % 8, each with its own L2) takes an eighth of that order, so that the tiles are
+    // fetched from memory once and not once per die, and no die has more than one workgroup more than another.  (Whole units of
+    // blocks per die before: 23 units of 11 blocks were two rounds of workgroups on seven dies of 32 compute units; 2776 rows of
+    // one KV head over 22097 tokens, d = 64, 87 us of this kernel.)
+    const uint32_t n_work = static_cast<uint32_t>(shp.n_seq * shp.n_kv_heads) * static_cast<uint32_t>(shp.n_splits * shp.n_row_groups);
+    const uint32_t per_die = (n_work + kXcds - 1) / kXcds;
+    const uint32_t work = (blockIdx.x % kXcds) * per_die + blockIdx.x / kXcds;
+    if (work >= n_work) return;   // (whole workgroup, before any barrier)
+    const uint32_t unit = work / static_cast<uint32_t>(shp.n_row_groups);
+    const int grp = static_cast<int>(work - unit * static_cast<uint32_t>(shp.n_row_groups));
+    const int64_t pair = unit / static_cast<uint32_t>(shp.n_splits);
+    const int split = static_cast<int>(unit % static_cast<uint32_t>(shp.n_splits));
+    const int64_t group_id = pair * shp.n_row_groups + grp;
+    const int seq = static_cast<int>(static_cast<uint32_t>(pair) / static_cast<uint32_t>(shp.n_kv_heads));
+    const int kvh = static_cast<int>(static_cast<uint32_t>(pair) % static_cast<uint32_t>(shp.n_kv_heads));
     const int len = min(max(seq_lens[seq], 0), shp.max_len);
     const int n_tiles = (len + kWave - 1) / kWave;
     const int base = n_tiles / shp.n_splits, rem = n_tiles % shp.n_splits;
@@ -101,31 +98,99 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
     const int tile_end = tile_begin + base + (split < rem ? 1 : 0);
 
     const bool paged = pt.table != nullptr;
-    const int kvh = static_cast<int>(pair % shp.n_kv_heads);
     const char *k_region = reinterpret_cast<const char *>(cache) + (paged ? 0 : pair * shp.t_capacity * (P::GRANULES * 16));
     const char *v_pair = reinterpret_cast<const char *>(v) + (paged ? 0 : pair * shp.t_capacity * ROWB);
 
-    // Q^T operands of this wave's 32 rows: lane (n, h) holds coordinates 16 kk + 8 h .. + 8 of row n as
-    // bf16 hi and lo.  The rotated queries lie [coordinate][row] with the ROWS rows of the block adjacent.
-    const float *qg = q_rot + group_id * (static_cast<int64_t>(P::QS) * ROWS) + wave * 32 + n;
+    // Q^T operands of this wave's 32 rows: lane (n, h) holds coordinates 16 kk + 8 h .. + 8 of row n as bf16 hi and lo.
     union BF8 { uint32_t u[4]; bf16x8_t b; };
     BF8 qh[KK], ql[KK];
+    // The rows are asked for here and rotated in place (rotate_queries below).
+    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+    u32x4_t q_raw[KK], q_more[KK];   // bf16 queries: the words of q_raw, two each
+    uint32_t q_neg[KK];
+    const int q_row = grp * ROWS + wave * 32 + n;
+    auto load_queries = [&]() __attribute__((always_inline)) {
+        typedef uint32_t u32x4a_t __attribute__((ext_vector_type(4), aligned(4)));   // (queries are aligned to 4 bytes)
+        const int row = min(q_row, shp.rows_per_kv - 1);
+        const int qi = row / shp.heads_per_kv, head = kvh * shp.heads_per_kv + row % shp.heads_per_kv;
+        const int64_t base_q = ((static_cast<int64_t>(seq) * shp.n_q + qi) * shp.n_q_heads + head) * D + 8 * h;
+        const int es = shp.q_is_bf16 ? 2 : 4, second = shp.q_is_bf16 ? 0 : 16;   // (one path: the arrays written by two are kept in scratch memory)
+        const char *src = static_cast<const char *>(shp.q) + base_q * es;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            // (in units of log2: the scores come out as exponents of two)
-            const float a = qg[(16 * kk + 8 * h + 2 * e) * ROWS] * kLog2e, b = qg[(16 * kk + 8 * h + 2 * e + 1) * ROWS] * kLog2e;
-            const uint32_t ab = __float_as_uint(a), bb = __float_as_uint(b);
-            qh[kk].u[e] = __builtin_amdgcn_perm(bb, ab, 0x07060302u);
-            const float al = a - __uint_as_float(ab & 0xffff0000u), bl = b - __uint_as_float(bb & 0xffff0000u);
-            ql[kk].u[e] = __builtin_amdgcn_perm(__float_as_uint(bl), __float_as_uint(al), 0x07060302u);
+        for (int kk = 0; kk < KK; ++kk) {
+            q_raw[kk] = *reinterpret_cast<const u32x4a_t *>(src + 16 * kk * es);
+            q_more[kk] = *reinterpret_cast<const u32x4a_t *>(src + 16 * kk * es + second);
         }
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) q_neg[kk] = shp.signs[kvh * (D / 8) + 2 * kk + h];
+    };
+    // q_rot = scale H (s . q) of the 32 rows at once, all in registers (the same additions as rotate_queries_kernel's: the
+    // butterflies of the element index's bits in ascending order, bit 3 is the lane's half).  The rotation was a launch of its own whose
+    // 4-byte stores lay ROWS x 4 bytes apart: 53 us of 4005 for 3600 queries x 24 heads at d = 64, 19 of 325 for 509 x 32 at d = 128.
+    auto rotate_queries = [&]() __attribute__((always_inline)) {
+        float x[KK][8];
+        const bool live = q_row < shp.rows_per_kv;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const u32x4_t lower = q_raw[kk], upper = q_more[kk];
+                const uint32_t pair_word = lower[e / 2], own_word = e < 4 ? lower[e & 3] : upper[e & 3];
+                const uint32_t bits = shp.q_is_bf16 ? ((e & 1) ? pair_word & 0xffff0000u : pair_word << 16) : own_word;
+                x[kk][e] = live ? __uint_as_float(bits ^ ((q_neg[kk] << (31 - e)) & 0x80000000u)) : 0.0f;
+            }
+#pragma unroll
+        for (int m = 1; m < 8; m <<= 1)
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if ((e & m) == 0) {
+                        const float a = x[kk][e], b = x[kk][e | m];
+                        x[kk][e] = a + b;
+                        x[kk][e | m] = a - b;
+                    }
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) {
+                float a = x[kk][e], b = x[kk][e + 1];
+                swap32(a, b);                       // a: lower halves' of elements e | e + 1, b: the upper halves'
+                float sum = a + b, diff = a - b;
+                swap32(sum, diff);
+                x[kk][e] = sum;
+                x[kk][e + 1] = diff;
+            }
+#pragma unroll
+        for (int m = 1; m < KK; m <<= 1)
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk)
+                if ((kk & m) == 0) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float a = x[kk][e], b = x[kk | m][e];
+                        x[kk][e] = a + b;
+                        x[kk | m][e] = a - b;
+                    }
+                }
+        const float norm = shp.scale * (D == 64 ? 0.125f : 0.08838834764831845f);
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                // (in units of log2: the scores come out as exponents of two)
+                const float a = x[kk][2 * e] * norm * kLog2e, b = x[kk][2 * e + 1] * norm * kLog2e;
+                const uint32_t ab = __float_as_uint(a), bb = __float_as_uint(b);
+                qh[kk].u[e] = __builtin_amdgcn_perm(bb, ab, 0x07060302u);
+                const float al = a - __uint_as_float(ab & 0xffff0000u), bl = b - __uint_as_float(bb & 0xffff0000u);
+                ql[kk].u[e] = __builtin_amdgcn_perm(__float_as_uint(bl), __float_as_uint(al), 0x07060302u);
+            }
+    };
 
     // ---- staging: global -> registers -> LDS tile ---------------------------------------------------
     uint32_t w[P::NWORDS];          // this lane's record of the tile being staged
     uint4 vp[VP];                   // its value pieces: key `lane`, channels 8 (wave + NW i) .. + 8
-    auto load_tile = [&](int tile) {
+    auto load_tile = [&](int tile) __attribute__((always_inline)) {
         typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
         typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
         constexpr int USED = (P::RECORD_BYTES + 3) / 4;
@@ -199,7 +264,7 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
             *reinterpret_cast<uint4 *>(&sm.kl[buf][lane][wv * CW + 8 * g8]) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
         }
     };
-    auto stage_tile = [&](int buf) {
+    auto stage_tile = [&](int buf) __attribute__((always_inline)) {
         switch (wave) {
             case 0: stage_block(std::integral_constant<int, 0>{}, buf); break;
             case 1: stage_block(std::integral_constant<int, 1>{}, buf); break;
@@ -243,8 +308,20 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
 #pragma unroll
         for (int e = 0; e < 16; ++e) oacc[nb][e] = 0.0f;
 
+    // Start: queries and first tile are asked for, then the tables (one copy: the lookups are a small part of this kernel) are
+    // built and the queries rotated.  A split without tiles leaves an empty partial.
     if (tile_begin < tile_end) {
+        load_queries();
         load_tile(tile_begin);
+        if (wave < 4) {   // a level per lane, of one array per wavefront
+            typedef const float __attribute__((address_space(4))) *arg_t;
+            const float level = ((arg_t)__builtin_amdgcn_kernarg_segment_ptr())[wave * kMaxLevels + lane];
+            (wave < 2 ? sm.c_xi[wave] : sm.c_rho[wave - 2])[lane] = level;
+        }
+        __syncthreads();
+        build_dir_lut<P::BD0>(sm.dir0, sm.c_xi[0], tid, kWave * NW);
+        if constexpr (P::NCLASS == 2) build_dir_lut<P::BD1>(sm.dir1, sm.c_xi[1], tid, kWave * NW);
+        rotate_queries();
         __syncthreads();                       // tables complete
         stage_tile(0);
         load_tile(min(tile_begin + 1, tile_end - 1));
@@ -353,7 +430,6 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
 
     // partial of each row: element e of block nb is channel 32 nb + 8 (e / 4) + 4 h + e % 4 of row n
     const int row = wave * 32 + n;
-    const int grp = static_cast<int>(group_id % shp.n_row_groups);
     if (grp * ROWS + row < shp.rows_per_kv) {
         const int64_t prow = (group_id * ROWS + row) * shp.n_splits + split;
 #pragma unroll
@@ -371,14 +447,15 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
 }
 
 template <class P>
-int launch_decode_mq(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *cache,
+int launch_decode_mq(const octopus_codebooks_t &cb, const DecodeShape &s, const float *, const void *cache,
                      const void *v, const int32_t *seq_lens, float *part_ml, float *part_acc, hipStream_t stream,
                      PageTable pt) {
     const DeviceBooks books = device_books(cb);
-    const int64_t units = static_cast<int64_t>(s.n_seq) * s.n_kv_heads * s.n_splits;
-    const int64_t wgs = (units + kXcds - 1) / kXcds * kXcds * s.n_row_groups;   // see the kernel's work mapping
+    const int64_t work = static_cast<int64_t>(s.n_seq) * s.n_kv_heads * s.n_splits * s.n_row_groups;
+    const int64_t wgs = (work + kXcds - 1) / kXcds * kXcds;   // see the kernel's work mapping
+    if (wgs * s.rows_per_pass * 2 > UINT32_MAX) return static_cast<int>(hipErrorInvalidValue);   // (threads of a launch)
     auto go = [&](auto kernel, int waves) {
-        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(wgs)), dim3(kWave * waves), 0, stream, books, s, q_rot,
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(wgs)), dim3(kWave * waves), 0, stream, books, s,
                            static_cast<const uint4 *>(cache), static_cast<const uint16_t *>(v), seq_lens, part_ml, part_acc,
                            pt);
     };

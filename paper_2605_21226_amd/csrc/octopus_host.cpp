@@ -579,9 +579,9 @@ static int32_t least_rows(const octopus_plan_t &plan, bool many_rows, bool bf16_
 
 // Whether the kernel that serves a call rotates its queries itself; else a kernel before it does.  matrix_kernel: the
 // kernel over bf16 values or the matrix-core kernel over quantised values (the vector-unit kernels read the rotated
-// queries through scalar loads, the many-row kernel from a layout of its own).
+// queries through scalar loads).
 static bool rotates_in_kernel(const octopus_plan_t &plan, bool many_rows, bool matrix_kernel) {
-    return !many_rows && matrix_kernel && joint_plan(plan);
+    return many_rows || (matrix_kernel && joint_plan(plan));
 }
 
 // Calls whose every (sequence, KV head, row group) is one workgroup's for a round of steps or two: the kernel writes the output
