@@ -27,7 +27,7 @@ namespace octopus {
 
 // Query rows per workgroup: 32 per wavefront, NW = 4 wavefronts (128 rows) or NW = 8 (256 rows, two wavefronts per SIMD
 // within 256 registers each).  The keys of a tile are decoded once per workgroup, so more rows mean less decoding; the host
-// picks 256 at d = 64 from 192 rows on, at d = 128 where a compute unit then walks fewer tiles in a row (many_rows_at_128).
+// picks 256 at d = 64 from 192 rows on, at d = 128 where the call is then faster (many_rows_splits).
 // What bounds it (cycles of a tile, timestamps, 8 wavefronts, d = 64, b = 4): first product 1050, softmax 1660, second
 // product 820, staging 1060 - 1400, barrier up to 700, of 5400.  A 32x32x16 product takes 32 cycles of the matrix core and
 // keeps the vector units of its SIMD from issuing for about 16 of them, so two wavefronts' 2 x 40 products and 2 x (about 30

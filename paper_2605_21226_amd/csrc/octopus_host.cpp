@@ -239,16 +239,16 @@ DecodeShape make_decode_shape(const octopus_plan_t &plan, int32_t n_seq, int32_t
         // Matrix-core kernel for many query rows: blocks of 128 rows (4 wavefronts), or of 256 rows (8
         // wavefronts) when there are rows enough; one workgroup per (block, split).  A compute unit runs 8 of these
         // wavefronts, or 4 with blocks of 128 rows at d = 128.  The blocks of 256 at d = 128 (wide_rows) came later than the
-        // documented workspace size, which stays that of blocks of 128: see many_rows_at_128.
+        // documented workspace size, which stays that of blocks of 128: see many_rows_splits.
         s.rows_per_pass = (plan.head_dim <= 64 ? s.rows_per_kv >= 192 : wide_rows) ? 256 : 128;
         s.n_row_groups = (s.rows_per_kv + s.rows_per_pass - 1) / s.rows_per_pass;
         const int64_t groups = static_cast<int64_t>(n_seq) * n_kv_heads * s.n_row_groups;
         const int64_t max_tiles = (len + OCTOPUS_TILE - 1) / OCTOPUS_TILE;
         const int64_t slots = (plan.head_dim <= 64 && s.rows_per_pass == 128) ? 512 : 256;
+        // The split count that the documented workspace size is that of (many_rows_splits chooses the call's own).
         // The workgroups run in rounds of `slots`.  Among the split counts (each split keeping at least 16 tiles)
         // the fullest last round wins, but every split writes a partial result per query row that the merge reads
-        // again: the smallest count within 3 % of the best fill is taken (the Lumiere-shaped batch: 7 splits
-        // at 98.4 % instead of 32 at 100 %, a fifth of the partial traffic).
+        // again: the smallest count within 3 % of the best fill is taken.
         auto fill = [&](int64_t n) {
             const int64_t wgs = groups * n, rounds = (wgs + slots - 1) / slots;
             return static_cast<double>(wgs) / static_cast<double>(rounds * slots);
@@ -612,36 +612,45 @@ static void set_division(DecodeShape *s, float *out, bool direct, bool vector_ke
     s->two_round_blocks = vector_kernel && head_dim <= 128 ? 1 : 0;
 }
 
-// Many query rows at d = 128, more than one block of 128: blocks of 256 rows, two wavefronts per SIMD, each key decoded for
-// twice the rows (one sequence of 15877 tokens, 8 KV heads, 2036 rows each: kernel 470 -> 330 us; with blocks of 128 the
-// one wavefront per SIMD spent 3000 of a tile's 7800 cycles decoding keys with its matrix core idle).  Their workspace has
-// to fit the documented size: fewer splits until it does, and if it never does the shape stays as it is.
-// They pay where a compute unit then walks fewer tiles one after the other (rounds of workgroups x tiles per split); a tile
-// of 256 rows takes 1.2 - 1.3 times one of 128, so where the chip is not full either way blocks of 128 on twice the compute
-// units are faster.  Calls with blocks of 128 / 256, tiles in a row n / w: 59 rows x 4 heads, 4245 tokens (17 / 17) 79.8 /
-// 85.8 us, 64 x 8, one KV head, 16384 (18 / 20) 80.6 / 96.7, 256 x 4, 1500 (24 / 24) 113 / 122; 72 x 8, 15396 (41 / 25)
-// 164 / 132, 900 x 4, one KV head, 20000 (38 / 19) 219 / 181, 160 x 1, 30000 (30 / 17) 129 / 92, 512 x 4, 4096 (32 / 16)
-// 153 / 122.  At a ratio of 5 / 4 either may win: 1000 x 4, two KV heads, 6000 at 4 bits (24 / 19) 117 / 122, 200 x 1, 20480
-// (20 / 16) 94.5 / 88.5; the line is at 4 / 3.
-static void many_rows_at_128(const octopus_codebooks_t *cb, int64_t max_len, DecodeShape *s, Workspace *w) {
-    if (cb->plan.head_dim != 128 || s->rows_per_kv <= 128) return;
-    DecodeShape wide = make_decode_shape(cb->plan, s->n_seq, s->n_q_heads, s->n_kv_heads, s->n_q, max_len, s->t_capacity, true, 8, 0,
-                                         1, true);
-    const size_t limit = plain_decode_workspace(cb, s->n_seq, s->n_q_heads, s->n_kv_heads, s->n_q, max_len);
-    Workspace ww = make_workspace(cb->plan, wide);
-    while (ww.total > limit && wide.n_splits > 1) {
-        --wide.n_splits;
-        ww = make_workspace(cb->plan, wide);
-    }
-    if (ww.total > limit) return;
+// Splits of the many-row kernel, and at d = 128 its block of query rows (128 or, two wavefronts per SIMD and each key decoded
+// for twice the rows, 256): those of the least cost, which is what the call takes in microseconds: rounds of workgroups (a die has an
+// eighth of them, see the kernel's work mapping) x (start + tiles of a split), and the partial results written and read again.
+// Splits of fewer than 16 tiles, never taken before, serve the short calls: 36 queries x 4 heads per KV head, 8 KV heads, 2908
+// tokens, d = 128, b = 4: 96 us with two splits (32 of 256 compute units had work), 32 with 16, both with the encode of the 36; 646 x 1, 1335
+// tokens 91 / 41, 56 x 8, 378 tokens 44 / 25; one KV head, 347 x 8, 22097 tokens, d = 64 100 / 61.
+// Best of all split counts up to 64 / the one taken here (attention call): 200 x 1, 8 KV heads, 1000 tokens 18.2 / 18.2 us, 300 x 4, 2 KV
+// heads, 20000 75.0 / 75.0, 64 x 8, 16384 35.6 / 35.6, 509 x 4, 8 KV heads, 15877 295 / 295, 1335 tokens above 31.6 / 32.5; d = 64: 70 x 4,
+// 1500 15.2 / 15.2, 315 x 4, 8 KV heads, 22923 153.7 / 153.7, 800 x 1, 24 KV heads, 9000 148.3 / 148.3.
+// The workspace has to fit the documented size, which is that of the split count of make_decode_shape.
+static double many_rows_cost(const octopus_plan_t &plan, const DecodeShape &s, int64_t max_len, int64_t n) {
     const int64_t tiles = (std::max<int64_t>(max_len, 1) + OCTOPUS_TILE - 1) / OCTOPUS_TILE;
-    auto in_a_row = [&](const DecodeShape &x) {
-        const int64_t wgs = static_cast<int64_t>(x.n_seq) * x.n_kv_heads * x.n_row_groups * x.n_splits;
-        return (wgs + 255) / 256 * ((tiles + x.n_splits - 1) / x.n_splits);
+    const int64_t work = static_cast<int64_t>(s.n_seq) * s.n_kv_heads * s.n_row_groups * n;
+    const int64_t slots = plan.head_dim <= 64 && s.rows_per_pass == 128 ? 64 : 32;   // workgroups a die runs at once
+    const int64_t rounds = ((work + 7) / 8 + slots - 1) / slots;
+    const double tile = plan.head_dim <= 64 ? 2.25 : (s.rows_per_pass == 256 ? 4.2 : 3.3);
+    const double rows = static_cast<double>(s.n_seq) * s.n_kv_heads * s.rows_per_kv;
+    return rounds * (8.0 + tile * ((tiles + n - 1) / n)) + rows * n * plan.head_dim * 2.0e-6;
+}
+
+static void many_rows_splits(const octopus_codebooks_t *cb, int64_t max_len, DecodeShape *s, Workspace *w) {
+    const size_t limit = plain_decode_workspace(cb, s->n_seq, s->n_q_heads, s->n_kv_heads, s->n_q, max_len);
+    const int64_t tiles = (std::max<int64_t>(max_len, 1) + OCTOPUS_TILE - 1) / OCTOPUS_TILE;
+    double best = many_rows_cost(cb->plan, *s, max_len, s->n_splits);
+    auto consider = [&](DecodeShape x) {
+        for (int64_t n = 1; n <= 64 && n <= tiles; ++n) {
+            x.n_splits = static_cast<int32_t>(n);
+            const double cost = many_rows_cost(cb->plan, x, max_len, n);
+            if (cost >= best) continue;
+            const Workspace ww = make_workspace(cb->plan, x);
+            if (ww.total > limit) break;
+            best = cost;
+            *s = x;
+            *w = ww;
+        }
     };
-    if (4 * in_a_row(wide) > 3 * in_a_row(*s)) return;
-    *s = wide;
-    *w = ww;
+    consider(*s);
+    if (cb->plan.head_dim == 128 && s->rows_per_kv > 128)
+        consider(make_decode_shape(cb->plan, s->n_seq, s->n_q_heads, s->n_kv_heads, s->n_q, max_len, s->t_capacity, true, 8, 0, 1, true));
 }
 
 static int attn_decode(const octopus_codebooks_t *cb, const void *q, int32_t q_dtype, int32_t n_seq,
@@ -699,7 +708,7 @@ static int attn_decode(const octopus_codebooks_t *cb, const void *q, int32_t q_d
         s = make_decode_shape(cb->plan, n_seq, n_q_heads, n_kv_heads, n_q, max_len, t_capacity, many_rows, rows_cap, vq_mfma);
         w = make_workspace(cb->plan, s);
     }
-    if (many_rows) many_rows_at_128(cb, max_len, &s, &w);
+    if (many_rows) many_rows_splits(cb, max_len, &s, &w);
     const bool vector_kernel = with_vq ? vq_mfma == 0 : v_dtype != OCTOPUS_DTYPE_BF16;
     if (vector_kernel) s.tiles_per_step = 1;   // (decode_kernel_valu; the workspace has room for either)
     set_queries(&s, q, q_dtype, signs, signs2, scale);
@@ -985,7 +994,7 @@ static int attn_decode_paged(const octopus_codebooks_t *cb, const void *q, int32
     DecodeShape s = make_decode_shape(cb->plan, n_seq, n_q_heads, n_kv_heads, n_q, max_len, reach, many_rows, rows_cap,
                                       vq_waves, least_rows(cb->plan, many_rows, v_bits == 0, with_qjl, n_q * (n_q_heads / n_kv_heads)));
     Workspace w = make_workspace(cb->plan, s);
-    if (many_rows) many_rows_at_128(cb, max_len, &s, &w);
+    if (many_rows) many_rows_splits(cb, max_len, &s, &w);
     set_queries(&s, q, q_dtype, signs, with_qjl ? signs2 : nullptr, scale);
     const bool direct = direct_output(s, out, win != nullptr, with_qjl || (v_bits != 0 && s.item_waves == 4) || !joint_plan(cb->plan));
     set_division(&s, out, direct, false, cb->plan.head_dim);   // (pages hold bf16 values, or quantised ones for the matrix-core kernel)

@@ -79,3 +79,15 @@ def test_calls_that_are_always_merged(shapes):
         assert shapes(kind, 128, 3, 1, 8, 2, 1, 64)[3] == 1
     for kind in (BF16, PAGED):
         assert shapes(kind, 128, 3, 1, 8, 8, 130, 100)[3] == 1           # blocks of many query rows
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_splits_of_many_query_rows(shapes, d):
+    """Short calls are cut until most compute units have a workgroup, never finer than tiles; the workspace keeps its documented size
+    (the call is refused otherwise)."""
+    for n_seq, n_qh, n_kv, n_q, max_len in [(1, 32, 8, 36, 2908), (1, 8, 8, 646, 1335), (1, 64, 8, 56, 378), (1, 1, 1, 33, 64), (3, 4, 2, 40, 129)]:
+        rows, groups, splits, merged = shapes(False, d, 3, n_seq, n_qh, n_kv, n_q, max_len)
+        assert merged == 1 and 1 <= splits <= -(-max_len // 64)
+        assert shapes(True, d, 3, n_seq, n_qh, n_kv, n_q, max_len) == (rows, groups, splits, merged)
+    rows, groups, splits, _ = shapes(False, d, 4, 1, 32, 8, 36, 2908)
+    assert 128 <= 8 * groups * splits <= 256 * (2 if d == 64 else 1)
