@@ -45,19 +45,40 @@ struct SeedGrid {
 // wavefront with such a key in it (one in 300; zero and non-finite keys as well) also looks at the nine.
 // Equal scores of two corners are decided in the order of Alg. 1's loop, which runs towards the axis where the
 // coordinate is negative.  Signs cost nothing (the products take |x| and |y|), the corners lie at constant offsets from the
-// first one, so there is no table of neighbours: 4 lookups a triplet instead of 15, 71 vector instructions instead of 115.
+// first one, so there is no table of neighbours: 4 lookups a triplet instead of 15, 61 vector instructions instead of 115.
 //
-// The bracket is found as the seed is, through a grid, here of 2^b_dir cells over [0, 1] (no cell holds two levels: the
-// least gap between neighbours is 1.8 cells) and one more cell for an |xi| that rounds to a few ulp beyond 1.  Cell entry
-// {K / 2 + j, level}: the bracket is j + (level < |xi|); a cell without a level, or whose level ends no bracket, has
-// level = +inf.
+// The bracket is a rounded polynomial of the coordinate (linear up to 4 direction bits, whose levels are nearly evenly
+// spaced; a square term at 5): its steps need not lie on the levels, the winner is a corner of either bracket where they part
+// (by the same margins; tests/test_encoder_corners.py takes the steps as they are).  For the same reason the coordinates
+// need no more than the hardware's reciprocal.  Before, a grid of cells in LDS gave the bracket: a lookup and a compare more per axis
+// (71 vector instructions a triplet) and a table to build.  With the closed form of lone coordinates (TWO_PADS below): 16 x 32768 tokens x
+// 8 KV heads, d = 128, b = 3 561 -> 521 us; 4 sequences at b = 2 / b = 4 143 -> 131.5 / 203 -> 183; d = 64, 8 x 32768 x 8, b = 3 / 4 151 -> 134 /
+// 287 -> 197; d = 256, 4 x 16384 x 8, b = 2.5 223 -> 210.
+constexpr int log2_of(int x) { return x <= 1 ? 0 : 1 + log2_of(x / 2); }
 template <int BD>
 struct CornerGrid {
     static constexpr int K = 1 << BD, H = K / 2;
-    static constexpr int NCELL = K + 1;
-    __device__ static __forceinline__ int cell_of(float x) { return static_cast<int>(x * static_cast<float>(K)); }
+    // steps of the bracket: w = |xi| - 1 / 2 -> round(w (kSlope - kBend |w|) + H / 2 - 1), in 0 .. H - 2 for |w| <= kReach
+    static constexpr float kSlope = BD <= 3 ? 4.25f : (BD == 4 ? 8.4f : 17.2f), kBend = BD == 5 ? 1.8f : 0.0f;
+    static constexpr float kReach = BD <= 3 ? 0.34f : (BD == 4 ? 0.41f : 0.455f);
+    static constexpr uint32_t kOne = 0x4B000000u;   // the bits of 2^23: added to a number below 2^22 it leaves its integer in the low bits
+    // H + bracket, above it the bits of kOne; any w, NaN included
+    __device__ static __forceinline__ uint32_t bracket(float w) {
+        w = __builtin_amdgcn_fmed3f(w, -kReach, kReach);
+        const float slope = kBend != 0.0f ? fmaf(fabsf(w), -kBend, kSlope) : kSlope;
+        return __float_as_uint(fmaf(w, slope, 8388608.0f + static_cast<float>(H + H / 2 - 1)));
+    }
     // the margins next to an axis shrink with the levels: 2 |p_x| times the first level, and less where z < 0
     static constexpr float near_axis() { return BD <= 3 ? 1e-5f : 1.25e-6f * K; }
+    // What lane l adds to bracket(x) REP * 16 + bracket(y) H * REP * 16, modulo 2^32, for the byte offset of the bracket's first corner
+    // in its copy of the quadrant table.  (Opaque: taken apart, its large part keeps the table's address out of the LDS
+    // instructions' offsets.)
+    template <int REP>
+    __device__ static __forceinline__ uint32_t corner_start(int lane) {
+        uint32_t at = 0u - (kOne + H) * (REP * 16u) - (kOne + H) * (H * REP * 16u) + (static_cast<uint32_t>(lane) & (REP - 1)) * 16u;
+        asm volatile("" : "+v"(at));
+        return at;
+    }
 };
 
 // The direction table holds ONE QUADRANT of the code grid: a Lloyd-Max codebook of the symmetric marginal is
@@ -86,14 +107,14 @@ template <class P>
 constexpr int encode_threads() { return encode_waves<P>() * kWave; }
 
 // float2 entries of a class's grid (rep: its copies, lane l reads copy l mod rep) and of a neighbour table.
-constexpr int grid_cells(int bd, bool corners, int rep) { return bd < 1 ? 1 : (corners ? (1 << bd) + 1 : 8 * (1 << bd)) * rep; }
+constexpr int grid_cells(int bd, bool corners, int rep) { return bd < 1 || corners ? 1 : 8 * (1 << bd) * rep; }
 constexpr int axis_entries(int bd, bool corners) { return bd < 1 || corners ? 1 : (1 << bd) * 3; }
 template <class P, bool QJL, bool CORNERS>
 struct EncodeSmem {
     float u[3 * P::NTRI][kURow];           // rotated coordinates [coordinate][key]
     __attribute__((aligned(16))) uint32_t rec[P::NWORDS][kWave];   // packed records [word][key]
     static constexpr int REP = encode_table_rep<P::D, (P::BD0 > P::BD1 ? P::BD0 : P::BD1)>();
-    static constexpr int CREP = (CORNERS ? 8 : 2) / (P::D <= 128 ? 1 : 2);   // copies of the grid
+    static constexpr int CREP = P::D <= 128 ? 2 : 1;   // copies of the grid
     static constexpr int NX = P::BD0 > 2 || P::BD1 > 2 ? 1 << (P::BD0 > P::BD1 ? P::BD0 : P::BD1) : 4;
     static constexpr int NR = 1 << (P::BN0 > P::BN1 ? P::BN0 : P::BN1);
     float4 lut0[quadrant_entries(P::BD0) * REP];
@@ -196,31 +217,6 @@ __device__ __forceinline__ void build_seed_grid(float2 *cell, const float *bnd, 
         const float first = bnd[below];       // +inf past the last one
 #pragma unroll
         for (int r = 0; r < REP; ++r) cell[c * REP + r] = make_float2(__int_as_float(below), first);
-    }
-}
-
-// CornerGrid's cells: the cell of every level that separates two brackets (the positive ones but the first and the last),
-// one level per thread, then, per cell, how many of them lie in lower ones.
-template <int BD>
-__device__ __forceinline__ void build_level_cells(int *level_cell, const float *c_xi, int tid) {
-    using G = CornerGrid<BD>;
-    if (tid < kMaxLevels) level_cell[tid] = tid < G::H - 2 ? G::cell_of(c_xi[G::H + 1 + min(tid, G::H - 2)]) : G::NCELL;
-}
-template <int BD, int REP>
-__device__ __forceinline__ void build_corner_grid(float2 *cell, const float *c_xi, const int *level_cell, int tid, int nthreads) {
-    using G = CornerGrid<BD>;
-#pragma unroll 1
-    for (int c = tid; c < G::NCELL; c += nthreads) {
-        int below = 0;
-#pragma unroll
-        for (int k = 0; k < G::H; k += 4) {   // (entries past the last such level are in no lower cell; four exist)
-            const int4 at = *reinterpret_cast<const int4 *>(level_cell + k);
-            below += (at.x < c ? 1 : 0) + (at.y < c ? 1 : 0) + (at.z < c ? 1 : 0) + (at.w < c ? 1 : 0);
-        }
-        const float level = level_cell[below] == c ? c_xi[G::H + 1 + below] : INFINITY;
-        const float2 entry = make_float2(__int_as_float(G::H + below), level);
-#pragma unroll
-        for (int r = 0; r < REP; ++r) cell[c * REP + r] = entry;
     }
 }
 
@@ -344,35 +340,44 @@ __device__ __forceinline__ void encode_triplet(float x, float y, float z, const 
 // The same triplet with the four corners of its bracket as candidates; `valid`: the key is one that is stored (the others
 // are zeros, which would send every wavefront of a short append through the nine candidates); `pads`: how many of the
 // triplet's coordinates lie past the head dimension (y, z: zero).
-template <int BD, int BN, int REP, int CREP>
-__device__ __forceinline__ void encode_triplet_corners(float x, float y, float z, const float4 *lut, const float2 *cell,
+// TWO_PADS: the plan's last triplet has one coordinate of its own (d = 64 and 256), and y = z = 0 there: the outermost level of
+// x and, of the two next to eta = 0, the one that comes first.  (It lies on both axes, so every key looked at the nine: one
+// triplet in 22 at d = 64.)
+template <int BD, int BN, int REP, bool TWO_PADS>
+__device__ __forceinline__ void encode_triplet_corners(float x, float y, float z, const float4 *lut, uint32_t corner_start,
                                                        const float *bnd_xi, const float *bnd_rho, int lane, bool valid, int pads,
                                                        uint32_t *dir_field, uint32_t *nrm_index) {
     using G = CornerGrid<BD>;
     constexpr int K = G::K, H = G::H, M = 1 << BN;
-    // Eq. (oct-encode), as in encode_triplet
-    const float l1 = fabsf(x) + fabsf(y) + fabsf(z);
-    const float l1c = fmaxf(l1, kEps);
-    float inv = __builtin_amdgcn_rcpf(l1c);
-    inv = fmaf(fmaf(-l1c, inv, 1.0f), inv, inv);
-    const float px = x * inv, py = y * inv;
     const int neg_x = __float_as_int(x) >> 31, neg_y = __float_as_int(y) >> 31;   // 0 or -1
+    const char *base = reinterpret_cast<const char *>(lut + (lane & (REP - 1)));
     float best;
     uint32_t best_code;
-    int jx = H, jy = H;   // K / 2 + bracket
-    const char *base = reinterpret_cast<const char *>(lut + (lane & (REP - 1)));
+    uint32_t jx = G::kOne + H, jy = G::kOne + H;   // K / 2 + bracket
+    bool known;   // the winner is among the four
+    if (TWO_PADS && pads > 1) {
+        const float n = *reinterpret_cast<const float *>(base + (H - 1) * REP * 16);
+        best = fabsf(x) * n;
+        best_code = (static_cast<uint32_t>(~neg_x) & (K - 1)) | ((H - 1) << BD);
+        known = fabsf(x) > kEps && fabsf(x) < INFINITY;
+        if constexpr (H > 1) jx = G::bracket(fabsf(x) * __builtin_amdgcn_rcpf(fmaxf(fabsf(x), kEps)) - 0.5f);   // (where it is not)
+    } else {
+    // Eq. (oct-encode), as in encode_triplet, but that the reciprocal is the hardware's (about one unit in the last place)
+    const float l1 = fabsf(x) + fabsf(y) + fabsf(z);
+    const float inv = __builtin_amdgcn_rcpf(fmaxf(l1, kEps));
+    const float px = x * inv, py = y * inv;
     if constexpr (H == 1) {   // one level on either side: the signs are the code
         const float4 n = *reinterpret_cast<const float4 *>(base);
         best = fmaf(z, n.z, fmaf(fabsf(y), n.y, fabsf(x) * n.x));
         best_code = static_cast<uint32_t>((1 + neg_x) | ((1 + neg_y) << BD));
     } else {
-        const float xi = z < 0.0f ? 1.0f - fabsf(py) : fabsf(px), eta = z < 0.0f ? 1.0f - fabsf(px) : fabsf(py);
-        const float2 ex = cell[G::cell_of(xi) * CREP + (lane & (CREP - 1))];
-        const float2 ey = cell[G::cell_of(eta) * CREP + (lane & (CREP - 1))];
-        jx = __float_as_int(ex.x) + (ex.y < xi ? 1 : 0);
-        jy = __float_as_int(ey.x) + (ey.y < eta ? 1 : 0);
-        asm("" : "+v"(jx), "+v"(jy));   // (else the compare is kept apart and added a second time below)
-        const char *at = base + (jx * REP + jy * (H * REP)) * 16 - (H * REP + H * H * REP) * 16;
+        const float wx = fabsf(px) - 0.5f, wy = fabsf(py) - 0.5f;   // |xi| - 1 / 2 and |eta| - 1 / 2, where z < 0 folded over
+        jx = G::bracket(z < 0.0f ? -wy : wx);
+        jy = G::bracket(z < 0.0f ? -wx : wy);
+        uint32_t off;   // (written out: the compiler makes three instructions of the two shift-adds)
+        asm("v_lshl_add_u32 %0, %1, %2, %3" : "=v"(off) : "v"(jy), "n"(log2_of(H * REP * 16)), "v"(corner_start));
+        asm("v_lshl_add_u32 %0, %1, %2, %3" : "=v"(off) : "v"(jx), "n"(log2_of(REP * 16)), "v"(off));
+        const char *at = reinterpret_cast<const char *>(lut) + off;
         float sc[4];
 #pragma unroll
         for (int a = 0; a < 2; ++a)
@@ -390,12 +395,15 @@ __device__ __forceinline__ void encode_triplet_corners(float x, float y, float z
         const float lower = up_x ? sc[2] : sc[0], upper = up_x ? sc[3] : sc[1];
         const bool up_y = __float_as_int(upper) - neg_y > __float_as_int(lower);
         // K / 2 + level on the positive side of an axis, its complement on the negative one
-        const uint32_t code = static_cast<uint32_t>((jx + (up_x ? 1 : 0)) | ((jy + (up_y ? 1 : 0)) << BD));
-        const uint32_t flip = (static_cast<uint32_t>(neg_x) & (K - 1)) | (static_cast<uint32_t>(neg_y) & ~(K - 1u));
+        const uint32_t code = (jx + (up_x ? 1u : 0u)) | ((jy + (up_y ? 1u : 0u)) << BD);
+        uint32_t flip;
+        asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(flip) : "n"(K - 1), "v"(neg_x), "v"(neg_y));
         best_code = (code ^ flip) & (K * K - 1u);
     }
+    known = fminf(fminf(fabsf(px), fabsf(py)), l1 * (G::near_axis() / kEps)) > G::near_axis();
+    }
     // next to an axis, below the divisor's clamp, or not a number: the nine candidates around the seed
-    if (valid && !(fminf(fminf(fabsf(px), fabsf(py)), l1 * (G::near_axis() / kEps)) > G::near_axis())) {
+    if (valid && !known) {
         if (pads > 1) y = 0.0f;   // (zero times a scale factor that is not a number)
         if (pads > 0) z = 0.0f;
         const float l1x = fmaxf(fabsf(x) + fabsf(y) + fabsf(z), kEps);
@@ -414,7 +422,7 @@ __device__ __forceinline__ void encode_triplet_corners(float x, float y, float z
             const int h = v > 0.0f ? j + (b < v ? 1 : 0) : j + (b <= -v ? 1 : 0);
             return v > 0.0f ? h : (v <= 0.0f ? K - 1 - h : 0);   // (not a number: the first)
         };
-        const int sx = seed(xi, jx), sy = seed(eta, jy);
+        const int sx = seed(xi, static_cast<int>(jx - G::kOne)), sy = seed(eta, static_cast<int>(jy - G::kOne));
         best = -INFINITY;
         best_code = static_cast<uint32_t>(min(sx + 1, K - 1) | (min(sy + 1, K - 1) << BD));   // (no candidate is a number)
 #pragma clang loop unroll(disable)
@@ -634,17 +642,10 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
     int *bnd_cell = reinterpret_cast<int *>(&sm.rec[0][0]);   // (no record is being built yet)
     build_boundaries<P::BD0>(sm.bnd_xi[0], CORNERS ? nullptr : bnd_cell, sm.c_xi[0], tid);
     if constexpr (P::NCLASS == 2) build_boundaries<P::BD1>(sm.bnd_xi[1], CORNERS ? nullptr : bnd_cell + kMaxLevels, sm.c_xi[1], tid);
-    if constexpr (CORNERS) {   // (the grid is over the levels; the boundaries serve the keys next to an axis)
-        build_level_cells<P::BD0>(bnd_cell, sm.c_xi[0], tid);
-        if constexpr (P::NCLASS == 2) build_level_cells<P::BD1>(bnd_cell + kMaxLevels, sm.c_xi[1], tid);
-    }
     build_encode_lut<P::BD0, REP, CORNERS>(sm.lut0, sm.nbx0, sm.nby0, sm.c_xi[0], tid, NT);
     if constexpr (P::NCLASS == 2) build_encode_lut<P::BD1, REP, CORNERS>(sm.lut1, sm.nbx1, sm.nby1, sm.c_xi[1], tid, NT);
-    __syncthreads();
-    if constexpr (CORNERS) {
-        build_corner_grid<P::BD0, CREP>(sm.cell0, sm.c_xi[0], bnd_cell, tid, NT);
-        if constexpr (P::NCLASS == 2) build_corner_grid<P::BD1, CREP>(sm.cell1, sm.c_xi[1], bnd_cell + kMaxLevels, tid, NT);
-    } else {
+    if constexpr (!CORNERS) {   // (with the corners the boundaries serve the keys next to an axis only)
+        __syncthreads();
         build_seed_grid<P::BD0, CREP>(sm.cell0, sm.bnd_xi[0], bnd_cell, tid, NT);
         if constexpr (P::NCLASS == 2) build_seed_grid<P::BD1, CREP>(sm.cell1, sm.bnd_xi[1], bnd_cell + kMaxLevels, tid, NT);
     }
@@ -764,6 +765,8 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
             }
             const float *thr0 = THR0_REG ? thr0_reg : sm.bnd_rho[0];
             const float *thr1 = THR1_REG ? thr1_reg : sm.bnd_rho[P::NCLASS - 1];
+            const uint32_t corner0 = CornerGrid<P::BD0>::template corner_start<REP>(lane);
+            [[maybe_unused]] const uint32_t corner1 = P::NCLASS == 2 ? CornerGrid<(P::BD1 > 0 ? P::BD1 : 1)>::template corner_start<REP>(lane) : 0u;
             const float norm = sm.sumsq[lane];
             const bool valid = tile * kWave + lane >= tok_lo && tile * kWave + lane < tok_hi;
             // (gathered fields cost registers: with nine candidates those of two classes up to d = 128 spill, and of 32 norm levels and
@@ -787,7 +790,7 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
                         encode_triplet_any<P::BD0, P::BN0, REP, CREP>(x, y, z, sm.lut0, sm.cell0, sm.bnd_xi[0],
                                                                       sm.bnd_rho[0], lane, mode, &dir_field, &nrm_index);
                     else if constexpr (CORNERS)
-                        encode_triplet_corners<P::BD0, P::BN0, REP, CREP>(x, y, z, sm.lut0, sm.cell0, sm.bnd_xi[0], thr0, lane,
+                        encode_triplet_corners<P::BD0, P::BN0, REP, 3 * P::NTRI - D == 2>(x, y, z, sm.lut0, corner0, sm.bnd_xi[0], thr0, lane,
                                                                           valid, 3 * i + 3 - D, &dir_field, &nrm_index);
                     else
                         encode_triplet<P::BD0, P::BN0, REP, CREP>(x, y, z, sm.lut0, sm.cell0, sm.nbx0, sm.nby0,
@@ -801,7 +804,7 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
                             encode_triplet_any<P::BD1, P::BN1, REP, CREP>(x, y, z, sm.lut1, sm.cell1, sm.bnd_xi[1],
                                                                           sm.bnd_rho[1], lane, mode, &dir_field, &nrm_index);
                         else if constexpr (CORNERS)
-                            encode_triplet_corners<P::BD1, P::BN1, REP, CREP>(x, y, z, sm.lut1, sm.cell1, sm.bnd_xi[1], thr1, lane,
+                            encode_triplet_corners<P::BD1, P::BN1, REP, 3 * P::NTRI - D == 2>(x, y, z, sm.lut1, corner1, sm.bnd_xi[1], thr1, lane,
                                                                               valid, 3 * i + 3 - D, &dir_field, &nrm_index);
                         else
                             encode_triplet<P::BD1, P::BN1, REP, CREP>(x, y, z, sm.lut1, sm.cell1, sm.nbx1, sm.nby1,
@@ -903,10 +906,10 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
     }
 }
 
-// One triplet without tables, for the append kernel below: the brackets by comparison with every level, the four corners
-// (next to an axis: the nine candidates) by Oct^-1 of their levels, which is what the tables hold.
+// One triplet without tables, for the append kernel below: the four corners (next to an axis: the nine candidates) by Oct^-1 of
+// their levels, which is what the tables hold.  only_x: y and z lie past the head dimension (TWO_PADS above).
 template <int BD, int BN>
-__device__ __forceinline__ void encode_triplet_alone(float x, float y, float z, const float *c_xi, const float *c_rho,
+__device__ __forceinline__ void encode_triplet_alone(float x, float y, float z, bool only_x, const float *c_xi, const float *c_rho,
                                                      uint32_t *dir_field, uint32_t *nrm_index) {
     using G = CornerGrid<BD>;
     constexpr int K = G::K, H = G::H, M = 1 << BN;
@@ -918,15 +921,14 @@ __device__ __forceinline__ void encode_triplet_alone(float x, float y, float z, 
     const int neg_x = __float_as_int(x) >> 31, neg_y = __float_as_int(y) >> 31;   // 0 or -1
     float best;
     uint32_t best_code;
-    if (fminf(fminf(fabsf(px), fabsf(py)), l1 * (G::near_axis() / kEps)) > G::near_axis()) {
-        const float xi = z < 0.0f ? 1.0f - fabsf(py) : fabsf(px), eta = z < 0.0f ? 1.0f - fabsf(px) : fabsf(py);
-        int jx = H, jy = H;   // K / 2 + bracket
-#pragma unroll
-        for (int k = 1; k < H - 1; ++k) {
-            const float level = c_xi[H + k];
-            jx += level < xi ? 1 : 0;
-            jy += level < eta ? 1 : 0;
-        }
+    const float wx = fabsf(px) - 0.5f, wy = fabsf(py) - 0.5f;
+    const int jx = H > 1 ? static_cast<int>(G::bracket(z < 0.0f ? -wy : wx) - G::kOne) : H;   // K / 2 + bracket
+    const int jy = H > 1 ? static_cast<int>(G::bracket(z < 0.0f ? -wx : wy) - G::kOne) : H;
+    const bool far = fminf(fminf(fabsf(px), fabsf(py)), l1 * (G::near_axis() / kEps)) > G::near_axis();
+    if (only_x && l1 > kEps && l1 < INFINITY) {
+        best = fabsf(x) * oct_decode(c_xi[K - 1], c_xi[H]).x;
+        best_code = (static_cast<uint32_t>(~neg_x) & (K - 1)) | ((H - 1) << BD);
+    } else if (far) {
         constexpr int ENDS = H > 1 ? 2 : 1;
         float sc[4];
 #pragma unroll
@@ -952,18 +954,18 @@ __device__ __forceinline__ void encode_triplet_alone(float x, float y, float z, 
             xi = (px >= 0.0f) ? fx : -fx;
             eta = (py >= 0.0f) ? fy : -fy;
         }
-        int jx = 0, jy = 0;   // boundaries strictly below
-#pragma clang loop unroll(disable)
-        for (int k = 0; k < K - 1; ++k) {
-            const float b = 0.5f * (c_xi[k] + c_xi[k + 1]);
-            jx += b < xi ? 1 : 0;
-            jy += b < eta ? 1 : 0;
-        }
+        // the seeds (boundaries strictly below the coordinates) from the brackets, as in encode_triplet_corners
+        auto seed = [&](float v, int j) __attribute__((always_inline)) {
+            const float b = H > 1 ? 0.5f * (c_xi[j] + c_xi[H > 1 ? j + 1 : 0]) : INFINITY;
+            const int h = v > 0.0f ? j + (b < v ? 1 : 0) : j + (b <= -v ? 1 : 0);
+            return v > 0.0f ? h : (v <= 0.0f ? K - 1 - h : 0);
+        };
+        const int sx = seed(xi, jx), sy = seed(eta, jy);
         best = -INFINITY;
-        best_code = static_cast<uint32_t>(min(jx + 1, K - 1) | (min(jy + 1, K - 1) << BD));   // (no candidate is a number)
+        best_code = static_cast<uint32_t>(min(sx + 1, K - 1) | (min(sy + 1, K - 1) << BD));   // (no candidate is a number)
 #pragma clang loop unroll(disable)
         for (int c = 0; c < 9; ++c) {
-            const int cx = min(max(jx + c / 3 - 1, 0), K - 1), cy = min(max(jy + c % 3 - 1, 0), K - 1);
+            const int cx = min(max(sx + c / 3 - 1, 0), K - 1), cy = min(max(sy + c % 3 - 1, 0), K - 1);
             const float4 n = oct_decode(c_xi[cx], c_xi[cy]);
             const float s = fmaf(z, n.z, fmaf(y, n.y, x * n.x));
             if (s > best) { best = s; best_code = static_cast<uint32_t>(cx | (cy << BD)); }
@@ -980,7 +982,8 @@ __device__ __forceinline__ void encode_triplet_alone(float x, float y, float z, 
 // spends 9 us on such a call whatever it holds, tables and a chain of six triplets per wavefront, each with its LDS round
 // trips; here nothing is built and every triplet is on its way at once.  Same codes bit for bit (the same operands in every
 // addition of the transform and of the norm).  Bound by that chain: load, norm, 7 stages,
-// triplet, store.
+// triplet, store.  (A lone last coordinate, at d = 64 and 256, went through the nine candidates one after the other: 88 keys x 8 KV heads at
+// d = 64 9.3 -> 4.9 us, one key x 2 at d = 256 8.1 -> 5.1.)
 template <class P, bool BF16>
 __global__ __launch_bounds__(kWave) void encode_few_kernel(DeviceBooks books, const void *__restrict__ keys, int64_t stride_seq,
                                                            int64_t stride_tok, int64_t stride_head, int32_t n_new,
@@ -1059,14 +1062,14 @@ __global__ __launch_bounds__(kWave) void encode_few_kernel(DeviceBooks books, co
         uint32_t dir, nrm;
         int dir_bit, nrm_bit, dir_bits, nrm_bits;
         if (P::NCLASS == 1 || i < P::NT0) {
-            encode_triplet_alone<P::BD0, P::BN0>(a, b, c, c_xi[0], c_rho[0], &dir, &nrm);
+            encode_triplet_alone<P::BD0, P::BN0>(a, b, c, 3 * i + 1 >= D, c_xi[0], c_rho[0], &dir, &nrm);
             dir_bits = 2 * P::BD0;
             nrm_bits = P::BN0;
             dir_bit = P::DIR0_BIT + i * dir_bits;
             nrm_bit = P::NRM0_BIT + i * nrm_bits;
         } else {
             constexpr int BD1 = P::BD1 > 0 ? P::BD1 : 1, BN1 = P::BN1 > 0 ? P::BN1 : 1;
-            encode_triplet_alone<BD1, BN1>(a, b, c, c_xi[P::NCLASS - 1], c_rho[P::NCLASS - 1], &dir, &nrm);
+            encode_triplet_alone<BD1, BN1>(a, b, c, 3 * i + 1 >= D, c_xi[P::NCLASS - 1], c_rho[P::NCLASS - 1], &dir, &nrm);
             dir_bits = 2 * BD1;
             nrm_bits = BN1;
             dir_bit = P::DIR1_BIT + (i - P::NT0) * dir_bits;
