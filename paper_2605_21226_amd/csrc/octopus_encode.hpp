@@ -74,8 +74,10 @@ struct CornerGrid {
     // in its copy of the quadrant table.  (Opaque: taken apart, its large part keeps the table's address out of the LDS
     // instructions' offsets.)
     template <int REP>
+    static constexpr uint32_t kCornerStart = 0u - (kOne + H) * (REP * 16u) - (kOne + H) * (H * REP * 16u);
+    template <int REP>
     __device__ static __forceinline__ uint32_t corner_start(int lane) {
-        uint32_t at = 0u - (kOne + H) * (REP * 16u) - (kOne + H) * (H * REP * 16u) + (static_cast<uint32_t>(lane) & (REP - 1)) * 16u;
+        uint32_t at = kCornerStart<REP> + (static_cast<uint32_t>(lane) & (REP - 1)) * 16u;
         asm volatile("" : "+v"(at));
         return at;
     }
@@ -765,8 +767,10 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
             }
             const float *thr0 = THR0_REG ? thr0_reg : sm.bnd_rho[0];
             const float *thr1 = THR1_REG ? thr1_reg : sm.bnd_rho[P::NCLASS - 1];
-            const uint32_t corner0 = CornerGrid<P::BD0>::template corner_start<REP>(lane);
-            [[maybe_unused]] const uint32_t corner1 = P::NCLASS == 2 ? CornerGrid<(P::BD1 > 0 ? P::BD1 : 1)>::template corner_start<REP>(lane) : 0u;
+            [[maybe_unused]] uint32_t corner0 = 0u, corner1 = 0u;
+            using Grid1 = CornerGrid<(P::BD1 > 0 ? P::BD1 : 1)>;
+            if constexpr (CORNERS) corner0 = CornerGrid<P::BD0>::template corner_start<REP>(lane);
+            if constexpr (CORNERS && P::NCLASS == 2 && !QJL) corner1 = Grid1::template corner_start<REP>(lane);
             const float norm = sm.sumsq[lane];
             const bool valid = tile * kWave + lane >= tok_lo && tile * kWave + lane < tok_hi;
             // (gathered fields cost registers: with nine candidates those of two classes up to d = 128 spill, and of 32 norm levels and
@@ -803,10 +807,14 @@ void encode_kernel(DeviceBooks books, const void *__restrict__ keys,
                         if constexpr (ANY)
                             encode_triplet_any<P::BD1, P::BN1, REP, CREP>(x, y, z, sm.lut1, sm.cell1, sm.bnd_xi[1],
                                                                           sm.bnd_rho[1], lane, mode, &dir_field, &nrm_index);
-                        else if constexpr (CORNERS)
+                        else if constexpr (CORNERS) {
+                            if constexpr (QJL) {   // (a register less across the loop: it spills at d = 128, b = 2.5)
+                                corner1 = corner0 + (Grid1::template kCornerStart<REP> - CornerGrid<P::BD0>::template kCornerStart<REP>);
+                                asm volatile("" : "+v"(corner1));
+                            }
                             encode_triplet_corners<P::BD1, P::BN1, REP, 3 * P::NTRI - D == 2>(x, y, z, sm.lut1, corner1, sm.bnd_xi[1], thr1, lane,
                                                                               valid, 3 * i + 3 - D, &dir_field, &nrm_index);
-                        else
+                        } else
                             encode_triplet<P::BD1, P::BN1, REP, CREP>(x, y, z, sm.lut1, sm.cell1, sm.nbx1, sm.nby1,
                                                                       sm.bnd_xi[1], thr1, lane, &dir_field, &nrm_index);
                         if (i == P::NT0 && i > i_first) {   // the second class has its own streams
