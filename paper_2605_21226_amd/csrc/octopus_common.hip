@@ -1,6 +1,6 @@
 // Dispatch by head dimension and the kernels that do not depend on the bit width.
 #include "octopus_decode.hpp"
-#include "octopus_window.hpp"
+#include "octopus_merge.hpp"
 
 namespace octopus {
 
@@ -254,55 +254,33 @@ int launch_rotate_queries(const octopus_plan_t &plan, const void *q, int q_dtype
 }
 
 template <int D>
-static int merge_d(const DecodeShape &s, const float *part_ml, const float *part_acc, const int32_t *seq_lens,
-                   float *out, const float *win_ml, const float *win_acc, hipStream_t stream) {
+static int merge_d(const DecodeShape &s, const float *part_ml, const float *part_acc, const int32_t *seq_lens, float *out,
+                   hipStream_t stream) {
     const int64_t rows = static_cast<int64_t>(s.n_seq) * s.n_q * s.n_q_heads;
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(rows)), dim3(kWave), 0, stream, s, part_ml,
-                           part_acc, seq_lens, out, win_ml, win_acc);
+    auto go = [&](auto kernel, const WindowCall &w) {
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(rows)), dim3(kWave), 0, stream, s, w, part_ml, part_acc, seq_lens, out);
     };
-    if (s.two_round_blocks != 0) go(merge_kernel<D, true>); else go(merge_kernel<D, false>);
+    // (with a window the values are bf16 or, over the vector-unit kernel's two-round blocks, fp32)
+    const WindowCall *w = s.window;
+    const bool two = s.two_round_blocks != 0;
+    if (w == nullptr) {
+        if (two) go(merge_kernel<D, true, 0>, WindowCall{}); else go(merge_kernel<D, false, 0>, WindowCall{});
+    } else if (w->v_is_bf16) {
+        if (two) return static_cast<int>(hipErrorInvalidValue);
+        if (w->k_is_bf16) go(merge_kernel<D, false, 4>, *w); else go(merge_kernel<D, false, 3>, *w);
+    } else {
+        if (w->k_is_bf16) go(merge_kernel<D, true, 2>, *w); else go(merge_kernel<D, true, 1>, *w);
+    }
     return static_cast<int>(hipGetLastError());
 }
 
 int launch_merge(const octopus_plan_t &plan, const DecodeShape &s, const float *part_ml, const float *part_acc,
-                 const int32_t *seq_lens, float *out, const float *win_ml, const float *win_acc, void *stream) {
+                 const int32_t *seq_lens, float *out, const float *, const float *, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     switch (plan.head_dim) {
-        case 64: return merge_d<64>(s, part_ml, part_acc, seq_lens, out, win_ml, win_acc, st);
-        case 128: return merge_d<128>(s, part_ml, part_acc, seq_lens, out, win_ml, win_acc, st);
-        case 256: return merge_d<256>(s, part_ml, part_acc, seq_lens, out, win_ml, win_acc, st);
-        default: return static_cast<int>(hipErrorInvalidValue);
-    }
-}
-
-template <int D>
-static int window_d(const DecodeShape &s, const void *q, int q_dtype, const void *k_win, int k_dtype,
-                    int64_t w_capacity, const int32_t *win_lens, const void *v, int v_dtype, const int32_t *seq_lens,
-                    float scale, float *win_ml, float *win_acc, float *scores_out, PageTable pt, hipStream_t stream) {
-    const int64_t rows = static_cast<int64_t>(s.n_seq) * s.n_q * s.n_q_heads;
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(rows)), dim3(kWave), 0, stream, s, q,
-                           q_dtype == OCTOPUS_DTYPE_BF16 ? 1 : 0, k_win, w_capacity, win_lens, v, seq_lens, scale, win_ml,
-                           win_acc, scores_out, pt);
-    };
-    const bool kb = k_dtype == OCTOPUS_DTYPE_BF16, vb = v_dtype == OCTOPUS_DTYPE_BF16;
-    if (kb && vb) go(window_kernel<D, true, true>);
-    else if (kb) go(window_kernel<D, true, false>);
-    else if (vb) go(window_kernel<D, false, true>);
-    else go(window_kernel<D, false, false>);
-    return static_cast<int>(hipGetLastError());
-}
-
-int launch_window(const octopus_plan_t &plan, const DecodeShape &s, const void *q, int q_dtype, const void *k_win,
-                  int k_dtype, int64_t w_capacity, const int32_t *win_lens, const void *v, int v_dtype,
-                  const int32_t *seq_lens, float scale, float *win_ml, float *win_acc, float *scores_out,
-                  void *stream, PageTable pt) {
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    switch (plan.head_dim) {
-        case 64: return window_d<64>(s, q, q_dtype, k_win, k_dtype, w_capacity, win_lens, v, v_dtype, seq_lens, scale, win_ml, win_acc, scores_out, pt, st);
-        case 128: return window_d<128>(s, q, q_dtype, k_win, k_dtype, w_capacity, win_lens, v, v_dtype, seq_lens, scale, win_ml, win_acc, scores_out, pt, st);
-        case 256: return window_d<256>(s, q, q_dtype, k_win, k_dtype, w_capacity, win_lens, v, v_dtype, seq_lens, scale, win_ml, win_acc, scores_out, pt, st);
+        case 64: return merge_d<64>(s, part_ml, part_acc, seq_lens, out, st);
+        case 128: return merge_d<128>(s, part_ml, part_acc, seq_lens, out, st);
+        case 256: return merge_d<256>(s, part_ml, part_acc, seq_lens, out, st);
         default: return static_cast<int>(hipErrorInvalidValue);
     }
 }

@@ -1952,166 +1952,6 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) void decode_kernel_valu(
     }   // segments
 }
 
-// ---- D8: merge of the split partials, one wavefront per output row -----------------------------------
-// out = sum_j w_j acc_j / sum_j w_j l_j with w_j = exp(m_j - max_j m_j) (the flash-decoding identity).
-// A split without tokens has m = -inf, l = 0 and a zero accumulator, so it needs no special case.
-// Bound by latency (one load for the lengths, then the partials): with one partial per segment instead of four per item
-// of work, a long sequence has a quarter of the rows to read (one head over 4096 tokens: 11.6 us with 128 partials).
-// TWO: the call may be divided into blocks of two rounds (shp.two_round_blocks).
-template <int D, bool TWO>
-__global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, const float *__restrict__ part_ml,
-                                                      const float *__restrict__ part_acc,
-                                                      const int32_t *__restrict__ seq_lens, float *__restrict__ out,
-                                                      const float *__restrict__ win_ml,
-                                                      const float *__restrict__ win_acc) {
-    // win_ml / win_acc (or NULL): one more partial per output row, that of a native-precision window
-    constexpr int CPT = D / kWave;  // channels per lane
-    constexpr int UN = 8;           // partial rows in flight per lane
-    __shared__ float wgt[kWave];
-    const int lane = threadIdx.x;
-    int lens = seq_lens[min(lane, shp.n_seq - 1)];   // asked for before anything is computed
-    // (a launch has fewer than 2^32 threads, so a row's index fits 32 bits; divided as 64 bits it is 300 instructions)
-    const uint32_t urow = blockIdx.x;  // (seq, qi, head)
-    const int64_t orow = urow;
-    const int head = static_cast<int>(urow % static_cast<uint32_t>(shp.n_q_heads));
-    const uint32_t query = urow / static_cast<uint32_t>(shp.n_q_heads);
-    const int qi = static_cast<int>(query % static_cast<uint32_t>(shp.n_q));
-    const int seq = static_cast<int>(query / static_cast<uint32_t>(shp.n_q));
-    const int kvh = head / shp.heads_per_kv;
-    const int row = qi * shp.heads_per_kv + head % shp.heads_per_kv;
-    const int grp = row / shp.rows_per_pass, r = row % shp.rows_per_pass;
-    // Partial j of this row is at prow0 + j * pstride, j < n_part.  The many-row kernel (blocks of 128 or 256 rows):
-    // one partial per split, adjacent.  Otherwise: one per segment of this row's (sequence, KV head, row group); the
-    // segments' slots are consecutive, one per workgroup that has steps of the pair (the work distribution above).
-    int64_t prow0;
-    int n_part, pstride;
-    if (shp.rows_per_pass >= 128) {
-        prow0 = (((static_cast<int64_t>(seq) * shp.n_kv_heads + kvh) * shp.n_row_groups + grp) * shp.rows_per_pass + r) *
-                shp.n_splits;
-        n_part = shp.n_splits;
-        pstride = 1;
-    } else {
-        const uint64_t G = static_cast<uint64_t>(shp.n_kv_heads) * shp.n_row_groups;
-        uint64_t total = 0, before = 0;
-        uint32_t st = 0, own = 0;   // steps of sequence s0 + lane, and of this row's
-        auto read = [&](int s0) {
-            if (s0 > 0 || shp.n_seq > kWave) lens = seq_lens[min(s0 + lane, shp.n_seq - 1)];
-            st = s0 + lane < shp.n_seq ? static_cast<uint32_t>(steps_of(lens, shp.max_len, shp.tiles_per_step)) : 0u;
-        };
-        auto add = [&](int s0, uint32_t x) {   // x: per lane, of sequences s0 ..
-            const uint32_t sum = wave_scan(x);
-            if (seq >= s0 && seq < s0 + kWave) {
-                own = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(st), seq - s0));
-                before = total + static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sum - x), seq - s0));
-            }
-            total += last_lane(sum);
-        };
-        for (int s0 = 0; s0 < shp.n_seq; s0 += kWave) {
-            read(s0);
-            add(s0, st);
-        }
-        const uint64_t sum = total;
-        total *= G;
-        Division div{kDivideEvenly, shp.item_waves == 8 ? 3 : 2, shp.tiles_per_step};
-        if (__builtin_expect(shp.kind_known != 0 || !Division::surely_even<TWO>(shp, st, sum, total, div.waves_log2), 0)) {
-            if (shp.kind_known != 0) div.kind = shp.kind_known;
-            else div.template set<TWO>(shp, sum, [&](int s0) __attribute__((always_inline)) { read(s0); return st; });
-            if (div.kind != kDivideEvenly) {
-                total = 0;
-                for (int s0 = 0; s0 < shp.n_seq; s0 += kWave) {
-                    read(s0);
-                    add(s0, div.units(st));
-                }
-                total *= G;
-            }
-        }
-        const int g = kvh * shp.n_row_groups + grp;
-        const uint64_t first = before * G + static_cast<uint64_t>(g) * div.units(own) + div.fixed();   // the pair's first quantum
-        n_part = 0;
-        int wg = 0;
-        if (own > 0u) {
-            wg = div.owner(total, first);
-            n_part = div.owner(total, first + ((div.quanta(own) - 1u) << div.units_log2())) - wg + 1;
-        }
-        prow0 = (wg + static_cast<int64_t>(seq) * static_cast<int64_t>(G) + g) * shp.rows_per_pass + r;
-        pstride = shp.rows_per_pass;
-    }
-    // The first UN accumulator rows are requested before anything waits for the (m, l) pairs: their addresses do
-    // not depend on them, and with the usual handful of partials per row this is all there is to read.
-    float x_first[UN][CPT];
-#pragma unroll
-    for (int u = 0; u < UN; ++u)
-#pragma unroll
-        for (int c = 0; c < CPT; ++c)
-            x_first[u][c] = n_part > 0 ? part_acc[(prow0 + static_cast<int64_t>(min(u, n_part - 1)) * pstride) * D +
-                                                  c * kWave + lane]
-                                       : 0.0f;   // (an empty sequence has no partial)
-    float m = -INFINITY;
-    for (int j = lane; j < n_part; j += kWave) m = fmaxf(m, part_ml[(prow0 + static_cast<int64_t>(j) * pstride) * 2]);
-    m = wave_max(m);
-    // the many-row kernel's maxima are in units of log2, the others' and the window's in natural ones
-    const float unit = shp.rows_per_pass >= 128 ? 1.0f : kLog2e;
-    const float m_win = win_ml != nullptr ? win_ml[orow * 2] * (kLog2e / unit) : -INFINITY;
-    m = fmaxf(m, m_win);
-    float a[CPT];
-#pragma unroll
-    for (int c = 0; c < CPT; ++c) a[c] = 0.0f;
-    float l = 0.0f;
-    if (win_ml != nullptr) {
-        const float f = (m_win == -INFINITY) ? 0.0f : exp2_raw((m_win - m) * unit);
-        if (lane == 0) l = f * win_ml[orow * 2 + 1];
-#pragma unroll
-        for (int c = 0; c < CPT; ++c) a[c] = f * win_acc[orow * D + c * kWave + lane];
-    }
-    for (int j0 = 0; j0 < n_part; j0 += kWave) {
-        const int j = j0 + lane;
-        float f = 0.0f;
-        if (j < n_part) {
-            const float2 ml = *reinterpret_cast<const float2 *>(part_ml + (prow0 + static_cast<int64_t>(j) * pstride) * 2);
-            f = (ml.x == -INFINITY) ? 0.0f : exp2_raw((ml.x - m) * unit);
-            l += f * ml.y;
-        }
-        __syncthreads();
-        wgt[lane] = f;
-        __syncthreads();
-        const int nj = min(kWave, n_part - j0);
-        for (int jj = 0; jj < nj; jj += UN) {
-            float x[UN][CPT];
-            if (j0 == 0 && jj == 0) {
-#pragma unroll
-                for (int u = 0; u < UN; ++u)
-#pragma unroll
-                    for (int c = 0; c < CPT; ++c) x[u][c] = x_first[u][c];
-            } else {
-#pragma unroll
-                for (int u = 0; u < UN; ++u)
-#pragma unroll
-                    for (int c = 0; c < CPT; ++c)
-                        x[u][c] = part_acc[(prow0 + static_cast<int64_t>(j0 + min(jj + u, nj - 1)) * pstride) * D +
-                                           c * kWave + lane];
-            }
-            auto take = [&](int u) __attribute__((always_inline)) {
-                const float fj = wgt[jj + u];
-#pragma unroll
-                for (int c = 0; c < CPT; ++c) a[c] = fmaf(fj, x[u][c], a[c]);
-            };
-            if (jj + UN <= nj) {
-#pragma unroll
-                for (int u = 0; u < UN; ++u) take(u);
-            } else {   // (partials past the last stay out: at weight zero an infinity in it would count again, as 0 * inf)
-#pragma unroll
-                for (int u = 0; u < UN - 1; ++u) {
-                    if (jj + u >= nj) break;
-                    take(u);
-                }
-            }
-        }
-    }
-    l = wave_sum(l);
-#pragma unroll
-    for (int c = 0; c < CPT; ++c) out[orow * D + c * kWave + lane] = (l > 0.0f) ? a[c] / l : 0.0f;
-}
-
 // ---- launch helpers -----------------------------------------------------------------------------
 template <class P>
 int launch_decode_mq(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *cache,

@@ -309,7 +309,7 @@ Workspace make_workspace(const octopus_plan_t &plan, const DecodeShape &s) {
     const size_t plan_bytes = up((static_cast<size_t>(s.n_seq) + 5) * sizeof(int32_t));
     w.q2_off = w.plan_off + plan_bytes;   // second rotation of the queries (QJL residual only)
     w.win_ml_off = w.q2_off + up(rows * static_cast<size_t>(plan.head_dim) * sizeof(float));
-    // partial of a native-precision window, one per output row (hybrid cache only)
+    // (not used any more, a partial of a native-precision window per output row: kept in the documented size)
     const size_t out_rows = static_cast<size_t>(s.n_seq) * s.n_q * s.n_q_heads;
     w.win_acc_off = w.win_ml_off + up(out_rows * 2 * sizeof(float));
     w.total = w.win_acc_off + up(out_rows * static_cast<size_t>(plan.head_dim) * sizeof(float));
@@ -741,14 +741,13 @@ static int attn_decode(const octopus_codebooks_t *cb, const void *q, int32_t q_d
                                 stream);
     }
     if (err == 0 && ev_after != nullptr) err = record_event(ev_after, stream);
-    float *win_ml = nullptr, *win_acc = nullptr;
-    if (err == 0 && win != nullptr) {
-        win_ml = reinterpret_cast<float *>(base + w.win_ml_off);
-        win_acc = reinterpret_cast<float *>(base + w.win_acc_off);
-        err = launch_window(cb->plan, s, q, q_dtype, win->k_window, win->k_dtype, win->w_capacity, win->win_lens, v,
-                            v_dtype, seq_lens, scale, win_ml, win_acc, scores_out, stream);
+    WindowCall window;
+    if (win != nullptr) {
+        window = WindowCall{win->k_window, v, win->w_capacity, win->win_lens, scores_out, PageTable{nullptr, 0, 0},
+                            win->k_dtype == OCTOPUS_DTYPE_BF16 ? 1 : 0, v_dtype == OCTOPUS_DTYPE_BF16 ? 1 : 0};
+        s.window = &window;
     }
-    if (err == 0 && s.out == nullptr) err = launch_merge(cb->plan, s, part_ml, part_acc, seq_lens, out, win_ml, win_acc, stream);
+    if (err == 0 && s.out == nullptr) err = launch_merge(cb->plan, s, part_ml, part_acc, seq_lens, out, nullptr, nullptr, stream);
     return err == 0 ? OCTOPUS_OK : OCTOPUS_EHIP;
 }
 
@@ -1021,15 +1020,12 @@ static int attn_decode_paged(const octopus_codebooks_t *cb, const void *q, int32
             err = launch_decode_paged(*cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, nullptr, stream);
     }
     if (err == 0 && ev_after != nullptr) err = record_event(ev_after, stream);
-    float *win_ml = nullptr, *win_acc = nullptr;
-    if (err == 0 && win != nullptr) {
-        // the window's value rows follow the compressed tokens in the sequence's pages
-        win_ml = reinterpret_cast<float *>(base + w.win_ml_off);
-        win_acc = reinterpret_cast<float *>(base + w.win_acc_off);
-        err = launch_window(cb->plan, s, q, q_dtype, win->k_window, win->k_dtype, win->w_capacity, win->win_lens, v_pool,
-                            OCTOPUS_DTYPE_BF16, seq_lens, scale, win_ml, win_acc, nullptr, stream, pt);
+    WindowCall window;
+    if (win != nullptr) {   // its value rows follow the compressed tokens in the sequence's pages
+        window = WindowCall{win->k_window, v_pool, win->w_capacity, win->win_lens, nullptr, pt, win->k_dtype == OCTOPUS_DTYPE_BF16 ? 1 : 0, 1};
+        s.window = &window;
     }
-    if (err == 0 && s.out == nullptr) err = launch_merge(cb->plan, s, part_ml, part_acc, seq_lens, out, win_ml, win_acc, stream);
+    if (err == 0 && s.out == nullptr) err = launch_merge(cb->plan, s, part_ml, part_acc, seq_lens, out, nullptr, nullptr, stream);
     return err == 0 ? OCTOPUS_OK : OCTOPUS_EHIP;
 }
 

@@ -33,6 +33,24 @@ inline int q_row_stride(int n_tri) { return (3 * n_tri + 3) & ~3; }
 // How the decode kernels divide a call's steps (octopus_decode.hpp).
 enum : int { kDivideEvenly, kBlockEach, kPairsWeighed, kPairEach };
 
+// Paged cache: logical 64-token tile j of sequence s lives in page table[s * stride + j] of a pool of n_pages
+// pages; table NULL: the contiguous cache.
+struct PageTable {
+    const int32_t *table;
+    int32_t stride;
+    int32_t n_pages;
+};
+
+// Native-precision window of a hybrid cache: the kernel that merges a row's partial results adds the window's (octopus_merge.hpp).
+struct WindowCall {
+    const void *k_win, *v;       // keys of the window; the value rows that follow the compressed tokens' (pt: in pages, t_capacity is what the table addresses)
+    int64_t w_capacity;
+    const int32_t *win_lens;
+    float *scores_out;           // or NULL
+    PageTable pt;
+    int32_t k_is_bf16, v_is_bf16;
+};
+
 struct DecodeShape {
     int32_t n_seq, n_q_heads, n_kv_heads, n_q;
     int32_t heads_per_kv;   // n_q_heads / n_kv_heads
@@ -54,6 +72,7 @@ struct DecodeShape {
     int32_t kind_known;     // kBlockEach or kPairEach where the host knows it whatever the lengths, else 0
     int32_t two_round_blocks;   // calls of one to two rounds of steps per workgroup go by blocks of two rounds (Division::set)
     int32_t pairs_fill;     // there may be as many (sequence, KV head, row group) pairs with tokens as workgroups (256)
+    const WindowCall *window;   // host memory, for launch_merge: the call's window, or NULL
 };
 
 // Plans whose every class has a joint table (2 b_dir + b_nrm <= 10) score on the matrix cores where the kernel over bf16
@@ -63,14 +82,6 @@ inline bool joint_plan(const octopus_plan_t &p) {
         if (2 * p.b_dir[c] + p.b_nrm[c] > 10) return false;
     return true;
 }
-
-// Paged cache: logical 64-token tile j of sequence s lives in page table[s * stride + j] of a pool of n_pages
-// pages; table NULL: the contiguous cache.
-struct PageTable {
-    const int32_t *table;
-    int32_t stride;
-    int32_t n_pages;
-};
 
 // Workspace carve-up (all offsets multiples of 256 bytes).
 struct Workspace {
@@ -103,15 +114,10 @@ int launch_decode_qjl(const octopus_codebooks_t &cb, const DecodeShape &s, const
                       float *part_acc, float *scores_out, int32_t *work_plan, void *stream);
 // Query rows one workgroup of the QJL decode kernel serves at most (8); 0 if the plan is not built.
 int qjl_rows_cap(const octopus_plan_t &plan);
-// win_ml / win_acc: the partial of a native-precision window per output row, or NULL
+// With s.window, of a native-precision window too.  (The two pointers before `stream`: not used; part of the signature, which the
+// host-side test drivers stub.)
 int launch_merge(const octopus_plan_t &plan, const DecodeShape &s, const float *part_ml, const float *part_acc,
-                 const int32_t *seq_lens, float *out, const float *win_ml, const float *win_acc, void *stream);
-// Attention partial (m, l, acc) per output row over the native-precision window that follows the
-// compressed tokens of each sequence; pt: the value rows lie in pages (s.t_capacity = what the table addresses).
-int launch_window(const octopus_plan_t &plan, const DecodeShape &s, const void *q, int q_dtype, const void *k_win,
-                  int k_dtype, int64_t w_capacity, const int32_t *win_lens, const void *v, int v_dtype,
-                  const int32_t *seq_lens, float scale, float *win_ml, float *win_acc, float *scores_out,
-                  void *stream, PageTable pt = PageTable{nullptr, 0, 0});
+                 const int32_t *seq_lens, float *out, const float *, const float *, void *stream);
 int launch_encode(const octopus_codebooks_t &cb, const void *keys, int key_dtype, int64_t stride_seq,
                   int64_t stride_tok, int64_t stride_head, int32_t n_seq, int32_t n_kv_heads, int32_t n_new,
                   const uint8_t *signs, void *cache, int64_t t_capacity, const int32_t *start_pos,
