@@ -2002,7 +2002,8 @@ int launch_decode_paged_plan(const octopus_codebooks_t &cb, const DecodeShape &s
         case 4: return launch_decode_paged_rg<P, 4>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream);
         case 8: return launch_decode_paged_rg<P, 8>(cb, s, q_rot, k_pool, v_pool, pt, seq_lens, part_ml, part_acc, stream);
         case 128:
-        case 256:   // the many-row kernel (d <= 128), which takes the page table as an argument
+        case 256:
+        case 512:   // the many-row kernel (d <= 128), which takes the page table as an argument
             if constexpr (P::D <= 128) return launch_decode_mq<P>(cb, s, q_rot, k_pool, v_pool, seq_lens, part_ml, part_acc, stream, pt);
             return static_cast<int>(hipErrorInvalidValue);
         default: break;
@@ -2050,7 +2051,8 @@ int launch_decode_mfma_plan(const octopus_codebooks_t &cb, const DecodeShape &s,
         case 4: return launch_decode_mfma_rg<P, 4, SCORES>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, stream);
         case 8: return launch_decode_mfma_rg<P, 8, SCORES>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, scores_out, stream);
         case 128:
-        case 256:   // the many-row kernel: rows per workgroup
+        case 256:
+        case 512:   // the many-row kernel: rows per workgroup
             if constexpr (P::D <= 128 && !SCORES)
                 return launch_decode_mq<P>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, stream);
             return static_cast<int>(hipErrorInvalidValue);

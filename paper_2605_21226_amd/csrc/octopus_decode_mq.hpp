@@ -1,11 +1,11 @@
 // Decode attention for many query rows per KV head (a chunk of queries against the whole cache, e.g. the
 // 3600 queries of a video frame): Alg. 2 with the roles of a dense attention kernel.  Here the work per
 // key is a dense contraction over hundreds of rows, so both products run on the matrix cores; the keys
-// are still decoded on the fly from the packed records, once per block of 128 or 256 query rows, into an LDS
+// are still decoded on the fly from the packed records, once per block of 128, 256 or 512 query rows, into an LDS
 // tile and never reach memory.
 //
-// A workgroup of 4 or 8 wavefronts owns 128 or 256 query rows of one (sequence, KV head) (32 per wavefront)
-// and a range of 64-token tiles.  Per tile:
+// A workgroup of 4 or 8 wavefronts owns 128, 256 or 512 query rows of one (sequence, KV head) (one or two blocks of 32 per
+// wavefront) and a range of 64-token tiles.  Per tile:
 //   * stage (all wavefronts, one tile ahead, double-buffered LDS): lane = key; the record is unpacked,
 //     gamma * rho^ * n^ is looked up and multiplied, split into two bf16 numbers (hi = upper 16 bits,
 //     lo = the rest) and written to the key tile [key][coordinate]; the values of the tile are written
@@ -25,9 +25,14 @@
 
 namespace octopus {
 
-// Query rows per workgroup: 32 per wavefront, NW = 4 wavefronts (128 rows) or NW = 8 (256 rows, two wavefronts per SIMD
-// within 256 registers each).  The keys of a tile are decoded once per workgroup, so more rows mean less decoding; the host
-// picks 256 at d = 64 from 192 rows on, at d = 128 where the call is then faster (many_rows_splits).
+// Query rows per workgroup: NW = 4 wavefronts (128 rows) or NW = 8 (256 rows, two wavefronts per SIMD within 256 registers
+// each), RB = 1 or (d = 64, 512 rows) 2 blocks of 32 rows per wavefront, one after the other on each tile.  The keys of a tile
+// are decoded once per workgroup, so more rows mean less decoding; the host picks what the call is fastest with
+// (many_rows_splits).
+// 512 rows: a tile takes 4.1 us, two of 256 rows 4.5 (3600 queries x 24 heads, 75600 tokens, b = 4: 3930 -> 3710 us; 800 x 24, 9000
+// tokens 169 -> 144).  Tried and slower: the blocks interleaved so that one's scores are computed during the other's exponentials
+// (registers: 6300 us and more), the remainders of the queries in LDS (4220), the two blocks sharing each read of keys and values, 32
+// keys at a time (3700: the reads are not what bounds it), last blocks of few rows started after all others (3950).
 // What bounds it (cycles of a tile, timestamps, 8 wavefronts, d = 64, b = 4): first product 1050, softmax 1660, second
 // product 820, staging 1060 - 1400, barrier up to 700, of 5400.  A 32x32x16 product takes 32 cycles of the matrix core and
 // keeps the vector units of its SIMD from issuing for about 16 of them, so two wavefronts' 2 x 40 products and 2 x (about 30
@@ -51,7 +56,7 @@ struct MqSmem {
     uint16_t vt[2][D][VST];
 };
 
-template <class P, int NW>
+template <class P, int NW, int RB>
 __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D <= 64 || NW == 8 ? 2 : 1))) void decode_kernel_mq(DeviceBooks books, DecodeShape shp,
                                                          const uint4 *__restrict__ cache,
                                                          const uint16_t *__restrict__ v,
@@ -65,7 +70,8 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
     constexpr int NB = D / 32;               // 32-channel blocks of the output
     constexpr int ROWB = D * 2;              // bytes per value row
     constexpr int TILEB = P::GRANULES * kWave * 16;
-    constexpr int ROWS = 32 * NW;            // query rows per workgroup
+    constexpr int ROWS = 32 * NW * RB;       // query rows per workgroup: row 32 (NW b + w) + n is row n of wavefront w's block b
+    constexpr bool REF_BY_PRODUCT = RB == 2;
     constexpr int VP = D / 8 / NW;           // 16-byte value pieces per thread and tile
     using S = MqSmem<P>;
     __shared__ S sm;
@@ -88,7 +94,6 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
     const int grp = static_cast<int>(work - unit * static_cast<uint32_t>(shp.n_row_groups));
     const int64_t pair = unit / static_cast<uint32_t>(shp.n_splits);
     const int split = static_cast<int>(unit % static_cast<uint32_t>(shp.n_splits));
-    const int64_t group_id = pair * shp.n_row_groups + grp;
     const int seq = static_cast<int>(static_cast<uint32_t>(pair) / static_cast<uint32_t>(shp.n_kv_heads));
     const int kvh = static_cast<int>(static_cast<uint32_t>(pair) % static_cast<uint32_t>(shp.n_kv_heads));
     const int len = min(max(seq_lens[seq], 0), shp.max_len);
@@ -103,15 +108,17 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
 
     // Q^T operands of this wave's 32 rows: lane (n, h) holds coordinates 16 kk + 8 h .. + 8 of row n as bf16 hi and lo.
     union BF8 { uint32_t u[4]; bf16x8_t b; };
-    BF8 qh[KK], ql[KK];
+    BF8 qh[RB][KK], ql[RB][KK];
     // The rows are asked for here and rotated in place (rotate_queries below).
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
     u32x4_t q_raw[KK], q_more[KK];   // bf16 queries: the words of q_raw, two each
     uint32_t q_neg[KK];
     const int q_row = grp * ROWS + wave * 32 + n;
-    auto load_queries = [&]() __attribute__((always_inline)) {
+    // blocks of this wavefront that have rows: the others' products are left out
+    const int live = __builtin_amdgcn_readfirstlane(min(RB, (max(shp.rows_per_kv - grp * ROWS - wave * 32, 0) + 32 * NW - 1) / (32 * NW)));
+    auto load_queries = [&](int rb) __attribute__((always_inline)) {
         typedef uint32_t u32x4a_t __attribute__((ext_vector_type(4), aligned(4)));   // (queries are aligned to 4 bytes)
-        const int row = min(q_row, shp.rows_per_kv - 1);
+        const int row = min(q_row + 32 * NW * rb, shp.rows_per_kv - 1);
         const int qi = row / shp.heads_per_kv, head = kvh * shp.heads_per_kv + row % shp.heads_per_kv;
         const int64_t base_q = ((static_cast<int64_t>(seq) * shp.n_q + qi) * shp.n_q_heads + head) * D + 8 * h;
         const int es = shp.q_is_bf16 ? 2 : 4, second = shp.q_is_bf16 ? 0 : 16;   // (one path: the arrays written by two are kept in scratch memory)
@@ -127,9 +134,10 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
     // q_rot = scale H (s . q) of the 32 rows at once, all in registers (the same additions as rotate_queries_kernel's: the
     // butterflies of the element index's bits in ascending order, bit 3 is the lane's half).  The rotation was a launch of its own whose
     // 4-byte stores lay ROWS x 4 bytes apart: 53 us of 4005 for 3600 queries x 24 heads at d = 64, 19 of 325 for 509 x 32 at d = 128.
-    auto rotate_queries = [&]() __attribute__((always_inline)) {
+    auto rotate_queries = [&](auto block) __attribute__((always_inline)) {
+        constexpr int rb = decltype(block)::value;
         float x[KK][8];
-        const bool live = q_row < shp.rows_per_kv;
+        const bool there = q_row + 32 * NW * rb < shp.rows_per_kv;
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
@@ -137,7 +145,7 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
                 const u32x4_t lower = q_raw[kk], upper = q_more[kk];
                 const uint32_t pair_word = lower[e / 2], own_word = e < 4 ? lower[e & 3] : upper[e & 3];
                 const uint32_t bits = shp.q_is_bf16 ? ((e & 1) ? pair_word & 0xffff0000u : pair_word << 16) : own_word;
-                x[kk][e] = live ? __uint_as_float(bits ^ ((q_neg[kk] << (31 - e)) & 0x80000000u)) : 0.0f;
+                x[kk][e] = there ? __uint_as_float(bits ^ ((q_neg[kk] << (31 - e)) & 0x80000000u)) : 0.0f;
             }
 #pragma unroll
         for (int m = 1; m < 8; m <<= 1)
@@ -181,9 +189,9 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
                 // (in units of log2: the scores come out as exponents of two)
                 const float a = x[kk][2 * e] * norm * kLog2e, b = x[kk][2 * e + 1] * norm * kLog2e;
                 const uint32_t ab = __float_as_uint(a), bb = __float_as_uint(b);
-                qh[kk].u[e] = __builtin_amdgcn_perm(bb, ab, 0x07060302u);
+                qh[rb][kk].u[e] = __builtin_amdgcn_perm(bb, ab, 0x07060302u);
                 const float al = a - __uint_as_float(ab & 0xffff0000u), bl = b - __uint_as_float(bb & 0xffff0000u);
-                ql[kk].u[e] = __builtin_amdgcn_perm(__float_as_uint(bl), __float_as_uint(al), 0x07060302u);
+                ql[rb][kk].u[e] = __builtin_amdgcn_perm(__float_as_uint(bl), __float_as_uint(al), 0x07060302u);
             }
     };
 
@@ -298,20 +306,33 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
     // rescaled) only when a score exceeds it by more than kHeadroom, which after the first tile is rare: a probability may
     // then be up to 2^kHeadroom, which floating point does not mind.
     constexpr float kHeadroom = 8.0f;
-    float m_ref = 0.0f, l_run = 0.0f;
-    f32x16_t c_ref;
+    float m_ref[RB], l_run[RB];
+    f32x16_t oacc[RB][NB];
+    f32x16_t c_ref[REF_BY_PRODUCT ? 1 : RB];
+    // REF_BY_PRODUCT: 16 registers a block are too many; the accumulators start from a product of ones with three bf16 numbers
+    // that add up to the reference (24 bits: exactly), in its first slots.
+    BF8 minus_ref[RB], ones;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) c_ref[e] = 0.0f;
-    f32x16_t oacc[NB];
+    for (int k = 0; k < 4; ++k) ones.u[k] = h == 0 ? (k == 0 ? 0x3f803f80u : (k == 1 ? 0x00003f80u : 0u)) : 0u;
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+    for (int rb = 0; rb < RB; ++rb) {
+        m_ref[rb] = l_run[rb] = 0.0f;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) oacc[nb][e] = 0.0f;
+        for (int k = 0; k < 4; ++k) minus_ref[rb].u[k] = 0u;
+        if constexpr (!REF_BY_PRODUCT) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) c_ref[rb][e] = 0.0f;
+        }
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) oacc[rb][nb][e] = 0.0f;
+    }
 
     // Start: queries and first tile are asked for, then the tables (one copy: the lookups are a small part of this kernel) are
     // built and the queries rotated.  A split without tiles leaves an empty partial.
     if (tile_begin < tile_end) {
-        load_queries();
+        load_queries(0);
         load_tile(tile_begin);
         if (wave < 4) {   // a level per lane, of one array per wavefront
             typedef const float __attribute__((address_space(4))) *arg_t;
@@ -321,7 +342,11 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
         __syncthreads();
         build_dir_lut<P::BD0>(sm.dir0, sm.c_xi[0], tid, kWave * NW);
         if constexpr (P::NCLASS == 2) build_dir_lut<P::BD1>(sm.dir1, sm.c_xi[1], tid, kWave * NW);
-        rotate_queries();
+        rotate_queries(std::integral_constant<int, 0>{});
+        if constexpr (RB == 2) {
+            load_queries(1);
+            rotate_queries(std::integral_constant<int, 1>{});
+        }
         __syncthreads();                       // tables complete
         stage_tile(0);
         load_tile(min(tile_begin + 1, tile_end - 1));
@@ -338,88 +363,107 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
             stage_tile(buf ^ 1);
             load_tile(min(tile + 2, tile_end - 1));
         }
-        // S^T = K^ Q^T for the tile's two blocks of 32 keys
-        f32x16_t sacc[2];
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
-            sacc[mb] = c_ref;
+        for (int rb = 0; rb < RB; ++rb) {
+            if (rb >= live) break;   // (uniform)
+            __builtin_amdgcn_sched_barrier(0);   // (or registers spill)
+            // S^T = K^ Q^T for the tile's two blocks of 32 keys
+            f32x16_t sacc[2];
 #pragma unroll
-            for (int kk = 0; kk < KK; ++kk) {
-                BF8 ah, al;
-                *reinterpret_cast<uint4 *>(ah.u) = *reinterpret_cast<const uint4 *>(&sm.kh[buf][32 * mb + n][16 * kk + 8 * h]);
-                *reinterpret_cast<uint4 *>(al.u) = *reinterpret_cast<const uint4 *>(&sm.kl[buf][32 * mb + n][16 * kk + 8 * h]);
-                sacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah.b, qh[kk].b, sacc[mb], 0, 0, 0);
-                sacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah.b, ql[kk].b, sacc[mb], 0, 0, 0);
-                sacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al.b, qh[kk].b, sacc[mb], 0, 0, 0);
+            for (int mb = 0; mb < 2; ++mb) {
+                if constexpr (REF_BY_PRODUCT) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) sacc[mb][e] = 0.0f;
+                    sacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones.b, minus_ref[rb].b, sacc[mb], 0, 0, 0);
+                } else {
+                    sacc[mb] = c_ref[rb];
+                }
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk) {
+                    BF8 ah, al;
+                    *reinterpret_cast<uint4 *>(ah.u) = *reinterpret_cast<const uint4 *>(&sm.kh[buf][32 * mb + n][16 * kk + 8 * h]);
+                    *reinterpret_cast<uint4 *>(al.u) = *reinterpret_cast<const uint4 *>(&sm.kl[buf][32 * mb + n][16 * kk + 8 * h]);
+                    sacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah.b, qh[rb][kk].b, sacc[mb], 0, 0, 0);
+                    sacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah.b, ql[rb][kk].b, sacc[mb], 0, 0, 0);
+                    sacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al.b, qh[rb][kk].b, sacc[mb], 0, 0, 0);
+                }
             }
-        }
-        // keys past the end of the sequence (last tile only): element e of block mb is key
-        // 32 mb + 8 (e / 4) + 4 h + e % 4
-        const int n_valid = len - tile * kWave;
-        if (n_valid < kWave) {
+            // keys past the end of the sequence (last tile only): element e of block mb is key
+            // 32 mb + 8 (e / 4) + 4 h + e % 4
+            const int n_valid = len - tile * kWave;
+            if (n_valid < kWave) {
+                const int valid = n_valid - 4 * h;
+#pragma unroll
+                for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        if (32 * mb + 8 * (e / 4) + (e % 4) >= valid) sacc[mb][e] = -INFINITY;
+            }
+            // online softmax of this lane's row (its other 32 keys of the tile are in lane + 32)
+            float mx = sacc[0][0];
 #pragma unroll
             for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    if (32 * mb + 8 * (e / 4) + 4 * h + (e % 4) >= n_valid) sacc[mb][e] = -INFINITY;
-        }
-        // online softmax of this lane's row (its other 32 keys of the tile are in lane + 32)
-        float mx = sacc[0][0];
+                for (int e = mb == 0 ? 1 : 0; e < 16; e += 2) mx = fmaxf(fmaxf(mx, sacc[mb][e]), sacc[mb][e + 1 < 16 ? e + 1 : e]);
+            {
+                float other = mx, own = mx;
+                swap32(own, other);                    // the row's other half of the tile is in lane ^ 32
+                mx = fmaxf(own, other);
+            }
+            const bool first = tile == tile_begin;
+            if (first || __ballot(mx > kHeadroom) != 0) {
+                const float delta = first ? mx : fmaxf(mx, 0.0f);
+                m_ref[rb] += delta;
+                if constexpr (REF_BY_PRODUCT) {
+                    const float r0 = -m_ref[rb], r1 = r0 - __uint_as_float(__float_as_uint(r0) & 0xffff0000u);
+                    const float r2 = r1 - __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
+                    minus_ref[rb].u[0] = __builtin_amdgcn_perm(__float_as_uint(r1), __float_as_uint(r0), 0x07060302u);
+                    minus_ref[rb].u[1] = __float_as_uint(r2) >> 16;
+                } else {
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+                    for (int e = 0; e < 16; ++e) c_ref[rb][e] = -m_ref[rb];
+                }
 #pragma unroll
-            for (int e = mb == 0 ? 1 : 0; e < 16; e += 2) mx = fmaxf(fmaxf(mx, sacc[mb][e]), sacc[mb][e + 1 < 16 ? e + 1 : e]);
-        {
-            float other = mx, own = mx;
-            swap32(own, other);                    // the row's other half of the tile is in lane ^ 32
-            mx = fmaxf(own, other);
-        }
-        const bool first = tile == tile_begin;
-        if (first || __ballot(mx > kHeadroom) != 0) {
-            const float delta = first ? mx : fmaxf(mx, 0.0f);
-            m_ref += delta;
+                for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) c_ref[e] = -m_ref;
+                    for (int e = 0; e < 16; ++e) sacc[mb][e] -= delta;
+                if (!first) {
+                    const float alpha = exp2_raw(-delta);
+                    l_run[rb] *= alpha;
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) oacc[rb][nb][e] *= alpha;
+                }
+            }
+            float psum = 0.0f;
+            BF8 ph[4], pl[4];   // per group of 16 keys: the 8 k-slots of this lane, hi and lo
 #pragma unroll
             for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) sacc[mb][e] -= delta;
-            if (!first) {
-                const float alpha = exp2_raw(-delta);
-                l_run *= alpha;
+                for (int e = 0; e < 16; e += 2) {
+                    const float p0 = exp2_raw(sacc[mb][e]), p1 = exp2_raw(sacc[mb][e + 1]);
+                    psum += p0 + p1;
+                    // (the remainders as v_dot2_f32_bf16 of the packed pair with (-1, 0): one instruction instead of two, and slower)
+                    const uint32_t b0 = __float_as_uint(p0), b1 = __float_as_uint(p1);
+                    const float l0 = p0 - __uint_as_float(b0 & 0xffff0000u), l1 = p1 - __uint_as_float(b1 & 0xffff0000u);
+                    ph[2 * mb + e / 8].u[(e % 8) / 2] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+                    pl[2 * mb + e / 8].u[(e % 8) / 2] = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
+                }
+            l_run[rb] += psum;
+            // O^T += V^T P^T
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
+            for (int g16 = 0; g16 < 4; ++g16)
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) oacc[nb][e] *= alpha;
-            }
+                for (int nb = 0; nb < NB; ++nb) {
+                    BF8 va;
+                    const uint16_t *vrow = &sm.vt[buf][32 * nb + n][16 * g16 + 4 * h];
+                    const uint2 x0 = *reinterpret_cast<const uint2 *>(vrow), x1 = *reinterpret_cast<const uint2 *>(vrow + 8);
+                    va.u[0] = x0.x; va.u[1] = x0.y; va.u[2] = x1.x; va.u[3] = x1.y;
+                    oacc[rb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va.b, ph[g16].b, oacc[rb][nb], 0, 0, 0);
+                    oacc[rb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va.b, pl[g16].b, oacc[rb][nb], 0, 0, 0);
+                }
         }
-        float psum = 0.0f;
-        BF8 ph[4], pl[4];   // per group of 16 keys: the 8 k-slots of this lane, hi and lo
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int e = 0; e < 16; e += 2) {
-                const float p0 = exp2_raw(sacc[mb][e]), p1 = exp2_raw(sacc[mb][e + 1]);
-                psum += p0 + p1;
-                // (the remainders as v_dot2_f32_bf16 of the packed pair with (-1, 0): one instruction instead of two, and slower)
-                const uint32_t b0 = __float_as_uint(p0), b1 = __float_as_uint(p1);
-                const float l0 = p0 - __uint_as_float(b0 & 0xffff0000u), l1 = p1 - __uint_as_float(b1 & 0xffff0000u);
-                ph[2 * mb + e / 8].u[(e % 8) / 2] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
-                pl[2 * mb + e / 8].u[(e % 8) / 2] = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
-            }
-        l_run += psum;
-        // O^T += V^T P^T
-#pragma unroll
-        for (int g16 = 0; g16 < 4; ++g16)
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                BF8 va;
-                const uint16_t *vrow = &sm.vt[buf][32 * nb + n][16 * g16 + 4 * h];
-                const uint2 x0 = *reinterpret_cast<const uint2 *>(vrow), x1 = *reinterpret_cast<const uint2 *>(vrow + 8);
-                va.u[0] = x0.x; va.u[1] = x0.y; va.u[2] = x1.x; va.u[3] = x1.y;
-                oacc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va.b, ph[g16].b, oacc[nb], 0, 0, 0);
-                oacc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va.b, pl[g16].b, oacc[nb], 0, 0, 0);
-            }
         // stage the next tile into the other buffer, request the one after
         if (!stage_first && tile + 1 < tile_end) {
             stage_tile(buf ^ 1);
@@ -429,18 +473,20 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
     }
 
     // partial of each row: element e of block nb is channel 32 nb + 8 (e / 4) + 4 h + e % 4 of row n
-    const int row = wave * 32 + n;
-    if (grp * ROWS + row < shp.rows_per_kv) {
-        const int64_t prow = (group_id * ROWS + row) * shp.n_splits + split;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        const int row = grp * ROWS + 32 * NW * rb + wave * 32 + n;
+        if (row >= shp.rows_per_kv) continue;
+        const int64_t prow = (pair * shp.rows_per_kv + row) * shp.n_splits + split;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4)
                 *reinterpret_cast<float4 *>(part_acc + prow * D + 32 * nb + 8 * q4 + 4 * h) =
-                    make_float4(oacc[nb][4 * q4], oacc[nb][4 * q4 + 1], oacc[nb][4 * q4 + 2], oacc[nb][4 * q4 + 3]);
-        const float l = l_run + __shfl_xor(l_run, 32, kWave);
+                    make_float4(oacc[rb][nb][4 * q4], oacc[rb][nb][4 * q4 + 1], oacc[rb][nb][4 * q4 + 2], oacc[rb][nb][4 * q4 + 3]);
+        const float l = l_run[rb] + __shfl_xor(l_run[rb], 32, kWave);
         if (h == 0) {
-            part_ml[prow * 2] = tile_begin < tile_end ? m_ref : -INFINITY;   // in units of log2
+            part_ml[prow * 2] = tile_begin < tile_end ? m_ref[rb] : -INFINITY;   // in units of log2
             part_ml[prow * 2 + 1] = l;
         }
     }
@@ -453,16 +499,18 @@ int launch_decode_mq(const octopus_codebooks_t &cb, const DecodeShape &s, const 
     const DeviceBooks books = device_books(cb);
     const int64_t work = static_cast<int64_t>(s.n_seq) * s.n_kv_heads * s.n_splits * s.n_row_groups;
     const int64_t wgs = (work + kXcds - 1) / kXcds * kXcds;   // see the kernel's work mapping
-    if (wgs * s.rows_per_pass * 2 > UINT32_MAX) return static_cast<int>(hipErrorInvalidValue);   // (threads of a launch)
+    if (wgs * std::min(s.rows_per_pass, 256) * 2 > UINT32_MAX) return static_cast<int>(hipErrorInvalidValue);   // (threads of a launch)
     auto go = [&](auto kernel, int waves) {
         hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(wgs)), dim3(kWave * waves), 0, stream, books, s,
                            static_cast<const uint4 *>(cache), static_cast<const uint16_t *>(v), seq_lens, part_ml, part_acc,
                            pt);
     };
     if (s.rows_per_pass == 128) {
-        go(decode_kernel_mq<P, 4>, 4);
+        go(decode_kernel_mq<P, 4, 1>, 4);
     } else if (s.rows_per_pass == 256) {
-        go(decode_kernel_mq<P, 8>, 8);
+        go(decode_kernel_mq<P, 8, 1>, 8);
+    } else if (P::D <= 64 && s.rows_per_pass == 512) {
+        if constexpr (P::D <= 64) go(decode_kernel_mq<P, 8, 2>, 8);
     } else {
         return static_cast<int>(hipErrorInvalidValue);
     }

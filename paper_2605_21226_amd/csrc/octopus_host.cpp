@@ -238,9 +238,9 @@ DecodeShape make_decode_shape(const octopus_plan_t &plan, int32_t n_seq, int32_t
     if (many_rows) {
         // Matrix-core kernel for many query rows: blocks of 128 rows (4 wavefronts), or of 256 rows (8
         // wavefronts) when there are rows enough; one workgroup per (block, split).  A compute unit runs 8 of these
-        // wavefronts, or 4 with blocks of 128 rows at d = 128.  The blocks of 256 at d = 128 (wide_rows) came later than the
-        // documented workspace size, which stays that of blocks of 128: see many_rows_splits.
-        s.rows_per_pass = (plan.head_dim <= 64 ? s.rows_per_kv >= 192 : wide_rows) ? 256 : 128;
+        // wavefronts, or 4 with blocks of 128 rows at d = 128.  Blocks of 256 at d = 128 and of 512 at d = 64 (wide_rows) came
+        // later than the documented workspace size, which stays that of blocks of 128 and 256: see many_rows_splits.
+        s.rows_per_pass = plan.head_dim <= 64 ? (wide_rows ? 512 : (s.rows_per_kv >= 192 ? 256 : 128)) : (wide_rows ? 256 : 128);
         s.n_row_groups = (s.rows_per_kv + s.rows_per_pass - 1) / s.rows_per_pass;
         const int64_t groups = static_cast<int64_t>(n_seq) * n_kv_heads * s.n_row_groups;
         const int64_t max_tiles = (len + OCTOPUS_TILE - 1) / OCTOPUS_TILE;
@@ -612,9 +612,10 @@ static void set_division(DecodeShape *s, float *out, bool direct, bool vector_ke
     s->two_round_blocks = vector_kernel && head_dim <= 128 ? 1 : 0;
 }
 
-// Splits of the many-row kernel, and at d = 128 its block of query rows (128 or, two wavefronts per SIMD and each key decoded
-// for twice the rows, 256): those of the least cost, which is what the call takes in microseconds: rounds of workgroups (a die has an
-// eighth of them, see the kernel's work mapping) x (start + tiles of a split), and the partial results written and read again.
+// Splits of the many-row kernel, and its block of query rows (at d = 128 128 or, two wavefronts per SIMD and each key decoded
+// for twice the rows, 256; at d = 64 from 257 rows on 256 or 512): those of the least cost, which is what the call takes in
+// microseconds: rounds of workgroups (a die has an eighth of them, see the kernel's work mapping) x (start + tiles of a split), and
+// the partial results written and read again.
 // Splits of fewer than 16 tiles, never taken before, serve the short calls: 36 queries x 4 heads per KV head, 8 KV heads, 2908
 // tokens, d = 128, b = 4: 96 us with two splits (32 of 256 compute units had work), 32 with 16, both with the encode of the 36; 646 x 1, 1335
 // tokens 91 / 41, 56 x 8, 378 tokens 44 / 25; one KV head, 347 x 8, 22097 tokens, d = 64 100 / 61.
@@ -627,21 +628,32 @@ static double many_rows_cost(const octopus_plan_t &plan, const DecodeShape &s, i
     const int64_t work = static_cast<int64_t>(s.n_seq) * s.n_kv_heads * s.n_row_groups * n;
     const int64_t slots = plan.head_dim <= 64 && s.rows_per_pass == 128 ? 64 : 32;   // workgroups a die runs at once
     const int64_t rounds = ((work + 7) / 8 + slots - 1) / slots;
-    const double tile = plan.head_dim <= 64 ? 2.25 : (s.rows_per_pass == 256 ? 4.2 : 3.3);
+    const double tile = plan.head_dim <= 64 ? (s.rows_per_pass == 512 ? 4.1 : 2.25) : (s.rows_per_pass == 256 ? 4.2 : 3.3);
     const double rows = static_cast<double>(s.n_seq) * s.n_kv_heads * s.rows_per_kv;
     return rounds * (8.0 + tile * ((tiles + n - 1) / n)) + rows * n * plan.head_dim * 2.0e-6;
+}
+
+// Where the partial results of the many-row kernel lie: one per query row and split, and it needs nothing else.
+static Workspace many_rows_workspace(const octopus_plan_t &plan, const DecodeShape &s) {
+    auto up = [](size_t x) { return (x + 255) & ~static_cast<size_t>(255); };
+    const size_t partials = static_cast<size_t>(s.n_seq) * s.n_kv_heads * s.rows_per_kv * s.n_splits;
+    Workspace w{};
+    w.part_acc_off = up(partials * 2 * sizeof(float));
+    w.total = w.part_acc_off + up(partials * static_cast<size_t>(plan.head_dim) * sizeof(float));
+    return w;
 }
 
 static void many_rows_splits(const octopus_codebooks_t *cb, int64_t max_len, DecodeShape *s, Workspace *w) {
     const size_t limit = plain_decode_workspace(cb, s->n_seq, s->n_q_heads, s->n_kv_heads, s->n_q, max_len);
     const int64_t tiles = (std::max<int64_t>(max_len, 1) + OCTOPUS_TILE - 1) / OCTOPUS_TILE;
+    *w = many_rows_workspace(cb->plan, *s);   // (always within the limit)
     double best = many_rows_cost(cb->plan, *s, max_len, s->n_splits);
     auto consider = [&](DecodeShape x) {
         for (int64_t n = 1; n <= 64 && n <= tiles; ++n) {
             x.n_splits = static_cast<int32_t>(n);
             const double cost = many_rows_cost(cb->plan, x, max_len, n);
             if (cost >= best) continue;
-            const Workspace ww = make_workspace(cb->plan, x);
+            const Workspace ww = many_rows_workspace(cb->plan, x);
             if (ww.total > limit) break;
             best = cost;
             *s = x;
@@ -649,7 +661,7 @@ static void many_rows_splits(const octopus_codebooks_t *cb, int64_t max_len, Dec
         }
     };
     consider(*s);
-    if (cb->plan.head_dim == 128 && s->rows_per_kv > 128)
+    if (s->rows_per_kv > (cb->plan.head_dim == 128 ? 128 : 256))
         consider(make_decode_shape(cb->plan, s->n_seq, s->n_q_heads, s->n_kv_heads, s->n_q, max_len, s->t_capacity, true, 8, 0, 1, true));
 }
 

@@ -55,7 +55,7 @@ struct DecodeShape {
     int32_t n_seq, n_q_heads, n_kv_heads, n_q;
     int32_t heads_per_kv;   // n_q_heads / n_kv_heads
     int32_t rows_per_kv;    // n_q * heads_per_kv query rows sharing one KV head
-    int32_t rows_per_pass;  // query rows one workgroup scores per key (1, 2, 4 or 8; 128 or 256: many-row kernel)
+    int32_t rows_per_pass;  // query rows one workgroup scores per key (1, 2, 4 or 8; 128, 256 or 512: many-row kernel)
     int32_t n_row_groups;   // ceil(rows_per_kv / rows_per_pass)
     int32_t n_splits;       // many-row kernel: workgroups sharing the tiles of one (sequence, KV head, row group)
     int32_t max_items;      // what the partials' part of the workspace is sized for (row groups of at most 8)

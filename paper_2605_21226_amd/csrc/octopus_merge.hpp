@@ -229,14 +229,13 @@ __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, WindowCal
         win_len = window.win_lens[seq];
         win.load_query(shp, orow, win_smem);
     }
-    // Partial j of this row is at prow0 + j * pstride, j < n_part.  The many-row kernel (blocks of 128 or 256 rows):
+    // Partial j of this row is at prow0 + j * pstride, j < n_part.  The many-row kernel (blocks of 128 rows or more):
     // one partial per split, adjacent.  Otherwise: one per segment of this row's (sequence, KV head, row group); the
     // segments' slots are consecutive, one per workgroup that has steps of the pair (the work distribution above).
     int64_t prow0;
     int n_part, pstride;
     if (shp.rows_per_pass >= 128) {
-        prow0 = (((static_cast<int64_t>(seq) * shp.n_kv_heads + kvh) * shp.n_row_groups + grp) * shp.rows_per_pass + r) *
-                shp.n_splits;
+        prow0 = ((static_cast<int64_t>(seq) * shp.n_kv_heads + kvh) * shp.rows_per_kv + row) * shp.n_splits;
         n_part = shp.n_splits;
         pstride = 1;
     } else {

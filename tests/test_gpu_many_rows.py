@@ -48,3 +48,19 @@ def test_decode_many_rows_blocks_of_256_at_128_paged(bits):
 
 def test_decode_many_rows_blocks_of_256_at_128_paged_with_window():
     run_paged_hybrid_case(128, 3, 9, 8, 8, 385, WIDE_LENS, [32, 5, 0, 7, 32, 1, 16, 31, 2], 32, "bf16", seed=700)
+
+
+# d = 64 with blocks of 512 rows (two blocks of 32 rows per wavefront): three of them, the last with 76 rows (wavefronts with one
+# block and with none), at every width, over pages and with a window; and several splits with a last block of 288 rows, where a row's
+# reference moves between tiles
+@pytest.mark.parametrize("bits", [1, 1.5, 2, 2.5, 3, 4])
+def test_decode_many_rows_blocks_of_512(bits):
+    run_decode_case(64, bits, 9, 8, 8, 1100, WIDE_LENS, "bf16", seed=int(800 + 10 * bits), want_scores=False)
+
+
+def test_decode_many_rows_blocks_of_512_several_splits():
+    run_decode_case(64, 3, 1, 24, 24, 800, [3000], "bf16", seed=901, want_scores=False)
+
+
+def test_decode_many_rows_blocks_of_512_paged_with_window():
+    run_paged_hybrid_case(64, 4, 9, 8, 8, 1100, WIDE_LENS, [32, 5, 0, 7, 32, 1, 16, 31, 2], 32, "bf16", seed=902)

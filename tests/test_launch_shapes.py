@@ -40,6 +40,16 @@ def test_calls_with_blocks_of_256_rows(shapes, bits, paged):
     assert shapes(paged, 64, bits, 1, 1, 1, 192, 1000)[0] == 256
 
 
+@pytest.mark.parametrize("bits", [1, 1.5, 2, 2.5, 3, 4])
+def test_calls_with_blocks_of_512_rows(shapes, bits):
+    """Many rows at d = 64, and the shapes of the GPU tests of these blocks; where 256 rows leave fewer rounds they stay."""
+    assert shapes(False, 64, bits, 9, 8, 8, 1100, 130)[:3] == (512, 3, 1)
+    assert shapes(PAGED_WINDOW, 64, bits, 9, 8, 8, 1100, 130)[:3] == (512, 3, 1)
+    assert shapes(False, 64, bits, 1, 24, 24, 800, 3000)[:3] == (512, 2, 5)
+    assert shapes(False, 64, bits, 1, 24, 24, 3600, 75600)[0] == 512
+    assert shapes(False, 64, bits, 9, 8, 8, 385, 130)[0] == 256 and shapes(False, 64, bits, 33, 8, 8, 256, 130)[0] == 256
+
+
 def test_calls_with_blocks_of_128_rows(shapes):
     for n_seq, n_qh, n_kv, n_q, max_len in [(1, 4, 1, 59, 4245), (1, 8, 1, 64, 16384), (2, 1, 1, 128, 64), (1, 2, 2, 140, 5000)]:
         assert shapes(False, 128, 3, n_seq, n_qh, n_kv, n_q, max_len)[0] == 128
