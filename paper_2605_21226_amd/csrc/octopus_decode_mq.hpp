@@ -33,11 +33,12 @@ namespace octopus {
 // tokens 169 -> 144).  Tried and slower: the blocks interleaved so that one's scores are computed during the other's exponentials
 // (registers: 6300 us and more), the remainders of the queries in LDS (4220), the two blocks sharing each read of keys and values, 32
 // keys at a time (3700: the reads are not what bounds it), last blocks of few rows started after all others (3950).
-// What bounds it (cycles of a tile, timestamps, 8 wavefronts, d = 64, b = 4): first product 1050, softmax 1660, second
-// product 820, staging 1060 - 1400, barrier up to 700, of 5400.  A 32x32x16 product takes 32 cycles of the matrix core and
-// keeps the vector units of its SIMD from issuing for about 16 of them, so two wavefronts' 2 x 40 products and 2 x (about 30
-// exponentials at quarter rate and 250 other vector instructions) per tile add up to some 4400 cycles of issue: the way down
-// is fewer vector instructions per score.
+// What bounds it: the issue of products and vector instructions.  Per tile and 32 rows a wavefront issues 40 products (32 cycles
+// of the matrix core each, for about 12 of which nothing else of its SIMD issues: 8 of them with 64 multiply-adds take 352
+// cycles, alone 286 and 281), 32 exponentials of 8 cycles, 150 other vector instructions of 4, and 85 - 100 for staging, shared by
+// its blocks: 3500 cycles for 256 rows by two wavefronts per SIMD, of the 4400 that a tile takes (2.25 us; the clock falls to
+// 1.95 GHz under this load).  Three wavefronts per SIMD (384 rows by twelve, 160 registers) take as long per row as 512 rows, so
+// it is not latency; the way down is fewer vector instructions per score.
 
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 constexpr int kXcds = 8;   // accelerator dies of the chip; consecutive workgroups go to consecutive dies

@@ -57,6 +57,13 @@ def test_encoders_do_not_spill(library):
     assert {n: v for n, v in found.items() if v > max([b for part, b in words.items() if part in n], default=0)} == {}
 
 
+def test_many_row_kernels_do_not_spill(library):
+    """decode_kernel_mq: 128 and 256 query rows at d = 64 and 128, 512 at d = 64; a spill of 100 registers took 1.7 - 2.8 times as long."""
+    found = {name: k[".private_segment_fixed_size"] for name, k in library.items() if "16decode_kernel_mq" in name}
+    assert len(found) == 6 * 2 + 6 * 3
+    assert {n: v for n, v in found.items() if v} == {}
+
+
 def test_scratch_of_the_heaviest_kernels_over_quantised_values(library):
     """Groups of 16, or eight rows, of 1 - 2 bit keys at d = 256 keep hundreds of bytes of a lane in scratch; together no more than
     before the maxima over a wavefront were taken for all rows at once."""
