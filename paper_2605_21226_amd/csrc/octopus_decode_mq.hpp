@@ -36,8 +36,8 @@ namespace octopus {
 // What bounds it: the issue of products and vector instructions.  Per tile and 32 rows a wavefront issues 40 products (32 cycles
 // of the matrix core each, for about 12 of which nothing else of its SIMD issues: 8 of them with 64 multiply-adds take 352
 // cycles, alone 286 and 281), 32 exponentials of 8 cycles, 150 other vector instructions of 4, and 85 - 100 for staging, shared by
-// its blocks: 3500 cycles for 256 rows by two wavefronts per SIMD, of the 4400 that a tile takes (2.25 us; the clock falls to
-// 1.95 GHz under this load).  Three wavefronts per SIMD (384 rows by twelve, 160 registers) take as long per row as 512 rows, so
+// its blocks: 3500 cycles for 256 rows by two wavefronts per SIMD, of the 4500 that a tile takes (2.25 us; the clock falls to
+// about 2 GHz under this load).  Three wavefronts per SIMD (384 rows by twelve, 160 registers) take as long per row as 512 rows, so
 // it is not latency; the way down is fewer vector instructions per score.
 
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
