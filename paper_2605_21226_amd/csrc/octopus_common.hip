@@ -253,6 +253,17 @@ int launch_rotate_queries(const octopus_plan_t &plan, const void *q, int q_dtype
     }
 }
 
+// Partial rows in flight per wavefront of the merge: 8, or 32 where a row may have more than 8 partials and the rows are few enough
+// to leave registers (more rows keep the memory busy with 8: 16288 rows of 4 partials take the same either way).  A row of many
+// partials was a chain of round trips, one per 8: one KV head of four rows over 100000 tokens 31.7 -> 23.6 us, 8 of one row over 20000
+// 19.1 -> 18.1, two of four over 40000 at d = 256 34.5 -> 31.6, one of eight rows over 41127 with a window 32.3 -> 30.6.  Calls of up to 8
+// partials are slower with the longer code (one fp32 row over 4096 tokens 17.3 -> 17.7).
+static bool deep_merge(const DecodeShape &s, int64_t rows) {
+    const int64_t round = static_cast<int64_t>(kWave) * s.tiles_per_step * s.item_waves * (s.two_round_blocks != 0 ? 2 : 1);
+    const int64_t most = s.rows_per_pass >= 128 ? s.n_splits : (s.max_len + round - 1) / round;
+    return rows <= 4096 && most > 8;
+}
+
 template <int D>
 static int merge_d(const DecodeShape &s, const float *part_ml, const float *part_acc, const int32_t *seq_lens, float *out,
                    hipStream_t stream) {
@@ -263,14 +274,18 @@ static int merge_d(const DecodeShape &s, const float *part_ml, const float *part
     // (with a window the values are bf16 or, over the vector-unit kernel's two-round blocks, fp32)
     const WindowCall *w = s.window;
     const bool two = s.two_round_blocks != 0;
-    if (w == nullptr) {
-        if (two) go(merge_kernel<D, true, 0>, WindowCall{}); else go(merge_kernel<D, false, 0>, WindowCall{});
-    } else if (w->v_is_bf16) {
-        if (two) return static_cast<int>(hipErrorInvalidValue);
-        if (w->k_is_bf16) go(merge_kernel<D, false, 4>, *w); else go(merge_kernel<D, false, 3>, *w);
-    } else {
-        if (w->k_is_bf16) go(merge_kernel<D, true, 2>, *w); else go(merge_kernel<D, true, 1>, *w);
-    }
+    if (w != nullptr && two && w->v_is_bf16) return static_cast<int>(hipErrorInvalidValue);
+    auto depth = [&](auto un) {
+        constexpr int UN = decltype(un)::value;
+        if (w == nullptr) {
+            if (two) go(merge_kernel<D, true, 0, UN>, WindowCall{}); else go(merge_kernel<D, false, 0, UN>, WindowCall{});
+        } else if (w->v_is_bf16) {
+            if (w->k_is_bf16) go(merge_kernel<D, false, 4, UN>, *w); else go(merge_kernel<D, false, 3, UN>, *w);
+        } else {
+            if (w->k_is_bf16) go(merge_kernel<D, true, 2, UN>, *w); else go(merge_kernel<D, true, 1, UN>, *w);
+        }
+    };
+    if (deep_merge(s, rows)) depth(std::integral_constant<int, 32>{}); else depth(std::integral_constant<int, 8>{});
     return static_cast<int>(hipGetLastError());
 }
 

@@ -196,16 +196,16 @@ struct WindowRow {
 // ---- D8: merge of the split partials, one wavefront per output row -----------------------------------
 // out = sum_j w_j acc_j / sum_j w_j l_j with w_j = exp(m_j - max_j m_j) (the flash-decoding identity).
 // A split without tokens has m = -inf, l = 0 and a zero accumulator, so it needs no special case.
-// Bound by latency (one load for the lengths, then the partials): with one partial per segment instead of four per item
+// Bound by latency (one load for the lengths, then the partials, UN at a time): with one partial per segment instead of four per item
 // of work, a long sequence has a quarter of the rows to read (one head over 4096 tokens: 11.6 us with 128 partials).
+// UN: partial rows in flight per lane, 8 or, where the partials may be many, 32 (deep_merge).
 // TWO: the call may be divided into blocks of two rounds (shp.two_round_blocks).
 // WIN: one more partial per output row, of a native-precision window: 1 + (bf16 keys) + 2 (bf16 values); 0: no window.
-template <int D, bool TWO, int WIN>
+template <int D, bool TWO, int WIN, int UN>
 __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, WindowCall window, const float *__restrict__ part_ml,
                                                       const float *__restrict__ part_acc,
                                                       const int32_t *__restrict__ seq_lens, float *__restrict__ out) {
     constexpr int CPT = D / kWave;  // channels per lane: CPT lane .. + CPT - 1
-    constexpr int UN = 8;           // partial rows in flight per lane
     __shared__ float wgt[kWave];
     const int lane = threadIdx.x;
     int lens = seq_lens[min(lane, shp.n_seq - 1)];   // asked for before anything is computed
@@ -284,22 +284,28 @@ __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, WindowCal
         prow0 = (wg + static_cast<int64_t>(seq) * static_cast<int64_t>(G) + g) * shp.rows_per_pass + r;
         pstride = shp.rows_per_pass;
     }
-    // The first UN accumulator rows are requested before anything waits for the (m, l) pairs: their addresses do
-    // not depend on them, and with the usual handful of partials per row this is all there is to read.
-    float x_first[UN][CPT];
+    // The first (m, l) pairs and UN accumulator rows are requested before anything waits: with the usual handful of partials per row
+    // this is all there is to read.
+    float2 ml_first = make_float2(-INFINITY, 0.0f);
+    if (lane < n_part) ml_first = *reinterpret_cast<const float2 *>(part_ml + (prow0 + static_cast<int64_t>(lane) * pstride) * 2);
+    float x[UN][CPT];
+    auto request = [&](int j0) __attribute__((always_inline)) {   // rows j0 .. + UN - 1, the last one's for those past it
+        static_for<0, UN / 8>([&](auto gg) {
+            constexpr int g = 8 * decltype(gg)::value;
+            if (j0 + g >= n_part) return;   // (uniform)
 #pragma unroll
-    for (int u = 0; u < UN; ++u) {
-#pragma unroll
-        for (int c = 0; c < CPT; ++c) x_first[u][c] = 0.0f;   // (an empty sequence has no partial)
-        if (n_part > 0) load_channels<CPT>(part_acc + (prow0 + static_cast<int64_t>(min(u, n_part - 1)) * pstride) * D + CPT * lane, x_first[u]);
-    }
+            for (int u = g; u < g + 8; ++u)
+                load_channels<CPT>(part_acc + (prow0 + static_cast<int64_t>(min(j0 + u, n_part - 1)) * pstride) * D + CPT * lane, x[u]);
+        });
+    };
+    request(0);
     float m_win = -INFINITY, l_win = 0.0f, a_win[CPT];
     if constexpr (WIN != 0) {
         asm volatile("" ::: "memory");   // (or the loads are moved to their use)
         win.run(shp, win_smem, orow, seq, kvh, own_len, win_len, m_win, l_win, a_win);
     }
-    float m = -INFINITY;
-    for (int j = lane; j < n_part; j += kWave) m = fmaxf(m, part_ml[(prow0 + static_cast<int64_t>(j) * pstride) * 2]);
+    float m = fmaxf(-INFINITY, ml_first.x);   // (a NaN stays out)
+    for (int j = lane + kWave; j < n_part; j += kWave) m = fmaxf(m, part_ml[(prow0 + static_cast<int64_t>(j) * pstride) * 2]);
     m = wave_max(m);
     // the many-row kernel's maxima are in units of log2, the others' and the window's in natural ones
     const float unit = shp.rows_per_pass >= 128 ? 1.0f : kLog2e;
@@ -321,7 +327,8 @@ __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, WindowCal
         const int j = j0 + lane;
         float f = 0.0f;
         if (j < n_part) {
-            const float2 ml = *reinterpret_cast<const float2 *>(part_ml + (prow0 + static_cast<int64_t>(j) * pstride) * 2);
+            float2 ml = ml_first;
+            if (j0 > 0) ml = *reinterpret_cast<const float2 *>(part_ml + (prow0 + static_cast<int64_t>(j) * pstride) * 2);
             f = (ml.x == -INFINITY) ? 0.0f : exp2_raw((ml.x - m) * unit);
             l += f * ml.y;
         }
@@ -330,17 +337,7 @@ __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, WindowCal
         __syncthreads();
         const int nj = min(kWave, n_part - j0);
         for (int jj = 0; jj < nj; jj += UN) {
-            float x[UN][CPT];
-            if (j0 == 0 && jj == 0) {
-#pragma unroll
-                for (int u = 0; u < UN; ++u)
-#pragma unroll
-                    for (int c = 0; c < CPT; ++c) x[u][c] = x_first[u][c];
-            } else {
-#pragma unroll
-                for (int u = 0; u < UN; ++u)
-                    load_channels<CPT>(part_acc + (prow0 + static_cast<int64_t>(j0 + min(jj + u, nj - 1)) * pstride) * D + CPT * lane, x[u]);
-            }
+            if (j0 + jj > 0) request(j0 + jj);
             auto take = [&](int u) __attribute__((always_inline)) {
                 const float fj = wgt[jj + u];
 #pragma unroll
@@ -350,11 +347,13 @@ __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, WindowCal
 #pragma unroll
                 for (int u = 0; u < UN; ++u) take(u);
             } else {   // (partials past the last stay out: at weight zero an infinity in it would count again, as 0 * inf)
-#pragma unroll
-                for (int u = 0; u < UN - 1; ++u) {
-                    if (jj + u >= nj) break;
-                    take(u);
-                }
+                static_for<0, UN / 8>([&](auto gg) {
+                    constexpr int g = 8 * decltype(gg)::value;
+                    if (jj + g >= nj) return;   // (uniform, as below)
+                    static_for<g, g + 8>([&](auto uu) {
+                        if (jj + decltype(uu)::value < nj) take(decltype(uu)::value);
+                    });
+                });
             }
         }
     }
