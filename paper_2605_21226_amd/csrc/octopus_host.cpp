@@ -622,6 +622,9 @@ static void set_division(DecodeShape *s, float *out, bool direct, bool vector_ke
 // Best of all split counts up to 64 / the one taken here (attention call): 200 x 1, 8 KV heads, 1000 tokens 18.2 / 18.2 us, 300 x 4, 2 KV
 // heads, 20000 75.0 / 75.0, 64 x 8, 16384 35.6 / 35.6, 509 x 4, 8 KV heads, 15877 295 / 295, 1335 tokens above 31.6 / 32.5; d = 64: 70 x 4,
 // 1500 15.2 / 15.2, 315 x 4, 8 KV heads, 22923 153.7 / 153.7, 800 x 1, 24 KV heads, 9000 148.3 / 148.3.
+// More than 64 splits are a second round of partials in the merge (3.5 us); they pay for few KV heads with long contexts: 200 rows of one
+// KV head over 40000 tokens, d = 128, 64 / 128 splits 54.6 / 43.8 us, 432 of two over 33236 54.5 / 47.8, 64 of each of two over 20000 34.0 / 31.3;
+// not for 300 of one over 10000, d = 64, 24.8 / 26.0 (80 splits), or 35 over 8000, d = 128, 23.2 / 24.0.
 // The workspace has to fit the documented size, which is that of the split count of make_decode_shape.
 static double many_rows_cost(const octopus_plan_t &plan, const DecodeShape &s, int64_t max_len, int64_t n) {
     const int64_t tiles = (std::max<int64_t>(max_len, 1) + OCTOPUS_TILE - 1) / OCTOPUS_TILE;
@@ -630,7 +633,7 @@ static double many_rows_cost(const octopus_plan_t &plan, const DecodeShape &s, i
     const int64_t rounds = ((work + 7) / 8 + slots - 1) / slots;
     const double tile = plan.head_dim <= 64 ? (s.rows_per_pass == 512 ? 4.1 : 2.25) : (s.rows_per_pass == 256 ? 4.2 : 3.3);
     const double rows = static_cast<double>(s.n_seq) * s.n_kv_heads * s.rows_per_kv;
-    return rounds * (8.0 + tile * ((tiles + n - 1) / n)) + rows * n * plan.head_dim * 2.0e-6;
+    return rounds * (8.0 + tile * ((tiles + n - 1) / n)) + rows * n * plan.head_dim * 2.0e-6 + (n > 64 ? 3.5 : 0.0);
 }
 
 // Where the partial results of the many-row kernel lie: one per query row and split, and it needs nothing else.
@@ -649,7 +652,8 @@ static void many_rows_splits(const octopus_codebooks_t *cb, int64_t max_len, Dec
     *w = many_rows_workspace(cb->plan, *s);   // (always within the limit)
     double best = many_rows_cost(cb->plan, *s, max_len, s->n_splits);
     auto consider = [&](DecodeShape x) {
-        for (int64_t n = 1; n <= 64 && n <= tiles; ++n) {
+        // (of the counts that leave a split the same number of tiles, the smallest)
+        for (int64_t n = 1, in_a_row = tiles; n <= 128; in_a_row = (tiles + n - 1) / n - 1, n = in_a_row > 0 ? (tiles + in_a_row - 1) / in_a_row : 129) {
             x.n_splits = static_cast<int32_t>(n);
             const double cost = many_rows_cost(cb->plan, x, max_len, n);
             if (cost >= best) continue;

@@ -31,3 +31,7 @@ def test_merge_of_many_partials_with_a_window(d, tokens):
 
 def test_merge_of_many_splits():
     run_decode_case(128, 3, 1, 1, 1, 40, [5000], "bf16", seed=78, want_scores=False)
+
+
+def test_merge_of_more_splits_than_lanes():
+    run_decode_case(128, 3, 1, 1, 1, 200, [40000], "bf16", seed=79, want_scores=False)

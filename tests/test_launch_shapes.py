@@ -101,3 +101,9 @@ def test_splits_of_many_query_rows(shapes, d):
         assert shapes(True, d, 3, n_seq, n_qh, n_kv, n_q, max_len) == (rows, groups, splits, merged)
     rows, groups, splits, _ = shapes(False, d, 4, 1, 32, 8, 36, 2908)
     assert 128 <= 8 * groups * splits <= 256 * (2 if d == 64 else 1)
+
+
+def test_more_splits_than_lanes_where_few_heads_have_long_contexts(shapes):
+    """The shape of the GPU test with more partials per row than a wavefront has lanes; a second round of them has to pay."""
+    assert shapes(False, 128, 3, 1, 1, 1, 200, 40000)[:3] == (128, 2, 125)
+    assert shapes(False, 64, 3, 1, 1, 1, 300, 10000)[2] <= 64 and shapes(False, 128, 3, 1, 1, 1, 35, 8000)[2] <= 64
