@@ -64,6 +64,14 @@ def test_many_row_kernels_do_not_spill(library):
     assert {n: v for n, v in found.items() if v} == {}
 
 
+def test_merge_kernels_do_not_spill(library):
+    """merge_kernel: three head dimensions, with and without two-round blocks and each kind of window, 8 or 32 partials in flight; in
+    scratch memory 32 of them were slower than 8."""
+    found = {name: k[".private_segment_fixed_size"] for name, k in library.items() if "12merge_kernel" in name}
+    assert len(found) == 3 * 6 * 2
+    assert {n: v for n, v in found.items() if v} == {}
+
+
 def test_scratch_of_the_heaviest_kernels_over_quantised_values(library):
     """Groups of 16, or eight rows, of 1 - 2 bit keys at d = 256 keep hundreds of bytes of a lane in scratch; together no more than
     before the maxima over a wavefront were taken for all rows at once."""
