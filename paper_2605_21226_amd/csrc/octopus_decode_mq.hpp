@@ -102,6 +102,7 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
     const int base = n_tiles / shp.n_splits, rem = n_tiles % shp.n_splits;
     const int tile_begin = split * base + min(split, rem);
     const int tile_end = tile_begin + base + (split < rem ? 1 : 0);
+    if (tile_begin >= tile_end) return;   // (a split past the sequence's last tile: nothing of it is written, and the merge does not read it)
 
     const bool paged = pt.table != nullptr;
     const char *k_region = reinterpret_cast<const char *>(cache) + (paged ? 0 : pair * shp.t_capacity * (P::GRANULES * 16));
@@ -331,27 +332,25 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
     }
 
     // Start: queries and first tile are asked for, then the tables (one copy: the lookups are a small part of this kernel) are
-    // built and the queries rotated.  A split without tiles leaves an empty partial.
-    if (tile_begin < tile_end) {
-        load_queries(0);
-        load_tile(tile_begin);
-        if (wave < 4) {   // a level per lane, of one array per wavefront
-            typedef const float __attribute__((address_space(4))) *arg_t;
-            const float level = ((arg_t)__builtin_amdgcn_kernarg_segment_ptr())[wave * kMaxLevels + lane];
-            (wave < 2 ? sm.c_xi[wave] : sm.c_rho[wave - 2])[lane] = level;
-        }
-        __syncthreads();
-        build_dir_lut<P::BD0>(sm.dir0, sm.c_xi[0], tid, kWave * NW);
-        if constexpr (P::NCLASS == 2) build_dir_lut<P::BD1>(sm.dir1, sm.c_xi[1], tid, kWave * NW);
-        rotate_queries(std::integral_constant<int, 0>{});
-        if constexpr (RB == 2) {
-            load_queries(1);
-            rotate_queries(std::integral_constant<int, 1>{});
-        }
-        __syncthreads();                       // tables complete
-        stage_tile(0);
-        load_tile(min(tile_begin + 1, tile_end - 1));
+    // built and the queries rotated.
+    load_queries(0);
+    load_tile(tile_begin);
+    if (wave < 4) {   // a level per lane, of one array per wavefront
+        typedef const float __attribute__((address_space(4))) *arg_t;
+        const float level = ((arg_t)__builtin_amdgcn_kernarg_segment_ptr())[wave * kMaxLevels + lane];
+        (wave < 2 ? sm.c_xi[wave] : sm.c_rho[wave - 2])[lane] = level;
     }
+    __syncthreads();
+    build_dir_lut<P::BD0>(sm.dir0, sm.c_xi[0], tid, kWave * NW);
+    if constexpr (P::NCLASS == 2) build_dir_lut<P::BD1>(sm.dir1, sm.c_xi[1], tid, kWave * NW);
+    rotate_queries(std::integral_constant<int, 0>{});
+    if constexpr (RB == 2) {
+        load_queries(1);
+        rotate_queries(std::integral_constant<int, 1>{});
+    }
+    __syncthreads();                       // tables complete
+    stage_tile(0);
+    load_tile(min(tile_begin + 1, tile_end - 1));
     __syncthreads();
 
     // With 8 wavefronts (two per SIMD: w and w + 4) the upper four stage the next tile BEFORE they work on
@@ -487,7 +486,7 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
                     make_float4(oacc[rb][nb][4 * q4], oacc[rb][nb][4 * q4 + 1], oacc[rb][nb][4 * q4 + 2], oacc[rb][nb][4 * q4 + 3]);
         const float l = l_run[rb] + __shfl_xor(l_run[rb], 32, kWave);
         if (h == 0) {
-            part_ml[prow * 2] = tile_begin < tile_end ? m_ref[rb] : -INFINITY;   // in units of log2
+            part_ml[prow * 2] = m_ref[rb];   // in units of log2
             part_ml[prow * 2 + 1] = l;
         }
     }

@@ -230,13 +230,15 @@ __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, WindowCal
         win.load_query(shp, orow, win_smem);
     }
     // Partial j of this row is at prow0 + j * pstride, j < n_part.  The many-row kernel (blocks of 128 rows or more):
-    // one partial per split, adjacent.  Otherwise: one per segment of this row's (sequence, KV head, row group); the
+    // one partial per split that has tiles, adjacent.  Otherwise: one per segment of this row's (sequence, KV head, row group); the
     // segments' slots are consecutive, one per workgroup that has steps of the pair (the work distribution above).
     int64_t prow0;
     int n_part, pstride;
     if (shp.rows_per_pass >= 128) {
         prow0 = ((static_cast<int64_t>(seq) * shp.n_kv_heads + kvh) * shp.rows_per_kv + row) * shp.n_splits;
-        n_part = shp.n_splits;
+        // splits past the last tile have written nothing (max_len may be far above a sequence's length)
+        const int len = min(max(WIN != 0 ? own_len : static_cast<int>(seq_lens[seq]), 0), shp.max_len);
+        n_part = min(shp.n_splits, (len + kWave - 1) / kWave);
         pstride = 1;
     } else {
         const uint64_t G = static_cast<uint64_t>(shp.n_kv_heads) * shp.n_row_groups;
