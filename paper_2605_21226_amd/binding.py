@@ -200,7 +200,10 @@ def _stream_ptr(stream):
     if _raw_stream is None:
         import torch
         torch.cuda.current_stream()      # (raises where there is no device)
-        _device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+        try:
+            _device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+        except AttributeError:           # (private names: another torch may lack them)
+            _device, _raw_stream = (lambda: None), (lambda device: torch.cuda.current_stream().cuda_stream)
     return _raw_stream(_device())
 
 
