@@ -49,7 +49,7 @@ struct SeedGrid {
 //
 // The bracket is a rounded polynomial of the coordinate (linear up to 4 direction bits, whose levels are nearly evenly
 // spaced; a square term at 5): its steps need not lie on the levels, the winner is a corner of either bracket where they part
-// (by the same margins; tests/test_encoder_corners.py takes the steps as they are).  For the same reason the coordinates
+// (by the same margins; tests/test_encoder_brackets.py takes the steps as they are).  For the same reason the coordinates
 // need no more than the hardware's reciprocal.  Before, a grid of cells in LDS gave the bracket: a lookup and a compare more per axis
 // (71 vector instructions a triplet) and a table to build.  With the closed form of lone coordinates (TWO_PADS below): 16 x 32768 tokens x
 // 8 KV heads, d = 128, b = 3 561 -> 521 us; 4 sequences at b = 2 / b = 4 143 -> 131.5 / 203 -> 183; d = 64, 8 x 32768 x 8, b = 3 / 4 151 -> 134 /
@@ -63,10 +63,11 @@ struct CornerGrid {
     static constexpr float kReach = BD <= 3 ? 0.34f : (BD == 4 ? 0.41f : 0.455f);
     static constexpr uint32_t kOne = 0x4B000000u;   // the bits of 2^23: added to a number below 2^22 it leaves its integer in the low bits
     // H + bracket, above it the bits of kOne; any w, NaN included
-    __device__ static __forceinline__ uint32_t bracket(float w) {
-        w = __builtin_amdgcn_fmed3f(w, -kReach, kReach);
+    __device__ static __forceinline__ uint32_t bracket(float w) { return bracket_within(__builtin_amdgcn_fmed3f(w, -kReach, kReach)); }
+    // the same for |w| <= kReach (the host's tests take the steps from here)
+    __host__ __device__ static __forceinline__ uint32_t bracket_within(float w) {
         const float slope = kBend != 0.0f ? fmaf(fabsf(w), -kBend, kSlope) : kSlope;
-        return __float_as_uint(fmaf(w, slope, 8388608.0f + static_cast<float>(H + H / 2 - 1)));
+        return __builtin_bit_cast(uint32_t, fmaf(w, slope, 8388608.0f + static_cast<float>(H + H / 2 - 1)));
     }
     // the margins next to an axis shrink with the levels: 2 |p_x| times the first level, and less where z < 0
     static constexpr float near_axis() { return BD <= 3 ? 1e-5f : 1.25e-6f * K; }

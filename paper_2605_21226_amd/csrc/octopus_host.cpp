@@ -319,7 +319,8 @@ Workspace make_workspace(const octopus_plan_t &plan, const DecodeShape &s) {
 // Upper halves of the Lloyd-Max codebooks of Eq. (oct-marginal) for 1, 3, 4 and 5 direction bits, as
 // octopus_build_codebooks builds them (the lower halves are their negatives).  For these levels the winner of Alg. 1's nine
 // candidates lies among four, by margins three times the encoder's rounding errors (tests/test_encoder_corners.py checks
-// the levels and the margins); a level may differ in its last two bits.
+// the levels, and the margins at one direction bit, tests/test_encoder_brackets.py those at 3 to 5); a level may differ in its last
+// two bits.
 bool corner_levels(const octopus_codebooks_t &cb) {
     static const float k1[] = {0.5f};
     static const float k3[] = {0.143009439f, 0.383984327f, 0.616015673f, 0.856990576f};

@@ -1,6 +1,10 @@
 """The encoder finds the bracket of a coordinate by rounding a polynomial of it, whose steps lie beside the levels, not on them.  The
 winner of Alg. 1's nine candidates is one of such a bracket's four corners all the same: checked here for every piece of the square,
 in 64 bits.  On the GPU: plans whose last triplet is one coordinate, where the four candidates are not looked at."""
+import os
+import shutil
+import subprocess
+
 import numpy as np
 import pytest
 
@@ -9,38 +13,41 @@ from test_encoder_corners import _books, _clip, _corner_levels, _special_keys, _
 
 torch = pytest.importorskip("torch")
 
-
-def _bracket(bd, v):
-    """The rounded polynomial in fp32, as CornerGrid::bracket computes it, and as an exact function of v."""
-    half = 1 << (bd - 1)
-    slope, bend, reach = {3: (4.25, 0.0, 0.34), 4: (8.4, 0.0, 0.41), 5: (17.2, 1.8, 0.455)}[bd]
-    w = np.clip(v - 0.5, -reach, reach)
-    return np.rint(w * (slope - bend * np.abs(w)) + half / 2 - 1).astype(int)
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = next((c for c in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", shutil.which("hipcc")) if c and os.path.exists(c)), None)
 
 
-def _steps(bd):
-    """Where the bracket changes, by bisection."""
-    half = 1 << (bd - 1)
-    assert _bracket(bd, 0.0) == 0 and _bracket(bd, 1.0) == half - 2
-    out = []
-    for j in range(1, half - 1):
-        lo, hi = 0.0, 1.0
-        for _ in range(60):
-            mid = 0.5 * (lo + hi)
-            lo, hi = (mid, hi) if _bracket(bd, mid) < j else (lo, mid)
-        out.append(hi)
-    return out
+@pytest.fixture(scope="module")
+def kernel_brackets(tmp_path_factory):
+    """{direction bits: (near_axis, steps)} of the encoder's own code, compiled for the CPU: fp32 with the fused multiply-add."""
+    if HIPCC is None:
+        pytest.skip("hipcc not found")
+    exe = str(tmp_path_factory.mktemp("host") / "bracket_driver")
+    res = subprocess.run([HIPCC, "-O2", "-std=c++17", "--offload-arch=gfx950", "--offload-host-only", "-x", "hip", "-I" + os.path.join(ROOT, "include"),
+                          "-I" + os.path.join(ROOT, "paper_2605_21226_amd", "csrc"), "-Wno-unused-command-line-argument",
+                          os.path.join(ROOT, "tests", "host", "bracket_driver.cpp"), "-o", exe], capture_output=True, text=True, timeout=600)
+    assert res.returncode == 0, res.stderr[-4000:]
+    res = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, res.stdout + res.stderr
+    found = {}
+    for line in res.stdout.splitlines():
+        bd, near_axis, at_zero, at_one, rises, *steps = line.split()
+        half = 1 << (int(bd) - 1)
+        assert (int(at_zero), int(at_one), int(rises)) == (0, half - 2, 1) and len(steps) == half - 2
+        found[int(bd)] = (float(near_axis), [float(x) for x in steps])
+    return found
 
 
-@pytest.mark.parametrize("bd,near_axis", [(3, 1e-5), (4, 2e-5), (5, 4e-5)])
-def test_the_winner_is_a_corner_of_the_rounded_bracket(bd, near_axis):
-    """Bound as in test_encoder_corners.py: two scores are off by under 1e-6 of the triplet's norm together (the reciprocal's unit in
-    the last place moves the point by 2e-7 and the steps by as much); every other candidate has to lose by 2.5e-6."""
+@pytest.mark.parametrize("bd", [3, 4, 5])
+def test_the_winner_is_a_corner_of_the_rounded_bracket(bd, kernel_brackets):
+    """Bound: two scores of a unit triplet are off by under 1e-6 together, as in test_encoder_corners.py (the reciprocal's unit in the last
+    place moves the point by 2e-7 and the steps by as much); every other candidate has to lose by 2.5e-6."""
     k, half = 1 << bd, 1 << (bd - 1)
     c = np.array(_books(bd).c_xi[0][:k], dtype=np.float64)
     n = _unit(c[:, None] + 0 * c, c[None, :] + 0 * c[:, None])
     mids = 0.5 * (c[1:] + c[:-1])
-    edges = [0.0] + _steps(bd) + [1.0]
+    near_axis, steps = kernel_brackets[bd]
+    edges = [0.0] + steps + [1.0]
     assert len(edges) == half and np.abs(np.array(edges[1:-1]) - c[half + 1:k - 1]).max() < 0.003
     checked, least = 0, np.inf
 

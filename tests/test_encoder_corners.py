@@ -40,48 +40,29 @@ def _clip(poly, f):
     return out
 
 
-@pytest.mark.parametrize("bd,near_axis", [(1, 1e-5), (3, 1e-5), (4, 2e-5), (5, 4e-5)])
-def test_the_winner_is_one_of_four(bd, near_axis):
-    """Bound: two scores of a unit triplet are off by at most 3 roundings of 2^-24 each plus 3 * 2^-24 of either table entry,
-    and the point by 3e-7 in xi and eta (levels up to 0.6 apart): under 1e-6 together.  Every candidate outside the four has
-    to lose to one of them by 2.5e-6 on the whole of a piece (the difference is linear there: its vertices decide)."""
-    k, half = 1 << bd, 1 << (bd - 1)
-    c = np.array(_books(bd).c_xi[0][:k], dtype=np.float64)
+def test_the_winner_is_one_of_four():
+    """One direction bit: one level on either side of an axis, so the corner in the quadrant that the signs of x and y name is the only
+    candidate of the encoder's (brackets, from 3 bits on: test_encoder_brackets.py).  Bound: two scores of a unit triplet are off by at
+    most 3 roundings of 2^-24 each plus 3 * 2^-24 of either table entry, and the point by 3e-7 in xi and eta (levels up to 0.6 apart):
+    under 1e-6 together.  Every other candidate has to lose by 2.5e-6 on the whole of a face's part (the difference is linear there:
+    its vertices decide)."""
+    near_axis = 1e-5
+    c = np.array(_books(1).c_xi[0][:2], dtype=np.float64)
     n = _unit(c[:, None] + 0 * c, c[None, :] + 0 * c[:, None])
-    mids = 0.5 * (c[1:] + c[:-1])
-    edges = [0.0] + list(c[half + 1:k - 1]) + [1.0]
+    rect = [np.array(p) for p in ((0.0, 0.0), (1.0, 0.0), (1.0, 1.0), (0.0, 1.0))]
     checked, least = 0, np.inf
-
-    def pieces(j):
-        cuts = [edges[j]] + [m for m in mids if edges[j] < m < edges[j + 1]] + [edges[j + 1]]
-        return zip(cuts[:-1], cuts[1:])
-    for jx in range(len(edges) - 1):
-        for jy in range(len(edges) - 1):
-            corners = {(half + jx + a, half + jy + b) for a in (0, 1) for b in (0, 1)} if half > 1 else {(1, 1)}
-            for x0, x1 in pieces(jx):
-                for y0, y1 in pieces(jy):
-                    sx, sy = np.searchsorted(mids, [0.5 * (x0 + x1), 0.5 * (y0 + y1)])
-                    nine = {(min(max(sx + a, 0), k - 1), min(max(sy + b, 0), k - 1)) for a in (-1, 0, 1) for b in (-1, 0, 1)}
-                    assert corners <= nine
-                    rect = [np.array(p) for p in ((x0, y0), (x1, y0), (x1, y1), (x0, y1))]
-                    for upper in (True, False):
-                        poly = _clip(rect, (lambda v: 1 - v[0] - v[1]) if upper else (lambda v: v[0] + v[1] - 1))
-                        for f in ([lambda v: v[0] - near_axis, lambda v: v[1] - near_axis] if upper else
-                                  [lambda v: 1 - v[1] - near_axis, lambda v: 1 - v[0] - near_axis]):
-                            poly = _clip(poly, f)
-                        if not poly:
-                            continue
-                        pts = np.array([[v[0], v[1], 1 - v[0] - v[1]] if upper else [1 - v[1], 1 - v[0], 1 - v[0] - v[1]]
-                                        for v in poly])
-                        pts /= np.linalg.norm(pts, axis=1, keepdims=True)
-                        for e in nine - corners:
-                            least = min(least, max((pts @ (n[t] - n[e])).min() for t in corners))
-                            checked += 1
+    for upper in (True, False):
+        poly = _clip(rect, (lambda v: 1 - v[0] - v[1]) if upper else (lambda v: v[0] + v[1] - 1))
+        for f in ([lambda v: v[0] - near_axis, lambda v: v[1] - near_axis] if upper else
+                  [lambda v: 1 - v[1] - near_axis, lambda v: 1 - v[0] - near_axis]):
+            poly = _clip(poly, f)
+        pts = np.array([[v[0], v[1], 1 - v[0] - v[1]] if upper else [1 - v[1], 1 - v[0], 1 - v[0] - v[1]] for v in poly])
+        pts /= np.linalg.norm(pts, axis=1, keepdims=True)
+        for e in ((0, 0), (0, 1), (1, 0)):
+            least = min(least, (pts @ (n[1, 1] - n[e])).min())
+            checked += 1
     print(f"{checked} candidates, least margin {least:.3g}")
-    assert checked and least >= 2.5e-6
-    # the grid over [0, 1] that finds the bracket holds at most one level per cell
-    cells = np.floor(c[half:] * k).astype(int)
-    assert np.all(np.diff(cells) > 0)
+    assert checked == 6 and least >= 2.5e-6
 
 
 def test_levels_the_four_candidates_are_taken_for():
