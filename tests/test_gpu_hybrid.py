@@ -18,7 +18,9 @@ from test_gpu_parity import make_inputs  # noqa: E402
 
 
 def run_hybrid_case(d, bits, n_seq, n_qh, n_kv, n_q, lens, win_lens, w_capacity, dtype, seed, want_scores=True,
-                    t_capacity=None):
+                    t_capacity=None, k_dtype=None):
+    """k_dtype: type of the window's keys, where it is not the queries' and values' `dtype`"""
+    k_dtype = k_dtype or dtype
     cb = binding.octopus_build_codebooks(d, bits)
     plan = oracle.make_plan(d, bits)
     tot = [int(a) + int(b) for a, b in zip(lens, win_lens)]
@@ -33,6 +35,8 @@ def run_hybrid_case(d, bits, n_seq, n_qh, n_kv, n_q, lens, win_lens, w_capacity,
             if L:
                 records[s, h, :L] = oracle.encode(plan, keys[s, :L, h].astype(np.float64), signs[h])
             k_win[s, h, :W] = keys[s, L:L + W, h]
+    if k_dtype != dtype:
+        k_win = to_dev(k_win, k_dtype).float().cpu().numpy()
     wl = synth.Workload("t", n_seq, n_qh, n_kv, d, T, bits, dtype, n_q=n_q)
     q = synth.queries(seed, wl)
     v = np.zeros((n_seq, n_kv, cap, d), dtype=np.float32)
@@ -47,7 +51,7 @@ def run_hybrid_case(d, bits, n_seq, n_qh, n_kv, n_q, lens, win_lens, w_capacity,
     lens_dev = torch.tensor(np.asarray(lens), dtype=torch.int32, device=DEV)
     win_dev = torch.tensor(np.asarray(win_lens), dtype=torch.int32, device=DEV)
     binding.octopus_attn_decode_hybrid(cb, to_dev(q, dtype), sign_bits_dev(signs), cache, cap, to_dev(v, dtype), lens_dev,
-                                       max_len, to_dev(k_win, dtype), win_dev, scale, out, ws, scores)
+                                       max_len, to_dev(k_win, k_dtype), win_dev, scale, out, ws, scores)
     torch.cuda.synchronize()
     out = out.cpu().numpy()
     scores = scores.cpu().numpy() if want_scores else None

@@ -9,6 +9,7 @@ torch = pytest.importorskip("torch")
 if not torch.cuda.is_available():
     pytest.skip("no GPU", allow_module_level=True)
 
+from test_gpu_hybrid import run_hybrid_case  # noqa: E402
 from test_gpu_paged import run_paged_hybrid_case  # noqa: E402
 from test_gpu_parity import run_decode_case  # noqa: E402
 
@@ -27,6 +28,18 @@ def test_merge_of_many_partials_fp32():
 @pytest.mark.parametrize("d,tokens", [(64, 512 * 33), (128, 512 * 9 - 100), (128, 512 * 70), (256, 256 * 33)])
 def test_merge_of_many_partials_with_a_window(d, tokens):
     run_paged_hybrid_case(d, 3, 1, 4, 1, 1, [tokens], [40], 48, "bf16", seed=d)
+
+
+@pytest.mark.parametrize("d,tokens", [(64, 512 * 33), (128, 512 * 9 - 100), (256, 256 * 33)])
+def test_merge_of_many_partials_with_a_window_of_fp32_keys(d, tokens):
+    run_paged_hybrid_case(d, 3, 1, 4, 1, 1, [tokens], [40], 48, "fp32", seed=d + 1)
+
+
+@pytest.mark.parametrize("v_dtype,k_dtype", [("fp32", "fp32"), ("fp32", "bf16"), ("bf16", "bf16"), ("bf16", "fp32")])
+@pytest.mark.parametrize("d,tokens", [(64, 512 * 33), (128, 512 * 9 - 100), (128, 512 * 33), (256, 256 * 33)])
+@pytest.mark.parametrize("want_scores", [False, True])
+def test_merge_of_many_partials_with_a_window_of_each_type(v_dtype, k_dtype, d, tokens, want_scores):
+    run_hybrid_case(d, 3, 1, 2, 1, 1, [tokens], [70], 80, v_dtype, seed=d + 2, want_scores=want_scores, k_dtype=k_dtype)
 
 
 def test_merge_of_many_splits():
