@@ -290,7 +290,7 @@ static int merge_d(const DecodeShape &s, const float *part_ml, const float *part
 }
 
 int launch_merge(const octopus_plan_t &plan, const DecodeShape &s, const float *part_ml, const float *part_acc,
-                 const int32_t *seq_lens, float *out, const float *, const float *, void *stream) {
+                 const int32_t *seq_lens, float *out, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     switch (plan.head_dim) {
         case 64: return merge_d<64>(s, part_ml, part_acc, seq_lens, out, st);

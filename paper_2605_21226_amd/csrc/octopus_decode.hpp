@@ -1954,8 +1954,8 @@ __global__ __launch_bounds__(kDecodeWaves *kWave) void decode_kernel_valu(
 
 // ---- launch helpers -----------------------------------------------------------------------------
 template <class P>
-int launch_decode_mq(const octopus_codebooks_t &cb, const DecodeShape &s, const float *q_rot, const void *cache,
-                     const void *v, const int32_t *seq_lens, float *part_ml, float *part_acc, hipStream_t stream,
+int launch_decode_mq(const octopus_codebooks_t &cb, const DecodeShape &s, const void *cache, const void *v,
+                     const int32_t *seq_lens, float *part_ml, float *part_acc, hipStream_t stream,
                      PageTable pt = PageTable{nullptr, 0, 0});   // pt: cache and v are pools of pages
 
 // bf16 values: the matrix-core kernels.  SCORES: the instantiation that also writes the scores (built in
@@ -2004,7 +2004,7 @@ int launch_decode_paged_plan(const octopus_codebooks_t &cb, const DecodeShape &s
         case 128:
         case 256:
         case 512:   // the many-row kernel (d <= 128), which takes the page table as an argument
-            if constexpr (P::D <= 128) return launch_decode_mq<P>(cb, s, q_rot, k_pool, v_pool, seq_lens, part_ml, part_acc, stream, pt);
+            if constexpr (P::D <= 128) return launch_decode_mq<P>(cb, s, k_pool, v_pool, seq_lens, part_ml, part_acc, stream, pt);
             return static_cast<int>(hipErrorInvalidValue);
         default: break;
     }
@@ -2054,7 +2054,7 @@ int launch_decode_mfma_plan(const octopus_codebooks_t &cb, const DecodeShape &s,
         case 256:
         case 512:   // the many-row kernel: rows per workgroup
             if constexpr (P::D <= 128 && !SCORES)
-                return launch_decode_mq<P>(cb, s, q_rot, cache, v, seq_lens, part_ml, part_acc, stream);
+                return launch_decode_mq<P>(cb, s, cache, v, seq_lens, part_ml, part_acc, stream);
             return static_cast<int>(hipErrorInvalidValue);
         default: return static_cast<int>(hipErrorInvalidValue);
     }

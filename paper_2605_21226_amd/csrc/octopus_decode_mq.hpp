@@ -337,7 +337,8 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
     load_tile(tile_begin);
     if (wave < 4) {   // a level per lane, of one array per wavefront
         typedef const float __attribute__((address_space(4))) *arg_t;
-        const float level = ((arg_t)__builtin_amdgcn_kernarg_segment_ptr())[wave * kMaxLevels + lane];
+        static_assert(kMaxLevels == kWave && offsetof(DeviceBooks, c_rho) == offsetof(DeviceBooks, c_xi) + 2 * kMaxLevels * sizeof(float), "four arrays in a row");
+        const float level = ((arg_t)__builtin_amdgcn_kernarg_segment_ptr())[offsetof(DeviceBooks, c_xi) / 4 + wave * kMaxLevels + lane];
         (wave < 2 ? sm.c_xi[wave] : sm.c_rho[wave - 2])[lane] = level;
     }
     __syncthreads();
@@ -493,9 +494,8 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
 }
 
 template <class P>
-int launch_decode_mq(const octopus_codebooks_t &cb, const DecodeShape &s, const float *, const void *cache,
-                     const void *v, const int32_t *seq_lens, float *part_ml, float *part_acc, hipStream_t stream,
-                     PageTable pt) {
+int launch_decode_mq(const octopus_codebooks_t &cb, const DecodeShape &s, const void *cache, const void *v,
+                     const int32_t *seq_lens, float *part_ml, float *part_acc, hipStream_t stream, PageTable pt) {
     const DeviceBooks books = device_books(cb);
     const int64_t work = static_cast<int64_t>(s.n_seq) * s.n_kv_heads * s.n_splits * s.n_row_groups;
     const int64_t wgs = (work + kXcds - 1) / kXcds * kXcds;   // see the kernel's work mapping

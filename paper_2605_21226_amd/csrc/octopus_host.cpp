@@ -305,14 +305,12 @@ Workspace make_workspace(const octopus_plan_t &plan, const DecodeShape &s) {
     const size_t ml_bytes = up(partials * 2 * sizeof(float));
     w.part_acc_off = w.part_ml_off + ml_bytes;
     const size_t acc_bytes = up(partials * static_cast<size_t>(plan.head_dim) * sizeof(float));
-    w.plan_off = w.part_acc_off + acc_bytes;      // (not used any more: kept in the documented size)
-    const size_t plan_bytes = up((static_cast<size_t>(s.n_seq) + 5) * sizeof(int32_t));
-    w.q2_off = w.plan_off + plan_bytes;   // second rotation of the queries (QJL residual only)
-    w.win_ml_off = w.q2_off + up(rows * static_cast<size_t>(plan.head_dim) * sizeof(float));
-    // (not used any more, a partial of a native-precision window per output row: kept in the documented size)
+    // (kept in the documented size, not used any more: a work plan before the second rotation, a window's partial per output row after it)
     const size_t out_rows = static_cast<size_t>(s.n_seq) * s.n_q * s.n_q_heads;
-    w.win_acc_off = w.win_ml_off + up(out_rows * 2 * sizeof(float));
-    w.total = w.win_acc_off + up(out_rows * static_cast<size_t>(plan.head_dim) * sizeof(float));
+    const size_t plan_bytes = up((static_cast<size_t>(s.n_seq) + 5) * sizeof(int32_t));
+    const size_t window_bytes = up(out_rows * 2 * sizeof(float)) + up(out_rows * static_cast<size_t>(plan.head_dim) * sizeof(float));
+    w.q2_off = w.part_acc_off + acc_bytes + plan_bytes;   // second rotation of the queries (QJL residual only)
+    w.total = w.q2_off + up(rows * static_cast<size_t>(plan.head_dim) * sizeof(float)) + window_bytes;
     return w;
 }
 
@@ -764,7 +762,7 @@ static int attn_decode(const octopus_codebooks_t *cb, const void *q, int32_t q_d
                             win->k_dtype == OCTOPUS_DTYPE_BF16 ? 1 : 0, v_dtype == OCTOPUS_DTYPE_BF16 ? 1 : 0};
         s.window = &window;
     }
-    if (err == 0 && s.out == nullptr) err = launch_merge(cb->plan, s, part_ml, part_acc, seq_lens, out, nullptr, nullptr, stream);
+    if (err == 0 && s.out == nullptr) err = launch_merge(cb->plan, s, part_ml, part_acc, seq_lens, out, stream);
     return err == 0 ? OCTOPUS_OK : OCTOPUS_EHIP;
 }
 
@@ -1042,7 +1040,7 @@ static int attn_decode_paged(const octopus_codebooks_t *cb, const void *q, int32
         window = WindowCall{win->k_window, v_pool, win->w_capacity, win->win_lens, nullptr, pt, win->k_dtype == OCTOPUS_DTYPE_BF16 ? 1 : 0, 1};
         s.window = &window;
     }
-    if (err == 0 && s.out == nullptr) err = launch_merge(cb->plan, s, part_ml, part_acc, seq_lens, out, nullptr, nullptr, stream);
+    if (err == 0 && s.out == nullptr) err = launch_merge(cb->plan, s, part_ml, part_acc, seq_lens, out, stream);
     return err == 0 ? OCTOPUS_OK : OCTOPUS_EHIP;
 }
 

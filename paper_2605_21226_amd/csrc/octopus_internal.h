@@ -85,7 +85,7 @@ inline bool joint_plan(const octopus_plan_t &p) {
 
 // Workspace carve-up (all offsets multiples of 256 bytes).
 struct Workspace {
-    size_t q_rot_off, part_ml_off, part_acc_off, plan_off, q2_off, win_ml_off, win_acc_off, total;
+    size_t q_rot_off, part_ml_off, part_acc_off, q2_off, total;
 };
 
 DecodeShape make_decode_shape(const octopus_plan_t &plan, int32_t n_seq, int32_t n_q_heads, int32_t n_kv_heads,
@@ -114,10 +114,9 @@ int launch_decode_qjl(const octopus_codebooks_t &cb, const DecodeShape &s, const
                       float *part_acc, float *scores_out, int32_t *work_plan, void *stream);
 // Query rows one workgroup of the QJL decode kernel serves at most (8); 0 if the plan is not built.
 int qjl_rows_cap(const octopus_plan_t &plan);
-// With s.window, of a native-precision window too.  (The two pointers before `stream`: not used; part of the signature, which the
-// host-side test drivers stub.)
+// With s.window, of a native-precision window too.
 int launch_merge(const octopus_plan_t &plan, const DecodeShape &s, const float *part_ml, const float *part_acc,
-                 const int32_t *seq_lens, float *out, const float *, const float *, void *stream);
+                 const int32_t *seq_lens, float *out, void *stream);
 int launch_encode(const octopus_codebooks_t &cb, const void *keys, int key_dtype, int64_t stride_seq,
                   int64_t stride_tok, int64_t stride_head, int32_t n_seq, int32_t n_kv_heads, int32_t n_new,
                   const uint8_t *signs, void *cache, int64_t t_capacity, const int32_t *start_pos,
