@@ -504,10 +504,11 @@ const char *octopus_strerror(int code);
  * _qjl, _vq and _hybrid forms, octopus_attn_decode_paged and its _hybrid, _vq and _qjl forms) records the HIP events `before` and `after` (hipEvent_t
  * passed as void*, caller-owned, created with timing enabled) on the call's stream immediately before and after
  * the launch of its fused decode kernel, i.e. around Alg. 2 proper without the split merge.  The query rotation is
- * inside where that kernel does it itself (plans up to 3 bits per coordinate, row groups of at most 8, bf16 values
- * or quantised values on the matrix cores); where a launch of its own does it,
- * it is outside.  The handles are per thread and are forgotten by that call whether it succeeds or not; NULL, NULL
- * cancels.  Returns OCTOPUS_OK, or OCTOPUS_EINVAL if only one of the two is NULL. */
+ * inside where that kernel does it itself: at every bit width where a call of 32 or more query rows per KV head goes to the kernel
+ * for many rows (bf16 values, no score output, no residual, d up to 128); with row groups of at most 8, plans up to 3 bits per
+ * coordinate over bf16 values or quantised values on the matrix cores.  Where a launch of its own does it,
+ * it is outside.  The native-precision window of a hybrid call is worked on by the launch that merges, after `after`.
+ * The handles are per thread and are forgotten by that call whether it succeeds or not; NULL, NULL cancels.  Returns OCTOPUS_OK, or OCTOPUS_EINVAL if only one of the two is NULL. */
 int octopus_profile_events(void *before, void *after);
 
 /* octopus_vq_on_matrix_cores: 1 if octopus_attn_decode_vq without score output serves this shape and value
