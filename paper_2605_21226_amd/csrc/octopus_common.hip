@@ -257,7 +257,10 @@ int launch_rotate_queries(const octopus_plan_t &plan, const void *q, int q_dtype
 // to leave registers (more rows keep the memory busy with 8: 16288 rows of 4 partials take the same either way).  A row of many
 // partials was a chain of round trips, one per 8: one KV head of four rows over 100000 tokens 31.7 -> 23.6 us, 8 of one row over 20000
 // 19.1 -> 18.1, two of four over 40000 at d = 256 34.5 -> 31.6, one of eight rows over 41127 with a window 32.3 -> 30.6.  Calls of up to 8
-// partials are slower with the longer code (one fp32 row over 4096 tokens 17.3 -> 17.7).
+// partials can be slower with the longer code (one fp32 row over 4096 tokens 17.3 -> 17.7), but how many a row has depends on the lengths:
+// counted is what it has at most, a sequence of max_len tokens alone.  So calls of many equal pairs, two or three partials a row,
+// take the longer code too, and pay nothing for it: 8 / 32 in flight, 16 x 32768 tokens, 8 KV heads of four rows 206.1 / 205.4 us, 32 x 8000
+// 109.5 / 109.4, 8 x 8000, eight rows 37.6 / 37.2, d = 64, 24 x 8000, eight rows 53.8 / 54.3, d = 256, 32 x 8000, two rows 200.6 / 200.2.
 static bool deep_merge(const DecodeShape &s, int64_t rows) {
     const int64_t round = static_cast<int64_t>(kWave) * s.tiles_per_step * s.item_waves * (s.two_round_blocks != 0 ? 2 : 1);
     const int64_t most = s.rows_per_pass >= 128 ? s.n_splits : (s.max_len + round - 1) / round;

@@ -33,11 +33,11 @@ namespace octopus {
 // tokens 169 -> 144).  Tried and slower: the blocks interleaved so that one's scores are computed during the other's exponentials
 // (registers: 6300 us and more), the remainders of the queries in LDS (4220), the two blocks sharing each read of keys and values, 32
 // keys at a time (3700: the reads are not what bounds it), last blocks of few rows started after all others (3950).
-// What bounds it: the issue of products and vector instructions.  Per tile and 32 rows a wavefront issues 40 products (32 cycles
-// of the matrix core each, for about 12 of which nothing else of its SIMD issues: 8 of them with 64 multiply-adds take 352
-// cycles, alone 286 and 281), 32 exponentials of 8 cycles, 150 other vector instructions of 4, and 85 - 100 for staging, shared by
-// its blocks: 3500 cycles for 256 rows by two wavefronts per SIMD, of the 4500 that a tile takes (2.25 us; the clock falls to
-// about 2 GHz under this load).  Three wavefronts per SIMD (384 rows by twelve, 160 registers) take as long per row as 512 rows, so
+// What bounds it: the issue of products and vector instructions.  On one SIMD, per wavefront of several, 64 multiply-adds take 152
+// cycles, 64 exponentials 520, 8 products 256, and the products with the multiply-adds 306: a product keeps others from issuing for
+// about 19 of its 32 cycles.  Per tile and 32 rows a wavefront issues 40 products, 32 exponentials, 150 other vector instructions
+// and 85 - 100 for staging, shared by its blocks: 40 x 19 + 32 x 8 + 245 x 2.4 cycles, 3200 for 256 rows by two wavefronts per SIMD, of the
+// 4500 that a tile takes (2.25 us; the clock falls to about 2 GHz under this load: busy cycles over the kernel's time).  Three wavefronts per SIMD (384 rows by twelve, 160 registers) take as long per row as 512 rows, so
 // it is not latency; the way down is fewer vector instructions per score.
 
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;

@@ -618,9 +618,14 @@ static void set_division(DecodeShape *s, float *out, bool direct, bool vector_ke
 // Splits of fewer than 16 tiles, never taken before, serve the short calls: 36 queries x 4 heads per KV head, 8 KV heads, 2908
 // tokens, d = 128, b = 4: 96 us with two splits (32 of 256 compute units had work), 32 with 16, both with the encode of the 36; 646 x 1, 1335
 // tokens 91 / 41, 56 x 8, 378 tokens 44 / 25; one KV head, 347 x 8, 22097 tokens, d = 64 100 / 61.
-// Best of all split counts up to 64 / the one taken here (attention call): 200 x 1, 8 KV heads, 1000 tokens 18.2 / 18.2 us, 300 x 4, 2 KV
-// heads, 20000 75.0 / 75.0, 64 x 8, 16384 35.6 / 35.6, 509 x 4, 8 KV heads, 15877 295 / 295, 1335 tokens above 31.6 / 32.5; d = 64: 70 x 4,
-// 1500 15.2 / 15.2, 315 x 4, 8 KV heads, 22923 153.7 / 153.7, 800 x 1, 24 KV heads, 9000 148.3 / 148.3.
+// The tile times stand for every bit width and for pages: best of all split counts and both blocks / the ones taken here (attention call,
+// b = 1.5 and b = 4), d = 128, 200 x 1, 8 KV heads, 1000 tokens 19.5 / 19.5 and 20.4 / 19.7 us, 509 x 4, 15877 287.5 / 287.4 and 292.7 / 292.1, 36 x 4,
+// 2908 27.0 / 27.1 and 27.8 / 27.7, 646 x 1, 1335 31.6 / 31.4 and 32.2 / 32.1, one KV head, 200 x 1, 40000 37.9 / 37.0 and 38.7 / 38.4; d = 64, 70 x 4,
+// 8 KV heads, 1500 20.2 / 19.6 and 20.1 / 19.9, one KV head, 347 x 1, 22097 26.3 / 26.4 and 26.6 / 26.6, 24 KV heads, 800 x 1, 9000 134.3 / 134.0
+// and 135.4 / 135.6; these and 56 x 8, 378 tokens, at b = 2, 2.5 and 3 and over pages within 1.5 % of the best as well.
+// Counted are sequences of max_len tokens.  In shorter ones the splits past the last tile leave after reading the length and the
+// merge skips them: 8 KV heads of 4 x 64 rows over 300 tokens of 16384, d = 128, 23.7 us, 32.9 with rows of zeros written and merged for each (26.2
+// with splits of 16 tiles of max_len).
 // More than 64 splits are a second round of partials in the merge (3.5 us); they pay for few KV heads with long contexts: 200 rows of one
 // KV head over 40000 tokens, d = 128, 64 / 128 splits 54.6 / 43.8 us, 432 of two over 33236 54.5 / 47.8, 64 of each of two over 20000 34.0 / 31.3;
 // not for 300 of one over 10000, d = 64, 24.8 / 26.0 (80 splits), or 35 over 8000, d = 128, 23.2 / 24.0.
