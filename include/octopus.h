@@ -508,7 +508,8 @@ const char *octopus_strerror(int code);
  * for many rows (bf16 values, no score output, no residual, d up to 128); with row groups of at most 8, plans up to 3 bits per
  * coordinate over bf16 values or quantised values on the matrix cores.  Where a launch of its own does it,
  * it is outside.  The native-precision window of a hybrid call is worked on by the launch that merges, after `after`.
- * The handles are per thread and are forgotten by that call whether it succeeds or not; NULL, NULL cancels.  Returns OCTOPUS_OK, or OCTOPUS_EINVAL if only one of the two is NULL. */
+ * The handles are per thread and are forgotten by that call whether it succeeds or not; NULL, NULL cancels.
+ * Returns OCTOPUS_OK, or OCTOPUS_EINVAL if only one of the two is NULL. */
 int octopus_profile_events(void *before, void *after);
 
 /* octopus_vq_on_matrix_cores: 1 if octopus_attn_decode_vq without score output serves this shape and value
