@@ -41,7 +41,7 @@ namespace octopus {
 // it is not latency; the way down is fewer vector instructions per score.
 
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-constexpr int kXcds = 8;   // accelerator dies of the chip; consecutive workgroups go to consecutive dies
+constexpr uint32_t kXcds = 8;   // accelerator dies of the chip; consecutive workgroups go to consecutive dies
 
 template <class P>
 struct MqSmem {
@@ -56,6 +56,57 @@ struct MqSmem {
     uint16_t kl[2][kWave][KST];
     uint16_t vt[2][D][VST];
 };
+
+// Which work a workgroup has.  The blocks of rows of one (sequence, KV head, split), a unit, read the same keys and values: they follow
+// each other in the order of the work, and each accelerator die (workgroup b runs on die b % 8, each with its own L2) takes an
+// eighth of that order, so that the tiles are fetched from memory once and not once per die, and no die has more workgroups than an
+// eighth of them, rounded up.  (Whole units of blocks per die before: 23 units of 11 blocks were two rounds of workgroups on seven dies of 32
+// compute units; 2776 rows of one KV head over 22097 tokens, d = 64, 87 us of this kernel.)
+__host__ __device__ inline uint32_t mq_position(uint32_t workgroup, uint32_t n_work) {
+    return (workgroup % kXcds) * ((n_work + kXcds - 1) / kXcds) + workgroup / kXcds;
+}
+struct MqWork {
+    uint32_t pair, split, grp;   // pair: sequence n_kv_heads + KV head
+};
+// In a row, a die has whole sequences, and with sequences of different lengths some dies have most of the tiles (24 KV heads of 528 rows
+// over 4376 and 226 tokens, d = 128, b = 4, took 198 us, as long as over twice 4376).  So the order may take every eighth pair, then every
+// eighth from the next one on: a die has pairs of every sequence.  With fewer KV heads than dies it takes the units so, and as the first
+// splits of a short sequence have its tiles, the splits of a pair are turned so that its first goes to another die than its neighbours'.
+// Whole units per die, by unit % 8 / in a row / spread: that call 164 / 198 / 119 us, 16 ragged to 1167, 24 KV heads x 48, d = 128, b = 4 150 / 111 /
+// 85, d = 64, 16 ragged to 8000, 8 x 64 85 / 82 / 69, 32 to 4000 93 / 83 / 69, 8 to 6000, 4 KV heads x 512, d = 128 128 / 114 / 106.
+// What it costs is that a die reads from every sequence, 1 - 2 us.  That is more than it gives where every workgroup has a compute unit of
+// its own and few tiles (d = 64, 16 ragged to 6352, one KV head of 196 rows 27.9 in a row / 30.3, d = 128, 5 to 3697, 2 x 238 32.4 / 34.3), from
+// about 16 tiles on it is less; of equal sequences in more than one round it is up to 3 % (d = 64, 16 x 105, 24 KV heads of 222 rows 58.5 / 60.1).
+__host__ __device__ inline bool mq_spreads(int32_t n_seq, int32_t n_splits, int32_t max_len, uint32_t n_work) {
+    return n_seq > 1 && (n_work > 256 || max_len / n_splits >= 16 * kWave);
+}
+// Every eighth of 0 .. n - 1, then every eighth from the next one on: number i of that order.
+__host__ __device__ inline uint32_t mq_spread(uint32_t i, uint32_t n) {
+    const uint32_t each = n / kXcds, more = n % kXcds;   // numbers of a residue, residues with one more
+    if (i < more * (each + 1)) {
+        const uint32_t residue = i / (each + 1);
+        return kXcds * (i - residue * (each + 1)) + residue;
+    }
+    const uint32_t rest = i - more * (each + 1), residue = rest / each;
+    return kXcds * (rest - residue * each) + more + residue;
+}
+__host__ __device__ inline MqWork mq_work(uint32_t position, uint32_t n_seq, uint32_t n_kv_heads, uint32_t n_splits, uint32_t n_row_groups,
+                                          bool spread) {
+    const uint32_t i = position / n_row_groups, grp = position - i * n_row_groups, n_pairs = n_seq * n_kv_heads;
+    uint32_t pair = i / n_splits, split = i - pair * n_splits;
+    if (spread) {
+        if (n_kv_heads >= kXcds) {
+            pair = mq_spread(pair, n_pairs);
+        } else {
+            const uint32_t unit = mq_spread(i, n_pairs * n_splits);
+            pair = unit / n_splits;
+            const uint32_t at = unit - pair * n_splits;
+            const uint32_t turn = n_splits >= kXcds ? (pair * (1u - n_splits)) % kXcds : (pair * n_splits / kXcds) % n_splits;
+            split = at >= turn ? at - turn : at + n_splits - turn;
+        }
+    }
+    return MqWork{pair, split, grp};
+}
 
 template <class P, int NW, int RB>
 __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D <= 64 || NW == 8 ? 2 : 1))) void decode_kernel_mq(DeviceBooks books, DecodeShape shp,
@@ -81,22 +132,16 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(P::D 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, h = lane >> 5;
 
-    // work: (sequence, KV head, block of ROWS rows, split) and the split's tiles.  The blocks of rows of one
-    // (sequence, KV head, split) read the same keys and values: they follow each other in the order of the work, and each
-    // accelerator die (workgroup b runs on die b % 8, each with its own L2) takes an eighth of that order, so that the tiles are
-    // fetched from memory once and not once per die, and no die has more than one workgroup more than another.  (Whole units of
-    // blocks per die before: 23 units of 11 blocks were two rounds of workgroups on seven dies of 32 compute units; 2776 rows of
-    // one KV head over 22097 tokens, d = 64, 87 us of this kernel.)
+    // work: (sequence, KV head, block of ROWS rows, split) and the split's tiles
     const uint32_t n_work = static_cast<uint32_t>(shp.n_seq * shp.n_kv_heads) * static_cast<uint32_t>(shp.n_splits * shp.n_row_groups);
-    const uint32_t per_die = (n_work + kXcds - 1) / kXcds;
-    const uint32_t work = (blockIdx.x % kXcds) * per_die + blockIdx.x / kXcds;
+    const uint32_t work = mq_position(blockIdx.x, n_work);
     if (work >= n_work) return;   // (whole workgroup, before any barrier)
-    const uint32_t unit = work / static_cast<uint32_t>(shp.n_row_groups);
-    const int grp = static_cast<int>(work - unit * static_cast<uint32_t>(shp.n_row_groups));
-    const int64_t pair = unit / static_cast<uint32_t>(shp.n_splits);
-    const int split = static_cast<int>(unit % static_cast<uint32_t>(shp.n_splits));
-    const int seq = static_cast<int>(static_cast<uint32_t>(pair) / static_cast<uint32_t>(shp.n_kv_heads));
-    const int kvh = static_cast<int>(static_cast<uint32_t>(pair) % static_cast<uint32_t>(shp.n_kv_heads));
+    const MqWork mine = mq_work(work, static_cast<uint32_t>(shp.n_seq), static_cast<uint32_t>(shp.n_kv_heads), static_cast<uint32_t>(shp.n_splits),
+                                static_cast<uint32_t>(shp.n_row_groups), mq_spreads(shp.n_seq, shp.n_splits, shp.max_len, n_work));
+    const int grp = static_cast<int>(mine.grp), split = static_cast<int>(mine.split);
+    const int64_t pair = mine.pair;
+    const int seq = static_cast<int>(mine.pair / static_cast<uint32_t>(shp.n_kv_heads));
+    const int kvh = static_cast<int>(mine.pair % static_cast<uint32_t>(shp.n_kv_heads));
     const int len = min(max(seq_lens[seq], 0), shp.max_len);
     const int n_tiles = (len + kWave - 1) / kWave;
     const int base = n_tiles / shp.n_splits, rem = n_tiles % shp.n_splits;

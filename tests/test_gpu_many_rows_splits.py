@@ -22,6 +22,19 @@ def test_decode_many_rows_small_splits(d, bits, n_kv, n_q, lens):
     run_decode_case(d, bits, len(lens), n_kv, n_kv, n_q, lens, "bf16", seed=d + n_q, want_scores=False)
 
 
+# sequences of different lengths in more than one round of workgroups, whose order is spread over the dies by pairs or by units; and in one
+# round with more than 16 tiles a split
+RAGGED = [190, 64, 0, 65, 1, 130, 20, 333, 5, 128]
+SPREAD = [(8, 33, RAGGED * 4), (3, 40, RAGGED * 10), (9, 300, RAGGED * 2), (24, 33, [2000, 70, 0, 1100, 300, 64, 1, 700]),
+          (2, 40, [6000] + RAGGED * 4)]
+
+
+@pytest.mark.parametrize("d,bits", [(64, 3), (128, 4)])
+@pytest.mark.parametrize("n_kv,n_q,lens", SPREAD)
+def test_decode_many_rows_spread_over_the_dies(d, bits, n_kv, n_q, lens):
+    run_decode_case(d, bits, len(lens), n_kv, n_kv, n_q, lens, "bf16", seed=d + n_q, want_scores=False)
+
+
 @pytest.mark.parametrize("d,n_qh,n_q", [(64, 2, 70), (64, 6, 65), (128, 4, 19), (128, 2, 131)])
 @pytest.mark.parametrize("q_dtype", ["bf16", "fp32"])
 def test_decode_many_rows_query_types_and_alignment(d, n_qh, n_q, q_dtype):
