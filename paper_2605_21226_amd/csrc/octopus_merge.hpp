@@ -237,7 +237,8 @@ __global__ __launch_bounds__(kWave) void merge_kernel(DecodeShape shp, WindowCal
     if (shp.rows_per_pass >= 128) {
         prow0 = ((static_cast<int64_t>(seq) * shp.n_kv_heads + kvh) * shp.rows_per_kv + row) * shp.n_splits;
         // splits past the last tile have written nothing (max_len may be far above a sequence's length)
-        const int len = min(max(WIN != 0 ? own_len : static_cast<int>(seq_lens[seq]), 0), shp.max_len);
+        const int asked = WIN != 0 ? own_len : (shp.n_seq <= kWave ? __builtin_amdgcn_readlane(lens, seq) : static_cast<int>(seq_lens[seq]));
+        const int len = min(max(asked, 0), shp.max_len);
         n_part = min(shp.n_splits, (len + kWave - 1) / kWave);
         pstride = 1;
     } else {
